@@ -195,6 +195,22 @@ template <> struct PackVec<uint16_t> {
     }
 };
 
+// Pass 2 folded into the head of pass 3: while its first rows are on their way every workgroup adds up the partial sums of
+// pass 1 (one per thread; exact sums, so every workgroup gets the same bits) and takes gamma = fp32(S / (N K)), Eq. (3): one
+// fp64 IEEE division, one rounding to fp32.  Workgroup 0 writes it out, once per 16-row block of the segment.  Returned: the
+// magnitude from which a weight's code is +-1.
+__device__ inline float pack_threshold(const double* __restrict__ partials, int nparts, int64_t count, float* __restrict__ gamma_out,
+                                       int64_t nout, double* sh_hi, double* sh_lo) {
+    dd part{0.0, 0.0};
+    if ((int)threadIdx.x < nparts) part = dd{partials[2 * threadIdx.x], partials[2 * threadIdx.x + 1]};
+    const double S = block_sum_dd<kPackThreads / kWave>(part, sh_hi, sh_lo);
+    const float g = (float)(S / (double)count);
+    if (blockIdx.x == 0)
+        for (int64_t o = threadIdx.x; o < nout; o += kPackThreads) gamma_out[o] = g;
+    const float d = g + kEps;                              // gamma + eps, one fp32 add (Eq. (1))
+    return ternary_threshold(d);                           // |w| >= thr  <=>  RoundClip(w / d) = +-1
+}
+
 // W, N: the rows being packed (a whole matrix, or one segment of it); they become row blocks rb_off ... of a
 // packed matrix of RB row blocks in all.
 template <typename T, bool kVec>
@@ -239,17 +255,7 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
     int64_t item = blockIdx.x;
     if (item < items) load(item, nxt);
 
-    // Pass 2 folded in: while the first rows are on their way every workgroup adds up the partial sums of pass 1
-    // (one per thread; exact sums, so every workgroup gets the same bits) and takes gamma = fp32(S / (N K)), Eq. (3):
-    // one fp64 IEEE division, one rounding to fp32.  Workgroup 0 writes it out, once per 16-row block of the segment.
-    dd part{0.0, 0.0};
-    if ((int)threadIdx.x < nparts) part = dd{partials[2 * threadIdx.x], partials[2 * threadIdx.x + 1]};
-    const double S = block_sum_dd<kPackThreads / kWave>(part, sh_hi, sh_lo);
-    const float g = (float)(S / (double)count);
-    if (blockIdx.x == 0)
-        for (int64_t o = threadIdx.x; o < nout; o += kPackThreads) gamma_out[o] = g;
-    const float d = g + kEps;                              // gamma + eps, one fp32 add (Eq. (1))
-    const float thr = ternary_threshold(d);                // |w| >= thr  <=>  RoundClip(w / d) = +-1
+    const float thr = pack_threshold(partials, nparts, count, gamma_out, nout, sh_hi, sh_lo);
 
     for (; item < items; item += gridDim.x) {
         float cur[4][4];
@@ -274,6 +280,79 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
         const int g = lane >> 4;
         // word index inside the chunk: ((g * 16 + row) * 4 + j) with row = 4 w + t, and lane & 15 = 4 t + j
         if (g < nq) packed[quad_index_2bit(4 * s, rb + rb_off, 0, Kq, RB) * 4 + g * 64 + 16 * w + (lane & 15)] = out;
+    }
+}
+
+// bf16 rows that start on 16-byte boundaries (K a multiple of 8): items of two K steps, so that a lane's load is 16 bytes
+// (columns 8l .. 8l+7 of the 512) and a row of an item one 1 KiB run, as in the fp32 form; with 8-byte loads the pass moved
+// half the bytes per request and ran at 2.9 TB/s (57344 x 8192, both passes: 496 us, now 350).  Two lanes complete a word; the pair holds the words of
+// the wave's four rows twice, so the even lane hands out rows 0 and 2, the odd lane rows 1 and 3, and two ds_bpermute per
+// step give lane 16 g + 4 t + j word j of quad column g for row 4w + t: four 64-byte runs per step, as above.
+__global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit_bf16x8(const uint16_t* __restrict__ W, int64_t N, int64_t K,
+                                                                           int64_t Kq, int64_t RB, int64_t rb_off,
+                                                                           const double* __restrict__ partials, int nparts, int64_t count,
+                                                                           float* __restrict__ gamma_out, int64_t nout,
+                                                                           uint32_t* __restrict__ packed) {
+    __shared__ double sh_hi[kPackThreads / kWave];
+    __shared__ double sh_lo[kPackThreads / kWave];
+    const int lane = threadIdx.x & (kWave - 1);
+    const int w = threadIdx.x >> 6;
+    const int odd = lane & 1;
+    const int pairs = (int)ceil_div(Kq, 8);                // items per row block
+    const int items = (int)ceil_div(N, kRowsPerBlock) * pairs;      // N K < 2^40: below 2^28 + 2^28
+    const int t_out = (lane >> 2) & 3;
+    const int src = (8 * (lane >> 4) + 2 * (lane & 3) + (t_out & 1)) << 2;      // of the item's first step; + 32 lanes for the second
+
+    auto load = [&](int item, uint4 (&q)[4]) {
+        item = items - 1 - item;
+        const int rb = item / pairs, sp = item - rb * pairs;
+        const int64_t k = 512 * (int64_t)sp + 8 * lane;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int64_t n = (int64_t)rb * kRowsPerBlock + 4 * w + t;
+            q[t] = make_uint4(0, 0, 0, 0);                  // padding rows / columns quantize to code 0
+            if (n < N && k < K) q[t] = load_streaming_b128(W + n * K + k);
+        }
+    };
+
+    uint4 nxt[4];
+    int item = blockIdx.x;
+    if (item < items) load(item, nxt);
+
+    const float thr = pack_threshold(partials, nparts, count, gamma_out, nout, sh_hi, sh_lo);
+
+    for (; item < items; item += gridDim.x) {
+        uint4 cur[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) cur[t] = nxt[t];
+        if (item + (int)gridDim.x < items) load(item + gridDim.x, nxt);
+        uint32_t c[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint32_t u[4] = {cur[t].x, cur[t].y, cur[t].z, cur[t].w};
+            uint32_t v = 0;                                 // columns 8 l + 4 h + b: bits 8 b + 2 (2 odd + h) of the word
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const uint32_t x = u[2 * h + (b >> 1)];
+                    v |= ternary_code2_threshold(__uint_as_float((b & 1) ? (x & 0xFFFF0000u) : (x << 16)), thr) << (8 * b + 2 * h);
+                }
+            v <<= 4 * odd;
+            c[t] = v | dpp_u32<0xB1>(v);                    // lane ^ 1
+        }
+        const int even_rows = (int)(odd ? c[1] : c[0]), odd_rows = (int)(odd ? c[3] : c[2]);
+        const int it = items - 1 - item;
+        const int rb = it / pairs, sp = it - rb * pairs;
+        const int g = lane >> 4;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(src + 128 * q, even_rows);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(src + 128 * q, odd_rows);
+            const int64_t s = 2 * (int64_t)sp + q;
+            const int64_t nq = (Kq - 4 * s) < 4 ? (Kq - 4 * s) : 4;     // quads of this step (the last may hold fewer, or none)
+            if (g < nq) packed[quad_index_2bit(4 * s, rb + rb_off, 0, Kq, RB) * 4 + g * 64 + 16 * w + (lane & 15)] = t_out < 2 ? lo : hi;
+        }
     }
 }
 
@@ -325,6 +404,9 @@ hipError_t launch_abs_sum(const void* W, bool bf16, int64_t N, int64_t K, double
     return hipGetLastError();
 }
 
+// 16-byte loads along the rows of a bf16 matrix
+static bool pack_bf16x8_ok(const void* W, int64_t K) { return K % 8 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0; }
+
 int quant_weights_max_sums() { return kPackThreads; }
 
 hipError_t launch_gamma_from_sums(const double* sums, int nsums, int64_t total_count, float* gamma, hipStream_t stream) {
@@ -343,14 +425,17 @@ hipError_t launch_pack_2bit_with_sums(const void* W, bool bf16, int64_t N, int64
     uint32_t* out = static_cast<uint32_t*>(packed);
 #define PACK(T_, V_) hipLaunchKernelGGL((ternarize_pack_2bit<T_, V_>), grid, dim3(kPackThreads), 0, stream, w, N, K, Kq, RB, (int64_t)0, \
                                         sums, nsums, total_count, gamma, (int64_t)1, out)
+#define PACK_BF16X8() hipLaunchKernelGGL(ternarize_pack_2bit_bf16x8, grid, dim3(kPackThreads), 0, stream, w, N, K, Kq, RB, (int64_t)0, \
+                                         sums, nsums, total_count, gamma, (int64_t)1, out)
     if (bf16) {
         const uint16_t* w = static_cast<const uint16_t*>(W);
-        if (vec) PACK(uint16_t, true); else PACK(uint16_t, false);
+        if (pack_bf16x8_ok(W, K)) PACK_BF16X8(); else if (vec) PACK(uint16_t, true); else PACK(uint16_t, false);
     } else {
         const float* w = static_cast<const float*>(W);
         if (vec) PACK(float, true); else PACK(float, false);
     }
 #undef PACK
+#undef PACK_BF16X8
     return hipGetLastError();
 }
 
@@ -372,14 +457,17 @@ hipError_t launch_quantize_weights_2bit(const void* W, bool bf16, int64_t N, int
     uint32_t* out = static_cast<uint32_t*>(packed);
 #define PACK(T_, V_) hipLaunchKernelGGL((ternarize_pack_2bit<T_, V_>), grid, dim3(kPackThreads), 0, stream, w, N, K, Kq, RBT, rb_off, \
                                         partials, blocks, count, gamma, nout, out)
+#define PACK_BF16X8() hipLaunchKernelGGL(ternarize_pack_2bit_bf16x8, grid, dim3(kPackThreads), 0, stream, w, N, K, Kq, RBT, rb_off, \
+                                         partials, blocks, count, gamma, nout, out)
     if (bf16) {
         const uint16_t* w = static_cast<const uint16_t*>(W);
-        if (vec) PACK(uint16_t, true); else PACK(uint16_t, false);
+        if (pack_bf16x8_ok(W, K)) PACK_BF16X8(); else if (vec) PACK(uint16_t, true); else PACK(uint16_t, false);
     } else {
         const float* w = static_cast<const float*>(W);
         if (vec) PACK(float, true); else PACK(float, false);
     }
 #undef PACK
+#undef PACK_BF16X8
     return hipGetLastError();
 }
 

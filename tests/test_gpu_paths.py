@@ -1,0 +1,38 @@
+"""GPU tests of single kernel forms at the sizes where each can go wrong -- the edges of its tiles, its remainders, the
+smallest and largest of its range -- against the CPU oracle (bit for bit: codes, scales, accumulators) or, where a form
+stands in for a slower one, against that one on the same inputs."""
+import numpy as np
+import pytest
+
+import oracle
+from layout_ref import decode_2bit
+from paper_2402_17764_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def dev_bf16(bits_u16):
+    return torch.from_numpy(bits_u16.view(np.int16).copy()).cuda().view(torch.bfloat16)
+
+
+def check_packed(gpu_lib, W, packed, gamma):
+    N, K = W.shape
+    codes_ref, gamma_ref = oracle.quantize_weights(W)
+    assert gamma.cpu().numpy()[0].tobytes() == np.float32(gamma_ref).tobytes(), "gamma bits differ"
+    dec, pad_zero = decode_2bit(packed.cpu().numpy(), N, K)
+    assert pad_zero and np.array_equal(dec, codes_ref)
+
+
+# the bf16 packing pass with 16-byte loads (K a multiple of 8): items of two K steps -- less than one, one, two, three steps,
+# partial last quads, rows that do not fill a row block, more items than workgroups
+@pytest.mark.parametrize("N,K", [(1, 8), (16, 64), (17, 256), (33, 264), (100, 512), (16, 520), (15, 776), (250, 4104), (2056, 8200)])
+def test_pack_bf16_rows_of_eight(gpu_lib, N, K):
+    W, bits = synth.to_bf16(synth.weights(N, K, config=2, layer=N % 5))
+    packed, gamma = gpu_lib.quantize_weights(dev_bf16(bits).view(N, K))
+    check_packed(gpu_lib, W, packed, gamma)
