@@ -446,7 +446,8 @@ bitnet_status bitnet_ffn_gate_up_fused(const void* x, bitnet_dtype x_dtype, int 
  * gamma (Eq. (3) over its rows) and its codes (Eq. (1)-(2) with that gamma), packed into one buffer with
  * the layout of the whole [N][K] matrix.
  *   gamma_rb   out, ceil(N / 16) floats (device): the gamma of the segment that each 16-row block belongs to
- *   workspace  as for bitnet_quantize_weights; used by one segment after the other in stream order
+ *   workspace  as for bitnet_quantize_weights
+ * Two launches for every sixteen segments, which are quantized side by side.
  * 2-bit format only (BITNET_ERR_FORMAT otherwise).
  *
  * bitnet_linear_segmented / bitnet_linear_fused_segmented: as bitnet_linear_variant / bitnet_linear_fused

@@ -433,19 +433,7 @@ bitnet_status bitnet_quantize_weights_segmented(const void* W, bitnet_dtype w_dt
     bitnet_quantize_weights_workspace(N, K, &need);
     if (workspace_bytes < need) return BITNET_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const int64_t rb_total = bitnet::ceil_div(N, 16);
-    int64_t row0 = 0;
-    for (int sgm = 0; sgm < nseg; ++sgm) {
-        const int64_t rows = seg_rows[sgm];
-        const char* Ws = static_cast<const char*>(W) + row0 * K * (int64_t)dtype_size(w_dtype);
-        // the launches of one segment finish with the workspace before the next segment's start (stream order)
-        hipError_t e = bitnet::launch_quantize_weights_2bit(Ws, w_dtype == BITNET_BF16, rows, K, packed,
-                                                            gamma_rb + row0 / 16, workspace, s, row0 / 16, rb_total,
-                                                            bitnet::ceil_div(rows, 16));
-        if (e != hipSuccess) return BITNET_ERR_HIP;
-        row0 += rows;
-    }
-    return BITNET_OK;
+    return from_hip(bitnet::launch_quantize_weights_2bit_segmented(W, w_dtype == BITNET_BF16, N, K, seg_rows, nseg, packed, gamma_rb, workspace, s));
 }
 
 static bitnet_status linear_fused_any(const void* x, bitnet_dtype x_dtype, const void* packed, const float* gamma,

@@ -32,10 +32,11 @@ int quant_weights_num_partials();
 // nout: how many consecutive floats receive gamma (one per 16-row block of a segment; 1 for a whole tensor)
 hipError_t launch_absmean_gamma(const void* W, bool bf16, int64_t N, int64_t K, float* gamma, void* workspace,
                                 hipStream_t stream, int64_t nout = 1);
-// rb_off / rb_total: the rows are row blocks rb_off ... of a packed matrix of rb_total row blocks (0: all of it)
 hipError_t launch_quantize_weights_2bit(const void* W, bool bf16, int64_t N, int64_t K, void* packed,
-                                        float* gamma, void* workspace, hipStream_t stream, int64_t rb_off = 0,
-                                        int64_t rb_total = 0, int64_t nout = 1);
+                                        float* gamma, void* workspace, hipStream_t stream);
+// consecutive row segments with a gamma each; gamma_rb: one per 16-row block of the whole matrix
+hipError_t launch_quantize_weights_2bit_segmented(const void* W, bool bf16, int64_t N, int64_t K, const int64_t* seg_rows, int nseg,
+                                                  void* packed, float* gamma_rb, void* workspace, hipStream_t stream);
 
 // one shard's share of Eq. (3): sum[0 .. 1] = the double-double (hi, lo) pair of sum |W| over these rows
 hipError_t launch_abs_sum(const void* W, bool bf16, int64_t N, int64_t K, double* sum, void* workspace, hipStream_t stream);

@@ -41,14 +41,32 @@ __device__ inline void add_abs(const uint4& q, dd (&part)[4]) {
     }
 }
 
-template <typename T>
-__global__ __launch_bounds__(kSumThreads) void abs_sum_partials(const T* __restrict__ W, int64_t count,
-                                                                int vec_ok, int64_t stream_vecs,
-                                                                double* __restrict__ partials) {
+// Row segments that are quantized side by side, each with a gamma of its own.  Both passes deal their workgroups out to
+// the segments in proportion to the rows, so that a merged matrix takes two launches and fills the chip however it is
+// divided: one pair of launches per segment ran a 9600 x 3200 fp32 matrix of three segments in 56.6 us, this in 43.7.
+struct Seg {
+    int64_t row0, rows;          // of W
+    int64_t count;               // elements under the mean of Eq. (3)
+    int64_t stream_vecs;         // 16-byte vectors of the segment that pass 1 reads with the streaming policy
+    int64_t g0, nout;            // gamma_out[g0 .. g0 + nout - 1] receive the segment's gamma
+    int part0, nparts;           // its partial sums; pass 1 has one workgroup for each
+    int pack0, npack;            // its workgroups of pass 3
+};
+constexpr int kMaxSegs = 16;     // of one launch; kernels for a whole matrix take a list of one
+template <int kSegs> struct SegList { int n; Seg s[kSegs]; };
+
+template <typename T, int kSegs>
+__global__ __launch_bounds__(kSumThreads) void abs_sum_partials(const T* __restrict__ W_all, int64_t K, SegList<kSegs> list,
+                                                                int vec_ok, double* __restrict__ partials) {
     constexpr int kPer = 16 / (int)sizeof(T);             // elements per 16-byte vector
+    int sg = 0;
+    while (sg + 1 < list.n && (int)blockIdx.x >= list.s[sg + 1].part0) ++sg;
+    const Seg& seg = list.s[sg];
+    const T* W = W_all + seg.row0 * K;
+    const int64_t count = seg.rows * K, stream_vecs = seg.stream_vecs;
     dd acc{0.0, 0.0};
-    const int64_t tid = (int64_t)blockIdx.x * kSumThreads + threadIdx.x;
-    const int64_t nthreads = (int64_t)gridDim.x * kSumThreads;
+    const int64_t tid = (int64_t)((int)blockIdx.x - seg.part0) * kSumThreads + threadIdx.x;
+    const int64_t nthreads = (int64_t)seg.nparts * kSumThreads;
     int64_t done = 0;
     if (vec_ok) {
         const int64_t nvec = count / kPer;
@@ -197,45 +215,51 @@ template <> struct PackVec<uint16_t> {
 
 // Pass 2 folded into the head of pass 3: while its first rows are on their way every workgroup adds up the partial sums of
 // pass 1 (one per thread; exact sums, so every workgroup gets the same bits) and takes gamma = fp32(S / (N K)), Eq. (3): one
-// fp64 IEEE division, one rounding to fp32.  Workgroup 0 writes it out, once per 16-row block of the segment.  Returned: the
-// magnitude from which a weight's code is +-1.
-__device__ inline float pack_threshold(const double* __restrict__ partials, int nparts, int64_t count, float* __restrict__ gamma_out,
-                                       int64_t nout, double* sh_hi, double* sh_lo) {
+// fp64 IEEE division, one rounding to fp32.  The segment's first workgroup writes it out, once per 16-row block of it.
+// Returned: the magnitude from which a weight's code is +-1.
+__device__ inline float pack_threshold(const double* __restrict__ partials, const Seg& seg, float* __restrict__ gamma_out,
+                                       double* sh_hi, double* sh_lo) {
     dd part{0.0, 0.0};
-    if ((int)threadIdx.x < nparts) part = dd{partials[2 * threadIdx.x], partials[2 * threadIdx.x + 1]};
+    partials += 2 * (int64_t)seg.part0;
+    if ((int)threadIdx.x < seg.nparts) part = dd{partials[2 * threadIdx.x], partials[2 * threadIdx.x + 1]};
     const double S = block_sum_dd<kPackThreads / kWave>(part, sh_hi, sh_lo);
-    const float g = (float)(S / (double)count);
-    if (blockIdx.x == 0)
-        for (int64_t o = threadIdx.x; o < nout; o += kPackThreads) gamma_out[o] = g;
+    const float g = (float)(S / (double)seg.count);
+    if ((int)blockIdx.x == seg.pack0)
+        for (int64_t o = threadIdx.x; o < seg.nout; o += kPackThreads) gamma_out[seg.g0 + o] = g;
     const float d = g + kEps;                              // gamma + eps, one fp32 add (Eq. (1))
     return ternary_threshold(d);                           // |w| >= thr  <=>  RoundClip(w / d) = +-1
 }
 
-// W, N: the rows being packed (a whole matrix, or one segment of it); they become row blocks rb_off ... of a
-// packed matrix of RB row blocks in all.
-template <typename T, bool kVec>
-__global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __restrict__ W, int64_t N, int64_t K,
+// A segment's rows become row blocks row0 / 16 ... of a packed matrix of RB row blocks in all (segments start on row
+// blocks).
+template <typename T, bool kVec, int kSegs>
+__global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __restrict__ W_all, int64_t K,
                                                                     int64_t Kq /* quads per row */, int64_t RB,
-                                                                    int64_t rb_off, const double* __restrict__ partials,
-                                                                    int nparts, int64_t count, float* __restrict__ gamma_out,
-                                                                    int64_t nout, uint32_t* __restrict__ packed) {
+                                                                    SegList<kSegs> list, const double* __restrict__ partials,
+                                                                    float* __restrict__ gamma_out, uint32_t* __restrict__ packed) {
+    int sg = 0;
+    while (sg + 1 < list.n && (int)blockIdx.x >= list.s[sg + 1].pack0) ++sg;
+    const Seg& seg = list.s[sg];
+    const T* W = W_all + seg.row0 * K;
+    const int64_t N = seg.rows, rb_off = seg.row0 / kRowsPerBlock;
+    const int stride = seg.npack;
     __shared__ double sh_hi[kPackThreads / kWave];
     __shared__ double sh_lo[kPackThreads / kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int w = threadIdx.x >> 6;
     const int i = lane & 3;
-    const int64_t steps = ceil_div(Kq, 4);
-    const int64_t items = ceil_div(N, kRowsPerBlock) * steps;
+    const int steps = (int)ceil_div(Kq, 4);
+    const int items = (int)(ceil_div(N, kRowsPerBlock) * steps);      // N K < 2^40: below 2^29
     // lane 16 g + 4 t + j takes its word from lane 16 g + 4 j + t (which selected row t's word below)
     const int src = ((lane & 48) | ((lane & 3) << 2) | ((lane >> 2) & 3)) << 2;
 
-    auto load = [&](int64_t item, float (&f)[4][4]) {
+    auto load = [&](int item, float (&f)[4][4]) {
         item = items - 1 - item;
-        const int64_t rb = item / steps, s = item - rb * steps;
-        const int64_t k = 256 * s + 4 * lane;
+        const int rb = item / steps, s = item - rb * steps;
+        const int64_t k = 256 * (int64_t)s + 4 * lane;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const int64_t n = rb * kRowsPerBlock + 4 * w + t;
+            const int64_t n = (int64_t)rb * kRowsPerBlock + 4 * w + t;
 #pragma unroll
             for (int b = 0; b < 4; ++b) f[t][b] = 0.f;     // padding rows / columns quantize to code 0
             if (n < N) {
@@ -252,18 +276,18 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
     };
 
     float nxt[4][4];
-    int64_t item = blockIdx.x;
+    int item = (int)blockIdx.x - seg.pack0;
     if (item < items) load(item, nxt);
 
-    const float thr = pack_threshold(partials, nparts, count, gamma_out, nout, sh_hi, sh_lo);
+    const float thr = pack_threshold(partials, seg, gamma_out, sh_hi, sh_lo);
 
-    for (; item < items; item += gridDim.x) {
+    for (; item < items; item += stride) {
         float cur[4][4];
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
             for (int b = 0; b < 4; ++b) cur[t][b] = nxt[t][b];
-        if (item + gridDim.x < items) load(item + gridDim.x, nxt);
+        if (item + stride < items) load(item + stride, nxt);
         uint32_t c[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -274,8 +298,9 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
         }
         const uint32_t sel = i == 0 ? c[0] : i == 1 ? c[1] : i == 2 ? c[2] : c[3];
         const uint32_t out = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)sel);
-        const int64_t it = items - 1 - item;
-        const int64_t rb = it / steps, s = it - rb * steps;
+        const int it = items - 1 - item;
+        const int rb = it / steps;
+        const int64_t s = it - rb * steps;
         const int64_t nq = (Kq - 4 * s) < 4 ? (Kq - 4 * s) : 4;     // quads of this step (the last may hold fewer)
         const int g = lane >> 4;
         // word index inside the chunk: ((g * 16 + row) * 4 + j) with row = 4 w + t, and lane & 15 = 4 t + j
@@ -288,18 +313,24 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
 // half the bytes per request and ran at 2.9 TB/s (57344 x 8192, both passes: 496 us, now 350).  Two lanes complete a word; the pair holds the words of
 // the wave's four rows twice, so the even lane hands out rows 0 and 2, the odd lane rows 1 and 3, and two ds_bpermute per
 // step give lane 16 g + 4 t + j word j of quad column g for row 4w + t: four 64-byte runs per step, as above.
-__global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit_bf16x8(const uint16_t* __restrict__ W, int64_t N, int64_t K,
-                                                                           int64_t Kq, int64_t RB, int64_t rb_off,
-                                                                           const double* __restrict__ partials, int nparts, int64_t count,
-                                                                           float* __restrict__ gamma_out, int64_t nout,
-                                                                           uint32_t* __restrict__ packed) {
+template <int kSegs>
+__global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit_bf16x8(const uint16_t* __restrict__ W_all, int64_t K,
+                                                                           int64_t Kq, int64_t RB, SegList<kSegs> list,
+                                                                           const double* __restrict__ partials,
+                                                                           float* __restrict__ gamma_out, uint32_t* __restrict__ packed) {
+    int sg = 0;
+    while (sg + 1 < list.n && (int)blockIdx.x >= list.s[sg + 1].pack0) ++sg;
+    const Seg& seg = list.s[sg];
+    const uint16_t* W = W_all + seg.row0 * K;
+    const int64_t N = seg.rows, rb_off = seg.row0 / kRowsPerBlock;
+    const int stride = seg.npack;
     __shared__ double sh_hi[kPackThreads / kWave];
     __shared__ double sh_lo[kPackThreads / kWave];
     const int lane = threadIdx.x & (kWave - 1);
     const int w = threadIdx.x >> 6;
     const int odd = lane & 1;
     const int pairs = (int)ceil_div(Kq, 8);                // items per row block
-    const int items = (int)ceil_div(N, kRowsPerBlock) * pairs;      // N K < 2^40: below 2^28 + 2^28
+    const int items = (int)(ceil_div(N, kRowsPerBlock) * pairs);      // N K < 2^40: below 2^29
     const int t_out = (lane >> 2) & 3;
     const int src = (8 * (lane >> 4) + 2 * (lane & 3) + (t_out & 1)) << 2;      // of the item's first step; + 32 lanes for the second
 
@@ -316,16 +347,16 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit_bf16x8(const
     };
 
     uint4 nxt[4];
-    int item = blockIdx.x;
+    int item = (int)blockIdx.x - seg.pack0;
     if (item < items) load(item, nxt);
 
-    const float thr = pack_threshold(partials, nparts, count, gamma_out, nout, sh_hi, sh_lo);
+    const float thr = pack_threshold(partials, seg, gamma_out, sh_hi, sh_lo);
 
-    for (; item < items; item += gridDim.x) {
+    for (; item < items; item += stride) {
         uint4 cur[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) cur[t] = nxt[t];
-        if (item + (int)gridDim.x < items) load(item + gridDim.x, nxt);
+        if (item + stride < items) load(item + stride, nxt);
         uint32_t c[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -362,50 +393,70 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit_bf16x8(const
 int quant_weights_num_partials() { return 2048; }
 
 // 16-byte vectors of W that pass 1 reads with the streaming policy: all but the last 192 MB (the memory-side cache
-// holds 256 MB; what it keeps of W is what pass 3 reads first)
-static int64_t abs_sum_stream_vecs(int64_t count, int64_t esz) {
-    const int64_t keep = ((int64_t)192 << 20) / 16;
+// holds 256 MB; what it keeps of W is what pass 3 reads first); each of several segments keeps its share of the 192 MB
+static int64_t abs_sum_stream_vecs(int64_t count, int64_t esz, double share) {
+    const int64_t keep = (int64_t)(share * (double)(((int64_t)192 << 20) / 16));
     const int64_t nvec = count * esz / 16;
     return nvec > keep ? nvec - keep : 0;
 }
 
-static int abs_sum_blocks(int64_t count) {
-    const int64_t want = ceil_div(count, (int64_t)kSumThreads * 16);
-    return (int)(want < 1 ? 1 : (want > kSumBlocks ? kSumBlocks : want));
+static int abs_sum_blocks(int64_t count, double share) {
+    const int64_t want = ceil_div(count, (int64_t)kSumThreads * 16), most = (int64_t)(share * kSumBlocks + 0.5);
+    const int64_t b = want < most ? want : most;
+    return (int)(b < 1 ? 1 : b);
 }
 
-static void launch_abs_sum_partials(const void* W, bool bf16, int64_t count, double* partials, int blocks, hipStream_t stream) {
-    const int vec_ok = (reinterpret_cast<uintptr_t>(W) % 16) == 0;
-    if (bf16)
-        hipLaunchKernelGGL(abs_sum_partials<uint16_t>, dim3(blocks), dim3(kSumThreads), 0, stream,
-                           static_cast<const uint16_t*>(W), count, vec_ok, abs_sum_stream_vecs(count, 2), partials);
-    else
-        hipLaunchKernelGGL(abs_sum_partials<float>, dim3(blocks), dim3(kSumThreads), 0, stream,
-                           static_cast<const float*>(W), count, vec_ok, abs_sum_stream_vecs(count, 4), partials);
+static int pack_blocks(int64_t rows, int64_t K, double share) {
+    const int64_t items = ceil_div(rows, kRowsPerBlock) * ceil_div(K, 256), most = (int64_t)(share * kPackBlocks + 0.5);
+    const int64_t b = items < most ? items : most;
+    return (int)(b < 1 ? 1 : b);
+}
+
+// the segments seg_rows[0 .. n-1] that follow one another from row row0 of a matrix of K columns, n <= kSegs
+template <int kSegs>
+static SegList<kSegs> make_segs(const int64_t* seg_rows, int n, int64_t row0, int64_t K, int64_t esz) {
+    SegList<kSegs> list{};
+    int64_t total = 0;
+    for (int i = 0; i < n; ++i) total += seg_rows[i];
+    int part = 0, pack = 0;
+    list.n = n;
+    for (int i = 0; i < n; ++i) {
+        const int64_t rows = seg_rows[i];
+        const double share = (double)rows / (double)total;
+        const int np = abs_sum_blocks(rows * K, share), nk = pack_blocks(rows, K, share);
+        list.s[i] = Seg{row0, rows, rows * K, abs_sum_stream_vecs(rows * K, esz, share), row0 / kRowsPerBlock, ceil_div(rows, kRowsPerBlock),
+                        part, np, pack, nk};
+        row0 += rows; part += np; pack += nk;
+    }
+    return list;
+}
+static_assert(kSumBlocks + kMaxSegs <= 2048, "the workspace holds 2048 partial sums");
+
+template <int kSegs>
+static void launch_abs_sum_partials(const void* W, bool bf16, int64_t K, const SegList<kSegs>& list, double* partials, hipStream_t stream) {
+    const int vec_ok = (reinterpret_cast<uintptr_t>(W) % 16) == 0;       // a segment starts a multiple of 32 bytes further on
+    const dim3 grid((unsigned)(list.s[list.n - 1].part0 + list.s[list.n - 1].nparts)), block(kSumThreads);
+    if (bf16) hipLaunchKernelGGL((abs_sum_partials<uint16_t, kSegs>), grid, block, 0, stream, static_cast<const uint16_t*>(W), K, list, vec_ok, partials);
+    else      hipLaunchKernelGGL((abs_sum_partials<float, kSegs>), grid, block, 0, stream, static_cast<const float*>(W), K, list, vec_ok, partials);
 }
 
 // Eq. (3) as passes 1 and 2 (the 5-trit packing reads gamma from memory; the 2-bit packing folds pass 2 into pass 3)
 hipError_t launch_absmean_gamma(const void* W, bool bf16, int64_t N, int64_t K, float* gamma, void* workspace,
                                 hipStream_t stream, int64_t nout) {
-    const int64_t count = N * K;
     double* partials = static_cast<double*>(workspace);
-    const int blocks = abs_sum_blocks(count);
-    launch_abs_sum_partials(W, bf16, count, partials, blocks, stream);
-    hipLaunchKernelGGL(finish_gamma, dim3(1), dim3(kFinishThreads), 0, stream, partials, blocks, count, gamma, nout);
+    const SegList<1> list = make_segs<1>(&N, 1, 0, K, bf16 ? 2 : 4);
+    launch_abs_sum_partials(W, bf16, K, list, partials, stream);
+    hipLaunchKernelGGL(finish_gamma, dim3(1), dim3(kFinishThreads), 0, stream, partials, list.s[0].nparts, N * K, gamma, nout);
     return hipGetLastError();
 }
 
 hipError_t launch_abs_sum(const void* W, bool bf16, int64_t N, int64_t K, double* sum, void* workspace, hipStream_t stream) {
-    const int64_t count = N * K;
     double* partials = static_cast<double*>(workspace);
-    const int blocks = abs_sum_blocks(count);
-    launch_abs_sum_partials(W, bf16, count, partials, blocks, stream);
-    hipLaunchKernelGGL(fold_abs_sum, dim3(1), dim3(kFinishThreads), 0, stream, partials, blocks, sum);
+    const SegList<1> list = make_segs<1>(&N, 1, 0, K, bf16 ? 2 : 4);
+    launch_abs_sum_partials(W, bf16, K, list, partials, stream);
+    hipLaunchKernelGGL(fold_abs_sum, dim3(1), dim3(kFinishThreads), 0, stream, partials, list.s[0].nparts, sum);
     return hipGetLastError();
 }
-
-// 16-byte loads along the rows of a bf16 matrix
-static bool pack_bf16x8_ok(const void* W, int64_t K) { return K % 8 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0; }
 
 int quant_weights_max_sums() { return kPackThreads; }
 
@@ -414,60 +465,56 @@ hipError_t launch_gamma_from_sums(const double* sums, int nsums, int64_t total_c
     return hipGetLastError();
 }
 
-hipError_t launch_pack_2bit_with_sums(const void* W, bool bf16, int64_t N, int64_t K, const double* sums, int nsums,
-                                      int64_t total_count, void* packed, float* gamma, hipStream_t stream) {
+// pass 3 over the segments of a packed matrix of RB row blocks
+template <int kSegs>
+static void launch_pack(const void* W, bool bf16, int64_t K, int64_t RB, const SegList<kSegs>& list, const double* partials, void* packed,
+                        float* gamma, hipStream_t stream) {
     const size_t esz = bf16 ? 2 : 4;
     const bool vec = (reinterpret_cast<uintptr_t>(W) % (4 * esz)) == 0 && (K % 4 == 0);
+    const bool bf16x8 = bf16 && K % 8 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0;     // 16-byte loads along the rows
     const int64_t Kq = ceil_div(K, kColsPerQuad);
-    const int64_t RB = ceil_div(N, kRowsPerBlock);
-    const int64_t items = RB * ceil_div(Kq, 4);
-    dim3 grid((unsigned)(items < kPackBlocks ? items : kPackBlocks));
+    const dim3 grid((unsigned)(list.s[list.n - 1].pack0 + list.s[list.n - 1].npack)), block(kPackThreads);
     uint32_t* out = static_cast<uint32_t*>(packed);
-#define PACK(T_, V_) hipLaunchKernelGGL((ternarize_pack_2bit<T_, V_>), grid, dim3(kPackThreads), 0, stream, w, N, K, Kq, RB, (int64_t)0, \
-                                        sums, nsums, total_count, gamma, (int64_t)1, out)
-#define PACK_BF16X8() hipLaunchKernelGGL(ternarize_pack_2bit_bf16x8, grid, dim3(kPackThreads), 0, stream, w, N, K, Kq, RB, (int64_t)0, \
-                                         sums, nsums, total_count, gamma, (int64_t)1, out)
-    if (bf16) {
-        const uint16_t* w = static_cast<const uint16_t*>(W);
-        if (pack_bf16x8_ok(W, K)) PACK_BF16X8(); else if (vec) PACK(uint16_t, true); else PACK(uint16_t, false);
-    } else {
-        const float* w = static_cast<const float*>(W);
-        if (vec) PACK(float, true); else PACK(float, false);
-    }
+#define PACK(T_, V_) hipLaunchKernelGGL((ternarize_pack_2bit<T_, V_, kSegs>), grid, block, 0, stream, static_cast<const T_*>(W), K, Kq, RB, list, \
+                                        partials, gamma, out)
+    if (bf16x8) hipLaunchKernelGGL((ternarize_pack_2bit_bf16x8<kSegs>), grid, block, 0, stream, static_cast<const uint16_t*>(W), K, Kq, RB, list,
+                                   partials, gamma, out);
+    else if (bf16) { if (vec) PACK(uint16_t, true); else PACK(uint16_t, false); }
+    else { if (vec) PACK(float, true); else PACK(float, false); }
 #undef PACK
-#undef PACK_BF16X8
+}
+
+hipError_t launch_pack_2bit_with_sums(const void* W, bool bf16, int64_t N, int64_t K, const double* sums, int nsums,
+                                      int64_t total_count, void* packed, float* gamma, hipStream_t stream) {
+    SegList<1> list = make_segs<1>(&N, 1, 0, K, bf16 ? 2 : 4);
+    list.s[0].nparts = nsums;
+    list.s[0].count = total_count;
+    list.s[0].nout = 1;
+    launch_pack(W, bf16, K, ceil_div(N, kRowsPerBlock), list, sums, packed, gamma, stream);
     return hipGetLastError();
 }
 
 hipError_t launch_quantize_weights_2bit(const void* W, bool bf16, int64_t N, int64_t K, void* packed,
-                                        float* gamma, void* workspace, hipStream_t stream, int64_t rb_off,
-                                        int64_t rb_total, int64_t nout) {
-    const int64_t count = N * K;
+                                        float* gamma, void* workspace, hipStream_t stream) {
     double* partials = static_cast<double*>(workspace);
-    const int blocks = abs_sum_blocks(count);
-    const size_t esz = bf16 ? 2 : 4;
-    const bool vec = (reinterpret_cast<uintptr_t>(W) % (4 * esz)) == 0 && (K % 4 == 0);
-    launch_abs_sum_partials(W, bf16, count, partials, blocks, stream);
+    SegList<1> list = make_segs<1>(&N, 1, 0, K, bf16 ? 2 : 4);
+    list.s[0].nout = 1;
+    launch_abs_sum_partials(W, bf16, K, list, partials, stream);
+    launch_pack(W, bf16, K, ceil_div(N, kRowsPerBlock), list, partials, packed, gamma, stream);
+    return hipGetLastError();
+}
 
-    const int64_t Kq = ceil_div(K, kColsPerQuad);
-    const int64_t RB = ceil_div(N, kRowsPerBlock);                       // row blocks packed by this call
-    const int64_t RBT = rb_total > 0 ? rb_total : RB;                      // ... of the whole packed matrix
-    const int64_t items = RB * ceil_div(Kq, 4);
-    dim3 grid((unsigned)(items < kPackBlocks ? items : kPackBlocks));
-    uint32_t* out = static_cast<uint32_t*>(packed);
-#define PACK(T_, V_) hipLaunchKernelGGL((ternarize_pack_2bit<T_, V_>), grid, dim3(kPackThreads), 0, stream, w, N, K, Kq, RBT, rb_off, \
-                                        partials, blocks, count, gamma, nout, out)
-#define PACK_BF16X8() hipLaunchKernelGGL(ternarize_pack_2bit_bf16x8, grid, dim3(kPackThreads), 0, stream, w, N, K, Kq, RBT, rb_off, \
-                                         partials, blocks, count, gamma, nout, out)
-    if (bf16) {
-        const uint16_t* w = static_cast<const uint16_t*>(W);
-        if (pack_bf16x8_ok(W, K)) PACK_BF16X8(); else if (vec) PACK(uint16_t, true); else PACK(uint16_t, false);
-    } else {
-        const float* w = static_cast<const float*>(W);
-        if (vec) PACK(float, true); else PACK(float, false);
+hipError_t launch_quantize_weights_2bit_segmented(const void* W, bool bf16, int64_t N, int64_t K, const int64_t* seg_rows, int nseg,
+                                                  void* packed, float* gamma_rb, void* workspace, hipStream_t stream) {
+    double* partials = static_cast<double*>(workspace);
+    int64_t row0 = 0;
+    for (int first = 0; first < nseg; first += kMaxSegs) {               // groups use the workspace one after the other (stream order)
+        const int n = nseg - first < kMaxSegs ? nseg - first : kMaxSegs;
+        const SegList<kMaxSegs> list = make_segs<kMaxSegs>(seg_rows + first, n, row0, K, bf16 ? 2 : 4);
+        launch_abs_sum_partials(W, bf16, K, list, partials, stream);
+        launch_pack(W, bf16, K, ceil_div(N, kRowsPerBlock), list, partials, packed, gamma_rb, stream);
+        for (int i = 0; i < n; ++i) row0 += seg_rows[first + i];
     }
-#undef PACK
-#undef PACK_BF16X8
     return hipGetLastError();
 }
 

@@ -36,3 +36,24 @@ def test_pack_bf16_rows_of_eight(gpu_lib, N, K):
     W, bits = synth.to_bf16(synth.weights(N, K, config=2, layer=N % 5))
     packed, gamma = gpu_lib.quantize_weights(dev_bf16(bits).view(N, K))
     check_packed(gpu_lib, W, packed, gamma)
+
+
+# segments quantized side by side: very unequal ones, more than one launch takes (16), rows of every load width
+@pytest.mark.parametrize("rows,K,bf16", [([16] * 17 + [5], 40, False), ([4096, 16, 7], 264, True), ([16, 2048, 512, 512], 1030, False),
+                                         ([3200, 3200, 3200], 520, True), ([48] * 35, 77, True)])
+def test_segments_side_by_side(gpu_lib, rows, K, bf16):
+    N = sum(rows)
+    W = synth.weights(N, K, config=1, layer=len(rows)) * np.repeat(np.linspace(0.5, 2.0, len(rows)), rows).astype(np.float32)[:, None]
+    bits = None
+    if bf16:
+        W, bits = synth.to_bf16(W)
+    packed, gamma_rb = gpu_lib.quantize_weights_segmented(dev_bf16(bits).view(N, K) if bf16 else dev(W), rows)
+    dec, pad_zero = decode_2bit(packed.cpu().numpy(), N, K)
+    assert pad_zero
+    g, row = gamma_rb.cpu().numpy(), 0
+    for r in rows:
+        codes_ref, gamma_ref = oracle.quantize_weights(np.ascontiguousarray(W[row:row + r]))
+        assert np.array_equal(dec[row:row + r], codes_ref)
+        blocks = g[row // 16:(row + r + 15) // 16]
+        assert np.all(blocks.view(np.uint32) == np.float32(gamma_ref).view(np.uint32))
+        row += r
