@@ -250,7 +250,8 @@ bitnet_status bitnet_swiglu_quantize(const void* gu, bitnet_dtype gu_dtype, int6
  *            accumulator, no scaling); element-aligned
  * The kernel is chosen by shape: the weight-streaming decode kernels for M <= 64 (and up to 256 tokens, with
  * K >= 5120 up to 512, on layers small enough that 256 workgroups of token tiles cover them: up to 4096-12288 output
- * features), the MFMA GEMM above, the reference kernel when xq is not 16-byte aligned or K is not a multiple of 16.
+ * features), the MFMA GEMM above; when xq is not 16-byte aligned or K is not a multiple of 16, forms of the decode kernel
+ * (up to 16 tokens) and of the GEMM that take rows of any length and alignment.
  */
 bitnet_status bitnet_linear(const int8_t* xq, const float* sx, const void* packed, const float* gamma,
                             int64_t M, int64_t N, int64_t K, bitnet_format f,
@@ -275,7 +276,9 @@ bitnet_status bitnet_linear_variant(const int8_t* xq, const float* sx, const voi
  *     batched_decode_loader  depth, LDS lookahead (the second form has a wave that only copies activations)
  *     prefill                tile tokens, tile rows, and 2 as a third parameter for the eight-wave form with two
  *                            K groups (512 tile rows: the eight-wave form with two row groups); grid y = split-K factor
- *     reference, trit5_decode, trit5_reference: no parameters
+ *     reference              K not a multiple of 16: parameters of the decode kernel (x_q source 8) or of the prefill tile
+ *                            that takes such rows; none for one thread per output
+ *     trit5_decode, trit5_reference: no parameters
  *   5-trit weights, more than 16 tokens and a workspace that holds the 2-bit copy (bitnet_linear_workspace_format):
  *   the plan of the 2-bit launch that follows the repacking pass, with " repack=trit5_to_2bit" appended
  */

@@ -26,6 +26,21 @@ __device__ inline uint4 load_streaming_b128(const void* p) {
     return make_uint4(r.x, r.y, r.z, r.w);
 }
 
+// 16 bytes from an address of any alignment, of which the first `avail` exist (the rest read as zero and are not touched).
+__device__ inline uint4 load_any16(const int8_t* p, int64_t avail) {
+    uint4 v = make_uint4(0, 0, 0, 0);
+    if (avail >= 16) {
+        __builtin_memcpy(&v, p, 16);                 // one 16-byte load: the hardware takes it at byte alignment
+    } else {
+        uint32_t u[4] = {0, 0, 0, 0};
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            if (i < avail) u[i >> 2] |= (uint32_t)(uint8_t)p[i] << (8 * (i & 3));
+        v = make_uint4(u[0], u[1], u[2], u[3]);
+    }
+    return v;
+}
+
 // bf16 bit pattern -> fp32 (exact).
 __device__ inline float bf16_to_f32(uint16_t h) { return __uint_as_float(((uint32_t)h) << 16); }
 

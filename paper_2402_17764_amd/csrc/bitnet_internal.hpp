@@ -92,6 +92,14 @@ hipError_t launch_linear_gemv_2bit(const int8_t* xq, const float* sx, const void
 // the M <= 16 kernel alone (linear_gemv.hip); launch_linear_gemv_2bit (linear_skinny.hip) routes M <= 4 to it
 hipError_t launch_linear_gemv16_2bit(const int8_t* xq, const float* sx, const void* packed, const float* gamma, int gstride,
                                      int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan = nullptr);
+// x_q rows of any length and alignment (K not a multiple of 16, or x_q not 16-byte aligned): up to 16 tokens that fit the LDS ...
+bool gemv_any_supports(int64_t M, int64_t N, int64_t K);
+hipError_t launch_linear_gemv_any_2bit(const int8_t* xq, const float* sx, const void* packed, const float* gamma, int gstride,
+                                       int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan = nullptr);
+// ... and any number (linear_gemm.hip)
+bool gemm_any_supports(int64_t N);
+hipError_t launch_linear_gemm_any_2bit(const int8_t* xq, const float* sx, const void* packed, const float* gamma, int gstride,
+                                       int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan = nullptr);
 bool gemv_fused_supports(int64_t M, int64_t N, int64_t K, const void* x);
 hipError_t launch_linear_fused_2bit(const void* x, bool bf16, const void* packed, const float* gamma, int gstride,
                                     int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream,

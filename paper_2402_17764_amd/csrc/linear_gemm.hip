@@ -28,6 +28,9 @@
 //     tile (128 x 512): both groups read the same activation stages, so the CU fetches a third less per MFMA than two
 //     separate workgroups do -- the K loop's losses are waves held at the issue of their loads while the vector-memory
 //     queues are full, and they shrink with the bytes a CU pulls in;
+//   * for activations whose rows are no multiple of 16 bytes (K not a multiple of 16, or an unaligned x_q), forms of the
+//     64-token tiles that stage them through registers instead: 16-byte loads at byte alignment, requested before the
+//     MFMAs of a step and written to LDS after them (LDS-direct loads want aligned addresses);
 //   * the epilogue rescales in registers, transposes each 32 x 64 fragment row through LDS and writes
 //     whole 16-byte pieces of output rows;
 //   * tile order: consecutive workgroups take consecutive token tiles of the same weight tile, so the
@@ -177,7 +180,8 @@ __device__ inline void gemm_epilogue(v16i (&acc)[kFM][kFN], const GemmOutCtx& c)
 
 // One output tile of 32 * kFM tokens (first token row0) x 128 * kFN * kNG weight rows (tile bn), by kKG * kNG groups of
 // four waves: kKG > 1 splits the K steps over the groups, kNG > 1 the weight rows (one of the two is 1).
-template <int kFM, int kFN, int kKG, int kNG>
+// kAny: activation rows of any length and alignment.
+template <int kFM, int kFN, int kKG, int kNG, bool kAny>
 __device__ __forceinline__ void gemm_tile(
         const int8_t* __restrict__ xq, const float* __restrict__ sx, const uint4* __restrict__ packed,
         const float* __restrict__ gamma, int gstride, int M, int64_t N, int64_t K, int Kq, int RB, int row0, int bn,
@@ -262,6 +266,23 @@ __device__ __forceinline__ void gemm_tile(
             __builtin_amdgcn_raw_ptr_buffer_load_lds(xrsrc, (__attribute__((address_space(3))) void*)(dst_stage + (copier * (4 * kCopies) + t * 4) * 256),
                                                      16, xoff[t], 0, 0, 0);
     };
+    // kAny: the same pieces of the stage through registers.  Bytes between K and the row's padded end belong to the next row
+    // and meet zero codes; only the end of x_q itself has to be kept to.
+    uint4 xr[kAny ? kCopies : 1];
+    auto fetch_x = [&](int step) {
+#pragma unroll
+        for (int t = 0; t < (kAny ? kCopies : 0); ++t) {
+            const int row = copier * (4 * kCopies) + t * 4 + cp_row;
+            const int64_t col = (int64_t)step * 256 + ((cp_slot ^ (row & 15)) << 4);
+            const int64_t m = row0 + min(row, rows_here - 1);
+            xr[t] = load_any16(xq + m * K + col, col < K ? M * K - (m * K + col) : 0);
+        }
+    };
+    auto put_x = [&](int stage) {
+#pragma unroll
+        for (int t = 0; t < (kAny ? kCopies : 0); ++t)
+            *reinterpret_cast<uint4*>(glds + stage * kGemmStageBytes + (copier * (4 * kCopies) + t * 4) * 256 + lane * 16) = xr[t];
+    };
     // For the weights a raw buffer per step as well: one whole step of the packed layout (RB KiB), the lane's
     // byte offset in it as the vector offset -- no 64-bit address arithmetic per load.
     auto load_w = [&](uint4 (&wq)[kFN][2], int step) {
@@ -342,7 +363,7 @@ __device__ __forceinline__ void gemm_tile(
     const int per_group = (step1 - step0 + kKG - 1) / kKG;
     const int my0 = step0 + grp * per_group, my1 = min(step1, my0 + per_group);
     auto issue = [&](uint4 (&into)[kFN][2], int step) {
-        copy_x(step, (step - my0) & 1);
+        if (kAny) fetch_x(step); else copy_x(step, (step - my0) & 1);
         if (step < full_steps) load_w(into, step); else load_w_tail(into, step);
     };
     auto one_step = [&](uint4 (&wcur)[kFN][2], uint4 (&wnxt)[kFN][2], int s) {
@@ -354,9 +375,13 @@ __device__ __forceinline__ void gemm_tile(
             const uint32_t km[2] = {keep_t0 | all, keep_t1 | all};
             if (s + 1 < my1) issue(wnxt, s + 1);
             compute(wcur, km, (s - my0) & 1);
+            if (kAny && s + 1 < my1) put_x((s + 1 - my0) & 1);     // every wave left that stage before this step's barrier
         }
     };
-    if (my0 < my1) issue(wa, my0);
+    if (my0 < my1) {
+        issue(wa, my0);
+        if (kAny) put_x(0);
+    }
     int it = 0;
 #pragma unroll 1
     for (; it + 1 < per_group; it += 2) {
@@ -408,8 +433,8 @@ constexpr int gemm_blocks_per_cu(int fm, int fn) { return fn == 1 ? (fm == 2 ? 4
 
 // blockIdx.y selects a split of the K steps (split-K: every split stores its int32 partial accumulators, [M][N] each,
 // one after the other at y; a second kernel adds them up and rescales).  One split: the whole product, stored as yt.
-template <int kFM, int kFN, int kKG = 1, int kNG = 1>
-__global__ __launch_bounds__(kGemmThreads * kKG * kNG, kKG * kNG > 1 ? 1 : gemm_blocks_per_cu(kFM, kFN)) void linear_gemm_2bit(
+template <int kFM, int kFN, int kKG = 1, int kNG = 1, bool kAny = false>
+__global__ __launch_bounds__(kGemmThreads * kKG * kNG, kKG * kNG > 1 ? 1 : gemm_blocks_per_cu(kFM, kFN) - (kAny ? 1 : 0)) void linear_gemm_2bit(
         const int8_t* __restrict__ xq, const float* __restrict__ sx, const uint4* __restrict__ packed,
         const float* __restrict__ gamma, int gstride, int M, int64_t N, int64_t K, int Kq, int RB, int tiles_m,
         int steps_per_split, void* __restrict__ y, OutType yt, int vec_store) {
@@ -418,7 +443,7 @@ __global__ __launch_bounds__(kGemmThreads * kKG * kNG, kKG * kNG > 1 ? 1 : gemm_
     const int step0 = blockIdx.y * steps_per_split;
     const int step1 = min(steps, step0 + steps_per_split);
     void* yp = static_cast<char*>(y) + (int64_t)blockIdx.y * M * N * 4;        // blockIdx.y > 0 only with int32 partials
-    gemm_tile<kFM, kFN, kKG, kNG>(xq, sx, packed, gamma, gstride, M, N, K, Kq, RB, (b % tiles_m) * (32 * kFM), b / tiles_m, step0, step1,
+    gemm_tile<kFM, kFN, kKG, kNG, kAny>(xq, sx, packed, gamma, gstride, M, N, K, Kq, RB, (b % tiles_m) * (32 * kFM), b / tiles_m, step0, step1,
                         yp, yt, vec_store);
 }
 
@@ -469,13 +494,13 @@ bool gemm_supports(int64_t M, int64_t N, int64_t K, const void* xq) {
     return M >= 1 && K % 16 == 0 && reinterpret_cast<uintptr_t>(xq) % 16 == 0 && ceil_div(N, kRowsPerBlock) < ((int64_t)1 << 21);
 }
 
-template <int kFM, int kFN, int kKG = 1, int kNG = 1>
+template <int kFM, int kFN, int kKG = 1, int kNG = 1, bool kAny = false>
 static hipError_t launch_gemm_tiles(const int8_t* xq, const float* sx, const void* packed, const float* gamma,
                                     int gstride, int64_t M, int64_t N, int64_t K, void* y, OutType yt,
                                     hipStream_t stream, int splits = 1, void* workspace = nullptr, LaunchPlan* plan = nullptr) {
     if (!plan) {
         static RaisedFlags raised = {};
-        const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(linear_gemm_2bit<kFM, kFN, kKG, kNG>), gemm_lds_bytes(kFM, kFN, kKG, kNG), raised);
+        const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(linear_gemm_2bit<kFM, kFN, kKG, kNG, kAny>), gemm_lds_bytes(kFM, kFN, kKG, kNG), raised);
         if (e != hipSuccess) return e;
     }
     const int Kq = (int)ceil_div(K, kColsPerQuad);
@@ -492,12 +517,13 @@ static hipError_t launch_gemm_tiles(const int8_t* xq, const float* sx, const voi
     const size_t esz = ot == OutType::BF16 ? 2 : 4;
     const int vec_store = (reinterpret_cast<uintptr_t>(out) % 16 == 0) && ((N * esz) % 16 == 0);
     if (plan) {
-        if (kNG > 1) plan->set("prefill", {32 * kFM, 128 * kFN * kNG}, (unsigned)(tiles_m * tiles_n), (unsigned)splits, kGemmThreads * kNG, gemm_lds_bytes(kFM, kFN, 1, kNG), splits);
-        else if (kKG > 1) plan->set("prefill", {32 * kFM, 128 * kFN, kKG}, (unsigned)(tiles_m * tiles_n), (unsigned)splits, kGemmThreads * kKG, gemm_lds_bytes(kFM, kFN, kKG), splits);
-        else plan->set("prefill", {32 * kFM, 128 * kFN}, (unsigned)(tiles_m * tiles_n), (unsigned)splits, kGemmThreads, gemm_lds_bytes(kFM, kFN, 1), splits);
+        const char* family = kAny ? "reference" : "prefill";
+        if (kNG > 1) plan->set(family, {32 * kFM, 128 * kFN * kNG}, (unsigned)(tiles_m * tiles_n), (unsigned)splits, kGemmThreads * kNG, gemm_lds_bytes(kFM, kFN, 1, kNG), splits);
+        else if (kKG > 1) plan->set(family, {32 * kFM, 128 * kFN, kKG}, (unsigned)(tiles_m * tiles_n), (unsigned)splits, kGemmThreads * kKG, gemm_lds_bytes(kFM, kFN, kKG), splits);
+        else plan->set(family, {32 * kFM, 128 * kFN}, (unsigned)(tiles_m * tiles_n), (unsigned)splits, kGemmThreads, gemm_lds_bytes(kFM, kFN, 1), splits);
         return hipSuccess;
     }
-    hipLaunchKernelGGL((linear_gemm_2bit<kFM, kFN, kKG, kNG>), dim3((unsigned)(tiles_m * tiles_n), (unsigned)splits), dim3(kGemmThreads * kKG * kNG),
+    hipLaunchKernelGGL((linear_gemm_2bit<kFM, kFN, kKG, kNG, kAny>), dim3((unsigned)(tiles_m * tiles_n), (unsigned)splits), dim3(kGemmThreads * kKG * kNG),
                        gemm_lds_bytes(kFM, kFN, kKG, kNG), stream, xq, sx, static_cast<const uint4*>(packed), gamma, gstride, (int)M, N, K, Kq, RB,
                        tiles_m, sps, out, ot, vec_store);
     if (split)
@@ -518,6 +544,21 @@ hipError_t launch_linear_gemm_2bit_shape(int fm, int fn, int kg, const int8_t* x
     GEMM_SHAPE(4, 2, 3);
 #undef GEMM_SHAPE
     return hipErrorInvalidValue;
+}
+
+bool gemm_any_supports(int64_t N) { return ceil_div(N, kRowsPerBlock) < ((int64_t)1 << 21); }
+
+// Activation rows of any length and alignment.  64-token tiles only (staging through registers takes 16 of them there).
+// Up to one 64 x 128 tile per CU: eight waves in two K groups; up to four: the same tile with four waves; beyond, 64 x 256.
+// 77 tokens, 2050 -> 1003, quantization included: 422 us with one thread per output, 24 with these (two calls; the host bounds it).
+hipError_t launch_linear_gemm_any_2bit(const int8_t* xq, const float* sx, const void* packed, const float* gamma, int gstride,
+                                       int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan) {
+    const int64_t tiles = ceil_div(M, 64) * ceil_div(N, 128);
+    if (tiles <= 256 && K > 256)
+        return launch_gemm_tiles<2, 1, 2, 1, true>(xq, sx, packed, gamma, gstride, M, N, K, y, yt, stream, 1, nullptr, plan);
+    if (tiles <= 1024)
+        return launch_gemm_tiles<2, 1, 1, 1, true>(xq, sx, packed, gamma, gstride, M, N, K, y, yt, stream, 1, nullptr, plan);
+    return launch_gemm_tiles<2, 2, 1, 1, true>(xq, sx, packed, gamma, gstride, M, N, K, y, yt, stream, 1, nullptr, plan);
 }
 
 size_t splitk_workspace_bytes(int64_t M, int64_t N, int splits) { return (size_t)splits * (size_t)M * (size_t)N * 4; }

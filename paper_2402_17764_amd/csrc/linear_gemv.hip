@@ -39,7 +39,8 @@ enum XMode : int {
     kXNormBf16 = 4,    // bf16 x: RMSNorm (with an optional gain) and the quantization done in the kernel
     kXNormF32 = 5,     // fp32 x, same
     kXSwigluBf16 = 6,  // bf16 [gate | up] rows of 2 K elements: SwiGLU gating and the quantization done in the kernel
-    kXSwigluF32 = 7    // fp32, same
+    kXSwigluF32 = 7,   // fp32, same
+    kXLdsAny = 8       // int8 x_q rows of any length and alignment, copied once per workgroup into LDS
 };
 // what the fused modes do to a token before its absmax quantization
 enum PreOp : int { kPreNone = 0, kPreRmsNorm = 1, kPreSwiglu = 2 };
@@ -317,7 +318,7 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_gemv16_2bit(
     extern __shared__ uint4 smem[];
     constexpr int kThreads = kS * kW * kWave;
     constexpr bool kFromLds = kX != kXGlobal;
-    constexpr bool kFused = kX >= kXFusedBf16;
+    constexpr bool kFused = kX >= kXFusedBf16 && kX <= kXSwigluF32;
     constexpr bool kNorm = kX == kXNormBf16 || kX == kXNormF32;
     constexpr bool kSwiglu = kX == kXSwigluBf16 || kX == kXSwigluF32;
     constexpr int kPre = kNorm ? kPreRmsNorm : kSwiglu ? kPreSwiglu : kPreNone;
@@ -428,12 +429,16 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_gemv16_2bit(
     for (int d = 0; d < kD; ++d) load(st[d], d);
     __builtin_amdgcn_sched_barrier(0);
 
-    if (kX == kXLds) {
+    if (kX == kXLds || kX == kXLdsAny) {
         const int nvec = M * (Kpad >> 4);
         for (int v = threadIdx.x; v < nvec; v += kThreads) {
             const int m = v / (Kpad >> 4), kv = v % (Kpad >> 4);
             uint4 val = make_uint4(0, 0, 0, 0);
-            if ((int64_t)kv * 16 + 16 <= K) val = reinterpret_cast<const uint4*>(xq + (int64_t)m * K)[kv];
+            if (kX == kXLdsAny) {                      // past the row: the next one's bytes meet zero codes, the end of x_q is kept to
+                if ((int64_t)kv * 16 < K) val = load_any16(xq + (int64_t)m * K + (int64_t)kv * 16, (int64_t)(M - m) * K - (int64_t)kv * 16);
+            } else if ((int64_t)kv * 16 + 16 <= K) {
+                val = reinterpret_cast<const uint4*>(xq + (int64_t)m * K)[kv];
+            }
             xlds[v] = val;
         }
         __syncthreads();
@@ -518,6 +523,7 @@ static size_t gemv16_x_lds_bytes(int64_t M, int64_t K) { return (size_t)M * ceil
 constexpr int kModesInt8 = 1;    // kXGlobal, kXLds
 constexpr int kModesFused = 2;   // kXFusedBf16, kXFusedF32
 constexpr int kModesPre = 4;     // RMSNorm and SwiGLU pre-operations
+constexpr int kModesAny = 8;     // kXLdsAny
 
 template <int kR, int kS, int kW, int kD, int kModes>
 static hipError_t launch16(int xmode, const void* x, const float* sx, const void* packed, const float* gamma, int gstride,
@@ -533,10 +539,10 @@ static hipError_t launch16(int xmode, const void* x, const float* sx, const void
     if (xmode == kXLds && header + lds_x > kGemvLdsBudget) xmode = kXGlobal;
     const size_t lds = header + (xmode != kXGlobal && lds_x > lds_fold ? lds_x : lds_fold);
     dim3 grid((unsigned)ceil_div(RB, kW * kR)), block(kS * kW * kWave);
-    const int need = xmode <= kXLds ? kModesInt8 : xmode <= kXFusedF32 ? kModesFused : kModesPre;
+    const int need = xmode == kXLdsAny ? kModesAny : xmode <= kXLds ? kModesInt8 : xmode <= kXFusedF32 ? kModesFused : kModesPre;
     if ((kModes & need) == 0) return hipErrorInvalidDeviceFunction;   // a dispatch rule asked a launch shape for a mode it is not built for
     if (plan) {
-        plan->set("decode", {kR, kS, kW, kD, xmode}, grid.x, 1, block.x, lds, 1);
+        plan->set(xmode == kXLdsAny ? "reference" : "decode", {kR, kS, kW, kD, xmode}, grid.x, 1, block.x, lds, 1);
         return hipSuccess;
     }
     const uint4* p = static_cast<const uint4*>(packed);
@@ -555,6 +561,9 @@ static hipError_t launch16(int xmode, const void* x, const float* sx, const void
         if (xmode == kXNormF32) { GO(kXNormF32); return hipGetLastError(); }
         if (xmode == kXSwigluBf16) { GO(kXSwigluBf16); return hipGetLastError(); }
         if (xmode == kXSwigluF32) { GO(kXSwigluF32); return hipGetLastError(); }
+    }
+    if constexpr ((kModes & kModesAny) != 0) {
+        if (xmode == kXLdsAny) { GO(kXLdsAny); return hipGetLastError(); }
     }
 #undef GO
     return hipErrorInvalidDeviceFunction;
@@ -685,6 +694,20 @@ static hipError_t dispatch16_fused(int xmode, const void* x, const void* packed,
     } else {
         GEMV16(1, 2, 2, 4, kModesFused | kModesPre, xmode);
     }
+}
+
+// x_q rows of any length and alignment, up to 16 tokens that fit the LDS: two K-split waves per row block where there are many
+// row blocks, four otherwise (the picks of the aligned kernel for one token on the same layers).
+bool gemv_any_supports(int64_t M, int64_t N, int64_t K) {
+    (void)N;
+    return M >= 1 && M <= 16 && kGemvLdsHeader * sizeof(uint4) + gemv16_x_lds_bytes(M, K) <= kGemvLdsBudget;
+}
+hipError_t launch_linear_gemv_any_2bit(const int8_t* x, const float* sx, const void* packed, const float* gamma, int gstride, int64_t M,
+                                       int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan) {
+    const float* gain = nullptr;
+    const float eps = 0.0f;
+    if (ceil_div(N, kRowsPerBlock) >= 1024) GEMV16(1, 2, 2, 4, kModesAny, kXLdsAny);
+    GEMV16(1, 4, 1, 4, kModesAny, kXLdsAny);
 }
 #undef GEMV16
 

@@ -57,3 +57,33 @@ def test_segments_side_by_side(gpu_lib, rows, K, bf16):
         blocks = g[row // 16:(row + r + 15) // 16]
         assert np.all(blocks.view(np.uint32) == np.float32(gamma_ref).view(np.uint32))
         row += r
+
+
+# x_q rows of any length and alignment: the decode form (up to 16 tokens, both its launch shapes, K below one 16-byte piece,
+# below and above one K step) and the tiles of the GEMM (two K groups, four waves, 64 x 256), each with ragged rows and tokens
+@pytest.mark.parametrize("M,N,K", [(1, 1, 1), (1, 40, 7), (3, 100, 255), (16, 33, 1001), (2, 16400, 259), (1, 300, 4097),
+                                   (17, 130, 5), (64, 128, 255), (65, 129, 257), (77, 1003, 2050), (100, 3000, 513), (200, 1000, 3333),
+                                   (1030, 2500, 301), (700, 25000, 77), (16, 50, 8001)])
+@pytest.mark.parametrize("y", ["I32", "F32", "BF16"])
+def test_rows_of_any_length(gpu_lib, M, N, K, y):
+    packed, gamma = gpu_lib.quantize_weights(dev(synth.weights(N, K, config=1, layer=M % 7)))
+    xq, sx = gpu_lib.quantize_acts(dev(synth.activations(M, K, config=1, layer=N % 7)))
+    yt = getattr(gpu_lib, y)
+    # x_q at the end of its allocation, one byte past an aligned address: nothing behind it may be needed
+    buf = torch.empty(M * K + 1, dtype=torch.int8, device="cuda")
+    buf[1:] = xq.reshape(-1)
+    big = torch.full((M * N + 64,), 7, dtype=gpu_lib._OUT[yt], device="cuda")
+    want = gpu_lib.linear(xq, sx, packed, gamma, N, y_dtype=yt, kernel=gpu_lib.KERNEL_REFERENCE)
+    assert torch.equal(gpu_lib.linear(xq, sx, packed, gamma, N, y_dtype=yt), want)
+    assert torch.equal(gpu_lib.linear(buf[1:].view(M, K), sx, packed, gamma, N, y_dtype=yt, y=big[:M * N].view(M, N)), want)
+    assert bool((big[M * N:] == 7).all())
+
+
+@pytest.mark.parametrize("M,N,K", [(5, 100, 130), (40, 300, 1030)])
+def test_rows_of_any_length_with_a_gamma_per_block(gpu_lib, M, N, K):
+    rows = [48, N - 48]
+    packed, gamma_rb = gpu_lib.quantize_weights_segmented(dev(synth.weights(N, K, config=1, layer=1)), rows)
+    xq, sx = gpu_lib.quantize_acts(dev(synth.activations(M, K, config=1, layer=2)))
+    want = gpu_lib.linear_segmented(xq, sx, packed, gamma_rb, N, kernel=gpu_lib.KERNEL_REFERENCE)
+    got = gpu_lib.linear_segmented(xq, sx, packed, gamma_rb, N)
+    assert torch.allclose(got, want, rtol=3 * 2.0 ** -23, atol=0.0)      # gamma * (s_x / 127) or (gamma * s_x) / 127: two roundings
