@@ -3,6 +3,7 @@
 Marshalling only: every function takes torch tensors that already live on the GPU (torch is used
 for device memory and streams, nothing else), checks dtype / shape / contiguity, passes raw device
 pointers and the current HIP stream through the C ABI, and raises BitnetError on a non-zero status.
+The entry points that a decode or prefill step calls once per layer do all of that in C++ (csrc/call.cpp, built as _call.so).
 There is no fallback: if the shared library has not been built, load() raises.  BITNET_HIP_LIBRARY names another build
 of the same library to load instead (the host-sanitized one of paper_2402_17764_amd.build.build_library(sanitize=True)).
 """
@@ -39,6 +40,7 @@ SYMBOLS = [
 ]
 
 _lib = None
+_call = None          # the native marshalling of the hot entry points, bound to _lib
 
 
 class BitnetError(RuntimeError):
@@ -50,7 +52,7 @@ class BitnetError(RuntimeError):
 
 def load():
     """Load libbitnet_hip.so (built by paper_2402_17764_amd.build).  Raises if it is missing."""
-    global _lib
+    global _lib, _call
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -89,8 +91,19 @@ def load():
     lib.bitnet_ffn_gate_up_fused.argtypes = [vp, ci, ci, vp, ctypes.c_float, vp, vp, ci, i64, i64, i64, ci, vp, ci, vp]
     for name in SYMBOLS[2:]:
         getattr(lib, name).restype = ci
-    _lib = lib
+    try:
+        from . import _call as native
+    except ImportError as e:
+        raise RuntimeError("native call path not built: run `python -m paper_2402_17764_amd.build` (%s)" % e)
+    native.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in SYMBOLS}, BitnetError)
+    _call, _lib = native, lib
     return lib
+
+
+def _native():
+    if _call is None:
+        load()
+    return _call
 
 
 def _check(status, where):
@@ -198,67 +211,24 @@ def quantize_weights_sharded(W, sums, total_rows, fmt=PACK_2BIT, packed=None, ga
 
 def quantize_acts(x, xq=None, sx=None):
     """x [M,K] fp32/bf16 -> (x_q int8 [M,K], s_x float32 [M]); Section 2."""
-    lib = load()
-    xp = _dev(x, "x", _FLOAT, 2)
-    M, K = x.shape
-    if xq is None:
-        xq = torch.empty((M, K), dtype=torch.int8, device=x.device)
-    if sx is None:
-        sx = torch.empty(M, dtype=torch.float32, device=x.device)
-    _check(lib.bitnet_quantize_acts(xp, _FLOAT[x.dtype], M, K, _dev(xq, "xq", (torch.int8,)),
-                                    _dev(sx, "sx", (torch.float32,)), _stream()), "bitnet_quantize_acts")
-    return xq, sx
+    return _native().quantize_acts(x, xq, sx)
 
 
 def rmsnorm_quantize(x, g=None, eps=1e-6, xq=None, sx=None):
     """RMSNorm (optional gain g [K], float32) fused with the activation quantization:
     x [M,K] fp32/bf16 -> (x_q int8 [M,K], s_x float32 [M])."""
-    lib = load()
-    xp = _dev(x, "x", _FLOAT, 2)
-    M, K = x.shape
-    if xq is None:
-        xq = torch.empty((M, K), dtype=torch.int8, device=x.device)
-    if sx is None:
-        sx = torch.empty(M, dtype=torch.float32, device=x.device)
-    gp = None if g is None else _dev(g, "g", (torch.float32,))
-    if g is not None and tuple(g.shape) != (K,):
-        raise ValueError("g must have one entry per column")
-    _check(lib.bitnet_rmsnorm_quantize(xp, _FLOAT[x.dtype], gp, float(eps), M, K, _dev(xq, "xq", (torch.int8,)),
-                                       _dev(sx, "sx", (torch.float32,)), _stream()), "bitnet_rmsnorm_quantize")
-    return xq, sx
+    return _native().rmsnorm_quantize(x, g, eps, xq, sx)
 
 
 def swiglu_quantize(gu, hq=None, sh=None):
     """SwiGLU gating fused with the activation quantization: gu [M,2F] fp32/bf16 (gate | up) ->
     (h_q int8 [M,F], s_h float32 [M]) with h = silu(gate) * up."""
-    lib = load()
-    gp = _dev(gu, "gu", _FLOAT, 2)
-    M, F2 = gu.shape
-    if F2 % 2:
-        raise ValueError("gu must have an even number of columns")
-    F = F2 // 2
-    if hq is None:
-        hq = torch.empty((M, F), dtype=torch.int8, device=gu.device)
-    if sh is None:
-        sh = torch.empty(M, dtype=torch.float32, device=gu.device)
-    _check(lib.bitnet_swiglu_quantize(gp, _FLOAT[gu.dtype], M, F, _dev(hq, "hq", (torch.int8,)),
-                                      _dev(sh, "sh", (torch.float32,)), _stream()), "bitnet_swiglu_quantize")
-    return hq, sh
+    return _native().swiglu_quantize(gu, hq, sh)
 
 
 def linear(xq, sx, packed, gamma, N, fmt=PACK_2BIT, y_dtype=F32, y=None, kernel=KERNEL_AUTO):
     """y [M,N] = (x_q . Wt^T) * gamma * s_x / 127 (or the raw int32 accumulator for y_dtype=I32)."""
-    lib = load()
-    M, K = xq.shape
-    if y is None:
-        y = torch.empty((M, N), dtype=_OUT[y_dtype], device=xq.device)
-    args = (_dev(xq, "xq", (torch.int8,), 2), _dev(sx, "sx", (torch.float32,)), _dev(packed, "packed"),
-            _dev(gamma, "gamma", (torch.float32,)), M, N, K, fmt, _dev(y, "y", (_OUT[y_dtype],)), y_dtype)
-    if kernel == KERNEL_AUTO:
-        _check(lib.bitnet_linear(*args, _stream()), "bitnet_linear")
-    else:
-        _check(lib.bitnet_linear_variant(*args, kernel, _stream()), "bitnet_linear_variant")
-    return y
+    return _native().linear(xq, sx, packed, gamma, N, fmt, y_dtype, y, kernel)
 
 
 def linear_workspace(M, N, K, fmt=PACK_2BIT):
@@ -309,29 +279,12 @@ def entry_describe(entry, M, N, K, x_dtype=BF16, fmt=PACK_2BIT, workspace_bytes=
 def linear_ws(xq, sx, packed, gamma, N, workspace, fmt=PACK_2BIT, y_dtype=F32, y=None, kernel=KERNEL_AUTO,
               gamma_per_block=False):
     """bitnet_linear with a scratch buffer (uint8 tensor or None) that lets the prefill kernel split K."""
-    lib = load()
-    M, K = xq.shape
-    if y is None:
-        y = torch.empty((M, N), dtype=_OUT[y_dtype], device=xq.device)
-    wp = None if workspace is None else _dev(workspace, "workspace")
-    wb = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(lib.bitnet_linear_ws(_dev(xq, "xq", (torch.int8,), 2), _dev(sx, "sx", (torch.float32,)), _dev(packed, "packed"),
-                                _dev(gamma, "gamma", (torch.float32,)), 1 if gamma_per_block else 0, M, N, K, fmt,
-                                _dev(y, "y", (_OUT[y_dtype],)), y_dtype, kernel, wp, wb, _stream()), "bitnet_linear_ws")
-    return y
+    return _native().linear_ws(xq, sx, packed, gamma, N, fmt, y_dtype, y, kernel, workspace, gamma_per_block)
 
 
 def linear_fused(x, packed, gamma, N, fmt=PACK_2BIT, y_dtype=F32, y=None):
     """Decode path in one launch: activation quantization fused into the weight-streaming kernel."""
-    lib = load()
-    xp = _dev(x, "x", _FLOAT, 2)
-    M, K = x.shape
-    if y is None:
-        y = torch.empty((M, N), dtype=_OUT[y_dtype], device=x.device)
-    _check(lib.bitnet_linear_fused(xp, _FLOAT[x.dtype], _dev(packed, "packed"), _dev(gamma, "gamma", (torch.float32,)),
-                                   M, N, K, fmt, _dev(y, "y", (_OUT[y_dtype],)), y_dtype, _stream()),
-           "bitnet_linear_fused")
-    return y
+    return _native().linear_fused(x, packed, gamma, N, fmt, y_dtype, y, False)
 
 
 def quantize_weights_segmented(W, seg_rows, fmt=PACK_2BIT, packed=None, gamma_rb=None, workspace=None):
@@ -357,84 +310,30 @@ def quantize_weights_segmented(W, seg_rows, fmt=PACK_2BIT, packed=None, gamma_rb
 
 def linear_segmented(xq, sx, packed, gamma_rb, N, fmt=PACK_2BIT, y_dtype=F32, y=None, kernel=KERNEL_AUTO):
     """bitnet_linear with one gamma per 16-row block (gamma_rb from quantize_weights_segmented)."""
-    lib = load()
-    M, K = xq.shape
-    if y is None:
-        y = torch.empty((M, N), dtype=_OUT[y_dtype], device=xq.device)
-    if gamma_rb.numel() < (N + 15) // 16:
-        raise ValueError("gamma_rb needs one entry per 16-row block")
-    _check(lib.bitnet_linear_segmented(_dev(xq, "xq", (torch.int8,), 2), _dev(sx, "sx", (torch.float32,)),
-                                       _dev(packed, "packed"), _dev(gamma_rb, "gamma_rb", (torch.float32,)), M, N, K, fmt,
-                                       _dev(y, "y", (_OUT[y_dtype],)), y_dtype, kernel, _stream()),
-           "bitnet_linear_segmented")
-    return y
+    return _native().linear_segmented(xq, sx, packed, gamma_rb, N, fmt, y_dtype, y, kernel)
 
 
 def linear_fused_segmented(x, packed, gamma_rb, N, fmt=PACK_2BIT, y_dtype=F32, y=None):
     """bitnet_linear_fused with one gamma per 16-row block."""
-    lib = load()
-    xp = _dev(x, "x", _FLOAT, 2)
-    M, K = x.shape
-    if y is None:
-        y = torch.empty((M, N), dtype=_OUT[y_dtype], device=x.device)
-    if gamma_rb.numel() < (N + 15) // 16:
-        raise ValueError("gamma_rb needs one entry per 16-row block")
-    _check(lib.bitnet_linear_fused_segmented(xp, _FLOAT[x.dtype], _dev(packed, "packed"),
-                                             _dev(gamma_rb, "gamma_rb", (torch.float32,)), M, N, K, fmt,
-                                             _dev(y, "y", (_OUT[y_dtype],)), y_dtype, _stream()),
-           "bitnet_linear_fused_segmented")
-    return y
+    return _native().linear_fused(x, packed, gamma_rb, N, fmt, y_dtype, y, True)
 
 
 def rmsnorm_linear_fused(x, g, eps, packed, gamma, N, fmt=PACK_2BIT, y_dtype=F32, y=None, segmented=False):
     """y = BitLinear(RMSNorm(x) * g) in one launch (decode path; g [K] float32 or None).  With segmented=True
     `gamma` holds one scale per 16-row block (from quantize_weights_segmented)."""
-    lib = load()
-    xp = _dev(x, "x", _FLOAT, 2)
-    M, K = x.shape
-    if y is None:
-        y = torch.empty((M, N), dtype=_OUT[y_dtype], device=x.device)
-    gp = None if g is None else _dev(g, "g", (torch.float32,))
-    if g is not None and tuple(g.shape) != (K,):
-        raise ValueError("g must have one entry per column")
-    if segmented and gamma.numel() < (N + 15) // 16:
-        raise ValueError("gamma needs one entry per 16-row block")
-    fn = lib.bitnet_rmsnorm_linear_fused_segmented if segmented else lib.bitnet_rmsnorm_linear_fused
-    _check(fn(xp, _FLOAT[x.dtype], gp, float(eps), _dev(packed, "packed"), _dev(gamma, "gamma", (torch.float32,)),
-              M, N, K, fmt, _dev(y, "y", (_OUT[y_dtype],)), y_dtype, _stream()),
-           "bitnet_rmsnorm_linear_fused_segmented" if segmented else "bitnet_rmsnorm_linear_fused")
-    return y
+    return _native().rmsnorm_linear_fused(x, g, eps, packed, gamma, N, fmt, y_dtype, y, segmented)
 
 
 def swiglu_linear_fused(gu, packed, gamma, N, fmt=PACK_2BIT, y_dtype=F32, y=None):
     """y = BitLinear(silu(gate) * up) in one launch (decode path): gu [M,2F] fp32/bf16 (gate | up), packed an [N,F] matrix."""
-    lib = load()
-    gp = _dev(gu, "gu", _FLOAT, 2)
-    M, F2 = gu.shape
-    if F2 % 2:
-        raise ValueError("gu must hold a gate and an up half")
-    if y is None:
-        y = torch.empty((M, N), dtype=_OUT[y_dtype], device=gu.device)
-    _check(lib.bitnet_swiglu_linear_fused(gp, _FLOAT[gu.dtype], _dev(packed, "packed"), _dev(gamma, "gamma", (torch.float32,)),
-                                          M, N, F2 // 2, fmt, _dev(y, "y", (_OUT[y_dtype],)), y_dtype, _stream()),
-           "bitnet_swiglu_linear_fused")
-    return y
+    return _native().swiglu_linear_fused(gu, packed, gamma, N, fmt, y_dtype, y)
 
 
 def ffn_gate_up_fused(x, packed, gamma, F, norm=False, g=None, eps=1e-6, gamma_per_block=False, fmt=PACK_2BIT,
                       h_dtype=F32, h=None):
     """h [M,F] = silu(y_gate) * y_up with [y_gate | y_up] = BitLinear(pre(x)) over a merged gate|up matrix [2F,K] in one
     decode launch; pre = RMSNorm (gain g or None, eps) when norm, else the plain absmax quantization."""
-    lib = load()
-    xp = _dev(x, "x", _FLOAT, 2)
-    M, K = x.shape
-    if h is None:
-        h = torch.empty((M, F), dtype=_OUT[h_dtype], device=x.device)
-    gp = None if g is None else _dev(g, "g", (torch.float32,))
-    _check(lib.bitnet_ffn_gate_up_fused(xp, _FLOAT[x.dtype], 1 if norm else 0, gp, float(eps), _dev(packed, "packed"),
-                                        _dev(gamma, "gamma", (torch.float32,)), 1 if gamma_per_block else 0, M, F, K, fmt,
-                                        _dev(h, "h", (_OUT[h_dtype],)), h_dtype, _stream()), "bitnet_ffn_gate_up_fused")
-    return h
+    return _native().ffn_gate_up_fused(x, packed, gamma, F, norm, g, eps, gamma_per_block, fmt, h_dtype, h)
 
 
 def unpack_weights(packed, N, K, fmt=PACK_2BIT, codes=None):

@@ -175,6 +175,27 @@ def build_floors(verbose: bool = False) -> str:
     return lib
 
 
+def build_call(verbose: bool = False) -> str:
+    """_call.so: the native argument marshalling of binding.py (host code only, against torch's headers and libraries)."""
+    import sysconfig
+    from torch.utils import cpp_extension as ext
+    lib = os.path.join(HERE, "_call.so")
+    tmp = lib + ".tmp.%d" % os.getpid()
+    libdir = ext.library_paths()[0]
+    cmd = [HIPCC, "-O2", "-std=c++17", "-fPIC", "-shared", "-x", "c++", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-Wno-deprecated-declarations"]
+    cmd += [f for p in ext.include_paths("cuda") + [sysconfig.get_paths()["include"]] for f in ("-isystem", p)]
+    cmd += ["-I", os.path.join(ROOT, "include"), os.path.join(CSRC, "call.cpp"), "-o", tmp, "-L", libdir, "-Wl,-rpath," + libdir,
+            "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("hipcc failed on call.cpp:\n" + r.stderr)
+    os.replace(tmp, lib)
+    if verbose:
+        print("built", lib)
+    return lib
+
+
 if __name__ == "__main__":
     build_library(verbose=True)
+    build_call(verbose=True)
     build_floors(verbose=True)

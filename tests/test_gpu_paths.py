@@ -87,3 +87,47 @@ def test_rows_of_any_length_with_a_gamma_per_block(gpu_lib, M, N, K):
     want = gpu_lib.linear_segmented(xq, sx, packed, gamma_rb, N, kernel=gpu_lib.KERNEL_REFERENCE)
     got = gpu_lib.linear_segmented(xq, sx, packed, gamma_rb, N)
     assert torch.allclose(got, want, rtol=3 * 2.0 ** -23, atol=0.0)      # gamma * (s_x / 127) or (gamma * s_x) / 127: two roundings
+
+
+def test_native_marshalling_checks_its_arguments(gpu_lib):
+    """What binding.py's entry points refuse, and that a non-default stream, given outputs and keyword arguments arrive."""
+    B, M, N, K = gpu_lib, 3, 64, 128
+    packed, gamma = B.quantize_weights(dev(synth.weights(N, K)))
+    x = dev(synth.activations(M, K))
+    xq, sx = B.quantize_acts(x)
+    f64 = x.double()
+    for call, err in [(lambda: B.quantize_acts(f64), TypeError), (lambda: B.quantize_acts(x.t()), ValueError),
+                      (lambda: B.quantize_acts(x[0]), ValueError), (lambda: B.quantize_acts(x, xq=xq.int()), TypeError),
+                      (lambda: B.rmsnorm_quantize(x, g=torch.ones(K - 1, device="cuda")), ValueError),
+                      (lambda: B.rmsnorm_quantize(x, eps="a"), ValueError),
+                      (lambda: B.rmsnorm_quantize(x, eps=-1.0), B.BitnetError),
+                      (lambda: B.swiglu_quantize(x[:, :127].contiguous()), ValueError),
+                      (lambda: B.linear(x, sx, packed, gamma, N), TypeError), (lambda: B.linear(xq, sx.double(), packed, gamma, N), TypeError),
+                      (lambda: B.linear(xq, sx, packed, gamma, N, y_dtype=9), KeyError), (lambda: B.linear(xq, sx, packed, gamma, 16.5), TypeError),
+                      (lambda: B.linear(xq, sx, packed, gamma, 0), B.BitnetError),
+                      (lambda: B.linear(xq, sx, packed, gamma, N, y=torch.empty(M, N, device="cuda", dtype=torch.bfloat16)), TypeError),
+                      (lambda: B.linear(xq, sx, packed, gamma, N, fmt=7), B.BitnetError),
+                      (lambda: B.linear(xq, sx, packed, gamma, N, kernel=77), B.BitnetError),
+                      (lambda: B.linear_segmented(xq, sx, packed, gamma, N), ValueError),
+                      (lambda: B.linear_fused_segmented(x, packed, gamma, N), ValueError),
+                      (lambda: B.rmsnorm_linear_fused(x, None, 1e-6, packed, gamma, N, segmented=True), ValueError),
+                      (lambda: B.ffn_gate_up_fused(x, packed, gamma, 24), B.BitnetError),
+                      (lambda: B.ffn_gate_up_fused(x, packed, gamma, 32, h_dtype=B.I32), B.BitnetError)]:
+        with pytest.raises(err):
+            call()
+    with pytest.raises(B.BitnetError) as e:
+        B.linear(xq, sx, packed, gamma, N, fmt=7)
+    assert e.value.status == 4 and "bitnet_linear" in str(e.value)
+    want = B.linear(xq, sx, packed, gamma, N, y_dtype=B.BF16)
+    y, s = torch.empty(M, N, device="cuda", dtype=torch.bfloat16), torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        assert B.linear(xq=xq, sx=sx, packed=packed, gamma=gamma, N=np.int64(N), y_dtype=B.BF16, y=y) is y
+    s.synchronize()
+    assert torch.equal(y, want)
+    graph = torch.cuda.CUDAGraph()          # captured where the current stream says, replayed on new inputs
+    with torch.cuda.graph(graph):
+        yg = B.linear_fused(x, packed, gamma, N, y_dtype=B.BF16)
+    x.mul_(-1.0)
+    graph.replay()
+    assert torch.equal(yg, -want)
