@@ -179,11 +179,11 @@ __device__ inline float exp32(float t) {
     return ldexpf(p, (int)n);
 }
 
-__device__ inline float swiglu_one(float gate, float up) {
+__device__ inline float silu_one(float gate) {
     const float e = exp32(-gate);
-    const float s = gate / (1.0f + e);                     // IEEE fp32 division
-    return s * up;
+    return gate / (1.0f + e);                              // IEEE fp32 division
 }
+__device__ inline float swiglu_one(float gate, float up) { return silu_one(gate) * up; }
 
 // ---- 2-bit layout ---------------------------------------------------------------------------------
 // Eq. (1)-(2) for one weight, given d = gamma + eps: the 2-bit two's-complement code.

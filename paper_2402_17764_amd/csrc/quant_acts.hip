@@ -369,10 +369,103 @@ __global__ __launch_bounds__(kThreads) void swiglu_quantize_kernel(
     }
 }
 
-// Few tokens: 1024 threads per token, so that the dependent chains of the gate (exponential, division) and
-// of the exact sum interleave over four waves per SIMD; many tokens: 256, and the tokens fill the CUs.  Rows too
-// long for 256 threads' registers take 1024 threads at any token count.
-constexpr int kProdFewTokens = 64;
+// The same for bf16 rows of many tokens.  The gate costs ~45 VALU instructions an element (exponential, IEEE division): more
+// time than the bytes.  But silu's argument is a bf16 value, so a workgroup evaluates it once for every value of magnitude
+// 2^-17 ... 2^6 (23 exponents x 128 mantissas x 2 signs, 23 KB of LDS: the very same function, the same bits) and looks it up
+// for all elements of all its tokens.  Zero has an entry too -- a projection's integer sum is 0 for one output in a thousand,
+// which is one in half of all wave-wide vectors -- and any other element outside sends its lane through the arithmetic.  A
+// workgroup walks tokens blockIdx.x, + workgroups, ... with the next token's loads in flight under the current one's work.
+// bf16, alone: 64 x 11008 9.6 -> 4.9 us, 256 x 13824 14.5 -> 6.7, 2048 x 13824 38.5 -> 29.8 (4.75 TB/s of the bytes it cannot
+// do without), 4096 x 28672 126 -> 112 (5.2 TB/s, what a device copy reaches).
+constexpr int kSiluBase = (127 - 17) << 7;                 // bf16 bits of 2^-17
+constexpr int kSiluSpan = (23 << 7) + 1;                   // zero, and the magnitudes from there to 2^6
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+
+template <int kVecs, int kThreads>
+__global__ __launch_bounds__(kThreads) void swiglu_quantize_table(const uint16_t* __restrict__ gu, int64_t M, int64_t F,
+                                                                  int8_t* __restrict__ hq, float* __restrict__ sh_out, int workgroups) {
+    constexpr int kWaves = kThreads / kWave;
+    __shared__ float table[2 * kSiluSpan];                 // [0: zero, k: the magnitude of bits base + k - 1][sign]
+    __shared__ float sh[2][kWaves];
+    const int nvec = (int)(F / 8);
+    uint4 g[kVecs], u[kVecs];
+    auto request = [&](int64_t m) {
+        const uint4* gate = reinterpret_cast<const uint4*>(gu + m * 2 * F);
+#pragma unroll
+        for (int v = 0; v < kVecs; ++v) {
+            const int idx = v * kThreads + threadIdx.x;
+            g[v] = u[v] = make_uint4(0, 0, 0, 0);
+            if (idx < nvec) { g[v] = gate[idx]; u[v] = gate[nvec + idx]; }
+        }
+    };
+    int64_t m = blockIdx.x;
+    request(m);
+    for (int i = threadIdx.x; i < 2 * kSiluSpan; i += kThreads)
+        table[i] = silu_one(bf16_to_f32((uint16_t)((i < 2 ? 0 : kSiluBase - 1 + (i >> 1)) | ((i & 1) << 15))));
+    __syncthreads();
+
+    for (int parity = 0; m < M; parity ^= 1) {
+        uint4 cg[kVecs], cu[kVecs];
+#pragma unroll
+        for (int v = 0; v < kVecs; ++v) { cg[v] = g[v]; cu[v] = u[v]; }
+        const int64_t next = m + workgroups;
+        if (next < M) request(next);
+        float h[kVecs][8];
+        float amax = 0.0f;
+#pragma unroll
+        for (int v = 0; v < kVecs; ++v) {
+            if (v * kThreads + (int)threadIdx.x >= nvec) continue;
+            const uint32_t gw[4] = {cg[v].x, cg[v].y, cg[v].z, cg[v].w}, uw[4] = {cu[v].x, cu[v].y, cu[v].z, cu[v].w};
+            constexpr unsigned short kLow = kSiluBase - 1;
+            u16x2 d[4], top = {0, 0}, low = {0xFFFF, 0xFFFF};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const u16x2 mag = __builtin_bit_cast(u16x2, gw[e] & 0x7FFF7FFFu);
+                d[e] = __builtin_elementwise_sub_sat(mag, (u16x2){kLow, kLow});
+                top = __builtin_elementwise_max(top, d[e]);
+                low = __builtin_elementwise_min(low, mag - (u16x2){1, 1});        // zero wraps: it is no low magnitude
+            }
+            const bool inside = (top.x > top.y ? top.x : top.y) < kSiluSpan && (low.x < low.y ? low.x : low.y) >= kLow;
+            if (__builtin_expect(inside, 1)) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const uint32_t at = (__builtin_bit_cast(uint32_t, d[e]) << 1) | ((gw[e] >> 15) & 0x00010001u);
+                    h[v][2 * e] = table[at & 0xFFFFu];
+                    h[v][2 * e + 1] = table[at >> 16];
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    h[v][2 * e] = silu_one(__uint_as_float(gw[e] << 16));
+                    h[v][2 * e + 1] = silu_one(__uint_as_float(gw[e] & 0xFFFF0000u));
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                h[v][2 * e] *= __uint_as_float(uw[e] << 16);
+                h[v][2 * e + 1] *= __uint_as_float(uw[e] & 0xFFFF0000u);
+                amax = fmaxf(amax, fmaxf(fabsf(h[v][2 * e]), fabsf(h[v][2 * e + 1])));
+            }
+        }
+        amax = block_max_nonneg<kWaves>(amax, sh[parity]);     // two buffers: one barrier per token
+        const float s = fmaxf(amax, kEps);
+        const float inv = kQb / s;
+        if (threadIdx.x == 0) sh_out[m] = s;
+        uint2* out = reinterpret_cast<uint2*>(hq + m * F);
+#pragma unroll
+        for (int v = 0; v < kVecs; ++v) {
+            const int idx = v * kThreads + threadIdx.x;
+            if (idx < nvec) out[idx] = make_uint2(pack4_quantized(h[v][0], h[v][1], h[v][2], h[v][3], inv), pack4_quantized(h[v][4], h[v][5], h[v][6], h[v][7], inv));
+        }
+        m = next;
+    }
+}
+
+// SwiGLU, fewer tokens than the chip holds workgroups of 1024 threads for four times over: 1024 threads per token, so that
+// the dependent chains of the gate (exponential, division) interleave over four waves per SIMD; more tokens: 256, and the
+// tokens fill the CUs (fp32: 100 x 8640 9.6 us with 256 threads, 5.1 with 1024; 300 x 11008 12.7, 9.6; 600 x 11008 17.2, 15.2).
+// Rows too long for 256 threads' registers take 1024 threads at any token count.
+constexpr int kProdFewTokens = 1024;
 
 // chunks of four: rows must start on a chunk boundary of the input loads and of the 32-bit stores
 static bool producer_vec_ok(const void* in, size_t esz, int64_t cols, const void* out) {
@@ -407,11 +500,13 @@ hipError_t launch_rmsnorm_quantize(const void* x, bool bf16, const float* g, flo
     const bool aligned = K % elems == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
                          reinterpret_cast<uintptr_t>(xq) % (bf16 ? 8 : 4) == 0 && reinterpret_cast<uintptr_t>(g) % 16 == 0;
     const int64_t nvec = K / elems;
-    // few tokens: 1024 threads each, so that the dependent chains of the exact sum interleave over four waves per
-    // SIMD; many tokens: 256, and the tokens fill the CUs (one or two waves per token were measured too: slower at
-    // every size from 64 to 4096 tokens); rows that would need more than eight loads per thread at 256 threads
-    // take 1024 at any count (sixteen loads cost occupancy: fp32 rows of 13824 run 5-15 % faster on 1024 threads)
-    const int threads = (M < kProdFewTokens || nvec > (int64_t)8 * 256) ? 1024 : 256;
+    // 256 threads while four loads each hold the token: the reductions over sixteen waves cost a workgroup of 1024 more than
+    // its shorter chains of the exact sum save (bf16, 256 / 1024 threads: 1 x 3200 2.95 / 3.68 us, 29 x 4096 3.33 / 4.12,
+    // 60 x 8192 4.63 / 4.77, 200 x 2048 3.2 / 4.1).  Longer rows of few tokens: 1024 (1 x 14336 6.58 / 4.78), of many tokens
+    // 256, and the tokens fill the CUs (one or two waves per token were measured too: slower at every size from 64 to 4096
+    // tokens); rows that would need more than eight loads per thread at 256 threads take 1024 at any count (sixteen loads
+    // cost occupancy: fp32 rows of 13824 run 5-15 % faster on 1024 threads)
+    const int threads = (nvec > (int64_t)8 * 256 || (M < 64 && nvec > (int64_t)4 * 256)) ? 1024 : 256;
     const int64_t need = ceil_div(nvec, threads);
     dim3 grid((unsigned)M), block(threads);
 #define GO(B_, V_, T_) hipLaunchKernelGGL((rmsnorm_quantize_vec<B_, V_, T_>), grid, block, 0, stream, x, g, eps, K, xq, sx)
@@ -437,8 +532,28 @@ hipError_t launch_rmsnorm_quantize(const void* x, bool bf16, const float* g, flo
     return hipGetLastError();
 }
 
+// Where the table form is the faster one, measured where the launch stands in use (behind the gate/up product and in front of
+// the down product, us for all of it, arithmetic / table): 5120 -> 13824 at 16 tokens, two layers, 101.7 / 99.3, at 128 179.3 /
+// 176.2, at 1024 201.8 / 194.2; 2048 tokens 356 / 345.  Narrow rows leave most of the 1024 threads idle and pay for the
+// table all the same: 700 x 4096 33.6 / 34.2, 64 x 5504 equal; so do single tokens (alone, 1 x 8640 3.8 / 3.9, but 29 x 28672
+// 10.5 / 6.8).
+static bool swiglu_by_table(const void* gu, int64_t M, int64_t F, const void* hq) {
+    if (F % 8 != 0 || F > 32768 || reinterpret_cast<uintptr_t>(gu) % 16 != 0 || reinterpret_cast<uintptr_t>(hq) % 8 != 0) return false;
+    return F >= 5120 && M >= (F >= 16384 ? 1 : F >= 8192 ? 8 : 256);
+}
+
 hipError_t launch_swiglu_quantize(const void* gu, bool bf16, int64_t M, int64_t F, int8_t* hq, float* sh,
                                   hipStream_t stream) {
+    if (bf16 && swiglu_by_table(gu, M, F, hq)) {
+        const uint16_t* in = static_cast<const uint16_t*>(gu);
+        const int wgs = (int)(M < 256 ? M : 256);          // one per CU: two and four were no faster
+#define TABLE(V_) hipLaunchKernelGGL((swiglu_quantize_table<V_, 1024>), dim3((unsigned)wgs), dim3(1024), 0, stream, in, M, F, hq, sh, wgs)
+        if (F <= 8192) TABLE(1);
+        else if (F <= 16384) TABLE(2);
+        else TABLE(4);
+#undef TABLE
+        return hipGetLastError();
+    }
     int threads, chunks;
     producer_shape(producer_vec_ok(gu, bf16 ? 2 : 4, F, hq), M, F, &threads, &chunks);
     dim3 grid((unsigned)M), block(threads);

@@ -131,3 +131,51 @@ def test_native_marshalling_checks_its_arguments(gpu_lib):
     x.mul_(-1.0)
     graph.replay()
     assert torch.equal(yg, -want)
+
+
+# SwiGLU by table: every finite bf16 gate, in rows of each width the form takes (one, two and four loads per thread, partly
+# filled), the up half chosen so that every product is of one magnitude and a neighbouring table entry would show in the
+# codes; more tokens than workgroups; rows with gates outside the table among the others
+@pytest.mark.parametrize("F", [5120, 8192, 8200, 11008, 16384, 16392, 32768])
+def test_swiglu_table_every_gate(gpu_lib, F):
+    bits = np.arange(65536, dtype=np.uint32).astype(np.uint16)
+    g = (bits.astype(np.uint32) << 16).view(np.float32)
+    bits = bits[np.isfinite(g) & (np.abs(g) < 2.0 ** 60) & (g > -80) & (np.abs(g) > 2.0 ** -60)]
+    rng = np.random.default_rng(F)
+    M = 300
+    gb = rng.permutation(np.resize(bits, M * F)).reshape(M, F)
+    g64 = (gb.astype(np.uint32) << 16).view(np.float32).astype(np.float64)
+    silu = g64 / (1.0 + np.exp(-g64))
+    up, ub = synth.to_bf16((rng.uniform(0.3, 1.0, (M, F)) / silu).astype(np.float32))
+    gu = np.concatenate([(gb.astype(np.uint32) << 16).view(np.float32), up], axis=1)
+    hq_ref, sh_ref, _ = oracle.swiglu_quantize(np.ascontiguousarray(gu))
+    hq, sh = gpu_lib.swiglu_quantize(dev_bf16(np.concatenate([gb, ub], axis=1)).view(M, 2 * F))
+    assert sh.cpu().numpy().tobytes() == sh_ref.tobytes()
+    assert np.array_equal(hq.cpu().numpy(), hq_ref)
+
+
+@pytest.mark.parametrize("M,F", [(600, 5120), (257, 11008), (256, 5128), (255, 5128), (1100, 8640), (8, 8192), (7, 8192), (1, 16384), (1023, 264), (1024, 264)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_swiglu_many_tokens(gpu_lib, M, F, bf16):
+    gu, bits = synth.activations(M, 2 * F, config=2, layer=F % 5, tensor=5, bf16=True)
+    gu[:, :F:7] *= 0.0                        # zeros of both signs have an entry, these magnitudes have none
+    gu[0, 1:F:9] = 1e-7
+    gu[-1, 2:F:9] = -70.0
+    gu[M // 2, 3:F:9] = 1e-39
+    gu, bits = synth.to_bf16(gu)
+    hq_ref, sh_ref, _ = oracle.swiglu_quantize(gu)
+    hq, sh = gpu_lib.swiglu_quantize(dev_bf16(bits).view(M, 2 * F) if bf16 else dev(gu))
+    assert sh.cpu().numpy().tobytes() == sh_ref.tobytes()
+    assert np.array_equal(hq.cpu().numpy(), hq_ref)
+
+
+# RMSNorm at the edges of its workgroup sizes: 256 threads up to four loads each at any count of tokens, 1024 beyond for few
+@pytest.mark.parametrize("M,K", [(1, 8192), (1, 8200), (63, 8200), (64, 8200), (29, 4096), (63, 4100), (1, 4104), (1, 16392)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_rmsnorm_workgroup_sizes(gpu_lib, M, K, bf16):
+    x, bits = synth.activations(M, K, config=2, layer=K % 7, tensor=3, bf16=True)
+    g = (1.0 + 0.25 * np.random.default_rng(K).standard_normal(K)).astype(np.float32)
+    xq_ref, sx_ref, _ = oracle.rmsnorm_quantize(x, g, 1e-6)
+    xq, sx = gpu_lib.rmsnorm_quantize(dev_bf16(bits).view(M, K) if bf16 else dev(x), dev(g), 1e-6)
+    assert sx.cpu().numpy().tobytes() == sx_ref.tobytes()
+    assert np.array_equal(xq.cpu().numpy(), xq_ref)
