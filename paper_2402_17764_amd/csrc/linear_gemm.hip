@@ -435,9 +435,13 @@ constexpr int gemm_blocks_per_cu(int fm, int fn) { return fn == 1 ? (fm == 2 ? 4
 // one after the other at y; a second kernel adds them up and rescales).  One split: the whole product, stored as yt.
 template <int kFM, int kFN, int kKG = 1, int kNG = 1, bool kAny = false>
 __global__ __launch_bounds__(kGemmThreads * kKG * kNG, kKG * kNG > 1 ? 1 : gemm_blocks_per_cu(kFM, kFN) - (kAny ? 1 : 0)) void linear_gemm_2bit(
-        const int8_t* __restrict__ xq, const float* __restrict__ sx, const uint4* __restrict__ packed,
-        const float* __restrict__ gamma, int gstride, int M, int64_t N, int64_t K, int Kq, int RB, int tiles_m,
-        int steps_per_split, void* __restrict__ y, OutType yt, int vec_store) {
+        const int8_t* __restrict__ xq, const uint4* __restrict__ packed, const float* __restrict__ gamma, const float* __restrict__ sx,
+        void* __restrict__ y, int N32, int K32, int M, uint32_t flags /* K steps per split, output type, gamma stride, vector stores */) {
+    const int64_t K = K32, N = N32;
+    const int Kq = (K32 + kColsPerQuad - 1) / kColsPerQuad;
+    const int RB = (int)((N + kRowsPerBlock - 1) / kRowsPerBlock), tiles_m = (int)(((int64_t)M + 32 * kFM - 1) / (32 * kFM));
+    const int steps_per_split = flags_number(flags), gstride = flags_gstride(flags), vec_store = flags_vec_store(flags);
+    const OutType yt = flags_out_type(flags);
     const int b = blockIdx.x;
     const int steps = (Kq + 3) >> 2;
     const int step0 = blockIdx.y * steps_per_split;
@@ -503,8 +507,6 @@ static hipError_t launch_gemm_tiles(const int8_t* xq, const float* sx, const voi
         const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(linear_gemm_2bit<kFM, kFN, kKG, kNG, kAny>), gemm_lds_bytes(kFM, kFN, kKG, kNG), raised);
         if (e != hipSuccess) return e;
     }
-    const int Kq = (int)ceil_div(K, kColsPerQuad);
-    const int RB = (int)ceil_div(N, kRowsPerBlock);
     const int tiles_m = (int)ceil_div(M, 32 * kFM);
     const int64_t tiles_n = ceil_div(N, 128 * kFN * kNG);
     const int steps = (int)ceil_div(K, 256);
@@ -524,8 +526,8 @@ static hipError_t launch_gemm_tiles(const int8_t* xq, const float* sx, const voi
         return hipSuccess;
     }
     hipLaunchKernelGGL((linear_gemm_2bit<kFM, kFN, kKG, kNG, kAny>), dim3((unsigned)(tiles_m * tiles_n), (unsigned)splits), dim3(kGemmThreads * kKG * kNG),
-                       gemm_lds_bytes(kFM, kFN, kKG, kNG), stream, xq, sx, static_cast<const uint4*>(packed), gamma, gstride, (int)M, N, K, Kq, RB,
-                       tiles_m, sps, out, ot, vec_store);
+                       gemm_lds_bytes(kFM, kFN, kKG, kNG), stream, xq, static_cast<const uint4*>(packed), gamma, sx, out, (int)N, (int)K, (int)M,
+                       product_flags(gstride, ot, vec_store) | (uint32_t)sps << 4);
     if (split)
         return launch_splitk_reduce(static_cast<const int32_t*>(workspace), splits, sx, gamma, gstride, 1, M, N, y, yt, stream);
     return hipGetLastError();

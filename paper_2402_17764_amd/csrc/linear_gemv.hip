@@ -299,6 +299,12 @@ __device__ inline void fused_quantize_wave_per_token(const void* __restrict__ xv
     __syncthreads();
 }
 
+// K steps of 256 columns per wave, rounded up to a multiple of the prefetch depth
+__host__ __device__ constexpr int gemv16_items(int Kq, int kS, int kD) {
+    const int steps = (Kq + 3) / 4, share = (steps + kS - 1) / kS;
+    return (share + kD - 1) / kD * kD;
+}
+
 // kR    row blocks (16 rows each) per wave
 // kS    waves that split K: wave ws takes steps ws, ws + kS, ...
 // kW    row slots per workgroup (waves with different row blocks), workgroup = kS * kW waves
@@ -309,11 +315,18 @@ __device__ inline void fused_quantize_wave_per_token(const void* __restrict__ xv
 //       N = 16 * pair_off -- the SwiGLU of the feed-forward block applied where its two operands meet
 template <int kR, int kS, int kW, int kD, int kX, bool kPair = false>
 __global__ __launch_bounds__(kS * kW * kWave) void linear_gemv16_2bit(
-        const void* __restrict__ xin /* x_q, or x for the fused modes */, const float* __restrict__ sx,
-        const uint4* __restrict__ packed, const float* __restrict__ gamma, int gstride /* 0: one gamma, 1: one per row block */,
-        int M, int64_t N, int64_t K, int Kq, int RB,
-        int items /* K steps per wave, rounded up to a multiple of kD */, void* __restrict__ y, OutType yt,
-        const float* __restrict__ gain /* RMSNorm modes: per-column gain or null */, float eps, int pair_off = 0) {
+        // 14 dwords (product_flags says why); RB row blocks, K steps per wave and the up half's offset follow from them
+        const void* __restrict__ xin /* x_q, or x for the fused modes */, const uint4* __restrict__ packed, const float* __restrict__ gamma,
+        const float* __restrict__ gain /* RMSNorm modes: per-column gain or null; int8 modes: s_x of the rows */, void* __restrict__ y,
+        int N32, int K32, uint32_t flags /* tokens, output type, gamma stride (0: one gamma, 1: one per row block) */, float eps) {
+    const float* sx = gain;
+    const int64_t K = K32, N = N32;
+    const int Kq = (K32 + kColsPerQuad - 1) / kColsPerQuad;
+    const int M = flags_number(flags), gstride = flags_gstride(flags);
+    const OutType yt = flags_out_type(flags);
+    const int pair_off = kPair ? N32 / kRowsPerBlock : 0;
+    const int RB = kPair ? 2 * pair_off : (int)((N + kRowsPerBlock - 1) / kRowsPerBlock);
+    const int items = gemv16_items(Kq, kS, kD);
     static_assert(!kPair || kR == 2, "a gate row block and an up row block per wave");
     extern __shared__ uint4 smem[];
     constexpr int kThreads = kS * kW * kWave;
@@ -529,10 +542,8 @@ template <int kR, int kS, int kW, int kD, int kModes>
 static hipError_t launch16(int xmode, const void* x, const float* sx, const void* packed, const float* gamma, int gstride,
                      int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, const float* gain, float eps,
                      LaunchPlan* plan = nullptr) {
-    const int Kq = (int)ceil_div(K, kColsPerQuad);
     const int RB = (int)ceil_div(N, kRowsPerBlock);
-    int items = (int)ceil_div(ceil_div(K, 256), kS);
-    items = (int)ceil_div(items, kD) * kD;
+    const uint32_t flags = product_flags(gstride, yt) | (uint32_t)M << 4;
     const size_t header = kGemvLdsHeader * sizeof(uint4);
     const size_t lds_fold = kS > 1 ? (size_t)kW * kS * kR * kWave * 16 : 0;
     const size_t lds_x = gemv16_x_lds_bytes(M, K);
@@ -546,8 +557,8 @@ static hipError_t launch16(int xmode, const void* x, const float* sx, const void
         return hipSuccess;
     }
     const uint4* p = static_cast<const uint4*>(packed);
-#define GO(X_) hipLaunchKernelGGL((linear_gemv16_2bit<kR, kS, kW, kD, X_>), grid, block, lds, stream, x, sx, p, gamma, gstride, (int)M, N, \
-                                  K, Kq, RB, items, y, yt, gain, eps)
+#define GO(X_) hipLaunchKernelGGL((linear_gemv16_2bit<kR, kS, kW, kD, X_>), grid, block, lds, stream, x, p, gamma, \
+                                  (X_) == kXNormBf16 || (X_) == kXNormF32 ? gain : sx, y, (int)N, (int)K, flags, eps)
     if constexpr ((kModes & kModesInt8) != 0) {
         if (xmode == kXGlobal) { GO(kXGlobal); return hipGetLastError(); }
         if (xmode == kXLds) { GO(kXLds); return hipGetLastError(); }
@@ -742,11 +753,8 @@ static void launch16_pair(int xmode, const void* x, const void* packed, const fl
                           int64_t F, int64_t K, void* h, OutType yt, hipStream_t stream, const float* gain, float eps,
                           LaunchPlan* plan) {
     constexpr int kR = 2;
-    const int Kq = (int)ceil_div(K, kColsPerQuad);
     const int pair_off = (int)(F / kRowsPerBlock);
-    const int RB = 2 * pair_off;
-    int items = (int)ceil_div(ceil_div(K, 256), kS);
-    items = (int)ceil_div(items, kD) * kD;
+    const uint32_t flags = product_flags(gstride, yt) | (uint32_t)M << 4;
     const size_t header = kGemvLdsHeader * sizeof(uint4);
     const size_t lds_fold = kS > 1 ? (size_t)kW * kS * kR * kWave * 16 : 0;
     const size_t lds_x = gemv16_x_lds_bytes(M, K);
@@ -757,8 +765,7 @@ static void launch16_pair(int xmode, const void* x, const void* packed, const fl
         return;
     }
     const uint4* p = static_cast<const uint4*>(packed);
-#define GO(X_) hipLaunchKernelGGL((linear_gemv16_2bit<kR, kS, kW, kD, X_, true>), grid, block, lds, stream, x, (const float*)nullptr, p, gamma, \
-                                  gstride, (int)M, F, K, Kq, RB, items, h, yt, gain, eps, pair_off)
+#define GO(X_) hipLaunchKernelGGL((linear_gemv16_2bit<kR, kS, kW, kD, X_, true>), grid, block, lds, stream, x, p, gamma, gain, h, (int)F, (int)K, flags, eps)
     switch (xmode) {
         case kXFusedBf16: GO(kXFusedBf16); break;
         case kXFusedF32: GO(kXFusedF32); break;

@@ -32,14 +32,18 @@ namespace bitnet {
 // the build checks that every instantiation compiles without scratch memory.
 template <int kMT, int kR, int kW, int kS, int kD, int kLx>
 __global__ __launch_bounds__(kS * kW * kWave) void linear_skinny_2bit(
-        const int8_t* __restrict__ xq_all, const float* __restrict__ sx_all, const uint4* __restrict__ packed,
-        const float* __restrict__ gamma, int gstride, int M_all /* blockIdx.z selects a tile of 16 * kMT tokens */,
-        int64_t N, int64_t K, int Kq, int RB, int spg,
-        int steps_per_split /* blockIdx.y selects a run of K steps (split-K: int32 partials, [M][N] each, one after the
-                               other at yv); one split: all steps */,
-        void* __restrict__ yv, OutType yt) {
+        // 14 dwords (product_flags says why); blockIdx.z selects a tile of 16 * kMT tokens, blockIdx.y a run of K steps
+        // (split-K: int32 partials, [M][N] each, one after the other at yv; one split: all steps)
+        const int8_t* __restrict__ xq_all, const uint4* __restrict__ packed, const float* __restrict__ gamma,
+        const float* __restrict__ sx_all, void* __restrict__ yv, int N32, int K32, uint32_t flags /* tokens, output type, gamma stride */,
+        int steps_per_split) {
 #if defined(__HIP_DEVICE_COMPILE__)      // the buffer-resource builtins exist in the device pass only
     extern __shared__ uint4 smem[];
+    const int64_t K = K32, N = N32;
+    const int Kq = (K32 + kColsPerQuad - 1) / kColsPerQuad;
+    const int RB = (int)((N + kRowsPerBlock - 1) / kRowsPerBlock), M_all = flags_number(flags), gstride = flags_gstride(flags);
+    const int spg = (steps_per_split + kS - 1) / kS;
+    const OutType yt = flags_out_type(flags);
     constexpr int kRing = kLx + 1;                     // LDS stages per group
     constexpr int kStageBytes = kMT * 16 * 256;        // tokens staged per step x 256 columns
     constexpr int kGroupBytes = kRing * kStageBytes;
@@ -239,11 +243,18 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_skinny_2bit(
 // Everything else (K groups, kR row blocks per wave, swizzled LDS tiles, fold) is as above.
 template <int kMT, int kR, int kW, int kS, int kD, int kLx>
 __global__ __launch_bounds__((kS * kW + 1) * kWave) void linear_skinny_ws_2bit(
-        const int8_t* __restrict__ xq_all, const float* __restrict__ sx_all, const uint4* __restrict__ packed,
-        const float* __restrict__ gamma, int gstride, int M_all, int64_t N, int64_t K, int Kq, int RB, int spg,
-        int steps_per_split /* as in linear_skinny_2bit */, void* __restrict__ yv, OutType yt) {
+        // as linear_skinny_2bit: blockIdx.z selects a tile of 16 * kMT tokens, blockIdx.y a run of K steps
+        // (split-K: int32 partials, [M][N] each, one after the other at yv; one split: all steps)
+        const int8_t* __restrict__ xq_all, const uint4* __restrict__ packed, const float* __restrict__ gamma,
+        const float* __restrict__ sx_all, void* __restrict__ yv, int N32, int K32, uint32_t flags /* tokens, output type, gamma stride */,
+        int steps_per_split) {
 #if defined(__HIP_DEVICE_COMPILE__)      // the buffer-resource builtins exist in the device pass only
     extern __shared__ uint4 smem[];
+    const int64_t K = K32, N = N32;
+    const int Kq = (K32 + kColsPerQuad - 1) / kColsPerQuad;
+    const int RB = (int)((N + kRowsPerBlock - 1) / kRowsPerBlock), M_all = flags_number(flags), gstride = flags_gstride(flags);
+    const int spg = (steps_per_split + kS - 1) / kS;
+    const OutType yt = flags_out_type(flags);
     constexpr int kRing = kLx + 1;                     // LDS stages per group
     constexpr int kStageBytes = kMT * 16 * 256;        // tokens staged per step x 256 columns
     constexpr int kGroupBytes = kRing * kStageBytes;
@@ -367,7 +378,7 @@ __global__ __launch_bounds__((kS * kW + 1) * kWave) void linear_skinny_ws_2bit(
         uint4 wst[kD][kR];
 #pragma unroll
         for (int d = 0; d < kD; ++d) load_w(wst[d], d);
-        int i0 = 0;
+            int i0 = 0;
         do {
 #pragma unroll
             for (int d = 0; d < kD; ++d) {
@@ -500,21 +511,19 @@ static hipError_t launch_skinny(const int8_t* xq, const float* sx, const void* p
         const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds, raised);
         if (e != hipSuccess) return e;
     }
-    const int Kq = (int)ceil_div(K, kColsPerQuad);
     const int RB = (int)ceil_div(N, kRowsPerBlock);
     const int steps = (int)ceil_div(K, 256);
     if (splits > steps) splits = steps;
     const int sps = (int)ceil_div(steps, splits);
     splits = (int)ceil_div(steps, sps);                 // no empty split
-    const int spg = (int)ceil_div(sps, kS);
     const bool split = splits > 1;                      // then int32 partials go to the workspace and a second launch adds them
     dim3 grid((unsigned)ceil_div(RB, kW * kR), (unsigned)splits, (unsigned)ceil_div(M, 16 * kMT));
     if (plan) {
         plan->set("batched_decode", {kMT, kR, kW, kS, kD, kLx}, grid.x * grid.z, grid.y, kS * kW * kWave, lds, splits);
         return hipSuccess;
     }
-    hipLaunchKernelGGL(kern, grid, dim3(kS * kW * kWave), lds, stream, xq, sx, static_cast<const uint4*>(packed), gamma,
-                       gstride, (int)M, N, K, Kq, RB, spg, sps, split ? workspace : y, split ? OutType::I32 : yt);
+    hipLaunchKernelGGL(kern, grid, dim3(kS * kW * kWave), lds, stream, xq, static_cast<const uint4*>(packed), gamma, sx,
+                       split ? workspace : y, (int)N, (int)K, product_flags(gstride, split ? OutType::I32 : yt) | (uint32_t)M << 4, sps);
     if (split)
         return launch_splitk_reduce(static_cast<const int32_t*>(workspace), splits, sx, gamma, gstride, 0, M, N, y, yt, stream);
     return hipGetLastError();
@@ -533,21 +542,19 @@ static hipError_t launch_skinny_ws(const int8_t* xq, const float* sx, const void
         const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(kern), (int)lds, raised);
         if (e != hipSuccess) return e;
     }
-    const int Kq = (int)ceil_div(K, kColsPerQuad);
     const int RB = (int)ceil_div(N, kRowsPerBlock);
     const int steps = (int)ceil_div(K, 256);
     if (splits > steps) splits = steps;
     const int sps = (int)ceil_div(steps, splits);
     splits = (int)ceil_div(steps, sps);                 // no empty split
-    const int spg = (int)ceil_div(sps, kS);
     const bool split = splits > 1;                      // then int32 partials go to the workspace and a second launch adds them
     dim3 grid((unsigned)ceil_div(RB, kW * kR), (unsigned)splits, (unsigned)ceil_div(M, 16 * kMT));
     if (plan) {
         plan->set("batched_decode_loader", {kMT, kR, kW, kS, kD, kLx}, grid.x * grid.z, grid.y, (kS * kW + 1) * kWave, lds, splits);
         return hipSuccess;
     }
-    hipLaunchKernelGGL(kern, grid, dim3((kS * kW + 1) * kWave), lds, stream, xq, sx, static_cast<const uint4*>(packed), gamma,
-                       gstride, (int)M, N, K, Kq, RB, spg, sps, split ? workspace : y, split ? OutType::I32 : yt);
+    hipLaunchKernelGGL(kern, grid, dim3((kS * kW + 1) * kWave), lds, stream, xq, static_cast<const uint4*>(packed), gamma, sx,
+                       split ? workspace : y, (int)N, (int)K, product_flags(gstride, split ? OutType::I32 : yt) | (uint32_t)M << 4, sps);
     if (split)
         return launch_splitk_reduce(static_cast<const int32_t*>(workspace), splits, sx, gamma, gstride, 0, M, N, y, yt, stream);
     return hipGetLastError();

@@ -155,9 +155,12 @@ __device__ inline v4i trit_as_v4i(const uint4& u) {
 // branch-free masked loop, out-of-range steps / rows / tokens redirected and zeroed)
 template <int kR, int kS, int kD>
 __global__ __launch_bounds__(kS * kWave) void linear_gemv16_trit5(
-        const int8_t* __restrict__ xq, const float* __restrict__ sx, const uint4* __restrict__ packed,
-        const float* __restrict__ gamma, int M, int64_t N, int64_t K, int RB, int steps, int items,
-        void* __restrict__ y, OutType yt) {
+        const int8_t* __restrict__ xq, const uint4* __restrict__ packed, const float* __restrict__ gamma, const float* __restrict__ sx,
+        void* __restrict__ y, int N32, int K32, uint32_t flags /* tokens, output type */) {
+    const int64_t K = K32, N = N32;
+    const int M = flags_number(flags), RB = (int)((N + kRowsPerBlock - 1) / kRowsPerBlock), steps = (K32 + kTritStep - 1) / kTritStep;
+    const int items = ((steps + kS - 1) / kS + kD - 1) / kD * kD;
+    const OutType yt = flags_out_type(flags);
     __shared__ uint2 lut[256];                       // byte -> {digits 0..3 as 4 operand bytes, digit 4 as 1 byte}
     __shared__ v4i fold[kS][kR][kWave];
     const int lane = threadIdx.x & (kWave - 1);
@@ -412,11 +415,8 @@ template <int kR, int kS, int kD>
 static void launch_trit5(const int8_t* xq, const float* sx, const void* packed, const float* gamma, int64_t M, int64_t N,
                          int64_t K, void* y, OutType yt, hipStream_t stream) {
     const int RB = (int)ceil_div(N, kRowsPerBlock);
-    const int steps = (int)ceil_div(K, kTritStep);
-    int items = (int)ceil_div(steps, kS);
-    items = (int)ceil_div(items, kD) * kD;
-    hipLaunchKernelGGL((linear_gemv16_trit5<kR, kS, kD>), dim3((unsigned)ceil_div(RB, kR)), dim3(kS * kWave), 0, stream, xq, sx,
-                       static_cast<const uint4*>(packed), gamma, (int)M, N, K, RB, steps, items, y, yt);
+    hipLaunchKernelGGL((linear_gemv16_trit5<kR, kS, kD>), dim3((unsigned)ceil_div(RB, kR)), dim3(kS * kWave), 0, stream, xq,
+                       static_cast<const uint4*>(packed), gamma, sx, y, (int)N, (int)K, product_flags(0, yt) | (uint32_t)M << 4);
 }
 
 hipError_t launch_linear_gemv_trit5(const int8_t* xq, const float* sx, const void* packed, const float* gamma,
