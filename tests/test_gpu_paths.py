@@ -179,3 +179,16 @@ def test_rmsnorm_workgroup_sizes(gpu_lib, M, K, bf16):
     xq, sx = gpu_lib.rmsnorm_quantize(dev_bf16(bits).view(M, K) if bf16 else dev(x), dev(g), 1e-6)
     assert sx.cpu().numpy().tobytes() == sx_ref.tobytes()
     assert np.array_equal(xq.cpu().numpy(), xq_ref)
+
+
+# ... and with the gain requested ahead of the reduction (up to 256 tokens), every count of loads per thread
+@pytest.mark.parametrize("M,K", [(256, 1032), (257, 1032), (256, 2056), (100, 7176), (5, 20488)])
+@pytest.mark.parametrize("bf16", [False, True])
+@pytest.mark.parametrize("with_gain", [False, True])
+def test_rmsnorm_gain_first(gpu_lib, M, K, bf16, with_gain):
+    x, bits = synth.activations(M, K, config=2, layer=K % 7, tensor=3, bf16=True)
+    g = (1.0 + 0.25 * np.random.default_rng(K).standard_normal(K)).astype(np.float32) if with_gain else None
+    xq_ref, sx_ref, _ = oracle.rmsnorm_quantize(x, g, 1e-6)
+    xq, sx = gpu_lib.rmsnorm_quantize(dev_bf16(bits).view(M, K) if bf16 else dev(x), None if g is None else dev(g), 1e-6)
+    assert sx.cpu().numpy().tobytes() == sx_ref.tobytes()
+    assert np.array_equal(xq.cpu().numpy(), xq_ref)
