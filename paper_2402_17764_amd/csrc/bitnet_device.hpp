@@ -81,15 +81,17 @@ __device__ inline uint32_t dpp_u32(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, kCtrl, 0xF, 0xF, true);
 }
 
+__device__ inline float readlane_f32(float v, int lane) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane)); }
+
 // max over the 64 lanes of non-negative finite floats; every lane gets the result.
 __device__ inline float wave_max_nonneg(float v) {
     v = fmaxf(v, dpp_f32<0xB1>(v));     // lane ^ 1
     v = fmaxf(v, dpp_f32<0x4E>(v));     // lane ^ 2
     v = fmaxf(v, dpp_f32<0x141>(v));    // other quad of the 8
     v = fmaxf(v, dpp_f32<0x140>(v));    // other half of the 16
-    v = fmaxf(v, __shfl_xor(v, 16, kWave));
-    v = fmaxf(v, __shfl_xor(v, 32, kWave));
-    return v;
+    // the four rows through scalar reads, which take less time than two ds_bpermute steps
+    const float a = readlane_f32(v, 0), b = readlane_f32(v, 16), c = readlane_f32(v, 32), d = readlane_f32(v, 48);
+    return fmaxf(fmaxf(a, b), fmaxf(c, d));
 }
 
 // OR over each aligned group of four lanes; every lane of the group gets the result.
@@ -144,6 +146,34 @@ __device__ inline dd wave_sum_dd(dd v) {
     dd_add_dd(w, dd{readlane_f64(v.hi, 32), readlane_f64(v.lo, 32)});
     dd_add_dd(w, dd{readlane_f64(v.hi, 48), readlane_f64(v.lo, 48)});
     return w;
+}
+
+// The sum over a wave in plain fp64; every lane gets the result.
+__device__ inline double wave_sum_f64(double v) {
+    v += dpp_f64<0xB1>(v);
+    v += dpp_f64<0x4E>(v);
+    v += dpp_f64<0x141>(v);
+    v += dpp_f64<0x140>(v);
+    return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
+}
+
+// RMSNorm's r = (float)(1 / sqrt(S / K + eps)), whose definition takes S exactly and rounds every step to fp64, from a sum S
+// that carries ordinary fp64 rounding errors -- wherever that decides the float.  S here has a chain of at most 64 + 16 + 10
+// additions of non-negative terms behind it, i.e. a relative error below 2^-46; S / K + eps by a reciprocal adds three
+// roundings, y (hardware reciprocal square root, a step of third and one of second order) a few more; the definition's own
+// fp64 value is within four roundings of the true one.  All of that is below 2^-44 of y, and rounding to float is monotone: if
+// y (1 - 2^-44) and y (1 + 2^-44) round to the same float, it is the definition's.  They do not for about one token in half a
+// million (false is returned; for S = 0 or not finite too), and the caller then takes the exact sum.
+__device__ inline bool rms_from_rounded_sum(double S, double inv_K, float eps, float* r) {
+    const double a = S * inv_K + (double)eps;
+    double y = __builtin_amdgcn_rsq(a);
+    double e = __builtin_fma(-(a * y), y, 1.0);
+    y = __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+    e = __builtin_fma(-(a * y), y, 1.0);
+    y = __builtin_fma(y * 0.5, e, y);
+    const float lo = (float)(y * (1.0 - 0x1p-44)), hi = (float)(y * (1.0 + 0x1p-44));
+    *r = lo;
+    return lo == hi;
 }
 
 // ... and over the block (the waves in order); every thread gets the result.

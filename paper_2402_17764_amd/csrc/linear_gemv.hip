@@ -144,27 +144,55 @@ __device__ inline void fused_quantize_to_lds(const void* __restrict__ xv, const 
         const bool regs = m == 0 && row0_in_regs;
         float r = 1.0f;
         if (kNorm) {
-            // two interleaved accumulators: the sums are exact, so splitting them only shortens the dependent chain
-            dd acc{0.0, 0.0}, acc2{0.0, 0.0};
-            auto add_squares = [&](const uint4& q) {
-                float f[kE];
-                vec_expand<kBf16>(q, f);
+            // the sum in plain fp64 (the squares are exact); it decides r except for a token in half a million
+            auto each_vec = [&](auto&& use) {
+                if (regs) {
 #pragma unroll
-                for (int e = 0; e < kE; e += 2) {
-                    dd_add_double(acc, (double)f[e] * (double)f[e]);
-                    dd_add_double(acc2, (double)f[e + 1] * (double)f[e + 1]);
+                    for (int v = 0; v < kFusedRegVecs; ++v)
+                        if (v * kThreads + (int)threadIdx.x < nvec) use(row0[v]);     // clamped duplicates do not count
+                } else {
+                    for (int v = threadIdx.x; v < nvec; v += kThreads) use(row[v]);
                 }
             };
-            if (regs) {
+            bool decided = false;
+            if (nvec <= 64 / kE * kThreads) {                        // at most 64 elements a thread: the bound of rms_from_rounded_sum
+                double s0 = 0.0, s1 = 0.0;
+                each_vec([&](const uint4& q) {
+                    float f[kE];
+                    vec_expand<kBf16>(q, f);
 #pragma unroll
-                for (int v = 0; v < kFusedRegVecs; ++v)
-                    if (v * kThreads + (int)threadIdx.x < nvec) add_squares(row0[v]);     // clamped duplicates do not count
-            } else {
-                for (int v = threadIdx.x; v < nvec; v += kThreads) add_squares(row[v]);
+                    for (int e = 0; e < kE; e += 2) {
+                        s0 = __builtin_fma((double)f[e], (double)f[e], s0);
+                        s1 = __builtin_fma((double)f[e + 1], (double)f[e + 1], s1);
+                    }
+                });
+                double S = wave_sum_f64(s0 + s1);
+                if (kWaves > 1) {
+                    if ((threadIdx.x & 63) == 0) sh_hi[threadIdx.x >> 6] = S;
+                    __syncthreads();
+                    S = sh_hi[0];
+#pragma unroll
+                    for (int w = 1; w < kWaves; ++w) S += sh_hi[w];
+                }
+                decided = rms_from_rounded_sum(S, 1.0 / (double)K, eps, &r);      // the same for all threads
             }
-            dd_add_dd(acc, acc2);
-            const double ms = block_sum_dd<kWaves>(acc, sh_hi, sh_lo) / (double)K;
-            r = (float)(1.0 / sqrt(ms + (double)eps));
+            if (__builtin_expect(!decided, 0)) {
+                // two interleaved double-double accumulators: the sums are exact, so splitting them only shortens the dependent chain
+                dd acc{0.0, 0.0}, acc2{0.0, 0.0};
+                each_vec([&](const uint4& q) {
+                    float f[kE];
+                    vec_expand<kBf16>(q, f);
+#pragma unroll
+                    for (int e = 0; e < kE; e += 2) {
+                        dd_add_double(acc, (double)f[e] * (double)f[e]);
+                        dd_add_double(acc2, (double)f[e + 1] * (double)f[e + 1]);
+                    }
+                });
+                dd_add_dd(acc, acc2);
+                __syncthreads();                                     // the waves' sums have been read
+                const double ms = block_sum_dd<kWaves>(acc, sh_hi, sh_lo) / (double)K;
+                r = (float)(1.0 / sqrt(ms + (double)eps));
+            }
         }
         // The values that get quantized, for one vector of columns (kNorm, kSwiglu): the same operations wherever
         // they are evaluated, so the same values.  slot >= 0: vector `slot` of the token held in registers.

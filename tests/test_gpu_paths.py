@@ -192,3 +192,36 @@ def test_rmsnorm_gain_first(gpu_lib, M, K, bf16, with_gain):
     xq, sx = gpu_lib.rmsnorm_quantize(dev_bf16(bits).view(M, K) if bf16 else dev(x), None if g is None else dev(g), 1e-6)
     assert sx.cpu().numpy().tobytes() == sx_ref.tobytes()
     assert np.array_equal(xq.cpu().numpy(), xq_ref)
+
+
+def undecided_rows(K, want, seed):
+    """Rows of K values whose 1 / sqrt(mean square) lies within 2^-45 of where two floats meet: a sum with fp64 rounding errors
+    does not decide r for them."""
+    rng, found, tried = np.random.default_rng(seed), [], 0
+    while sum(len(f) for f in found) < want and tried < 40_000_000:
+        x = rng.standard_normal((1_000_000, K)).astype(np.float32)
+        y = 1.0 / np.sqrt((x.astype(np.float64) ** 2).sum(axis=1) / K + np.float64(np.float32(1e-6)))
+        found.append(x[(y * (1 - 2.0 ** -45)).astype(np.float32) != (y * (1 + 2.0 ** -45)).astype(np.float32)])
+        tried += len(x)
+    return np.concatenate(found)
+
+
+def test_rmsnorm_exact_sum_where_the_rounded_one_does_not_decide(gpu_lib):
+    K, N = 16, 32
+    x = undecided_rows(K, 6, 7)
+    assert len(x) >= 3
+    W = synth.weights(N, K)
+    packed, gamma = gpu_lib.quantize_weights(dev(W))
+    for rows in (x, x[:1], np.repeat(x, 100, axis=0), np.concatenate([x, np.zeros((2, K), np.float32)])):
+        xq_ref, sx_ref, _ = oracle.rmsnorm_quantize(rows, None, 1e-6)
+        xq, sx = gpu_lib.rmsnorm_quantize(dev(rows), None, 1e-6)
+        assert sx.cpu().numpy().tobytes() == sx_ref.tobytes()
+        assert np.array_equal(xq.cpu().numpy(), xq_ref)
+    for m in (1, 2, 3):      # the decode launch with the norm in front, tokens decided and undecided in one call
+        rows = np.concatenate([x[:m], synth.activations(3, K)])
+        xq_ref, sx_ref, _ = oracle.rmsnorm_quantize(rows, None, 1e-6)
+        got = gpu_lib.rmsnorm_linear_fused(dev(rows), None, 1e-6, packed, gamma, N)
+        want = gpu_lib.linear(dev(xq_ref), dev(sx_ref), packed, gamma, N)
+        assert torch.equal(got, want)
+    z = torch.zeros(2, K, device="cuda")      # nothing to norm, eps = 0: 1 / 0 is the definition's business, the codes are zero
+    assert int(gpu_lib.rmsnorm_quantize(z, None, 1e-6)[0].abs().max()) == 0
