@@ -308,17 +308,24 @@ hipError_t launch_linear_reference_trit5(const int8_t* xq, const float* sx, cons
 // ---------------------------------------------------------------------------------------------------
 // repacking between the two formats on the device (no weights in full precision needed)
 // ---------------------------------------------------------------------------------------------------
-// 320 columns are one step of the 5-trit layout (4 quads of 80) and five quads of the 2-bit layout (64 each): one
-// thread moves the 320 codes of one row.  Consecutive threads take consecutive rows of a 16-row block, so their
-// 16-byte loads and stores form 256-byte runs in both layouts.
+// 320 columns are one step of the 5-trit layout (4 quads of 80) and five quads of the 2-bit layout (64 each).
 //
-// 5-trit -> 2-bit.  A 5-trit byte p of quad g holds quad columns 4p .. 4p+3, i.e. step columns 80 g + 4 p + (0 .. 3):
-// four columns that the 2-bit layout keeps in one 32-bit word (word (80 g + 4 p) / 16 of the step), in field i = p & 3
-// of its four bytes; the table gives those four 2-bit codes already spread to bits 0, 8, 16, 24.  The sixteen fifth
-// digits of a quad are step columns 80 g + 64 .. 80 g + 79: exactly one word.
-__global__ __launch_bounds__(256) void repack_trit5_to_2bit(const uint4* __restrict__ in, int64_t RB, int64_t steps5,
-                                                            int64_t Kq2, uint4* __restrict__ out) {
+// 5-trit -> 2-bit: a wave moves one chunk of the 5-trit layout (16 rows x 320 columns, 1 KiB in, 1280 bytes out), lane
+// 16 g + r quad g of row r -- with a thread per row and step a 4096 x 11008 matrix gave the chip two wavefronts per SIMD and
+// took 7.6 us (300 tokens on it, quantization and product included: 34.6 -> 33.6 us; 100 tokens on 27648 x 5120 33.4 -> 31.6).  A 5-trit byte p of quad g holds quad columns 4p .. 4p+3, i.e. step columns 80 g + 4 p + (0 .. 3): four
+// columns that the 2-bit layout keeps in one 32-bit word (word (80 g + 4 p) / 16 of the step), in field i = p & 3 of its four
+// bytes; the table gives those four 2-bit codes already spread to bits 0, 8, 16, 24.  The sixteen fifth digits of a quad are
+// step columns 80 g + 64 .. 80 g + 79: exactly one word.  The lane's five words go through LDS (the wave's own 1280 bytes, whose
+// accesses complete in order), from where 80 lanes' worth of 16-byte quads are stored in runs of 256 bytes.
+constexpr int kRepackWaves = 4;
+__global__ __launch_bounds__(kRepackWaves * kWave) void repack_trit5_to_2bit(const uint4* __restrict__ in, int64_t RB, int64_t chunks,
+                                                                             int64_t Kq2, uint4* __restrict__ out) {
     __shared__ uint2 lut[256];                       // byte -> {codes 0..3 as 2-bit fields at bits 0, 8, 16, 24; code 4}
+    __shared__ uint32_t tiles[kRepackWaves][16 * 20];      // [row][word]
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const int64_t chunk = (int64_t)blockIdx.x * kRepackWaves + wave;
+    uint4 q = make_uint4(0, 0, 0, 0);
+    if (chunk < chunks) q = in[64 * chunk + lane];
     {
         const int b = threadIdx.x;
         uint32_t sp = 0, c4 = 0;
@@ -330,14 +337,11 @@ __global__ __launch_bounds__(256) void repack_trit5_to_2bit(const uint4* __restr
         lut[b] = make_uint2(sp, c4);
     }
     __syncthreads();
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= 16 * RB * steps5) return;
-    const int r = (int)(idx & 15);
-    const int64_t rb = (idx >> 4) % RB, s5 = (idx >> 4) / RB;
-    uint32_t words[20];                              // the row's 320 codes as twenty 2-bit words of 16 columns
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const uint4 q = in[64 * (RB * s5 + rb) + 16 * g + r];
+    if (chunk >= chunks) return;                     // whole waves; no workgroup barrier below
+    const int64_t s5 = chunk / RB, rb = chunk - s5 * RB;
+    uint32_t* tile = tiles[wave];
+    {
+        const int g = lane >> 4, r = lane & 15;
         const uint32_t wd[4] = {q.x, q.y, q.z, q.w};
         uint32_t fifth = 0;
 #pragma unroll
@@ -349,19 +353,21 @@ __global__ __launch_bounds__(256) void repack_trit5_to_2bit(const uint4* __restr
                 w |= e.x << (2 * i);
                 fifth |= e.y << (8 * i + 2 * j);                                // column 64 + p = 64 + 4 j + i: byte i, field j
             }
-            words[5 * g + j] = w;
+            tile[r * 20 + 5 * g + j] = w;
         }
-        words[5 * g + 4] = fifth;
+        tile[r * 20 + 5 * g + 4] = fifth;
     }
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-    for (int q5 = 0; q5 < 5; ++q5) {
+    for (int h = 0; h < 2; ++h) {
+        const int p = h * kWave + lane, q5 = p >> 4, r = p & 15;               // piece p: quad q5 of row r
         const int64_t kq = 5 * s5 + q5;
-        if (kq < Kq2)
-            out[quad_index_2bit(kq, rb, r, Kq2, RB)] = make_uint4(words[4 * q5], words[4 * q5 + 1], words[4 * q5 + 2], words[4 * q5 + 3]);
+        if (q5 < 5 && kq < Kq2) out[quad_index_2bit(kq, rb, r, Kq2, RB)] = *reinterpret_cast<const uint4*>(tile + r * 20 + 4 * q5);
     }
 }
 
-// 2-bit -> 5-trit: the same move backwards; 2-bit quads past the matrix's last one read as zero codes.
+// 2-bit -> 5-trit: the same move backwards, one thread per row and 320 columns (consecutive threads take consecutive rows of a
+// 16-row block, so their 16-byte loads and stores form 256-byte runs in both layouts); 2-bit quads past the matrix's last one read as zero codes.
 __global__ __launch_bounds__(256) void repack_2bit_to_trit5(const uint4* __restrict__ in, int64_t RB, int64_t steps5,
                                                             int64_t Kq2, uint4* __restrict__ out) {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -396,12 +402,11 @@ __global__ __launch_bounds__(256) void repack_2bit_to_trit5(const uint4* __restr
 
 hipError_t launch_repack(const void* in, bool in_trit5, int64_t N, int64_t K, void* out, hipStream_t stream) {
     const int64_t RB = ceil_div(N, kRowsPerBlock), steps5 = ceil_div(K, kTritStep), Kq2 = ceil_div(K, kColsPerQuad);
-    dim3 grid((unsigned)ceil_div(16 * RB * steps5, 256));
     if (in_trit5)
-        hipLaunchKernelGGL(repack_trit5_to_2bit, grid, dim3(256), 0, stream, static_cast<const uint4*>(in), RB, steps5, Kq2,
-                           static_cast<uint4*>(out));
+        hipLaunchKernelGGL(repack_trit5_to_2bit, dim3((unsigned)ceil_div(RB * steps5, kRepackWaves)), dim3(kRepackWaves * kWave), 0, stream,
+                           static_cast<const uint4*>(in), RB, RB * steps5, Kq2, static_cast<uint4*>(out));
     else
-        hipLaunchKernelGGL(repack_2bit_to_trit5, grid, dim3(256), 0, stream, static_cast<const uint4*>(in), RB, steps5, Kq2,
+        hipLaunchKernelGGL(repack_2bit_to_trit5, dim3((unsigned)ceil_div(16 * RB * steps5, 256)), dim3(256), 0, stream, static_cast<const uint4*>(in), RB, steps5, Kq2,
                            static_cast<uint4*>(out));
     return hipGetLastError();
 }
