@@ -349,9 +349,15 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_gemv16_2bit(
         int N32, int K32, uint32_t flags /* tokens, output type, gamma stride (0: one gamma, 1: one per row block) */, float eps) {
     const float* sx = gain;
     const int64_t K = K32, N = N32;
+    const int tile0 = kX == kXLdsAny ? 16 * (int)blockIdx.y : 0;      // kXLdsAny: this workgroup's first token, 16 per workgroup
     const int Kq = (K32 + kColsPerQuad - 1) / kColsPerQuad;
-    const int M = flags_number(flags), gstride = flags_gstride(flags);
+    const int M_rest = flags_number(flags) - tile0, M = kX == kXLdsAny ? min(M_rest, 16) : M_rest, gstride = flags_gstride(flags);
     const OutType yt = flags_out_type(flags);
+    if (kX == kXLdsAny) {
+        xin = static_cast<const char*>(xin) + tile0 * K;
+        sx += tile0;
+        y = static_cast<char*>(y) + tile0 * N * (yt == OutType::BF16 ? 2 : 4);
+    }
     const int pair_off = kPair ? N32 / kRowsPerBlock : 0;
     const int RB = kPair ? 2 * pair_off : (int)((N + kRowsPerBlock - 1) / kRowsPerBlock);
     const int items = gemv16_items(Kq, kS, kD);
@@ -476,7 +482,7 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_gemv16_2bit(
             const int m = v / (Kpad >> 4), kv = v % (Kpad >> 4);
             uint4 val = make_uint4(0, 0, 0, 0);
             if (kX == kXLdsAny) {                      // past the row: the next one's bytes meet zero codes, the end of x_q is kept to
-                if ((int64_t)kv * 16 < K) val = load_any16(xq + (int64_t)m * K + (int64_t)kv * 16, (int64_t)(M - m) * K - (int64_t)kv * 16);
+                if ((int64_t)kv * 16 < K) val = load_any16(xq + (int64_t)m * K + (int64_t)kv * 16, (int64_t)(M_rest - m) * K - (int64_t)kv * 16);
             } else if ((int64_t)kv * 16 + 16 <= K) {
                 val = reinterpret_cast<const uint4*>(xq + (int64_t)m * K)[kv];
             }
@@ -557,6 +563,7 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_gemv16_2bit(
 // host side
 // ---------------------------------------------------------------------------------------------------
 constexpr size_t kGemvLdsBudget = 65536;
+constexpr size_t kGemvAnyLdsBudget = 80 * 1024;      // kXLdsAny: two workgroups per CU
 
 static size_t gemv16_x_lds_bytes(int64_t M, int64_t K) { return (size_t)M * ceil_div(K, 256) * 256; }
 
@@ -574,14 +581,14 @@ static hipError_t launch16(int xmode, const void* x, const float* sx, const void
     const uint32_t flags = product_flags(gstride, yt) | (uint32_t)M << 4;
     const size_t header = kGemvLdsHeader * sizeof(uint4);
     const size_t lds_fold = kS > 1 ? (size_t)kW * kS * kR * kWave * 16 : 0;
-    const size_t lds_x = gemv16_x_lds_bytes(M, K);
+    const size_t lds_x = gemv16_x_lds_bytes(xmode == kXLdsAny && M > 16 ? 16 : M, K);
     if (xmode == kXLds && header + lds_x > kGemvLdsBudget) xmode = kXGlobal;
     const size_t lds = header + (xmode != kXGlobal && lds_x > lds_fold ? lds_x : lds_fold);
-    dim3 grid((unsigned)ceil_div(RB, kW * kR)), block(kS * kW * kWave);
+    dim3 grid((unsigned)ceil_div(RB, kW * kR), xmode == kXLdsAny ? (unsigned)ceil_div(M, 16) : 1u), block(kS * kW * kWave);
     const int need = xmode == kXLdsAny ? kModesAny : xmode <= kXLds ? kModesInt8 : xmode <= kXFusedF32 ? kModesFused : kModesPre;
     if ((kModes & need) == 0) return hipErrorInvalidDeviceFunction;   // a dispatch rule asked a launch shape for a mode it is not built for
     if (plan) {
-        plan->set(xmode == kXLdsAny ? "reference" : "decode", {kR, kS, kW, kD, xmode}, grid.x, 1, block.x, lds, 1);
+        plan->set(xmode == kXLdsAny ? "reference" : "decode", {kR, kS, kW, kD, xmode}, grid.x * grid.y, 1, block.x, lds, 1);
         return hipSuccess;
     }
     const uint4* p = static_cast<const uint4*>(packed);
@@ -602,7 +609,15 @@ static hipError_t launch16(int xmode, const void* x, const float* sx, const void
         if (xmode == kXSwigluF32) { GO(kXSwigluF32); return hipGetLastError(); }
     }
     if constexpr ((kModes & kModesAny) != 0) {
-        if (xmode == kXLdsAny) { GO(kXLdsAny); return hipGetLastError(); }
+        if (xmode == kXLdsAny) {
+            if (lds > kGemvLdsBudget) {
+                static RaisedFlags raised = {};
+                const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(linear_gemv16_2bit<kR, kS, kW, kD, kXLdsAny>), (int)kGemvAnyLdsBudget, raised);
+                if (e != hipSuccess) return e;
+            }
+            GO(kXLdsAny);
+            return hipGetLastError();
+        }
     }
 #undef GO
     return hipErrorInvalidDeviceFunction;
@@ -735,11 +750,16 @@ static hipError_t dispatch16_fused(int xmode, const void* x, const void* packed,
     }
 }
 
-// x_q rows of any length and alignment, up to 16 tokens that fit the LDS: two K-split waves per row block where there are many
-// row blocks, four otherwise (the picks of the aligned kernel for one token on the same layers).
+// x_q rows of any length and alignment: up to 16 tokens that fit the LDS, and more in tiles of 16 over grid y while the 64 x 128
+// tiles of the GEMM would be few (the weights then come from the L2 for every tile but the first).  Two K-split waves per row
+// block where there are many row blocks, four otherwise (the picks of the aligned kernel for one token on the same layers).
+// Up to two workgroups per CU of that form (quantization included, us, this form / the GEMM's tiles: 77 tokens, 2050 -> 1003, 315
+// workgroups, 10.6 / 13.6; 150, 2777 -> 500, 320, 11.0 / 18.1; 40, 3900 -> 1900, 357, 11.2 / 19.1; but 200, 3333 -> 1000, 819,
+// 20.6 / 18.0).
 bool gemv_any_supports(int64_t M, int64_t N, int64_t K) {
-    (void)N;
-    return M >= 1 && M <= 16 && kGemvLdsHeader * sizeof(uint4) + gemv16_x_lds_bytes(M, K) <= kGemvLdsBudget;
+    const size_t lds = kGemvLdsHeader * sizeof(uint4) + gemv16_x_lds_bytes(M < 16 ? M : 16, K);
+    if (M < 1 || lds > kGemvAnyLdsBudget) return false;
+    return M <= 16 || ceil_div(M, 16) * ceil_div(N, kRowsPerBlock) <= 512;
 }
 hipError_t launch_linear_gemv_any_2bit(const int8_t* x, const float* sx, const void* packed, const float* gamma, int gstride, int64_t M,
                                        int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan) {

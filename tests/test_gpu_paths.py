@@ -63,7 +63,10 @@ def test_segments_side_by_side(gpu_lib, rows, K, bf16):
 # below and above one K step) and the tiles of the GEMM (two K groups, four waves, 64 x 256), each with ragged rows and tokens
 @pytest.mark.parametrize("M,N,K", [(1, 1, 1), (1, 40, 7), (3, 100, 255), (16, 33, 1001), (2, 16400, 259), (1, 300, 4097),
                                    (17, 130, 5), (64, 128, 255), (65, 129, 257), (77, 1003, 2050), (100, 3000, 513), (200, 1000, 3333),
-                                   (1030, 2500, 301), (700, 25000, 77), (16, 50, 8001)])
+                                   (1030, 2500, 301), (700, 25000, 77), (16, 50, 8001),
+                                   # more than 16 tokens in tiles over the grid: a full and a partial last tile, K beyond 64 KiB of
+                                   # LDS, the most workgroups of the form and one more
+                                   (32, 70, 333), (40, 1900, 3900), (33, 100, 5000), (8192, 16, 33), (8193, 16, 33)])
 @pytest.mark.parametrize("y", ["I32", "F32", "BF16"])
 def test_rows_of_any_length(gpu_lib, M, N, K, y):
     packed, gamma = gpu_lib.quantize_weights(dev(synth.weights(N, K, config=1, layer=M % 7)))
@@ -225,3 +228,22 @@ def test_rmsnorm_exact_sum_where_the_rounded_one_does_not_decide(gpu_lib):
         assert torch.equal(got, want)
     z = torch.zeros(2, K, device="cuda")      # nothing to norm, eps = 0: 1 / 0 is the definition's business, the codes are zero
     assert int(gpu_lib.rmsnorm_quantize(z, None, 1e-6)[0].abs().max()) == 0
+
+
+# x in rows of any length and alignment through the quantizer that holds a row in registers: less than one load, whole loads and
+# a rest of every size class, the longest rows it takes and the first beyond, a base one element past an aligned address
+@pytest.mark.parametrize("M,K", [(3, 1), (5, 7), (4, 9), (2, 2047), (77, 2050), (9, 4099), (2, 8187), (2, 8191), (2, 16381), (2, 16391), (300, 333)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_quantize_acts_rows_of_any_length(gpu_lib, M, K, bf16):
+    x, bits = synth.activations(M, K, config=2, layer=K % 7, tensor=3, bf16=True)
+    xq_ref, sx_ref = oracle.quantize_acts(x)
+    xd = dev_bf16(bits).view(M, K) if bf16 else dev(x)
+    off = torch.empty(M * K + 1, dtype=xd.dtype, device="cuda")
+    off[1:] = xd.reshape(-1)
+    out = torch.full((M * K + 65,), 0x55, dtype=torch.int8, device="cuda")
+    for src in (xd, off[1:].view(M, K)):
+        for dst in (None, out[1:1 + M * K].view(M, K)):
+            xq, sx = gpu_lib.quantize_acts(src, xq=dst)
+            assert sx.cpu().numpy().tobytes() == sx_ref.tobytes()
+            assert np.array_equal(xq.cpu().numpy(), xq_ref)
+    assert bool((out[1 + M * K:] == 0x55).all()) and int(out[0]) == 0x55
