@@ -832,7 +832,12 @@ hipError_t launch_linear_fused_swiglu_out_2bit(const void* x, bool bf16, bool no
     // and no K split, four pairs per workgroup up to 1024 pairs (at most 256 workgroups), eight beyond.
     const int64_t pairs = F / kRowsPerBlock;
     if (!norm && pairs <= 700) launch16_pair<4, 1, 4>(xmode, x, packed, gamma, gstride, M, F, K, h, yt, stream, gain, eps, plan);
-    else if (pairs <= 1024) {
+    else if (M <= 2 && pairs <= 512 && K <= 2560) {
+        // up to ten K steps: a wave that walks them alone takes longer over its loads than the norm that more workgroups repeat
+        // (one token through eight decoder layers in a graph, us: 1024 wide 136.4 -> 129.7, 1536 147.3 -> 131.4, 2048 156.1 ->
+        // 149.9, 2560 165.6 -> 161.6; 3200 wide 608 -> 635 for 26)
+        launch16_pair<4, 1, 2>(xmode, x, packed, gamma, gstride, M, F, K, h, yt, stream, gain, eps, plan);
+    } else if (pairs <= 1024) {
         // depth 5 or 4, whichever pads the K walk less (16 steps at depth 5 walk 20: 7B gate/up with the norm 10.5 -> 9.5 us)
         const int64_t steps = ceil_div(K, 256);
         if (walk_efficiency(steps, 1, 5) >= walk_efficiency(steps, 1, 4))

@@ -247,3 +247,21 @@ def test_quantize_acts_rows_of_any_length(gpu_lib, M, K, bf16):
             assert sx.cpu().numpy().tobytes() == sx_ref.tobytes()
             assert np.array_equal(xq.cpu().numpy(), xq_ref)
     assert bool((out[1 + M * K:] == 0x55).all()) and int(out[0]) == 0x55
+
+
+# the gate/up launch with the norm in front on narrow layers: K split over four waves, fewer steps than waves to a partial
+# eleventh, one and two tokens; and its neighbours (three tokens, eleven steps, 513 pairs)
+@pytest.mark.parametrize("M,F,K", [(1, 2752, 1024), (2, 4096, 1536), (1, 16, 16), (2, 48, 528), (1, 8192, 2560), (1, 1008, 2064), (3, 1008, 1040),
+                                   (1, 1008, 2576), (1, 8208, 528)])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_gate_up_with_norm_on_narrow_layers(gpu_lib, M, F, K, bf16):
+    B = gpu_lib
+    x, bits = synth.activations(M, K, config=2, layer=F % 5, bf16=True)
+    g = (1.0 + 0.25 * np.random.default_rng(K).standard_normal(K)).astype(np.float32)
+    packed, gamma = B.quantize_weights(dev(synth.weights(2 * F, K, config=1, layer=2)))
+    xd = dev_bf16(bits).view(M, K) if bf16 else dev(x)
+    gu = B.linear(*B.rmsnorm_quantize(xd, dev(g), 1e-6), packed, gamma, 2 * F)      # fp32 gate and up, each step against the oracle elsewhere
+    h = B.ffn_gate_up_fused(xd, packed, gamma, F, norm=True, g=dev(g), eps=1e-6)
+    hq_ref, sh_ref, _ = oracle.swiglu_quantize(gu.cpu().numpy())
+    hq, sh = B.quantize_acts(h)
+    assert sh.cpu().numpy().tobytes() == sh_ref.tobytes() and np.array_equal(hq.cpu().numpy(), hq_ref)
