@@ -265,3 +265,25 @@ def test_gate_up_with_norm_on_narrow_layers(gpu_lib, M, F, K, bf16):
     hq_ref, sh_ref, _ = oracle.swiglu_quantize(gu.cpu().numpy())
     hq, sh = B.quantize_acts(h)
     assert sh.cpu().numpy().tobytes() == sh_ref.tobytes() and np.array_equal(hq.cpu().numpy(), hq_ref)
+
+
+# the |W| sum of bf16 weights: vectors of eight whose exponents lie just within and just beyond what one fp32 sum takes exactly,
+# zeros among them, denormals, all of it mixed; gamma bit for bit
+@pytest.mark.parametrize("spread", [0, 11, 12, 13, 14, 40, 100])
+@pytest.mark.parametrize("N,K", [(64, 264), (2048, 3072), (3, 40)])
+def test_abs_sum_bf16_exponent_spread(gpu_lib, N, K, spread):
+    rng = np.random.default_rng([spread, N])
+    W = (rng.uniform(1.0, 2.0, (N, K)) * 2.0 ** -rng.integers(0, spread + 1, (N, K)) * rng.choice([-1.0, 1.0], (N, K))).astype(np.float32)
+    W[rng.random((N, K)) < 0.05] = 0.0
+    if spread == 100:
+        W *= np.float32(2.0 ** -30)          # down to denormals
+    W, bits = synth.to_bf16(W)
+    packed, gamma = gpu_lib.quantize_weights(dev_bf16(bits).view(N, K))
+    check_packed(gpu_lib, W, packed, gamma)
+    s = gpu_lib.abs_sum(dev_bf16(bits).view(N, K)).cpu().numpy()
+    from fractions import Fraction
+    if N * K < 100_000:
+        got, want = Fraction(float(s[0])) + Fraction(float(s[1])), sum(map(Fraction, np.abs(W).astype(np.float64).ravel().tolist()))
+        # 8 bits, a spread of up to 40 and 15 bits of count fit a pair of doubles; a spread of 100 does not, and each of up to
+        # 2^15 additions may round the low word, which is below 2^15 roundings of the high one, by 2^-53 of itself
+        assert got == want if spread <= 40 else abs(got - want) <= want * Fraction(2) ** (15 + 15 - 53 - 53)
