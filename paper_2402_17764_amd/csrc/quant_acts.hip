@@ -2,9 +2,10 @@
 // are scaled per token into [-Q_b, Q_b], Q_b = 127, with no zero point).
 //
 // One workgroup per token.  The token is read once into registers (16-byte loads), the absmax is
-// reduced with DPP / shuffle steps inside each wave and through LDS across waves, then the same
-// registers are scaled, rounded (ties to even) and written as packed int8.  Tokens too long for the
-// register budget, or rows that are not 16-byte aligned, take a two-sweep path that re-reads x.
+// reduced with DPP steps and scalar reads inside each wave and through LDS across waves, then the same
+// registers are scaled, rounded (ties to even) and written as packed int8; rows of any length and alignment
+// take the same loads at element alignment.  Tokens too long for the register budget take a two-sweep path that
+// re-reads x.
 #include "bitnet_device.hpp"
 #include "bitnet_internal.hpp"
 

@@ -8,7 +8,7 @@
 //                              cache), takes the decision of Eq. (1)-(2) in fp32 and writes the packed
 //                              layout one 1 KiB (row block, K step) chunk per workgroup pass
 //
-// The whole path is HBM-bound at 8.25 B per weight (two reads of W, one packed write).  Both reading passes
+// The whole path is HBM-bound at 8.25 B per fp32 weight, 4.25 per bf16 one (two reads of W, one packed write).  Both reading passes
 // are shaped by what a plain read loop reaches on this chip: 8 waves per CU with four 16-byte loads each in
 // flight read 6.1-6.2 TB/s, 32 waves per CU 5.1-5.3 TB/s.
 #include "bitnet_device.hpp"
