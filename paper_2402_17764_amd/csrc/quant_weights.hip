@@ -29,9 +29,10 @@ __device__ inline float widen1(uint16_t v) { return bf16_to_f32(v); }
 // |.| of the 4 (fp32) or 8 (bf16) elements of one 16-byte vector, added to the accumulators.
 //
 // bf16: eight magnitudes of 8 significant bits whose exponents lie within 13 of one another add up in fp32 without rounding
-// (8 + 13 + 3 bits), so that one double-double addition takes all eight; a vector with a wider spread (zeros do not count: one
-// in a thousand of normally distributed weights) takes eight.  The sum is exact either way.  With eight conversions and
-// double-double additions for every vector the pass was close to VALU-bound: 57344 x 8192, both passes, 346.6 -> 338.2 us.
+// (8 + 13 + 3 bits), and below 2^125 without passing the largest float, so that one double-double addition takes all eight; a
+// vector with a wider spread (zeros do not count: one in a thousand of normally distributed weights) or a larger magnitude takes
+// eight.  The sum is exact either way.  With eight conversions and double-double additions for every vector the pass was close
+// to VALU-bound: 57344 x 8192, both passes, 346.6 -> 338.2 us.
 typedef unsigned short sum_u16x2 __attribute__((ext_vector_type(2)));
 template <typename T>
 __device__ inline void add_abs(const uint4& q, dd (&part)[4], int slot) {
@@ -48,8 +49,9 @@ __device__ inline void add_abs(const uint4& q, dd (&part)[4], int slot) {
         top = __builtin_elementwise_max(top, mag);
         low = __builtin_elementwise_min(low, mag - (sum_u16x2){1, 1});           // a zero wraps to the top: it does not count
     }
-    const int widest = (int)(top.x > top.y ? top.x : top.y) - (int)(low.x < low.y ? low.x : low.y);      // exponents from bit 7 up
-    if (__builtin_expect(widest <= 12 * 128, 1)) {
+    const int largest = (int)(top.x > top.y ? top.x : top.y);                    // exponents from bit 7 up
+    const int widest = largest - (int)(low.x < low.y ? low.x : low.y);
+    if (__builtin_expect(widest <= 12 * 128 && largest < (127 + 125) * 128, 1)) {
         float f[8];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {

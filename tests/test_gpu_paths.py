@@ -287,3 +287,27 @@ def test_abs_sum_bf16_exponent_spread(gpu_lib, N, K, spread):
         # 8 bits, a spread of up to 40 and 15 bits of count fit a pair of doubles; a spread of 100 does not, and each of up to
         # 2^15 additions may round the low word, which is below 2^15 roundings of the high one, by 2^-53 of itself
         assert got == want if spread <= 40 else abs(got - want) <= want * Fraction(2) ** (15 + 15 - 53 - 53)
+
+
+# ... and near the top of bf16's range: eight magnitudes whose fp32 sum would, or would just not, pass the largest float (eight
+# times 2^125 is 2^128), alone and among smaller ones; every entry point that takes the sum
+@pytest.mark.parametrize("top", [1.9 * 2.0 ** 124, 255 / 128 * 2.0 ** 124, 2.0 ** 125, 9.97e37, 255 / 128 * 2.0 ** 127])
+@pytest.mark.parametrize("spread", [0, 3, 12])
+@pytest.mark.parametrize("N,K", [(16, 64), (48, 1032)])
+def test_abs_sum_bf16_near_the_top_of_the_range(gpu_lib, N, K, top, spread):
+    rng = np.random.default_rng([spread, K])
+    W = (np.float32(top) * 2.0 ** -rng.integers(0, spread + 1, (N, K)) * rng.choice([-1.0, 1.0], (N, K))).astype(np.float32)
+    W, bits = synth.to_bf16(W)
+    Wd = dev_bf16(bits).view(N, K)
+    packed, gamma = gpu_lib.quantize_weights(Wd)
+    check_packed(gpu_lib, W, packed, gamma)
+    assert np.isfinite(gamma.cpu().numpy()).all()
+    from fractions import Fraction
+    s = gpu_lib.abs_sum(Wd).cpu().numpy()
+    assert Fraction(float(s[0])) + Fraction(float(s[1])) == sum(map(Fraction, np.abs(W).astype(np.float64).ravel().tolist()))
+    codes_ref, gamma_ref = oracle.quantize_weights(W)
+    packed5, gamma5 = gpu_lib.quantize_weights(Wd, gpu_lib.PACK_TRIT5)
+    assert gamma5.cpu().numpy().tobytes() == np.float32(gamma_ref).tobytes()
+    assert np.array_equal(gpu_lib.unpack_weights(packed5, N, K, gpu_lib.PACK_TRIT5).cpu().numpy(), codes_ref)
+    packed_s, gamma_s = gpu_lib.quantize_weights_segmented(Wd, [N])
+    assert torch.equal(packed_s, packed) and bool((gamma_s == gamma).all())
