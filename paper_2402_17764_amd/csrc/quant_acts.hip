@@ -442,14 +442,36 @@ __global__ __launch_bounds__(kThreads) void swiglu_quantize_kernel(
 
 // The same for bf16 rows of many tokens.  The gate costs ~45 VALU instructions an element (exponential, IEEE division): more
 // time than the bytes.  But silu's argument is a bf16 value, so a workgroup evaluates it once for every value of magnitude
-// 2^-17 ... 2^6 (23 exponents x 128 mantissas x 2 signs, 23 KB of LDS: the very same function, the same bits) and looks it up
+// 2^-15 ... 2^8 (23 exponents x 128 mantissas x 2 signs, 23 KB of LDS: the very same function, the same bits) and looks it up
 // for all elements of all its tokens.  Zero has an entry too -- a projection's integer sum is 0 for one output in a thousand,
-// which is one in half of all wave-wide vectors -- and any other element outside sends its lane through the arithmetic.  A
+// which is one in half of all wave-wide vectors -- and a wave that holds any other magnitude goes through silu_beyond_table.  A
 // workgroup walks tokens blockIdx.x, + workgroups, ... with the next token's loads in flight under the current one's work.
-// bf16, alone: 64 x 11008 9.6 -> 4.9 us, 256 x 13824 14.5 -> 6.7, 2048 x 13824 38.5 -> 29.8 (4.75 TB/s of the bytes it cannot
-// do without), 4096 x 28672 126 -> 112 (5.2 TB/s, what a device copy reaches).
-constexpr int kSiluBase = (127 - 17) << 7;                 // bf16 bits of 2^-17
-constexpr int kSiluSpan = (23 << 7) + 1;                   // zero, and the magnitudes from there to 2^6
+// bf16, alone, arithmetic / table: 64 x 11008 8.9 / 5.0 us, 256 x 5120 5.4 / 4.7, 2048 x 13824 38.5 / 25.4, 4096 x 28672 134 / 113
+// (5.2 TB/s, what a device copy reaches).  Gates that are all beyond the table (around 1e4, or 1e-5): 64 x 11008 6.0, 2048 x 13824
+// 31.3, 4096 x 28672 126; only for a few tokens does the table then not pay for itself (1 x 16384 5.7 / 6.6, ordinary gates 4.8).
+constexpr int kSiluBase = (127 - 15) << 7;                 // bf16 bits of 2^-15
+constexpr int kSiluLimit = (127 + 8) << 7;                 // ... and of 2^8
+constexpr int kSiluSpan = kSiluLimit - kSiluBase + 1;      // zero, and the magnitudes in between
+
+// silu of any bf16 value, with the table's help: the bits of silu_one, checked for every one of the 65536.  From 88 on
+// exp32(-gate) is one constant for each sign, and silu a multiple of the gate: the entry of the same mantissa in [2^7, 2^8)
+// times a power of two.  Below 2^-15 the exponential's polynomial comes down to its last three terms, and the divisor is so
+// close to 2 that a quotient from the first term of a series needs one correction.
+__device__ inline float silu_beyond_table(uint32_t bits, const float* table) {
+    const float g = __uint_as_float(bits << 16);
+    const uint32_t mag = bits & 0x7FFFu, sign = bits >> 15;
+    const bool high = mag >= (uint32_t)kSiluLimit;
+    const uint32_t at = high ? (uint32_t)(kSiluLimit - 128) | (mag & 127u) : mag;
+    const uint32_t d = at < (uint32_t)kSiluBase ? 0u : at - (uint32_t)(kSiluBase - 1);
+    float v = table[2 * d + sign] * (high ? __uint_as_float(((mag >> 7) - 7u) << 23) : 1.0f);
+    const float s = 1.0f + __builtin_fmaf(-g, __builtin_fmaf(g, -0.5f, 1.0f), 1.0f);
+    const float q = __builtin_fmaf(0.5f * g, __builtin_fmaf(s, -0.5f, 1.0f), 0.5f * g);     // g / s by a term of its series ...
+    if (mag - 1u < (uint32_t)(kSiluBase - 1))              // ... and the remainder over barely less than 2
+        v = __builtin_fmaf(__builtin_fmaf(-q, s, g), 0x1.000002p-1f, q);
+    if (mag >= 0x7F80u) v = g;                             // infinities keep their sign, NaN stays
+    return v;
+}
+
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 template <int kVecs, int kThreads>
@@ -497,7 +519,7 @@ __global__ __launch_bounds__(kThreads) void swiglu_quantize_table(const uint16_t
                 low = __builtin_elementwise_min(low, mag - (u16x2){1, 1});        // zero wraps: it is no low magnitude
             }
             const bool inside = (top.x > top.y ? top.x : top.y) < kSiluSpan && (low.x < low.y ? low.x : low.y) >= kLow;
-            if (__builtin_expect(inside, 1)) {
+            if (__builtin_expect(!__any(!inside), 1)) {             // the same for the wave
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
                     const uint32_t at = (__builtin_bit_cast(uint32_t, d[e]) << 1) | ((gw[e] >> 15) & 0x00010001u);
@@ -507,8 +529,8 @@ __global__ __launch_bounds__(kThreads) void swiglu_quantize_table(const uint16_t
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    h[v][2 * e] = silu_one(__uint_as_float(gw[e] << 16));
-                    h[v][2 * e + 1] = silu_one(__uint_as_float(gw[e] & 0xFFFF0000u));
+                    h[v][2 * e] = silu_beyond_table(gw[e] & 0xFFFFu, table);
+                    h[v][2 * e + 1] = silu_beyond_table(gw[e] >> 16, table);
                 }
             }
 #pragma unroll

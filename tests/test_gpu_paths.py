@@ -157,13 +157,44 @@ def test_swiglu_table_every_gate(gpu_lib, F):
     assert np.array_equal(hq.cpu().numpy(), hq_ref)
 
 
+# ... and every bf16 gate there is, bit for bit: a token's scale is the |h| of its largest element, so tokens that hold one gate
+# throughout, and tokens whose other elements are gated to zero, show the fp32 silu of each gate; against the arithmetic form,
+# which fp32 input takes, on the same values
+@pytest.mark.parametrize("alone", [True, False])
+def test_swiglu_table_bits_of_every_gate(gpu_lib, alone):
+    F, M = 5120, 8192
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    for first in range(0, 65536, M):
+        bits = torch.arange(first, first + M, device="cuda", dtype=torch.int32)
+        gate = (bits << 16).view(torch.float32)
+        finite = torch.isfinite(gate)
+        g64 = gate.double()
+        silu = torch.where(gate < -80, g64 / 1.65e38, g64 * torch.sigmoid(g64)).abs().clamp_min(2.0 ** -140)
+        up = (1.0 / silu).clamp_max(3.38e38).clamp_min(2.0 ** -126)                     # |h| near 1 (0.01 for the least of gates)
+        gu = torch.randn(M, 2 * F, device="cuda", generator=gen)
+        gu[:, F:] = up[:, None].float() if alone else 0.0
+        if alone:
+            gu[:, :F] = gate[:, None]
+        at = torch.randint(0, F, (M, 1), device="cuda", generator=gen)
+        gu.scatter_(1, at, gate[:, None])
+        gu.scatter_(1, at + F, up[:, None].float())
+        x = gu.bfloat16()
+        hq, sh = gpu_lib.swiglu_quantize(x)
+        hq_want, sh_want = gpu_lib.swiglu_quantize(x.float())
+        assert torch.equal(sh[finite].view(torch.int32), sh_want[finite].view(torch.int32))
+        assert torch.equal(hq[finite], hq_want[finite])
+        assert torch.equal(sh.isnan(), sh_want.isnan()) and torch.equal(sh.isinf(), sh_want.isinf())
+        near = finite & (gate != 0)
+        assert bool((sh[near] > 0.009).all())                                           # nothing hidden behind the least scale
+
+
 @pytest.mark.parametrize("M,F", [(600, 5120), (257, 11008), (256, 5128), (255, 5128), (1100, 8640), (8, 8192), (7, 8192), (1, 16384), (1023, 264), (1024, 264)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_swiglu_many_tokens(gpu_lib, M, F, bf16):
     gu, bits = synth.activations(M, 2 * F, config=2, layer=F % 5, tensor=5, bf16=True)
     gu[:, :F:7] *= 0.0                        # zeros of both signs have an entry, these magnitudes have none
     gu[0, 1:F:9] = 1e-7
-    gu[-1, 2:F:9] = -70.0
+    gu[-1, 2:F:9] = -700.0
     gu[M // 2, 3:F:9] = 1e-39
     gu, bits = synth.to_bf16(gu)
     hq_ref, sh_ref, _ = oracle.swiglu_quantize(gu)
