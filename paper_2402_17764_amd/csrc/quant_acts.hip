@@ -637,11 +637,12 @@ hipError_t launch_rmsnorm_quantize(const void* x, bool bf16, const float* g, flo
 // Where the table form is the faster one, measured where the launch stands in use (behind the gate/up product and in front of
 // the down product, us for all of it, arithmetic / table): 5120 -> 13824 at 16 tokens, two layers, 101.7 / 99.3, at 128 179.3 /
 // 176.2, at 1024 201.8 / 194.2; 2048 tokens 356 / 345.  Narrow rows leave most of the 1024 threads idle and pay for the
-// table all the same: 700 x 4096 33.6 / 34.2, 64 x 5504 equal; so do single tokens (alone, 1 x 8640 3.8 / 3.9, but 29 x 28672
-// 10.5 / 6.8).
+// table all the same: 700 x 4096 33.6 / 34.2, 64 x 5504 equal; so do few tokens of up to 9216 elements (alone, 8 x 8192 3.9 / 4.3,
+// 29 x 8640 4.3 / 4.5, 63 x 9600 4.9 / 4.8; eight layers of 3072 -> 8192 at 10 tokens 264 / 265.3, of 4096 -> 9600 at 16 302.9 / 301.2),
+// while wide ones gain at any count (alone, 1 x 16384 5.7 / 4.6, 1 x 28672 8.8 / 6.0, 29 x 28672 10.5 / 6.8).
 static bool swiglu_by_table(const void* gu, int64_t M, int64_t F, const void* hq) {
     if (F % 8 != 0 || F > 32768 || reinterpret_cast<uintptr_t>(gu) % 16 != 0 || reinterpret_cast<uintptr_t>(hq) % 8 != 0) return false;
-    return F >= 5120 && M >= (F >= 16384 ? 1 : F >= 8192 ? 8 : 256);
+    return F >= 5120 && M >= (F >= 16384 ? 1 : F >= 9216 ? 8 : F >= 8192 ? 64 : 256);
 }
 
 hipError_t launch_swiglu_quantize(const void* gu, bool bf16, int64_t M, int64_t F, int8_t* hq, float* sh,
