@@ -554,11 +554,16 @@ __global__ __launch_bounds__(kThreads) void swiglu_quantize_table(const uint16_t
     }
 }
 
-// SwiGLU, fewer tokens than the chip holds workgroups of 1024 threads for four times over: 1024 threads per token, so that
-// the dependent chains of the gate (exponential, division) interleave over four waves per SIMD; more tokens: 256, and the
-// tokens fill the CUs (fp32: 100 x 8640 9.6 us with 256 threads, 5.1 with 1024; 300 x 11008 12.7, 9.6; 600 x 11008 17.2, 15.2).
-// Rows too long for 256 threads' registers take 1024 threads at any token count.
-constexpr int kProdFewTokens = 1024;
+// SwiGLU, threads per token.  Few tokens: 1024, so that the dependent chains of the gate (exponential, division) interleave over
+// four waves per SIMD; many: 256, and the tokens fill the CUs.  From 64 to 1023 tokens it is the row that decides: with 1024 threads
+// the chip runs fewer tokens at a time, which pays while the row gives all of them work (fp32, 256 threads / 1024: 100 x 8640 9.6 /
+// 5.1 us, 600 x 11008 17.2 / 15.2, 1000 x 4096 9.2 / 8.8; bf16: 500 x 1536 3.6 / 3.4, 800 x 2560 5.5 / 5.3) and not on narrow rows (bf16,
+// 600 x 264 2.7 / 3.4, 1000 x 1024 3.6 / 4.3).  The sweeping form, whose chains are longer, from half as wide a row on (fp32, 600 x
+// 1001 4.9 / 4.6, 800 x 1001 5.2 / 5.4).  Rows too long for 256 threads' registers take 1024 at any token count.
+static bool producer_wide(bool vec, int64_t M, int64_t cols) {
+    if (M < 64 || cols > (int64_t)kProdMaxChunks * 256 * 4) return true;
+    return M < 1024 && (vec ? cols > 1024 && cols >= 3 * M : cols > 256 && 2 * cols >= 3 * M);
+}
 
 // chunks of four: rows must start on a chunk boundary of the input loads and of the 32-bit stores
 static bool producer_vec_ok(const void* in, size_t esz, int64_t cols, const void* out) {
@@ -568,7 +573,7 @@ static bool producer_vec_ok(const void* in, size_t esz, int64_t cols, const void
 
 // threads per token and register chunks per thread for a row of `cols` elements (chunks == 0: the sweeping form)
 static void producer_shape(bool vec, int64_t M, int64_t cols, int* threads, int* chunks) {
-    *threads = (M < kProdFewTokens || cols > (int64_t)kProdMaxChunks * 256 * 4) ? 1024 : 256;
+    *threads = producer_wide(vec, M, cols) ? 1024 : 256;
     *chunks = 0;
     if (!vec) return;
     const int64_t need = ceil_div(cols, (int64_t)*threads * 4);

@@ -188,7 +188,9 @@ def test_swiglu_table_bits_of_every_gate(gpu_lib, alone):
         assert bool((sh[near] > 0.009).all())                                           # nothing hidden behind the least scale
 
 
-@pytest.mark.parametrize("M,F", [(600, 5120), (257, 11008), (256, 5128), (255, 5128), (1100, 8640), (8, 8192), (7, 8192), (63, 9208), (64, 8192), (8, 9216), (7, 9216), (1, 16384), (1023, 264), (1024, 264)])
+@pytest.mark.parametrize("M,F", [(600, 5120), (257, 11008), (256, 5128), (255, 5128), (1100, 8640), (8, 8192), (7, 8192), (63, 9208), (64, 8192), (8, 9216), (7, 9216), (1, 16384), (1023, 264), (1024, 264),
+                                 # 1024 threads a token or 256: rows on either side of the rule, read in chunks and element by element
+                                 (64, 1024), (64, 1028), (600, 1796), (600, 1800), (64, 256), (64, 257), (300, 449), (300, 451)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_swiglu_many_tokens(gpu_lib, M, F, bf16):
     gu, bits = synth.activations(M, 2 * F, config=2, layer=F % 5, tensor=5, bf16=True)
