@@ -37,7 +37,8 @@ __device__ inline float block_max_nonneg(float v, float* sh) {
 // register count and with it the number of resident tokens per CU in proportion to K); 1024 threads for the rows
 // 256 threads cannot hold.
 // kAny: rows that start anywhere and need not fill their last load (K of any length, any base): the same loads and stores at
-// element alignment, and the last K % kElems elements one by one in the thread that comes after the row's whole loads.
+// element alignment, and the last K % kElems elements one each in the threads that come after the row's whole loads (in one thread
+// they were up to seven loads and seven stores in a row: 30000 x 503 bf16 41 us, now 18; one element a thread throughout 28).
 template <bool kBf16, int kVecs, int kThreads, bool kAny = false>
 __global__ __launch_bounds__(kThreads) void quantize_acts_vec(const void* __restrict__ xv, int64_t K,
                                                               int8_t* __restrict__ xq, float* __restrict__ sx) {
@@ -57,15 +58,9 @@ __global__ __launch_bounds__(kThreads) void quantize_acts_vec(const void* __rest
             if (idx < nvec) raw[v] = row[idx];
         } else if (idx < nvec) {
             __builtin_memcpy(&raw[v], reinterpret_cast<const char*>(row) + (int64_t)idx * 16, 16);
-        } else if (idx == nvec && rest) {
-            uint32_t u[4] = {0, 0, 0, 0};
-#pragma unroll
-            for (int e = 0; e < kElems; ++e) {
-                if (e >= rest) continue;
-                if (kBf16) u[e >> 1] |= (uint32_t)reinterpret_cast<const uint16_t*>(row)[(int64_t)nvec * 8 + e] << (16 * (e & 1));
-                else u[e & 3] = reinterpret_cast<const uint32_t*>(row)[(int64_t)nvec * 4 + e];
-            }
-            raw[v] = make_uint4(u[0], u[1], u[2], u[3]);
+        } else if (idx < nvec + rest) {
+            const int64_t at = (int64_t)nvec * (kElems - 1) + idx;
+            raw[v].x = kBf16 ? reinterpret_cast<const uint16_t*>(row)[at] : reinterpret_cast<const uint32_t*>(row)[at];
         }
     }
 #pragma unroll
@@ -90,7 +85,7 @@ __global__ __launch_bounds__(kThreads) void quantize_acts_vec(const void* __rest
 #pragma unroll
     for (int v = 0; v < kVecs; ++v) {
         const int idx = v * kThreads + threadIdx.x;
-        if (idx >= nvec + (rest ? 1 : 0)) continue;
+        if (idx >= nvec + rest) continue;
         const uint32_t u[4] = {raw[v].x, raw[v].y, raw[v].z, raw[v].w};
         if (kAny) {
             uint32_t code[2];
@@ -103,14 +98,8 @@ __global__ __launch_bounds__(kThreads) void quantize_acts_vec(const void* __rest
                 code[0] = pack4_quantized(__uint_as_float(u[0]), __uint_as_float(u[1]), __uint_as_float(u[2]), __uint_as_float(u[3]), inv);
                 code[1] = 0;
             }
-            int8_t* dst = out + (int64_t)idx * kElems;
-            if (idx < nvec) {
-                __builtin_memcpy(dst, code, kElems);
-            } else {
-#pragma unroll
-                for (int e = 0; e < kElems; ++e)
-                    if (e < rest) dst[e] = (int8_t)(code[e >> 2] >> (8 * (e & 3)));
-            }
+            if (idx < nvec) __builtin_memcpy(out + (int64_t)idx * kElems, code, kElems);
+            else out[(int64_t)nvec * (kElems - 1) + idx] = (int8_t)code[0];
         } else if (kBf16) {
             const uint32_t lo = pack4_quantized(__uint_as_float(u[0] << 16), __uint_as_float(u[0] & 0xFFFF0000u),
                                                 __uint_as_float(u[1] << 16), __uint_as_float(u[1] & 0xFFFF0000u), inv);
@@ -693,14 +682,16 @@ hipError_t launch_quantize_acts(const void* x, bool bf16, int64_t M, int64_t K, 
     // (bf16 at 1024 threads and 16 loads per thread would spill: such rows, beyond 65536 elements, sweep instead)
     if (aligned && need <= ((threads == 1024 && bf16) ? 8 : kActMaxVec)) {
         if (bf16) PICK(true); else PICK(false);
-    } else if (nvec < 8 * kActThreads && reinterpret_cast<uintptr_t>(x) % (bf16 ? 2 : 4) == 0) {
-        // rows of any length and alignment that 256 threads hold in eight loads each, the partly filled last one included
-        // (200 x 3333 fp32, its product behind it: 20.4 us with element loads in two sweeps, 18.0)
+    } else if (nvec < 8 * kActThreads && K * (bf16 ? 2 : 4) >= 256 && reinterpret_cast<uintptr_t>(x) % (bf16 ? 2 : 4) == 0) {
+        // rows of any length and alignment that 256 threads hold in eight loads each (a ninth only for the last elements)
+        // (200 x 3333 fp32, its product behind it: 20.4 us with element loads in two sweeps, 18.0).  Rows of less than 256 bytes are
+        // done sooner by a thread per element (bf16, 8192 x 33 4.7 us, in loads of eight elements 5.6; 8192 x 129 6.4 / 6.1)
         block = dim3(kActThreads);
-        const int64_t slots = nvec + 1;
+        const int64_t slots = nvec + K % elems;
 #define ANY(B_, V_) hipLaunchKernelGGL((quantize_acts_vec<B_, V_, kActThreads, true>), grid, block, 0, stream, x, K, xq, sx)
-        if (bf16) { if (slots <= 2 * kActThreads) ANY(true, 2); else ANY(true, 8); }
-        else      { if (slots <= 2 * kActThreads) ANY(false, 2); else ANY(false, 8); }
+#define PICK_ANY(B_) do { if (slots <= 2 * kActThreads) ANY(B_, 2); else if (slots <= 8 * kActThreads) ANY(B_, 8); else ANY(B_, 9); } while (0)
+        if (bf16) PICK_ANY(true); else PICK_ANY(false);
+#undef PICK_ANY
 #undef ANY
     } else {
         block = dim3(kActThreads);

@@ -265,7 +265,9 @@ def test_rmsnorm_exact_sum_where_the_rounded_one_does_not_decide(gpu_lib):
 
 # x in rows of any length and alignment through the quantizer that holds a row in registers: less than one load, whole loads and
 # a rest of every size class, the longest rows it takes and the first beyond, a base one element past an aligned address
-@pytest.mark.parametrize("M,K", [(3, 1), (5, 7), (4, 9), (2, 2047), (77, 2050), (9, 4099), (2, 8187), (2, 8191), (2, 16381), (2, 16391), (300, 333)])
+@pytest.mark.parametrize("M,K", [(3, 1), (5, 7), (4, 9), (2, 2047), (77, 2050), (9, 4099), (2, 8187), (2, 8191), (2, 16381), (2, 16391), (300, 333),
+                                 # the shortest rows it takes, and those whose last elements need a ninth load
+                                 (3, 63), (3, 65), (3, 127), (3, 129), (2, 16383), (2, 8189)])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_quantize_acts_rows_of_any_length(gpu_lib, M, K, bf16):
     x, bits = synth.activations(M, K, config=2, layer=K % 7, tensor=3, bf16=True)
