@@ -205,7 +205,7 @@ static bitnet_status linear_any(const int8_t* xq, const float* sx, const void* p
         else if (bitnet::gemm_supports(M, N, K, xq)) which = BITNET_KERNEL_GEMM;
         else if (bitnet::gemv_any_supports(M, N, K))       // rows of any length and alignment: the same kernels, x_q staged otherwise
             return from_hip(bitnet::launch_linear_gemv_any_2bit(xq, sx, packed, gamma, gstride, M, N, K, y, yt, s));
-        else if (bitnet::gemm_any_supports(N))
+        else if (bitnet::gemm_any_supports(M, N))
             return from_hip(bitnet::launch_linear_gemm_any_2bit(xq, sx, packed, gamma, gstride, M, N, K, y, yt, s));
         else which = BITNET_KERNEL_REFERENCE;
     }
@@ -369,7 +369,7 @@ bitnet_status bitnet_linear_describe(int64_t M, int64_t N, int64_t K, bitnet_for
         if (e != hipSuccess) return BITNET_ERR_HIP;
     } else if (bitnet::gemv_any_supports(M, N, K)) {
         if (bitnet::launch_linear_gemv_any_2bit(xq, fp, vp, fp, 0, M, N, K, vp, OutType::BF16, nullptr, &plan) != hipSuccess) return BITNET_ERR_HIP;
-    } else if (bitnet::gemm_any_supports(N)) {
+    } else if (bitnet::gemm_any_supports(M, N)) {
         if (bitnet::launch_linear_gemm_any_2bit(xq, fp, vp, fp, 0, M, N, K, vp, OutType::BF16, nullptr, &plan) != hipSuccess) return BITNET_ERR_HIP;
     } else {
         plan.kernel = "reference";

@@ -27,6 +27,8 @@ inline hipError_t raise_dynamic_lds(const void* kernel, int bytes, RaisedFlags& 
     return e;
 }
 
+constexpr int64_t kMaxGridThreads = (int64_t)1 << 32;      // a launch takes fewer threads than this along a grid dimension
+
 // Small arguments of the product kernels in one word.  Their arguments are kept to 14 dwords, all of which arrive in scalar
 // registers with the wave (the build asks for it); anything beyond is a load that is cold whenever the launch before streamed
 // weights through the caches, either in front of the first address or, where only the epilogue uses it, at the end.
@@ -110,7 +112,7 @@ bool gemv_any_supports(int64_t M, int64_t N, int64_t K);
 hipError_t launch_linear_gemv_any_2bit(const int8_t* xq, const float* sx, const void* packed, const float* gamma, int gstride,
                                        int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan = nullptr);
 // ... and any number (linear_gemm.hip)
-bool gemm_any_supports(int64_t N);
+bool gemm_any_supports(int64_t M, int64_t N);
 hipError_t launch_linear_gemm_any_2bit(const int8_t* xq, const float* sx, const void* packed, const float* gamma, int gstride,
                                        int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan = nullptr);
 bool gemv_fused_supports(int64_t M, int64_t N, int64_t K, const void* x);

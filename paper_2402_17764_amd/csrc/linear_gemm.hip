@@ -548,7 +548,9 @@ hipError_t launch_linear_gemm_2bit_shape(int fm, int fn, int kg, const int8_t* x
     return hipErrorInvalidValue;
 }
 
-bool gemm_any_supports(int64_t N) { return ceil_div(N, kRowsPerBlock) < ((int64_t)1 << 21); }
+bool gemm_any_supports(int64_t M, int64_t N) {
+    return ceil_div(N, kRowsPerBlock) < ((int64_t)1 << 21) && ceil_div(M, 64) * ceil_div(N, 256) * kGemmThreads < kMaxGridThreads;
+}
 
 // Activation rows of any length and alignment.  64-token tiles only (staging through registers takes 16 of them there).
 // Up to one 64 x 128 tile per CU: eight waves in two K groups; up to four: the same tile with four waves; beyond, 64 x 256.

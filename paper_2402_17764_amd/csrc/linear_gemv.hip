@@ -758,7 +758,7 @@ static hipError_t dispatch16_fused(int xmode, const void* x, const void* packed,
 // 20.6 / 18.0).
 bool gemv_any_supports(int64_t M, int64_t N, int64_t K) {
     const size_t lds = kGemvLdsHeader * sizeof(uint4) + gemv16_x_lds_bytes(M < 16 ? M : 16, K);
-    if (M < 1 || lds > kGemvAnyLdsBudget) return false;
+    if (M < 1 || lds > kGemvAnyLdsBudget || ceil_div(N, 2 * kRowsPerBlock) * 256 >= kMaxGridThreads) return false;
     return M <= 16 || ceil_div(M, 16) * ceil_div(N, kRowsPerBlock) <= 512;
 }
 hipError_t launch_linear_gemv_any_2bit(const int8_t* x, const float* sx, const void* packed, const float* gamma, int gstride, int64_t M,

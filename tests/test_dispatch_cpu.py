@@ -228,6 +228,15 @@ def test_every_launch_shape_is_within_the_hardware_limits():
     assert kernels == {"reference", "decode", "batched_decode", "batched_decode_loader", "prefill"}
 
 
+@pytest.mark.parametrize("M,N,K,fits", [(1, 2 ** 29 - 32, 130, True), (1, 2 ** 29 - 31, 130, False), (16, 2 ** 30, 17, False), (17, 2 ** 25, 3, False),
+                                        (2 ** 30 - 64, 16, 17, True), (2 ** 30 - 63, 16, 17, False), (2 ** 31 - 1, 1, 7, False)])
+def test_ragged_launches_stay_within_the_grid_limit(M, N, K, fits):
+    """K not a multiple of 16 at sizes that only the one-thread-per-output kernel can launch: a grid dimension holds fewer
+    than 2^32 threads, and what does not fit is left to that kernel (which has no parameters), not refused."""
+    d = B.linear_describe(M, N, K)
+    assert d["grid"][0] * d["block"] < 2 ** 32 and (d["block"] != 0) == fits, d
+
+
 def test_decode_shapes_on_large_layers_follow_the_measured_cases():
     """One or two tokens on layers of 1024 row blocks and more take x_q from LDS (last parameter 1): two K-split waves
     per row block where four waves split K evenly, eight single-row-block waves without a split where they cannot
