@@ -318,12 +318,13 @@ hipError_t launch_linear_reference_trit5(const int8_t* xq, const float* sx, cons
 // step columns 80 g + 64 .. 80 g + 79: exactly one word.  The lane's five words go through LDS (the wave's own 1280 bytes, whose
 // accesses complete in order), from where 80 lanes' worth of 16-byte quads are stored in runs of 256 bytes.
 constexpr int kRepackWaves = 4;
-__global__ __launch_bounds__(kRepackWaves * kWave) void repack_trit5_to_2bit(const uint4* __restrict__ in, int64_t RB, int64_t chunks,
+constexpr int64_t kRepackChunks = (int64_t)1 << 25;      // of one launch: 2^31 threads, half of what a grid dimension holds
+__global__ __launch_bounds__(kRepackWaves * kWave) void repack_trit5_to_2bit(const uint4* __restrict__ in, int64_t RB, int64_t first, int64_t chunks,
                                                                              int64_t Kq2, uint4* __restrict__ out) {
     __shared__ uint2 lut[256];                       // byte -> {codes 0..3 as 2-bit fields at bits 0, 8, 16, 24; code 4}
     __shared__ uint32_t tiles[kRepackWaves][16 * 20];      // [row][word]
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    const int64_t chunk = (int64_t)blockIdx.x * kRepackWaves + wave;
+    const int64_t chunk = first + (int64_t)blockIdx.x * kRepackWaves + wave;
     uint4 q = make_uint4(0, 0, 0, 0);
     if (chunk < chunks) q = in[64 * chunk + lane];
     {
@@ -402,12 +403,17 @@ __global__ __launch_bounds__(256) void repack_2bit_to_trit5(const uint4* __restr
 
 hipError_t launch_repack(const void* in, bool in_trit5, int64_t N, int64_t K, void* out, hipStream_t stream) {
     const int64_t RB = ceil_div(N, kRowsPerBlock), steps5 = ceil_div(K, kTritStep), Kq2 = ceil_div(K, kColsPerQuad);
-    if (in_trit5)
-        hipLaunchKernelGGL(repack_trit5_to_2bit, dim3((unsigned)ceil_div(RB * steps5, kRepackWaves)), dim3(kRepackWaves * kWave), 0, stream,
-                           static_cast<const uint4*>(in), RB, RB * steps5, Kq2, static_cast<uint4*>(out));
-    else
+    if (!in_trit5) {
         hipLaunchKernelGGL(repack_2bit_to_trit5, dim3((unsigned)ceil_div(16 * RB * steps5, 256)), dim3(256), 0, stream, static_cast<const uint4*>(in), RB, steps5, Kq2,
                            static_cast<uint4*>(out));
+        return hipGetLastError();
+    }
+    const int64_t chunks = RB * steps5;
+    for (int64_t first = 0; first < chunks; first += kRepackChunks) {
+        const int64_t n = chunks - first < kRepackChunks ? chunks - first : kRepackChunks;
+        hipLaunchKernelGGL(repack_trit5_to_2bit, dim3((unsigned)ceil_div(n, kRepackWaves)), dim3(kRepackWaves * kWave), 0, stream,
+                           static_cast<const uint4*>(in), RB, first, first + n, Kq2, static_cast<uint4*>(out));
+    }
     return hipGetLastError();
 }
 

@@ -346,3 +346,27 @@ def test_abs_sum_bf16_near_the_top_of_the_range(gpu_lib, N, K, top, spread):
     assert np.array_equal(gpu_lib.unpack_weights(packed5, N, K, gpu_lib.PACK_TRIT5).cpu().numpy(), codes_ref)
     packed_s, gamma_s = gpu_lib.quantize_weights_segmented(Wd, [N])
     assert torch.equal(packed_s, packed) and bool((gamma_s == gamma).all())
+
+
+def test_repack_of_more_chunks_than_one_launch_takes(gpu_lib):
+    """5-trit -> 2-bit with a wave per chunk (16 rows x 320 columns): 2^26 chunks would be 2^32 threads.  64 GiB of codes in; what
+    comes out is compared, at both ends and where one launch ends, with the repacking of those rows alone."""
+    B, K, N = gpu_lib, 1, 2 ** 30 + 40
+    torch.cuda.empty_cache()
+    blocks = -(-N // 16)
+    if torch.cuda.mem_get_info()[0] < (90 << 30):
+        pytest.skip("needs 90 GiB of GPU memory")
+    p5 = torch.empty(B.packed_bytes(N, K, B.PACK_TRIT5), dtype=torch.uint8, device="cuda")
+    p2 = torch.empty(B.packed_bytes(N, K), dtype=torch.uint8, device="cuda")
+    assert p5.numel() == blocks * 1024 and p2.numel() == blocks * 256
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    spots = [(0, 40), (2 ** 25 - 20, 40), (2 ** 26 - 20, 20), (blocks - 7, 7)]          # row blocks: first, how many
+    for at, n in spots:
+        p5[at * 1024:(at + n) * 1024] = torch.randint(0, 243, (n * 1024,), dtype=torch.uint8, device="cuda", generator=gen)
+        p2[at * 256:(at + n) * 256] = 0x5A
+    B.repack_weights(p5, N, K, B.PACK_TRIT5, B.PACK_2BIT, out=p2)
+    for at, n in spots:
+        want = B.repack_weights(p5[at * 1024:(at + n) * 1024], 16 * n, K, B.PACK_TRIT5, B.PACK_2BIT)
+        assert torch.equal(p2[at * 256:(at + n) * 256], want)
+    del p5, p2
+    torch.cuda.empty_cache()
