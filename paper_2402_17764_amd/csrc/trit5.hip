@@ -312,17 +312,18 @@ hipError_t launch_linear_reference_trit5(const int8_t* xq, const float* sx, cons
 //
 // 5-trit -> 2-bit: a wave moves one chunk of the 5-trit layout (16 rows x 320 columns, 1 KiB in, 1280 bytes out), lane
 // 16 g + r quad g of row r -- with a thread per row and step a 4096 x 11008 matrix gave the chip two wavefronts per SIMD and
-// took 7.6 us (300 tokens on it, quantization and product included: 34.6 -> 33.6 us; 100 tokens on 27648 x 5120 33.4 -> 31.6).  A 5-trit byte p of quad g holds quad columns 4p .. 4p+3, i.e. step columns 80 g + 4 p + (0 .. 3): four
-// columns that the 2-bit layout keeps in one 32-bit word (word (80 g + 4 p) / 16 of the step), in field i = p & 3 of its four
-// bytes; the table gives those four 2-bit codes already spread to bits 0, 8, 16, 24.  The sixteen fifth digits of a quad are
-// step columns 80 g + 64 .. 80 g + 79: exactly one word.  The lane's five words go through LDS (the wave's own 1280 bytes, whose
-// accesses complete in order), from where 80 lanes' worth of 16-byte quads are stored in runs of 256 bytes.
+// took 7.6 us (300 tokens on it, quantization and product included: 34.6 -> 33.6 us; 100 tokens on 27648 x 5120 33.4 -> 31.6).
+// A 5-trit byte p of quad g holds quad columns 4p .. 4p+3, i.e. step columns 80 g + 4 p + (0 .. 3): four columns that the 2-bit
+// layout keeps in one 32-bit word (word (80 g + 4 p) / 16 of the step), in field i = p & 3 of its four bytes; the table gives
+// those four 2-bit codes already spread to bits 0, 8, 16, 24.  The sixteen fifth digits of a quad are step columns 80 g + 64 ..
+// 80 g + 79: exactly one word.  The lane's five words go through LDS (the wave's own 1280 bytes, whose accesses complete in
+// order), from where 80 lanes' worth of 16-byte quads are stored in runs of 256 bytes.
 constexpr int kRepackWaves = 4;
 constexpr int64_t kRepackChunks = (int64_t)1 << 25;      // of one launch: 2^31 threads, half of what a grid dimension holds
 __global__ __launch_bounds__(kRepackWaves * kWave) void repack_trit5_to_2bit(const uint4* __restrict__ in, int64_t RB, int64_t first, int64_t chunks,
                                                                              int64_t Kq2, uint4* __restrict__ out) {
     __shared__ uint2 lut[256];                       // byte -> {codes 0..3 as 2-bit fields at bits 0, 8, 16, 24; code 4}
-    __shared__ uint32_t tiles[kRepackWaves][16 * 20];      // [row][word]
+    __shared__ __align__(16) uint32_t tiles[kRepackWaves][16 * 20];      // [row][word]; read back in 16-byte pieces
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const int64_t chunk = first + (int64_t)blockIdx.x * kRepackWaves + wave;
     uint4 q = make_uint4(0, 0, 0, 0);
@@ -358,7 +359,9 @@ __global__ __launch_bounds__(kRepackWaves * kWave) void repack_trit5_to_2bit(con
         }
         tile[r * 20 + 5 * g + 4] = fifth;
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the other lanes' words: an order for the compiler, no instruction
     __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const int p = h * kWave + lane, q5 = p >> 4, r = p & 15;               // piece p: quad q5 of row r
@@ -368,7 +371,8 @@ __global__ __launch_bounds__(kRepackWaves * kWave) void repack_trit5_to_2bit(con
 }
 
 // 2-bit -> 5-trit: the same move backwards, one thread per row and 320 columns (consecutive threads take consecutive rows of a
-// 16-row block, so their 16-byte loads and stores form 256-byte runs in both layouts); 2-bit quads past the matrix's last one read as zero codes.
+// 16-row block, so their 16-byte loads and stores form 256-byte runs in both layouts); 2-bit quads past the matrix's last one
+// read as zero codes.
 __global__ __launch_bounds__(256) void repack_2bit_to_trit5(const uint4* __restrict__ in, int64_t RB, int64_t steps5,
                                                             int64_t Kq2, uint4* __restrict__ out) {
     const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
