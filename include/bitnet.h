@@ -251,7 +251,8 @@ bitnet_status bitnet_swiglu_quantize(const void* gu, bitnet_dtype gu_dtype, int6
  * The kernel is chosen by shape: the weight-streaming decode kernels for M <= 64 (and up to 256 tokens, with
  * K >= 5120 up to 512, on layers small enough that 256 workgroups of token tiles cover them: up to 4096-12288 output
  * features), the MFMA GEMM above; when xq is not 16-byte aligned or K is not a multiple of 16, forms of the decode kernel
- * (up to 16 tokens) and of the GEMM that take rows of any length and alignment.
+ * (up to 16 tokens, and more while its workgroups are few) and of the GEMM that take rows of any length and alignment, or
+ * the reference kernel where it is faster (K up to about twelve, more with many features and few tokens).
  */
 bitnet_status bitnet_linear(const int8_t* xq, const float* sx, const void* packed, const float* gamma,
                             int64_t M, int64_t N, int64_t K, bitnet_format f,

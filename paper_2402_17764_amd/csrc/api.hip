@@ -165,6 +165,31 @@ bitnet_status bitnet_swiglu_quantize(const void* gu, bitnet_dtype gu_dtype, int6
                                                    static_cast<hipStream_t>(stream)));
 }
 
+// Activation rows of any length and alignment (2-bit weights): the decode kernel or the MFMA GEMM with x_q staged at byte alignment,
+// or the kernel with one thread per output.  That one takes every size, and is the fastest on rows of a few elements: it costs
+// what its K loop takes (0.165 us a column), or its threads (0.65 us per million products) and workgroups do; the others a staging
+// of x_q and a pass over tiles that such rows hardly fill, most of all where one launch has tens of thousands of tiles.  us, one
+// thread per output / the others: 1 x 100000, K = 3 2.7 / 9.5, K = 24 6.4 / 10.3, K = 40 9.4 / 10.6; 4 x 1000000, K = 17 58 / 66, K = 31
+// 87 / 93, K = 40 111 / 88; 64 x 100, K = 5 2.9 / 4.2, K = 12 4.0 / 4.1, K = 17 4.9 / 3.6; 1000 x 1000, K = 3 6.1 / 6.1, K = 9 9.8 / 6.3;
+// 4096 x 4096, K = 1 43 / 18; 200000 x 16, K = 1 99 / 36.
+enum class AnyRows { Decode, Prefill, ThreadPerOutput };
+static AnyRows any_rows_kernel(int64_t M, int64_t N, int64_t K) {
+    const bool decode = bitnet::gemv_any_supports(M, N, K);
+    if (!decode && !bitnet::gemm_any_supports(M, N)) return AnyRows::ThreadPerOutput;
+    const double outputs = (double)M * (double)(64 * bitnet::ceil_div(N, 64)), groups = (double)M * (double)bitnet::ceil_div(N, 256);
+    const double busy = 0.5e-3 * groups + 0.65e-6 * outputs * (double)K, chain = 0.165 * (double)K;
+    const double per_output = 1.9 + (busy > chain ? busy : chain);
+    double tiled;
+    if (decode) {
+        const int64_t RB = bitnet::ceil_div(N, 16), wgs = bitnet::ceil_div(M, 16) * (RB >= 1024 ? bitnet::ceil_div(RB, 2) : RB);
+        tiled = 3.1 + 0.05 * (double)(K % 16) + (0.002 + 0.00015 * (double)(M < 16 ? M : 16)) * (double)(wgs > 256 ? wgs - 256 : 0);
+    } else {
+        const int64_t tiles = bitnet::ceil_div(M, 64) * bitnet::ceil_div(N, 128);
+        tiled = 4.2 + 0.011 * (double)(tiles > 128 ? tiles - 128 : 0);
+    }
+    return per_output < tiled ? AnyRows::ThreadPerOutput : decode ? AnyRows::Decode : AnyRows::Prefill;
+}
+
 static bitnet_status linear_any(const int8_t* xq, const float* sx, const void* packed, const float* gamma,
                                 int gstride, int64_t M, int64_t N, int64_t K, bitnet_format f, void* y,
                                 bitnet_dtype y_dtype, bitnet_kernel which, void* stream) {
@@ -203,11 +228,11 @@ static bitnet_status linear_any(const int8_t* xq, const float* sx, const void* p
     if (which == BITNET_KERNEL_AUTO) {
         if (bitnet::gemv_supports(M, N, K, xq)) which = BITNET_KERNEL_GEMV;
         else if (bitnet::gemm_supports(M, N, K, xq)) which = BITNET_KERNEL_GEMM;
-        else if (bitnet::gemv_any_supports(M, N, K))       // rows of any length and alignment: the same kernels, x_q staged otherwise
-            return from_hip(bitnet::launch_linear_gemv_any_2bit(xq, sx, packed, gamma, gstride, M, N, K, y, yt, s));
-        else if (bitnet::gemm_any_supports(M, N))
-            return from_hip(bitnet::launch_linear_gemm_any_2bit(xq, sx, packed, gamma, gstride, M, N, K, y, yt, s));
-        else which = BITNET_KERNEL_REFERENCE;
+        else switch (any_rows_kernel(M, N, K)) {
+            case AnyRows::Decode: return from_hip(bitnet::launch_linear_gemv_any_2bit(xq, sx, packed, gamma, gstride, M, N, K, y, yt, s));
+            case AnyRows::Prefill: return from_hip(bitnet::launch_linear_gemm_any_2bit(xq, sx, packed, gamma, gstride, M, N, K, y, yt, s));
+            default: which = BITNET_KERNEL_REFERENCE;
+        }
     }
     if (((int)which & ~0xFF) == 0x100) {               // prefill kernel, tile forced: 0x100 | two K groups << 7 | fm << 4 | fn
         const int fm = ((int)which >> 4) & 0x7, fn = (int)which & 0x7, wide = ((int)which >> 3) & 1;
@@ -251,7 +276,7 @@ bitnet_status bitnet_linear_workspace(int64_t M, int64_t N, int64_t K, size_t* b
     const int64_t tiles = ((M + 63) / 64) * ((N + 127) / 128);
     const int skinny_splits = bitnet::skinny_splitk_splits(M, N, K);
     // (the batched-decode kernels serve up to 256 tokens on small layers; x_q is assumed aligned here)
-    if (K % 16 != 0) *bytes = 0;                       // the reference kernel runs such shapes
+    if (K % 16 != 0) *bytes = 0;                       // the kernel forms for such rows never split K
     else if (bitnet::gemv_supports(M, N, K, nullptr)) *bytes = skinny_splits > 1 ? bitnet::splitk_workspace_bytes(M, N, skinny_splits) : 0;
     else *bytes = tiles < 512 ? bitnet::splitk_workspace_bytes(M, N, 8) : 0;
     return BITNET_OK;
@@ -367,12 +392,13 @@ bitnet_status bitnet_linear_describe(int64_t M, int64_t N, int64_t K, bitnet_for
         const hipError_t e = bitnet::launch_linear_gemm_2bit(xq, fp, vp, fp, 0, M, N, K, vp, OutType::BF16, nullptr, ws, workspace_bytes,
                                                             0, &plan);
         if (e != hipSuccess) return BITNET_ERR_HIP;
-    } else if (bitnet::gemv_any_supports(M, N, K)) {
-        if (bitnet::launch_linear_gemv_any_2bit(xq, fp, vp, fp, 0, M, N, K, vp, OutType::BF16, nullptr, &plan) != hipSuccess) return BITNET_ERR_HIP;
-    } else if (bitnet::gemm_any_supports(M, N)) {
-        if (bitnet::launch_linear_gemm_any_2bit(xq, fp, vp, fp, 0, M, N, K, vp, OutType::BF16, nullptr, &plan) != hipSuccess) return BITNET_ERR_HIP;
     } else {
-        plan.kernel = "reference";
+        const AnyRows any = any_rows_kernel(M, N, K);
+        hipError_t e = hipSuccess;
+        if (any == AnyRows::Decode) e = bitnet::launch_linear_gemv_any_2bit(xq, fp, vp, fp, 0, M, N, K, vp, OutType::BF16, nullptr, &plan);
+        else if (any == AnyRows::Prefill) e = bitnet::launch_linear_gemm_any_2bit(xq, fp, vp, fp, 0, M, N, K, vp, OutType::BF16, nullptr, &plan);
+        else plan.kernel = "reference";
+        if (e != hipSuccess) return BITNET_ERR_HIP;
     }
     return plan_to_text(plan, text, text_bytes);
 }

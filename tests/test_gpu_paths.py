@@ -66,7 +66,9 @@ def test_segments_side_by_side(gpu_lib, rows, K, bf16):
                                    (1030, 2500, 301), (700, 25000, 77), (16, 50, 8001),
                                    # more than 16 tokens in tiles over the grid: a full and a partial last tile, K beyond 64 KiB of
                                    # LDS, the most workgroups of the form and one more
-                                   (32, 70, 333), (40, 1900, 3900), (33, 100, 5000), (8192, 16, 33), (8193, 16, 33)])
+                                   (32, 70, 333), (40, 1900, 3900), (33, 100, 5000), (8192, 16, 33), (8193, 16, 33),
+                                   # the shortest rows these forms are chosen for (below, a thread per output is faster)
+                                   (5, 300, 15), (16, 500, 13), (3000, 1100, 1), (3000, 1100, 3)])
 @pytest.mark.parametrize("y", ["I32", "F32", "BF16"])
 def test_rows_of_any_length(gpu_lib, M, N, K, y):
     packed, gamma = gpu_lib.quantize_weights(dev(synth.weights(N, K, config=1, layer=M % 7)))
