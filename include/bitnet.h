@@ -277,9 +277,10 @@ bitnet_status bitnet_linear_variant(const int8_t* xq, const float* sx, const voi
  *     batched_decode_loader  depth, LDS lookahead (the second form has a wave that only copies activations)
  *     prefill                tile tokens, tile rows, and 2 as a third parameter for the eight-wave form with two
  *                            K groups (512 tile rows: the eight-wave form with two row groups); grid y = split-K factor
- *     reference              K not a multiple of 16: parameters of the decode kernel (x_q source 8) or of the prefill tile
- *                            that takes such rows; none for one thread per output
- *     trit5_decode, trit5_reference: no parameters
+ *     decode_any             K not a multiple of 16: as decode, up to 16 tokens per workgroup (x_q source 8: rows of any
+ *     prefill_any            length and alignment, through LDS), and as prefill (no split)
+ *     reference              one thread per output; no parameters, like
+ *     trit5_decode, trit5_reference
  *   5-trit weights, more than 16 tokens and a workspace that holds the 2-bit copy (bitnet_linear_workspace_format):
  *   the plan of the 2-bit launch that follows the repacking pass, with " repack=trit5_to_2bit" appended
  */

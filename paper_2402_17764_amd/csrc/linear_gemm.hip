@@ -519,7 +519,7 @@ static hipError_t launch_gemm_tiles(const int8_t* xq, const float* sx, const voi
     const size_t esz = ot == OutType::BF16 ? 2 : 4;
     const int vec_store = (reinterpret_cast<uintptr_t>(out) % 16 == 0) && ((N * esz) % 16 == 0);
     if (plan) {
-        const char* family = kAny ? "reference" : "prefill";
+        const char* family = kAny ? "prefill_any" : "prefill";
         if (kNG > 1) plan->set(family, {32 * kFM, 128 * kFN * kNG}, (unsigned)(tiles_m * tiles_n), (unsigned)splits, kGemmThreads * kNG, gemm_lds_bytes(kFM, kFN, 1, kNG), splits);
         else if (kKG > 1) plan->set(family, {32 * kFM, 128 * kFN, kKG}, (unsigned)(tiles_m * tiles_n), (unsigned)splits, kGemmThreads * kKG, gemm_lds_bytes(kFM, kFN, kKG), splits);
         else plan->set(family, {32 * kFM, 128 * kFN}, (unsigned)(tiles_m * tiles_n), (unsigned)splits, kGemmThreads, gemm_lds_bytes(kFM, kFN, 1), splits);

@@ -588,7 +588,7 @@ static hipError_t launch16(int xmode, const void* x, const float* sx, const void
     const int need = xmode == kXLdsAny ? kModesAny : xmode <= kXLds ? kModesInt8 : xmode <= kXFusedF32 ? kModesFused : kModesPre;
     if ((kModes & need) == 0) return hipErrorInvalidDeviceFunction;   // a dispatch rule asked a launch shape for a mode it is not built for
     if (plan) {
-        plan->set(xmode == kXLdsAny ? "reference" : "decode", {kR, kS, kW, kD, xmode}, grid.x * grid.y, 1, block.x, lds, 1);
+        plan->set(xmode == kXLdsAny ? "decode_any" : "decode", {kR, kS, kW, kD, xmode}, grid.x * grid.y, 1, block.x, lds, 1);
         return hipSuccess;
     }
     const uint4* p = static_cast<const uint4*>(packed);

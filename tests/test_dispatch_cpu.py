@@ -167,8 +167,10 @@ def test_batched_decode_beyond_64_tokens_only_as_one_round():
 
 
 def test_fallbacks_and_errors():
-    assert B.linear_describe(3, 100, 70)["kernel"] == "reference"                   # K not a multiple of 16
-    assert B.linear_describe(100, 64, 72)["kernel"] == "reference"
+    assert B.linear_describe(3, 100, 70)["kernel"] == "decode_any"                  # K not a multiple of 16
+    assert B.linear_describe(100, 64, 72)["kernel"] == "decode_any"
+    assert B.linear_describe(1000, 640, 72)["kernel"] == "prefill_any"
+    assert B.linear_describe(3, 100, 7)["kernel"] == "reference"                    # a few elements: one thread per output
     assert B.linear_describe(1, 17280, 3200, fmt=B.PACK_TRIT5)["kernel"] == "trit5_decode"
     assert B.linear_describe(100, 17280, 3200, fmt=B.PACK_TRIT5)["kernel"] == "trit5_decode"   # 16 tokens at a time
     # 5-trit weights with a workspace that holds the 2-bit copy: the repacking pass, then the 2-bit plan for the rest
@@ -200,12 +202,15 @@ def test_every_launch_shape_is_within_the_hardware_limits():
         M = rng.choice([1, 2, 3, 4, 5, 15, 16, 17, 33, 64, 65, 100, 128, 200, 256, 257, 400, 512, 513, 1000, 2048, 5000])
         N = rng.choice([1, 15, 16, 17, 100, 1000, 3200, 4096, 8192, 12288, 22016, 57344, 128256]) + rng.choice([0, 0, 0, 1, 16, 48])
         K = rng.choice([16, 64, 256, 272, 1024, 3200, 4096, 5120, 8640, 11008, 28672, 65536]) + rng.choice([0, 0, 0, 16, 64, 7])
+        if rng.random() < 0.05:
+            K = rng.randint(1, 63)
         ws = rng.choice([0, 0, 8 * M * N * 4])
         d = B.linear_describe(M, N, K, workspace_bytes=ws)
         kernels.add(d["kernel"])
         RB = ceil_div(N, 16)
+        assert (K % 16 != 0) == (d["kernel"] in ("reference", "decode_any", "prefill_any")), (M, N, K, d)
         if d["kernel"] == "reference":
-            assert K % 16 != 0, (M, N, K, d)
+            assert K < 100 and d["params"] == [], (M, N, K, d)       # short rows only: nothing else falls to it
             continue
         assert d["block"] % 64 == 0 and 64 <= d["block"] <= 1024, (M, N, K, d)
         assert d["lds"] <= LDS_PER_CU and 1 <= d["grid"][0] < 2 ** 31 and 1 <= d["grid"][1] < 65536, (M, N, K, d)
@@ -213,28 +218,37 @@ def test_every_launch_shape_is_within_the_hardware_limits():
         if d["kernel"] == "decode":
             kR, kS, kW, kD, _ = d["params"]
             assert (M <= 4 or (M <= 8 and RB < 1024)) and d["grid"][0] == ceil_div(RB, kR * kW) and d["block"] == 64 * kS * kW
+        elif d["kernel"] == "decode_any":      # 16 tokens a workgroup, padded rows of all of them in LDS (two workgroups per CU)
+            kR, kS, kW, kD, xsrc = d["params"]
+            tiles, held = ceil_div(M, 16), min(M, 16)
+            assert xsrc == 8 and d["grid"] == (ceil_div(RB, kR * kW) * tiles, 1) and d["block"] == 64 * kS * kW, (M, N, K, d)
+            assert M <= 16 or tiles * RB <= 512, (M, N, K, d)
+            assert d["lds"] <= 80 * 1024 and d["lds"] == 512 + max(held * ceil_div(K, 256) * 256, kW * kS * kR * 1024), (M, N, K, d)
         elif d["kernel"].startswith("batched_decode"):
             kMT, kR, kW, kS, kD, kLx = d["params"]
             assert 4 < M <= 512 and (M > 8 or RB >= 1024) and d["grid"][0] == ceil_div(RB, kR * kW) * ceil_div(M, 16 * kMT)
         else:
-            assert d["kernel"] == "prefill", (M, N, K, d)
+            assert d["kernel"] in ("prefill", "prefill_any"), (M, N, K, d)
             tm, tn = d["params"][:2]
             groups = d["params"][2] if len(d["params"]) == 3 else 2 if tn == 512 else 1
             assert d["grid"][0] == ceil_div(M, tm) * ceil_div(N, tn) and d["block"] == 256 * groups and groups in (1, 2)
-            if tn == 512:                    # two row groups: one workgroup per CU, at least 7/8 of a round of them
+            if d["kernel"] == "prefill_any":     # 64-token tiles, at most one round of the eight-wave form, never split
+                assert tm == 64 and (tn, groups) in ((128, 2), (128, 1), (256, 1)) and d["splits"] == 1, (M, N, K, d)
+                assert d["lds"] <= (LDS_PER_CU if groups == 2 else LDS_PER_CU // 2) and (groups == 1 or d["grid"][0] <= 256), (M, N, K, d)
+            elif tn == 512:                    # two row groups: one workgroup per CU, at least 7/8 of a round of them
                 assert d["grid"][0] >= 224 and d["splits"] == 1 and tm == 128, (M, N, K, d)
             elif groups == 2:                # one workgroup per CU, one round, never together with a split through memory
                 assert d["grid"][0] <= 256 and d["splits"] == 1 and (tm, tn) in ((96, 128), (64, 256)), (M, N, K, d)
-    assert kernels == {"reference", "decode", "batched_decode", "batched_decode_loader", "prefill"}
+    assert kernels == {"reference", "decode_any", "prefill_any", "decode", "batched_decode", "batched_decode_loader", "prefill"}
 
 
 def test_short_ragged_rows_follow_the_measured_cases():
     """K not a multiple of 16, rows of a few elements: one thread per output is the faster kernel (2.9 against 4.2 us, 6.4 against
     10.3, 87 against 93) until K or the outputs are many (4.9 against 3.6, 9.8 against 6.3, 111 against 88, 43 against 18)."""
     for (M, N, K) in [(1, 1, 1), (64, 100, 5), (1, 100000, 24), (4, 1000000, 17), (77, 1003, 9)]:
-        assert B.linear_describe(M, N, K)["params"] == [], (M, N, K)
+        assert B.linear_describe(M, N, K)["kernel"] == "reference", (M, N, K)
     for (M, N, K) in [(64, 100, 17), (1000, 1000, 9), (4, 1000000, 40), (4096, 4096, 1), (77, 1003, 17), (200000, 16, 1), (1, 4096, 1001)]:
-        assert B.linear_describe(M, N, K)["params"] != [], (M, N, K)
+        assert B.linear_describe(M, N, K)["kernel"] in ("decode_any", "prefill_any"), (M, N, K)
 
 
 @pytest.mark.parametrize("M,N,K,fits", [(1, 2 ** 29 - 32, 130, True), (1, 2 ** 29 - 31, 130, False), (16, 2 ** 30, 17, False), (17, 2 ** 25, 3, False),
@@ -243,7 +257,7 @@ def test_ragged_launches_stay_within_the_grid_limit(M, N, K, fits):
     """K not a multiple of 16 at sizes that only the one-thread-per-output kernel can launch: a grid dimension holds fewer
     than 2^32 threads, and what does not fit is left to that kernel (which has no parameters), not refused."""
     d = B.linear_describe(M, N, K)
-    assert d["grid"][0] * d["block"] < 2 ** 32 and (d["block"] != 0) == fits, d
+    assert d["grid"][0] * d["block"] < 2 ** 32 and (d["kernel"] != "reference") == fits, d
 
 
 def test_decode_shapes_on_large_layers_follow_the_measured_cases():
