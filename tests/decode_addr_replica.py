@@ -1,5 +1,5 @@
-"""Host replica of the address arithmetic of the M <= 16 decode kernel (csrc/linear_gemv.hip, linear_gemv16_2bit): for
-one launch -- template parameters, shape, launch geometry as the host code computes them -- it enumerates every
+"""Host replica of the address arithmetic of the M <= 16 decode kernel (csrc/linear_gemv.hip, linear_gemv16_2bit), and of how
+both kernel forms for activation rows of any length and alignment read x_q (any16_reads, prefill_any_x_span): for one launch -- template parameters, shape, launch geometry as the host code computes them -- it enumerates every
 workgroup, lane and K item and returns, per buffer, the lowest and highest byte touched, so that a CPU test can hold them
 against the buffer sizes.  It re-states the kernel's index expressions in numpy; it shares no code with the kernel."""
 import numpy as np
@@ -27,9 +27,32 @@ class Span:
         return self.lo is None or (self.lo >= 0 and self.hi <= size)
 
 
+def any16_reads(start, avail):
+    """(first byte, bytes) of load_any16 at `start` with `avail` bytes left of x_q: sixteen, or byte by byte what there is"""
+    return start, np.clip(avail, 0, 16)
+
+
+def prefill_any_x_span(fm, M, K, bounded=True):
+    """x_q bytes that a 32 fm-token tile of the prefill form for any rows reads, first and last tile, every K step (bounded=False:
+    as if each read were of sixteen bytes)."""
+    sp, tokens = Span(), 32 * fm
+    row, slot = np.arange(tokens, dtype=np.int64)[:, None], np.arange(16, dtype=np.int64)[None, :]
+    last = (ceil_div(M, tokens) - 1) * tokens
+    for row0 in {0, last}:
+        m = row0 + np.minimum(row, min(tokens, M - row0) - 1)
+        for step in range(ceil_div(K, 256)):
+            col = step * 256 + ((slot ^ (row & 15)) << 4)
+            first, n = any16_reads(m * K + col, np.where(col < K, M * K - (m * K + col), 0))
+            if not bounded:
+                n = np.where(col < K, 16, 0)
+            for nb in range(1, 17):
+                sp.add(first[n == nb], nb)
+    return sp
+
+
 def decode_launch_spans(kR, kS, kW, kD, xmode, pair, M, N, K, out_bytes=2, gstride=0):
     """N: output features (pair: F, the packed matrix has 2 F rows).  Returns (spans, sizes, lds_bytes, grid)."""
-    fused = xmode >= 2
+    fused = 2 <= xmode <= 7                                     # 8: x_q rows of any length and alignment, 16 tokens per workgroup
     bf16 = xmode in (2, 4, 6)
     norm, swiglu = xmode in (4, 5), xmode in (6, 7)
     Kq = ceil_div(K, 64)
@@ -40,22 +63,25 @@ def decode_launch_spans(kR, kS, kW, kD, xmode, pair, M, N, K, out_bytes=2, gstri
     tail_quads = 16 * (Kq - 4 * (steps - 1))
     Kpad = steps * 256
     lds_fold = kW * kS * kR * 64 * 16 if kS > 1 else 0
-    lds_x = M * ceil_div(K, 256) * 256
+    lds_x = min(M, 16 if xmode == 8 else M) * ceil_div(K, 256) * 256
     lds = HEADER + (lds_x if (xmode != 0 and lds_x > lds_fold) else lds_fold)
-    grid = ceil_div(pair_off, kW) if pair else ceil_div(RB, kW * kR)
+    groups = ceil_div(pair_off, kW) if pair else ceil_div(RB, kW * kR)      # workgroups of a token tile
+    tiles = [0, ceil_div(M, 16) - 1] if xmode == 8 else [0]     # first and last (the others lie between)
+    grid = groups * (ceil_div(M, 16) if xmode == 8 else 1)
     threads = kS * kW * 64
     esz = 2 if bf16 else 4
     kE = 8 if bf16 else 4
 
     sp = {k: Span() for k in ("packed", "x", "gamma", "sx", "y", "gain", "lds")}
-    blk = np.arange(grid, dtype=np.int64)[:, None]
+    blk = np.arange(groups, dtype=np.int64)[:, None]
     tid = np.arange(threads, dtype=np.int64)[None, :]
     lane, wave = tid & 63, tid >> 6
     r, g = lane & 15, lane >> 4
     ws, ww = wave % kS, wave // kS
     rbw = (blk * kW + ww) if pair else (blk * kW + ww) * kR
     rbc = [(np.minimum(rbw, pair_off - 1) + a * pair_off) if pair else np.minimum(rbw + a, RB - 1) for a in range(kR)]
-    mrow = np.minimum(r, M - 1)
+    held = min(M, 16) if xmode == 8 else M                      # tokens of the fullest workgroup
+    mrow = np.minimum(r, held - 1)
     wstride = RB * 64
     for item in range(items):
         sl = np.minimum(ws + item * kS, steps - 1)
@@ -75,6 +101,15 @@ def decode_launch_spans(kR, kS, kW, kD, xmode, pair, M, N, K, out_bytes=2, gstri
         ok = kv * 16 + 16 <= K
         sp["x"].add((m * K + kv * 16)[ok], 16)
         sp["lds"].add(HEADER + 16 * v, 16)
+    if xmode == 8:
+        for tile in tiles:
+            rest = M - 16 * tile                                # tokens from the tile's first to the last of all
+            v = np.arange(min(rest, 16) * (Kpad >> 4), dtype=np.int64)
+            m, kv = v // (Kpad >> 4), v % (Kpad >> 4)
+            first, n = any16_reads(16 * tile * K + m * K + kv * 16, np.where(kv * 16 < K, (rest - m) * K - kv * 16, 0))
+            for nb in range(1, 17):
+                sp["x"].add(first[n == nb], nb)
+            sp["lds"].add(HEADER + 16 * v, 16)
     if fused:
         nvec = K // kE
         row_bytes = (2 if swiglu else 1) * K * esz
@@ -107,12 +142,14 @@ def decode_launch_spans(kR, kS, kW, kD, xmode, pair, M, N, K, out_bytes=2, gstri
     for a in range(kR):
         sp["gamma"].add(4 * gstride * rbc[a], 4)
     if not fused:
-        sp["sx"].add(4 * mrow + 0 * blk, 4)
+        for tile in tiles:
+            sp["sx"].add(4 * (16 * tile + np.minimum(r, min(M - 16 * tile, held) - 1)) + 0 * blk, 4)
     for a in range(1 if pair else kR):
         n0 = (rbw if pair else rbw + a) * 16 + 4 * g
-        for e in range(4):
-            ok = (r < M) & (ws == 0) & (n0 + e < N)
-            sp["y"].add(out_bytes * (r * N + n0 + e)[ok], out_bytes)
+        for tile in tiles:
+            for e in range(4):
+                ok = (r < min(M - 16 * tile, held)) & (ws == 0) & (n0 + e < N)
+                sp["y"].add(out_bytes * ((16 * tile + r) * N + n0 + e)[ok], out_bytes)
     rows = 2 * N if pair else N
     sizes = {"packed": 16 * ceil_div(rows, 16) * 64 * ceil_div(K, 64) // 4,
              "x": M * (2 if swiglu else 1) * K * (esz if fused else 1), "gamma": 4 * (ceil_div(rows, 16) if gstride else 1),

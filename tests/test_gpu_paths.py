@@ -67,6 +67,11 @@ def test_segments_side_by_side(gpu_lib, rows, K, bf16):
                                    # more than 16 tokens in tiles over the grid: a full and a partial last tile, K beyond 64 KiB of
                                    # LDS, the most workgroups of the form and one more
                                    (32, 70, 333), (40, 1900, 3900), (33, 100, 5000), (8192, 16, 33), (8193, 16, 33),
+                                   # the most LDS a decode workgroup takes
+                                   (33, 100, 4863), (1, 40, 81407),
+                                   # K a multiple of 16, whole K steps among them, which the second call below brings here unaligned
+                                   (16, 100, 256), (3, 500, 272), (40, 300, 256), (2, 300, 4096), (300, 1000, 272), (100, 3000, 4096),
+                                   (2000, 9000, 256),
                                    # the shortest rows these forms are chosen for (below, a thread per output is faster)
                                    (5, 300, 15), (16, 500, 13), (3000, 1100, 1), (3000, 1100, 3)])
 @pytest.mark.parametrize("y", ["I32", "F32", "BF16"])
@@ -74,7 +79,7 @@ def test_rows_of_any_length(gpu_lib, M, N, K, y):
     packed, gamma = gpu_lib.quantize_weights(dev(synth.weights(N, K, config=1, layer=M % 7)))
     xq, sx = gpu_lib.quantize_acts(dev(synth.activations(M, K, config=1, layer=N % 7)))
     yt = getattr(gpu_lib, y)
-    # x_q at the end of its allocation, one byte past an aligned address: nothing behind it may be needed
+    # one byte past an aligned address (that nothing behind x_q is read is the business of the address replica on the CPU)
     buf = torch.empty(M * K + 1, dtype=torch.int8, device="cuda")
     buf[1:] = xq.reshape(-1)
     big = torch.full((M * N + 64,), 7, dtype=gpu_lib._OUT[yt], device="cuda")
