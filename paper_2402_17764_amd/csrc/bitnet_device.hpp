@@ -163,7 +163,7 @@ __device__ inline double wave_sum_f64(double v) {
 // roundings, y (hardware reciprocal square root, a step of third and one of second order) a few more; the definition's own
 // fp64 value is within four roundings of the true one.  All of that is below 2^-44 of y, and rounding to float is monotone: if
 // y (1 - 2^-44) and y (1 + 2^-44) round to the same float, it is the definition's.  They do not for about one token in half a
-// million (false is returned; for S = 0 or not finite too), and the caller then takes the exact sum.
+// million (false is returned; for S / K + eps = 0 or not finite too), and the caller then takes the exact sum.
 __device__ inline bool rms_from_rounded_sum(double S, double inv_K, float eps, float* r) {
     const double a = S * inv_K + (double)eps;
     double y = __builtin_amdgcn_rsq(a);

@@ -378,7 +378,7 @@ __global__ __launch_bounds__((kS * kW + 1) * kWave) void linear_skinny_ws_2bit(
         uint4 wst[kD][kR];
 #pragma unroll
         for (int d = 0; d < kD; ++d) load_w(wst[d], d);
-            int i0 = 0;
+        int i0 = 0;
         do {
 #pragma unroll
             for (int d = 0; d < kD; ++d) {

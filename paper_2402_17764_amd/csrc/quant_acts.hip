@@ -206,10 +206,10 @@ __device__ inline float rms_scale(dd v, int64_t K, float eps, double* sh_hi, dou
 //
 // Register-resident form: the token is read once, kVecs 16-byte loads per thread (the launcher picks the smallest
 // count that covers K), and stays in registers *as loaded* -- bf16 pairs are widened where they are used -- so that a
-// workgroup needs few registers and a CU holds many tokens at different stages: the kernel does more arithmetic than
-// memory traffic (nine fp64 operations per element for the exact sum), and only tokens in other phases can hide one
-// token's loads and reductions.  z is kept in registers between the absmax and the rounding where that takes at most
-// 32 of them and recomputed with the same two multiplications otherwise.
+// workgroup needs few registers and a CU holds many tokens at different stages: a token is a load, a reduction, a
+// load of the gain and another reduction in a row, and only tokens in other phases can hide one token's waits.  z is kept in
+// registers between the absmax and the rounding where that takes at most 32 of them and recomputed with the same two
+// multiplications otherwise.
 template <bool kBf16, int kVecs, int kThreads, bool kGainFirst>
 __global__ __launch_bounds__(kThreads) void rmsnorm_quantize_vec(
         const void* __restrict__ xv, const float* __restrict__ g, float eps, int64_t K, int8_t* __restrict__ xq,

@@ -337,9 +337,10 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
 
 // bf16 rows that start on 16-byte boundaries (K a multiple of 8): items of two K steps, so that a lane's load is 16 bytes
 // (columns 8l .. 8l+7 of the 512) and a row of an item one 1 KiB run, as in the fp32 form; with 8-byte loads the pass moved
-// half the bytes per request and ran at 2.9 TB/s (57344 x 8192, both passes: 496 us, now 350; 4096 x 4096 22.7, 19.1; 512 x 512 8.4, 7.5).  Two lanes complete a word; the pair holds the words of
-// the wave's four rows twice, so the even lane hands out rows 0 and 2, the odd lane rows 1 and 3, and two ds_bpermute per
-// step give lane 16 g + 4 t + j word j of quad column g for row 4w + t: four 64-byte runs per step, as above.
+// half the bytes per request and ran at 2.9 TB/s (57344 x 8192, both passes: 496 us, 350 with these; 4096 x 4096 22.7, 19.1; 512 x
+// 512 8.4, 7.5).  Two lanes complete a word; the pair holds the words of the wave's four rows twice, so the even lane hands out
+// rows 0 and 2, the odd lane rows 1 and 3, and two ds_bpermute per step give lane 16 g + 4 t + j word j of quad column g for row
+// 4w + t: four 64-byte runs per step, as above.
 template <int kSegs>
 __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit_bf16x8(const uint16_t* __restrict__ W_all, int64_t K,
                                                                            int64_t Kq, int64_t RB, SegList<kSegs> list,
