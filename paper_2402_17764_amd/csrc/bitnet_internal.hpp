@@ -29,6 +29,7 @@ inline hipError_t raise_dynamic_lds(const void* kernel, int bytes, RaisedFlags& 
 
 // A launch takes fewer threads than this along a grid dimension.  With more it reports success and runs some of them only.
 constexpr int64_t kMaxGridThreads = (int64_t)1 << 32;
+constexpr int64_t kMaxLoopBlocks = kMaxGridThreads / 256 / 2;      // of 256 threads, for kernels that loop over what is left
 
 // Small arguments of the product kernels in one word.  Their arguments are kept to 14 dwords, all of which arrive in scalar
 // registers with the wave (the build asks for it); anything beyond is a load that is cold whenever the launch before streamed

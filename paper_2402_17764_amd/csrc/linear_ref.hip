@@ -48,11 +48,11 @@ __global__ __launch_bounds__(256) void linear_reference_2bit(const int8_t* __res
 
 __global__ __launch_bounds__(256) void unpack_2bit(const uint32_t* __restrict__ packed, int64_t N, int64_t K, int64_t Kq,
                                                    int64_t RB, int8_t* __restrict__ codes) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= N * K) return;
-    const int64_t n = idx / K, k = idx % K;
-    const uint32_t w = load_word_2bit(packed, Kq, RB, n, k);
-    codes[idx] = (int8_t)code_value((w >> code_shift((int)(k & 15))) & 3u);
+    for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < N * K; idx += (int64_t)gridDim.x * 256) {
+        const int64_t n = idx / K, k = idx % K;
+        const uint32_t w = load_word_2bit(packed, Kq, RB, n, k);
+        codes[idx] = (int8_t)code_value((w >> code_shift((int)(k & 15))) & 3u);
+    }
 }
 
 hipError_t launch_linear_reference_2bit(const int8_t* xq, const float* sx, const void* packed,
@@ -73,7 +73,8 @@ hipError_t launch_linear_reference_2bit(const int8_t* xq, const float* sx, const
 
 hipError_t launch_unpack_2bit(const void* packed, int64_t N, int64_t K, int8_t* codes, hipStream_t stream) {
     const int64_t Kq = ceil_div(K, kColsPerQuad);
-    hipLaunchKernelGGL(unpack_2bit, dim3((unsigned)ceil_div(N * K, 256)), dim3(256), 0, stream,
+    const int64_t blocks = ceil_div(N * K, 256);
+    hipLaunchKernelGGL(unpack_2bit, dim3((unsigned)(blocks < kMaxLoopBlocks ? blocks : kMaxLoopBlocks)), dim3(256), 0, stream,
                        static_cast<const uint32_t*>(packed), N, K, Kq, ceil_div(N, kRowsPerBlock), codes);
     return hipGetLastError();
 }

@@ -110,11 +110,11 @@ __global__ __launch_bounds__(256) void ternarize_pack_trit5(const T* __restrict_
 // ---------------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void unpack_trit5(const uint8_t* __restrict__ packed, int64_t N, int64_t K, int64_t RB,
                                                     int8_t* __restrict__ codes) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= N * K) return;
-    int64_t bi; int dg;
-    trit5_locate(idx / K, idx % K, RB, &bi, &dg);
-    codes[idx] = (int8_t)trit5_digit(packed[bi], dg);
+    for (int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x; idx < N * K; idx += (int64_t)gridDim.x * 256) {
+        int64_t bi; int dg;
+        trit5_locate(idx / K, idx % K, RB, &bi, &dg);
+        codes[idx] = (int8_t)trit5_digit(packed[bi], dg);
+    }
 }
 
 __global__ __launch_bounds__(256) void linear_reference_trit5(const int8_t* __restrict__ xq, const float* __restrict__ sx,
@@ -287,7 +287,8 @@ hipError_t launch_pack_trit5(const void* W, bool bf16, int64_t N, int64_t K, con
 }
 
 hipError_t launch_unpack_trit5(const void* packed, int64_t N, int64_t K, int8_t* codes, hipStream_t stream) {
-    hipLaunchKernelGGL(unpack_trit5, dim3((unsigned)ceil_div(N * K, 256)), dim3(256), 0, stream,
+    const int64_t blocks = ceil_div(N * K, 256);
+    hipLaunchKernelGGL(unpack_trit5, dim3((unsigned)(blocks < kMaxLoopBlocks ? blocks : kMaxLoopBlocks)), dim3(256), 0, stream,
                        static_cast<const uint8_t*>(packed), N, K, ceil_div(N, kRowsPerBlock), codes);
     return hipGetLastError();
 }

@@ -389,3 +389,20 @@ def test_repack_of_more_chunks_than_one_launch_takes(gpu_lib):
         assert torch.equal(p2[at * 256:(at + n) * 256], want)
     del p5, p2
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("fmt", ["PACK_2BIT", "PACK_TRIT5"])
+def test_unpack_of_more_weights_than_one_launch_has_threads(gpu_lib, fmt):
+    """65552 x 65536 codes: more than 2^32 of them.  The weights are 0 and +-0.02, so their signs are the codes."""
+    B, N, K = gpu_lib, 65552, 65536
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < (40 << 30):
+        pytest.skip("needs 40 GiB of GPU memory")
+    sign = torch.randint(-1, 2, (N, K), dtype=torch.int8, device="cuda", generator=torch.Generator(device="cuda").manual_seed(9))
+    W = sign.bfloat16().mul_(0.02)
+    packed, _ = B.quantize_weights(W, getattr(B, fmt))
+    del W
+    codes = B.unpack_weights(packed, N, K, getattr(B, fmt), codes=torch.full((N, K), 9, dtype=torch.int8, device="cuda"))
+    assert torch.equal(codes, sign)
+    del sign, codes, packed
+    torch.cuda.empty_cache()
