@@ -580,8 +580,23 @@ static void producer_shape(bool vec, int64_t M, int64_t cols, int* threads, int*
         }                                                                                                        \
     } while (0)
 
+// A workgroup per token and up to 1024 threads in it: tokens beyond what a launch has threads for come in further launches.
+constexpr int64_t kTokenSlab = kMaxGridThreads / 1024 / 2;
+template <typename Launch>
+static hipError_t in_token_slabs(int64_t M, Launch&& launch) {
+    for (int64_t m0 = 0; m0 < M; m0 += kTokenSlab) {
+        const hipError_t e = launch(m0, M - m0 < kTokenSlab ? M - m0 : kTokenSlab);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 hipError_t launch_rmsnorm_quantize(const void* x, bool bf16, const float* g, float eps, int64_t M, int64_t K,
                                    int8_t* xq, float* sx, hipStream_t stream) {
+    if (M > kTokenSlab)
+        return in_token_slabs(M, [&](int64_t m0, int64_t n) {
+            return launch_rmsnorm_quantize(static_cast<const char*>(x) + m0 * K * (bf16 ? 2 : 4), bf16, g, eps, n, K, xq + m0 * K, sx + m0, stream);
+        });
     const int elems = bf16 ? 8 : 4;
     const int max_vecs = bf16 ? 8 : 16;                            // 64 token elements per thread at most
     const bool aligned = K % elems == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
@@ -641,6 +656,10 @@ static bool swiglu_by_table(const void* gu, int64_t M, int64_t F, const void* hq
 
 hipError_t launch_swiglu_quantize(const void* gu, bool bf16, int64_t M, int64_t F, int8_t* hq, float* sh,
                                   hipStream_t stream) {
+    if (M > kTokenSlab)
+        return in_token_slabs(M, [&](int64_t m0, int64_t n) {
+            return launch_swiglu_quantize(static_cast<const char*>(gu) + m0 * 2 * F * (bf16 ? 2 : 4), bf16, n, F, hq + m0 * F, sh + m0, stream);
+        });
     if (bf16 && swiglu_by_table(gu, M, F, hq)) {
         const uint16_t* in = static_cast<const uint16_t*>(gu);
         const int wgs = (int)(M < 256 ? M : 256);          // one per CU: two and four were no faster
@@ -663,6 +682,10 @@ hipError_t launch_swiglu_quantize(const void* gu, bool bf16, int64_t M, int64_t 
 
 hipError_t launch_quantize_acts(const void* x, bool bf16, int64_t M, int64_t K, int8_t* xq, float* sx,
                                 hipStream_t stream) {
+    if (M > kTokenSlab)
+        return in_token_slabs(M, [&](int64_t m0, int64_t n) {
+            return launch_quantize_acts(static_cast<const char*>(x) + m0 * K * (bf16 ? 2 : 4), bf16, n, K, xq + m0 * K, sx + m0, stream);
+        });
     const int elems = bf16 ? 8 : 4;
     const bool aligned = (reinterpret_cast<uintptr_t>(x) % 16 == 0) && (K % elems == 0) &&
                          (reinterpret_cast<uintptr_t>(xq) % 8 == 0);

@@ -406,3 +406,22 @@ def test_unpack_of_more_weights_than_one_launch_has_threads(gpu_lib, fmt):
     assert torch.equal(codes, sign)
     del sign, codes, packed
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("kind", ["acts", "rmsnorm", "swiglu"])
+def test_producers_on_more_tokens_than_one_launch_has_threads(gpu_lib, kind):
+    """2^24 + 40 tokens, a workgroup of 256 threads each: more than 2^32 threads.  Against the same tokens in two calls."""
+    B, M, K = gpu_lib, 2 ** 24 + 40, 48
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < (40 << 30):
+        pytest.skip("needs 40 GiB of GPU memory")
+    call = {"acts": B.quantize_acts, "rmsnorm": B.rmsnorm_quantize, "swiglu": B.swiglu_quantize}[kind]
+    x = torch.randn(M, K * (2 if kind == "swiglu" else 1), device="cuda", generator=torch.Generator(device="cuda").manual_seed(4)).bfloat16()
+    q, s = torch.full((M, K), 5, dtype=torch.int8, device="cuda"), torch.full((M,), -1.0, device="cuda")
+    call(x, **dict(zip(("hq", "sh") if kind == "swiglu" else ("xq", "sx"), (q, s))))
+    half = M // 2 + 3
+    for at, part in ((0, x[:half]), (half, x[half:])):
+        q2, s2 = call(part)
+        assert torch.equal(q[at:at + len(part)], q2) and torch.equal(s[at:at + len(part)], s2)
+    del x, q, s, q2, s2
+    torch.cuda.empty_cache()
