@@ -495,7 +495,9 @@ hipError_t launch_splitk_reduce(const int32_t* part, int splits, const float* sx
 bool gemm_supports(int64_t M, int64_t N, int64_t K, const void* xq) {
     // per-lane activation offsets are 32-bit and relative to the tile's first row (128 * K fits for every K the
     // library accepts); one K step of the packed weights (1 KiB per 16-row block) is addressed as one raw buffer
-    return M >= 1 && K % 16 == 0 && reinterpret_cast<uintptr_t>(xq) % 16 == 0 && ceil_div(N, kRowsPerBlock) < ((int64_t)1 << 21);
+    // (and the threads of its smallest tiles, 64 x 128 outputs for 256 of them, have to fit a grid)
+    return M >= 1 && K % 16 == 0 && reinterpret_cast<uintptr_t>(xq) % 16 == 0 && ceil_div(N, kRowsPerBlock) < ((int64_t)1 << 21) &&
+           ceil_div(M, 64) * ceil_div(N, 128) * kGemmThreads < kMaxGridThreads;
 }
 
 template <int kFM, int kFN, int kKG = 1, int kNG = 1, bool kAny = false>

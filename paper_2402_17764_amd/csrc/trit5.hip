@@ -53,13 +53,16 @@ __device__ inline void trit_w4(const uint16_t* p, float (&w)[4]) {
 }
 
 constexpr int kTritTilePitch = 81;                   // words per tile row: 80 + 1
+// chunks (16 rows x 320 columns, a wave each) of one packing or repacking launch: half the threads that a grid dimension holds
+constexpr int64_t kLaunchChunks = (int64_t)1 << 25;
+
 template <typename T>
 __global__ __launch_bounds__(256) void ternarize_pack_trit5(const T* __restrict__ W, int64_t N, int64_t K, int64_t RB,
-                                                            int64_t steps, int vec_ok /* rows start on 4-element boundaries */,
+                                                            int64_t steps, int64_t first /* chunk of this launch */, int vec_ok /* rows start on 4-element boundaries */,
                                                             const float* __restrict__ gamma, uint4* __restrict__ packed) {
     __shared__ uint32_t tiles[4][kRowsPerBlock * kTritTilePitch];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-    const int64_t chunk = (int64_t)blockIdx.x * 4 + wave;             // = RB * step + row block: the chunk's place in the packed matrix
+    const int64_t chunk = first + (int64_t)blockIdx.x * 4 + wave;     // = RB * step + row block: the chunk's place in the packed matrix
     if (chunk >= RB * steps) return;                                   // whole waves leave; no workgroup barrier below
     const int64_t s = chunk / RB, rb = chunk - s * RB;
     const float d = gamma[0] + kEps;                                   // Eq. (1): gamma + eps
@@ -275,14 +278,17 @@ hipError_t launch_pack_trit5(const void* W, bool bf16, int64_t N, int64_t K, con
                              hipStream_t stream) {
     const int64_t RB = ceil_div(N, kRowsPerBlock);
     const int64_t steps = ceil_div(K, kTritStep);
-    dim3 grid((unsigned)ceil_div(RB * steps, 4));
     const int vec_ok = K % 4 == 0 && reinterpret_cast<uintptr_t>(W) % (bf16 ? 8 : 16) == 0;
-    if (bf16)
-        hipLaunchKernelGGL(ternarize_pack_trit5<uint16_t>, grid, dim3(256), 0, stream, static_cast<const uint16_t*>(W), N, K, RB,
-                           steps, vec_ok, gamma, static_cast<uint4*>(packed));
-    else
-        hipLaunchKernelGGL(ternarize_pack_trit5<float>, grid, dim3(256), 0, stream, static_cast<const float*>(W), N, K, RB,
-                           steps, vec_ok, gamma, static_cast<uint4*>(packed));
+    for (int64_t first = 0; first < RB * steps; first += kLaunchChunks) {
+        const int64_t n = RB * steps - first < kLaunchChunks ? RB * steps - first : kLaunchChunks;
+        const dim3 grid((unsigned)ceil_div(n, 4));
+        if (bf16)
+            hipLaunchKernelGGL(ternarize_pack_trit5<uint16_t>, grid, dim3(256), 0, stream, static_cast<const uint16_t*>(W), N, K, RB,
+                               steps, first, vec_ok, gamma, static_cast<uint4*>(packed));
+        else
+            hipLaunchKernelGGL(ternarize_pack_trit5<float>, grid, dim3(256), 0, stream, static_cast<const float*>(W), N, K, RB,
+                               steps, first, vec_ok, gamma, static_cast<uint4*>(packed));
+    }
     return hipGetLastError();
 }
 
@@ -320,7 +326,6 @@ hipError_t launch_linear_reference_trit5(const int8_t* xq, const float* sx, cons
 // 80 g + 79: exactly one word.  The lane's five words go through LDS (the wave's own 1280 bytes, whose accesses complete in
 // order), from where 80 lanes' worth of 16-byte quads are stored in runs of 256 bytes.
 constexpr int kRepackWaves = 4;
-constexpr int64_t kRepackChunks = (int64_t)1 << 25;      // of one launch: 2^31 threads, half of what a grid dimension holds
 __global__ __launch_bounds__(kRepackWaves * kWave) void repack_trit5_to_2bit(const uint4* __restrict__ in, int64_t RB, int64_t first, int64_t chunks,
                                                                              int64_t Kq2, uint4* __restrict__ out) {
     __shared__ uint2 lut[256];                       // byte -> {codes 0..3 as 2-bit fields at bits 0, 8, 16, 24; code 4}
@@ -414,8 +419,8 @@ hipError_t launch_repack(const void* in, bool in_trit5, int64_t N, int64_t K, vo
         return hipGetLastError();
     }
     const int64_t chunks = RB * steps5;
-    for (int64_t first = 0; first < chunks; first += kRepackChunks) {
-        const int64_t n = chunks - first < kRepackChunks ? chunks - first : kRepackChunks;
+    for (int64_t first = 0; first < chunks; first += kLaunchChunks) {
+        const int64_t n = chunks - first < kLaunchChunks ? chunks - first : kLaunchChunks;
         hipLaunchKernelGGL(repack_trit5_to_2bit, dim3((unsigned)ceil_div(n, kRepackWaves)), dim3(kRepackWaves * kWave), 0, stream,
                            static_cast<const uint4*>(in), RB, first, first + n, Kq2, static_cast<uint4*>(out));
     }
@@ -423,8 +428,8 @@ hipError_t launch_repack(const void* in, bool in_trit5, int64_t N, int64_t K, vo
 }
 
 bool gemv_trit5_supports(int64_t M, int64_t N, int64_t K, const void* xq) {
-    (void)N;
-    return M >= 1 && M <= 16 && K % 16 == 0 && reinterpret_cast<uintptr_t>(xq) % 16 == 0;
+    // two row blocks for the 128 threads of a workgroup, on a matrix this tall
+    return M >= 1 && M <= 16 && K % 16 == 0 && reinterpret_cast<uintptr_t>(xq) % 16 == 0 && ceil_div(N, kRowsPerBlock) * 64 < kMaxGridThreads;
 }
 
 template <int kR, int kS, int kD>

@@ -181,6 +181,8 @@ def test_fallbacks_and_errors():
     assert B.linear_describe(2048, 27648, 5120, fmt=B.PACK_TRIT5, workspace_bytes=need - 257)["repack"] is None
     assert B.linear_describe(16, 27648, 5120, fmt=B.PACK_TRIT5, workspace_bytes=need)["kernel"] == "trit5_decode"
     assert B.linear_describe(2048, 27648, 5120)["repack"] is None
+    assert B.linear_describe(1, 2 ** 30 - 16, 16, fmt=B.PACK_TRIT5)["kernel"] == "trit5_decode"
+    assert B.linear_describe(1, 2 ** 30, 16, fmt=B.PACK_TRIT5)["kernel"] == "trit5_reference"       # 2^32 threads of the decode kernel
     lib = B.load()
     buf = ctypes.create_string_buffer(128)
     assert lib.bitnet_linear_describe(1, 4096, 4096, 0, 0, None, 128) == 1
@@ -252,10 +254,11 @@ def test_short_ragged_rows_follow_the_measured_cases():
 
 
 @pytest.mark.parametrize("M,N,K,fits", [(1, 2 ** 29 - 32, 130, True), (1, 2 ** 29 - 31, 130, False), (16, 2 ** 30, 17, False), (17, 2 ** 25, 3, False),
-                                        (2 ** 30 - 64, 16, 17, True), (2 ** 30 - 63, 16, 17, False), (2 ** 31 - 1, 1, 7, False)])
-def test_ragged_launches_stay_within_the_grid_limit(M, N, K, fits):
-    """K not a multiple of 16 at sizes that only the one-thread-per-output kernel can launch: a grid dimension holds fewer
-    than 2^32 threads, and what does not fit is left to that kernel (which has no parameters), not refused."""
+                                        (2 ** 30 - 64, 16, 17, True), (2 ** 30 - 63, 16, 17, False), (2 ** 31 - 1, 1, 7, False),
+                                        (2 ** 30 - 64, 16, 16, True), (2 ** 30, 16, 16, False), (2 ** 31 - 1, 1, 64, False)])
+def test_launches_stay_within_the_grid_limit(M, N, K, fits):
+    """Sizes that only the one-thread-per-output kernel can launch: a grid dimension holds fewer than 2^32 threads, and what
+    does not fit is left to that kernel, which walks the tokens in slabs."""
     d = B.linear_describe(M, N, K)
     assert d["grid"][0] * d["block"] < 2 ** 32 and (d["kernel"] != "reference") == fits, d
 

@@ -425,3 +425,24 @@ def test_producers_on_more_tokens_than_one_launch_has_threads(gpu_lib, kind):
         assert torch.equal(q[at:at + len(part)], q2) and torch.equal(s[at:at + len(part)], s2)
     del x, q, s, q2, s2
     torch.cuda.empty_cache()
+
+
+def test_trit5_packing_of_more_chunks_than_one_launch_takes(gpu_lib):
+    """A wave per 16 rows x 320 columns, 2^26 of them and more; every weight is +-0.02, so that any part of the matrix has its gamma."""
+    B, K, N = gpu_lib, 1, 2 ** 30 + 40
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < (90 << 30):
+        pytest.skip("needs 90 GiB of GPU memory")
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    W = torch.randint(0, 2, (N, K), dtype=torch.uint8, device="cuda", generator=gen).bfloat16().sub_(0.5).mul_(0.04)
+    packed = torch.empty(B.packed_bytes(N, K, B.PACK_TRIT5), dtype=torch.uint8, device="cuda")
+    blocks = -(-N // 16)
+    spots = [(0, 40), (2 ** 25 - 20, 40), (2 ** 26 - 20, 20), (blocks - 7, 7)]          # row blocks: first, how many
+    for at, n in spots:
+        packed[at * 1024:(at + n) * 1024] = 0xFF
+    _, gamma = B.quantize_weights(W, B.PACK_TRIT5, packed=packed)
+    for at, n in spots:
+        want, g = B.quantize_weights(W[16 * at:16 * (at + n)], B.PACK_TRIT5)
+        assert torch.equal(g, gamma) and torch.equal(packed[at * 1024:(at + n) * 1024], want)
+    del W, packed
+    torch.cuda.empty_cache()
