@@ -778,8 +778,9 @@ hipError_t launch_linear_gemv16_2bit(const int8_t* xq, const float* sx, const vo
 }
 
 bool gemv_fused_supports(int64_t M, int64_t N, int64_t K, const void* x) {
-    (void)N;
+    // the launch of a matrix tall enough to pass a grid: 512 threads for eight row blocks from eight tokens on, for sixteen below
     return M >= 1 && M <= 16 && K % 16 == 0 && reinterpret_cast<uintptr_t>(x) % 16 == 0 &&
+           ceil_div(N, kRowsPerBlock * (M >= 8 ? 8 : 16)) * 512 < kMaxGridThreads &&
            kGemvLdsHeader * sizeof(uint4) + gemv16_x_lds_bytes(M, K) <= kGemvLdsBudget;
 }
 

@@ -428,8 +428,8 @@ hipError_t launch_repack(const void* in, bool in_trit5, int64_t N, int64_t K, vo
 }
 
 bool gemv_trit5_supports(int64_t M, int64_t N, int64_t K, const void* xq) {
-    // two row blocks for the 128 threads of a workgroup, on a matrix this tall
-    return M >= 1 && M <= 16 && K % 16 == 0 && reinterpret_cast<uintptr_t>(xq) % 16 == 0 && ceil_div(N, kRowsPerBlock) * 64 < kMaxGridThreads;
+    // the launch of a matrix tall enough to pass a grid: 128 threads for two row blocks
+    return M >= 1 && M <= 16 && K % 16 == 0 && reinterpret_cast<uintptr_t>(xq) % 16 == 0 && ceil_div(N, 2 * kRowsPerBlock) * 128 < kMaxGridThreads;
 }
 
 template <int kR, int kS, int kD>

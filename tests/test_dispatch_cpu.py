@@ -181,8 +181,8 @@ def test_fallbacks_and_errors():
     assert B.linear_describe(2048, 27648, 5120, fmt=B.PACK_TRIT5, workspace_bytes=need - 257)["repack"] is None
     assert B.linear_describe(16, 27648, 5120, fmt=B.PACK_TRIT5, workspace_bytes=need)["kernel"] == "trit5_decode"
     assert B.linear_describe(2048, 27648, 5120)["repack"] is None
-    assert B.linear_describe(1, 2 ** 30 - 16, 16, fmt=B.PACK_TRIT5)["kernel"] == "trit5_decode"
-    assert B.linear_describe(1, 2 ** 30, 16, fmt=B.PACK_TRIT5)["kernel"] == "trit5_reference"       # 2^32 threads of the decode kernel
+    assert B.linear_describe(1, 2 ** 30 - 32, 16, fmt=B.PACK_TRIT5)["kernel"] == "trit5_decode"
+    assert B.linear_describe(1, 2 ** 30 - 16, 16, fmt=B.PACK_TRIT5)["kernel"] == "trit5_reference"       # 2^32 threads of the decode kernel
     lib = B.load()
     buf = ctypes.create_string_buffer(128)
     assert lib.bitnet_linear_describe(1, 4096, 4096, 0, 0, None, 128) == 1
@@ -261,6 +261,17 @@ def test_launches_stay_within_the_grid_limit(M, N, K, fits):
     does not fit is left to that kernel, which walks the tokens in slabs."""
     d = B.linear_describe(M, N, K)
     assert d["grid"][0] * d["block"] < 2 ** 32 and (d["kernel"] != "reference") == fits, d
+
+
+def test_fused_launches_beyond_the_grid_limit_are_refused():
+    """they have no other kernel to go to"""
+    for M, N, ok in [(1, 2 ** 30, True), (7, 2 ** 31 - 256, True), (7, 2 ** 31 - 16, False), (8, 2 ** 30 - 128, True), (8, 2 ** 30 - 16, False)]:
+        if ok:
+            d = B.entry_describe(B.ENTRY_LINEAR_FUSED, M, N, 16)
+            assert d["grid"][0] * d["block"] < 2 ** 32
+        else:
+            with pytest.raises(B.BitnetError):
+                B.entry_describe(B.ENTRY_LINEAR_FUSED, M, N, 16)
 
 
 def test_decode_shapes_on_large_layers_follow_the_measured_cases():
