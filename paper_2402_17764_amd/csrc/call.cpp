@@ -110,11 +110,13 @@ bool truth(PyObject* o) {
 }
 
 at::ScalarType out_type(PyObject* code) {
-    switch (integer(code)) {
-        case BITNET_F32: return at::kFloat;
-        case BITNET_BF16: return at::kBFloat16;
-        case BITNET_I32: return at::kInt;
-        default: break;
+    if (PyIndex_Check(code)) {
+        switch (integer(code)) {
+            case BITNET_F32: return at::kFloat;
+            case BITNET_BF16: return at::kBFloat16;
+            case BITNET_I32: return at::kInt;
+            default: break;
+        }
     }
     PyErr_SetObject(PyExc_KeyError, code);
     throw Raised();

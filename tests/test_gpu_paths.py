@@ -113,7 +113,9 @@ def test_native_marshalling_checks_its_arguments(gpu_lib):
                       (lambda: B.rmsnorm_quantize(x, eps=-1.0), B.BitnetError),
                       (lambda: B.swiglu_quantize(x[:, :127].contiguous()), ValueError),
                       (lambda: B.linear(x, sx, packed, gamma, N), TypeError), (lambda: B.linear(xq, sx.double(), packed, gamma, N), TypeError),
-                      (lambda: B.linear(xq, sx, packed, gamma, N, y_dtype=9), KeyError), (lambda: B.linear(xq, sx, packed, gamma, 16.5), TypeError),
+                      (lambda: B.linear(xq, sx, packed, gamma, N, y_dtype=9), KeyError),
+                      (lambda: B.linear(xq, sx, packed, gamma, N, y_dtype=torch.float32), KeyError), (lambda: B.linear_fused(x, packed, gamma, N, y_dtype="F32"), KeyError),
+                      (lambda: B.linear(xq, sx, packed, gamma, 16.5), TypeError),
                       (lambda: B.linear(xq, sx, packed, gamma, 0), B.BitnetError),
                       (lambda: B.linear(xq, sx, packed, gamma, N, y=torch.empty(M, N, device="cuda", dtype=torch.bfloat16)), TypeError),
                       (lambda: B.linear(xq, sx, packed, gamma, N, fmt=7), B.BitnetError),
