@@ -141,12 +141,15 @@ const float* per_block(PyObject* o, const char* name, int64_t N) {
 
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
+// other threads may run until it goes out of scope, however that happens
+struct GilReleased {
+    PyThreadState* state = PyEval_SaveThread();
+    ~GilReleased() { PyEval_RestoreThread(state); }
+};
+
 template <typename F>
 void call(const char* where, F&& f) {
-    bitnet_status st;
-    Py_BEGIN_ALLOW_THREADS
-    st = f();
-    Py_END_ALLOW_THREADS
+    const bitnet_status st = [&] { GilReleased released; return f(); }();
     if (st == BITNET_OK) return;
     PyObject* e = PyObject_CallFunction(error_class, "is", (int)st, where);
     if (e) {
