@@ -156,8 +156,9 @@ __device__ inline v4i trit_as_v4i(const uint4& u) {
 
 // kR row blocks per wave, kS waves splitting K, kD steps of loads in flight (same scheme as the 2-bit kernel:
 // branch-free masked loop, out-of-range steps / rows / tokens redirected and zeroed)
+// Four waves per SIMD by declaration: with 129 registers the form with three steps in flight lost one of them.
 template <int kR, int kS, int kD>
-__global__ __launch_bounds__(kS * kWave) void linear_gemv16_trit5(
+__global__ __launch_bounds__(kS * kWave, 4) void linear_gemv16_trit5(
         const int8_t* __restrict__ xq, const uint4* __restrict__ packed, const float* __restrict__ gamma, const float* __restrict__ sx,
         void* __restrict__ y, int N32, int K32, uint32_t flags /* tokens, output type */) {
     const int64_t K = K32, N = N32;
@@ -225,7 +226,12 @@ __global__ __launch_bounds__(kS * kWave) void linear_gemv16_trit5(
 
     Stage st[kD];
 #pragma unroll
-    for (int d = 0; d < kD; ++d) load(st[d], d);
+    for (int d = 0; d < kD; ++d) {
+        load(st[d], d);
+        // a step's loads leave before the next one's addresses are worked out (3200 -> 17280, one token: all eighteen addresses first
+        // 6.85 us, so 6.65)
+        __builtin_amdgcn_sched_barrier(0);
+    }
     __syncthreads();                                  // table ready
     int i = 0;
     for (; i + kD < items; i += kD) {
