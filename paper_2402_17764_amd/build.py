@@ -15,7 +15,8 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libbitnet_hip.so")
 
-SOURCES = ["api.hip", "quant_weights.hip", "quant_acts.hip", "linear_ref.hip", "linear_gemv.hip", "linear_skinny.hip", "linear_gemm.hip", "trit5.hip", "static_scratch.hip"]
+SOURCES = ["api.hip", "quant_weights.hip", "quant_acts.hip", "linear_ref.hip", "linear_gemv.hip", "linear_decode.hip", "linear_skinny.hip", "linear_gemm.hip", "trit5.hip", "static_scratch.hip"]
+SOURCES += ["decode%s_%s.hip" % (k, t) for k in ("", "_norm", "_pair", "_norm_pair") for t in ("bf16", "f32")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

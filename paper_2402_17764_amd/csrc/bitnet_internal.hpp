@@ -136,6 +136,11 @@ hipError_t launch_linear_fused_swiglu_out_2bit(const void* x, bool bf16, bool no
                                                int64_t K, void* h, OutType yt, hipStream_t stream,
                                                LaunchPlan* plan = nullptr);
 
+// linear_decode.hip: the three fused launches above for up to four tokens that a workgroup's registers hold.  False (and nothing
+// launched) for what its kernel does not take; pair: N is F, y is h.
+bool launch_decode_fused(bool bf16, bool norm, bool pair, const void* x, const float* gain, float eps, const void* packed, const float* gamma,
+                         int gstride, int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan, hipError_t* status);
+
 // linear_gemm.hip
 bool gemm_supports(int64_t M, int64_t N, int64_t K, const void* xq);
 // workspace (may be null): room for split-K partials; force_splits > 0 picks the number of splits (1, 2, 4, 8) by hand

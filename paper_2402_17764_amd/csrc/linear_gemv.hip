@@ -786,12 +786,16 @@ bool gemv_fused_supports(int64_t M, int64_t N, int64_t K, const void* x) {
 
 hipError_t launch_linear_fused_2bit(const void* x, bool bf16, const void* packed, const float* gamma, int gstride,
                                     int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan) {
+    hipError_t e;
+    if (launch_decode_fused(bf16, false, false, x, nullptr, 0.0f, packed, gamma, gstride, M, N, K, y, yt, stream, plan, &e)) return e;
     return dispatch16_fused(bf16 ? kXFusedBf16 : kXFusedF32, x, packed, gamma, gstride, M, N, K, y, yt, stream, nullptr, 0.0f, plan);
 }
 
 hipError_t launch_rmsnorm_linear_fused_2bit(const void* x, bool bf16, const float* gain, float eps, const void* packed,
                                             const float* gamma, int gstride, int64_t M, int64_t N, int64_t K, void* y,
                                             OutType yt, hipStream_t stream, LaunchPlan* plan) {
+    hipError_t e;
+    if (launch_decode_fused(bf16, true, false, x, gain, eps, packed, gamma, gstride, M, N, K, y, yt, stream, plan, &e)) return e;
     return dispatch16_fused(bf16 ? kXNormBf16 : kXNormF32, x, packed, gamma, gstride, M, N, K, y, yt, stream, gain, eps, plan);
 }
 
@@ -827,18 +831,15 @@ static void launch16_pair(int xmode, const void* x, const void* packed, const fl
 hipError_t launch_linear_fused_swiglu_out_2bit(const void* x, bool bf16, bool norm, const float* gain, float eps,
                                                const void* packed, const float* gamma, int gstride, int64_t M, int64_t F,
                                                int64_t K, void* h, OutType yt, hipStream_t stream, LaunchPlan* plan) {
+    hipError_t e;
+    if (launch_decode_fused(bf16, norm, true, x, gain, eps, packed, gamma, gstride, M, F, K, h, yt, stream, plan, &e)) return e;
     const int xmode = norm ? (bf16 ? kXNormBf16 : kXNormF32) : (bf16 ? kXFusedBf16 : kXFusedF32);
     // From a sweep of fourteen launch shapes on the gate / up matrices of the 3B ... 70B family: without the
     // normalisation, up to 700 pairs one pair per workgroup with K split over four waves; otherwise one wave per pair
     // and no K split, four pairs per workgroup up to 1024 pairs (at most 256 workgroups), eight beyond.
     const int64_t pairs = F / kRowsPerBlock;
     if (!norm && pairs <= 700) launch16_pair<4, 1, 4>(xmode, x, packed, gamma, gstride, M, F, K, h, yt, stream, gain, eps, plan);
-    else if (M <= 2 && pairs <= 512 && K <= 2560) {
-        // up to ten K steps: a wave that walks them alone takes longer over its loads than the norm that more workgroups repeat
-        // (one token through eight decoder layers in a graph, us: 1024 wide 136.4 -> 129.7, 1536 147.3 -> 131.4, 2048 156.1 ->
-        // 149.9, 2560 165.6 -> 161.6; 3200 wide 608 -> 635 for 26)
-        launch16_pair<4, 1, 2>(xmode, x, packed, gamma, gstride, M, F, K, h, yt, stream, gain, eps, plan);
-    } else if (pairs <= 1024) {
+    else if (pairs <= 1024) {
         // depth 5 or 4, whichever pads the K walk less (16 steps at depth 5 walk 20: 7B gate/up with the norm 10.5 -> 9.5 us)
         const int64_t steps = ceil_div(K, 256);
         if (walk_efficiency(steps, 1, 5) >= walk_efficiency(steps, 1, 4))
