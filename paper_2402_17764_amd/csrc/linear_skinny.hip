@@ -30,6 +30,60 @@ namespace bitnet {
 // bare instruction because a fence-carrying barrier makes the compiler wait for every LDS-DMA load.
 // The count holds only while the loop issues no other vector-memory instruction, i.e. while nothing spills:
 // the build checks that every instantiation compiles without scratch memory.
+//
+// The last kD steps stand behind the loop and request nothing that is not there: with the loop's own prefetch a group of two
+// steps asked for four, and the end of the kernel waited for the two that nobody reads (29 tokens, 4096 -> 4096: twice the
+// traffic).  Fewer loads are then in flight behind the copy that a step waits for, last_younger() of them.
+template <int kN>
+__device__ inline void wait_loads() {                  // imm: vmcnt[3:0] | expcnt 7 << 4 | lgkmcnt 15 << 8 | vmcnt[5:4] << 14
+    __builtin_amdgcn_s_waitcnt((kN & 15) | 0x0F70 | ((kN >> 4) << 14));
+}
+// step d of the last kD: what was issued after its copy, in the steps -kLx ... -1 before it -- weights by those of the loop
+// (d < 0), copies by the ones whose target step exists
+constexpr int last_younger(int d, int kR, int kC, int kD, int kLx) {
+    int n = 0;
+    for (int t = d - kLx; t < d; ++t) n += (t < 0 ? kR : 0) + (t > d - kLx && t < kD - kLx ? kC : 0);
+    return n;
+}
+
+// The outputs of a wave's kR row blocks and kMT token tiles: four consecutive ones of a token per lane, in one store where rows and
+// base allow it (flags_vec_store; N is then a multiple of four).  As four stores of two bytes, each behind its own choice of the
+// type, they were most of the 1.2 us between a 29-token launch's last product and its end.
+template <int kMT, int kR>
+__device__ inline void store_tiles(void* y, OutType yt, bool wide, int64_t N, int M, int rbw, const v4i (&acc)[kR][kMT], const float (&gm)[kR],
+                                   const float (&sxm)[kMT]) {
+    const int lane = threadIdx.x & (kWave - 1), r = lane & 15, g = lane >> 4;
+    auto each = [&](auto&& put) {
+#pragma unroll
+        for (int t = 0; t < kMT; ++t) {
+            const int m = 16 * t + r;                                  // MFMA output column = token
+            if (m >= M) continue;
+#pragma unroll
+            for (int a = 0; a < kR; ++a) {
+                const int64_t n0 = (int64_t)(rbw + a) * 16 + 4 * g;
+                if (n0 < N) put((int64_t)m * N + n0, n0, acc[a][t], (gm[a] * sxm[t]) / kQb);
+            }
+        }
+    };
+    // (>> 6 drops the decode factor 64, exactly)
+    if (!wide) each([&](int64_t at, int64_t n0, const v4i& v, float scale) { store_row4(y, yt, at, n0, N, v, scale); });
+    else if (yt == OutType::BF16)
+        each([&](int64_t at, int64_t, const v4i& v, float scale) {
+            const uint32_t a = f32_to_bf16((float)(v.x >> 6) * scale), b = f32_to_bf16((float)(v.y >> 6) * scale);
+            const uint32_t c = f32_to_bf16((float)(v.z >> 6) * scale), d = f32_to_bf16((float)(v.w >> 6) * scale);
+            *reinterpret_cast<uint2*>(static_cast<uint16_t*>(y) + at) = make_uint2(a | b << 16, c | d << 16);
+        });
+    else if (yt == OutType::F32)
+        each([&](int64_t at, int64_t, const v4i& v, float scale) {
+            *reinterpret_cast<float4*>(static_cast<float*>(y) + at) =
+                make_float4((float)(v.x >> 6) * scale, (float)(v.y >> 6) * scale, (float)(v.z >> 6) * scale, (float)(v.w >> 6) * scale);
+        });
+    else
+        each([&](int64_t at, int64_t, const v4i& v, float) {
+            *reinterpret_cast<int4*>(static_cast<int32_t*>(y) + at) = make_int4(v.x >> 6, v.y >> 6, v.z >> 6, v.w >> 6);
+        });
+}
+
 template <int kMT, int kR, int kW, int kS, int kD, int kLx>
 __global__ __launch_bounds__(kS * kW * kWave) void linear_skinny_2bit(
         // 14 dwords (product_flags says why); blockIdx.z selects a tile of 16 * kMT tokens, blockIdx.y a run of K steps
@@ -44,6 +98,7 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_skinny_2bit(
     const int RB = (int)((N + kRowsPerBlock - 1) / kRowsPerBlock), M_all = flags_number(flags), gstride = flags_gstride(flags);
     const int spg = (steps_per_split + kS - 1) / kS;
     const OutType yt = flags_out_type(flags);
+    const bool wide = flags_vec_store(flags);
     constexpr int kRing = kLx + 1;                     // LDS stages per group
     constexpr int kStageBytes = kMT * 16 * 256;        // tokens staged per step x 256 columns
     constexpr int kGroupBytes = kRing * kStageBytes;
@@ -171,17 +226,17 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_skinny_2bit(
 
     // Steps are walked in groups of kD so that the register stages are indexed statically; the count is
     // padded to a whole group with steps whose weights are masked to zero, so the body has no guards.
-    const int padded = (spg + kD - 1) / kD * kD;                      // >= kD: the loop runs at least once
+    static_assert(kD == 2, "the last kD steps are written out");
+    const int padded = (spg + kD - 1) / kD * kD;                      // >= kD
     int i0 = 0;
-    do {
+    for (; i0 + kD < padded; i0 += kD) {
 #pragma unroll
         for (int d = 0; d < kD; ++d) {
             const int i = i0 + d;
             // loads issued after this wave's copy for step i: kR weight loads, then for each of the next
             // kLx - 1 steps kC copies and kR weight loads
-            // (imm: vmcnt[3:0] | expcnt 7 << 4 | lgkmcnt 15 << 8 | vmcnt[5:4] << 14)
             issue_fence();
-            __builtin_amdgcn_s_waitcnt((kYounger & 15) | 0x0F70 | ((kYounger >> 4) << 14));
+            wait_loads<kYounger>();
             __builtin_amdgcn_s_barrier();                              // stage i is complete, stage i - 1 is free
             issue_fence();
             copy_x(i + kLx, (i + kLx) % kRing);
@@ -189,13 +244,23 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_skinny_2bit(
             compute(wst[d], i, i % kRing);
             load_w(wst[d], i + kD);                                    // after the last use: reloaded in place
         }
-        i0 += kD;
-    } while (i0 < padded);
+    }
+    issue_fence();
+    wait_loads<last_younger(0, kR, kC, kD, kLx)>();
+    __builtin_amdgcn_s_barrier();
+    issue_fence();
+    if constexpr (kLx < kD) copy_x(i0 + kLx, (i0 + kLx) % kRing);
+    issue_fence();
+    compute(wst[0], i0, i0 % kRing);
+    issue_fence();
+    wait_loads<last_younger(1, kR, kC, kD, kLx)>();
+    __builtin_amdgcn_s_barrier();
+    issue_fence();
+    compute(wst[1], i0 + 1, (i0 + 1) % kRing);
     issue_fence();
 
     if constexpr (kS > 1) {
         // fold the K groups: groups 1 ... kS - 1 park their accumulators in LDS, group 0 adds them in order
-        __builtin_amdgcn_s_waitcnt(0);                                 // copies past the end have landed
         __syncthreads();
         v4i* fold = reinterpret_cast<v4i*>(lds);
         if (ks > 0) {
@@ -215,17 +280,7 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_skinny_2bit(
                     acc[a][t] += fold[(((q * kW + wv) * kR + a) * kMT + t) * kWave + lane];
     }
 
-#pragma unroll
-    for (int t = 0; t < kMT; ++t) {
-        const int m = 16 * t + r;                                      // MFMA output column = token
-        if (m >= M) continue;
-#pragma unroll
-        for (int a = 0; a < kR; ++a) {
-            const float scale = (gm[a] * sxm[t]) / kQb;
-            const int64_t n0 = (int64_t)(rbw + a) * 16 + 4 * g;
-            if (n0 < N) store_row4(y, yt, (int64_t)m * N + n0, n0, N, acc[a][t], scale);
-        }
-    }
+    store_tiles<kMT, kR>(y, yt, wide, N, M, rbw, acc, gm, sxm);
 #endif
 }
 
@@ -255,12 +310,13 @@ __global__ __launch_bounds__((kS * kW + 1) * kWave) void linear_skinny_ws_2bit(
     const int RB = (int)((N + kRowsPerBlock - 1) / kRowsPerBlock), M_all = flags_number(flags), gstride = flags_gstride(flags);
     const int spg = (steps_per_split + kS - 1) / kS;
     const OutType yt = flags_out_type(flags);
+    const bool wide = flags_vec_store(flags);
     constexpr int kRing = kLx + 1;                     // LDS stages per group
     constexpr int kStageBytes = kMT * 16 * 256;        // tokens staged per step x 256 columns
     constexpr int kGroupBytes = kRing * kStageBytes;
     constexpr int kCopies = kMT * 4;                   // 1 KiB wave-loads per stage (4 token rows each)
     constexpr int kYounger = (kLx - 1) * kS * kCopies; // copies issued after those of the step being awaited
-    static_assert(kLx >= 1 && kYounger < 64, "vmcnt is six bits");
+    static_assert(kLx >= 1 && kLx <= kD && kYounger < 64, "vmcnt is six bits");
     static_assert((kS - 1) * kW * kR * kMT * 1024 <= kS * kGroupBytes, "the fold reuses the activation ring");
     char* lds = reinterpret_cast<char*>(smem);
 
@@ -314,13 +370,24 @@ __global__ __launch_bounds__((kS * kW + 1) * kWave) void linear_skinny_ws_2bit(
             copy_x(p, p % kRing);
             issue_fence();                                             // step by step: the counted wait relies on it
         }
-        for (int i = 0; i < padded; ++i) {
+        for (int i = 0; i + kLx < padded; ++i) {
             issue_fence();
-            __builtin_amdgcn_s_waitcnt((kYounger & 15) | 0x0F70 | ((kYounger >> 4) << 14));   // step i has landed
+            wait_loads<kYounger>();                                    // step i has landed
             __builtin_amdgcn_s_barrier();                              // publish it; stage i - 1 is free
             issue_fence();
             copy_x(i + kLx, (i + kLx) % kRing);
         }
+        // the last kLx steps: nothing further to request
+        static_assert(kLx == 2 || kLx == 3, "the last steps are written out");
+        issue_fence();
+        if constexpr (kLx == 3) {
+            wait_loads<2 * kS * kCopies>();
+            __builtin_amdgcn_s_barrier();
+        }
+        wait_loads<kS * kCopies>();
+        __builtin_amdgcn_s_barrier();
+        wait_loads<0>();
+        __builtin_amdgcn_s_barrier();
         issue_fence();
     } else {
         // ---- compute waves
@@ -378,12 +445,19 @@ __global__ __launch_bounds__((kS * kW + 1) * kWave) void linear_skinny_ws_2bit(
         uint4 wst[kD][kR];
 #pragma unroll
         for (int d = 0; d < kD; ++d) load_w(wst[d], d);
+        auto meet = [] {                               // stage i is complete, and this wave's reads of stage i - 1 stay ahead
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0xF);
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0xF);
+            asm volatile("" ::: "memory");
+        };
         int i0 = 0;
         do {
 #pragma unroll
             for (int d = 0; d < kD; ++d) {
                 const int i = i0 + d;
-                __builtin_amdgcn_s_barrier();                          // stage i is complete
+                meet();
                 compute(wst[d], i, i % kRing);
                 load_w(wst[d], i + kD);                                // after the last use: reloaded in place
             }
@@ -392,7 +466,6 @@ __global__ __launch_bounds__((kS * kW + 1) * kWave) void linear_skinny_ws_2bit(
     }
 
     // fold the K groups (every wave meets the barriers; the loader has nothing to add)
-    __builtin_amdgcn_s_waitcnt(0);                                     // copies past the end have landed
     __syncthreads();
     if constexpr (kS > 1) {
         v4i* fold = reinterpret_cast<v4i*>(lds);
@@ -415,17 +488,7 @@ __global__ __launch_bounds__((kS * kW + 1) * kWave) void linear_skinny_ws_2bit(
         if (wave >= kS * kW) return;
     }
 
-#pragma unroll
-    for (int t = 0; t < kMT; ++t) {
-        const int m = 16 * t + r;                                      // MFMA output column = token
-        if (m >= M) continue;
-#pragma unroll
-        for (int a = 0; a < kR; ++a) {
-            const float scale = (gm[a] * sxm[t]) / kQb;
-            const int64_t n0 = (int64_t)(rbw + a) * 16 + 4 * g;
-            if (n0 < N) store_row4(y, yt, (int64_t)m * N + n0, n0, N, acc[a][t], scale);
-        }
-    }
+    store_tiles<kMT, kR>(y, yt, wide, N, M, rbw, acc, gm, sxm);
 #endif
 }
 
@@ -498,6 +561,11 @@ bool gemv_supports(int64_t M, int64_t N, int64_t K, const void* xq) {
     return skinny_shape(M, ceil_div(N, kRowsPerBlock), &kmt, &rpw);
 }
 
+// four consecutive outputs from a multiple of four on are one aligned store
+static bool wide_rows(const void* y, int64_t N, OutType yt) {
+    return N % 4 == 0 && reinterpret_cast<uintptr_t>(y) % (yt == OutType::BF16 ? 8 : 16) == 0;
+}
+
 template <int kMT, int kR, int kW, int kS, int kD, int kLx>
 static hipError_t launch_skinny(const int8_t* xq, const float* sx, const void* packed, const float* gamma, int gstride,
                                 int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream,
@@ -523,7 +591,7 @@ static hipError_t launch_skinny(const int8_t* xq, const float* sx, const void* p
         return hipSuccess;
     }
     hipLaunchKernelGGL(kern, grid, dim3(kS * kW * kWave), lds, stream, xq, static_cast<const uint4*>(packed), gamma, sx,
-                       split ? workspace : y, (int)N, (int)K, product_flags(gstride, split ? OutType::I32 : yt) | (uint32_t)M << 4, sps);
+                       split ? workspace : y, (int)N, (int)K, product_flags(gstride, split ? OutType::I32 : yt, wide_rows(split ? workspace : y, N, split ? OutType::I32 : yt)) | (uint32_t)M << 4, sps);
     if (split)
         return launch_splitk_reduce(static_cast<const int32_t*>(workspace), splits, sx, gamma, gstride, 0, M, N, y, yt, stream);
     return hipGetLastError();
@@ -554,7 +622,7 @@ static hipError_t launch_skinny_ws(const int8_t* xq, const float* sx, const void
         return hipSuccess;
     }
     hipLaunchKernelGGL(kern, grid, dim3((kS * kW + 1) * kWave), lds, stream, xq, static_cast<const uint4*>(packed), gamma, sx,
-                       split ? workspace : y, (int)N, (int)K, product_flags(gstride, split ? OutType::I32 : yt) | (uint32_t)M << 4, sps);
+                       split ? workspace : y, (int)N, (int)K, product_flags(gstride, split ? OutType::I32 : yt, wide_rows(split ? workspace : y, N, split ? OutType::I32 : yt)) | (uint32_t)M << 4, sps);
     if (split)
         return launch_splitk_reduce(static_cast<const int32_t*>(workspace), splits, sx, gamma, gstride, 0, M, N, y, yt, stream);
     return hipGetLastError();
