@@ -278,6 +278,222 @@ __global__ __launch_bounds__(kS * kWave, 4) void linear_gemv16_trit5(
 }
 
 // ---------------------------------------------------------------------------------------------------
+// the same product with the digits left to the matrix pipe, M <= 16, x_q in LDS
+// ---------------------------------------------------------------------------------------------------
+// The kernel above is bound by its table: sixteen look-ups of eight bytes per 80 weights and lane, at random addresses of one 2 KB
+// table, 15 clocks of the CU's LDS each (27648 x 5120 at four tokens: 11.2 us for 28 MB, here 9.9; sixteen 18.4, here
+// 12.7; what bounds it now is the arithmetic, 74 vector instructions a chunk and lane).  Here no digit is ever formed.  With
+// f_d = floor(byte / 3^d) a digit is t_d = f_d - 3 f_(d+1), so
+//     sum_d x_d t_d  =  sum_(d = 0..4) x_d f_d  -  3 sum_(d = 1..4) x_(d-1) f_d,
+// and the quotients are small enough for int8 operands: f_0 is the byte itself (taken as byte - 128), f_1 <= 80, f_2 <= 26, f_3 <= 8,
+// f_4 <= 2, each a multiplication away for two bytes at once in the 16-bit halves of a word:
+//     f_1 = (85 b + 83) >> 8,   2 f_2 = (57 b >> 8) & ~1,   2 f_3 = (19 b >> 8) & ~1,   8 f_4 = ((25 b + 46) >> 8) & ~7
+// (exact for the 243 byte values; the factors are shifted out of sums of their own): 18 vector instructions for the twenty weights
+// of a word.  Both sums come out of the same MFMA: eight tokens take columns 0 ... 7, and columns 8 ... 15 hold the same tokens'
+// activations one digit further back.  sum_d x_d (t_d - 1) is what a row needs; the ones and the 128s are two sums over a token,
+// added up once when its x_q is staged.
+// x_q is staged with the columns of a quad ordered by digit, [d][p]: 16 bytes are one lane's operand of f_d.
+constexpr int kTritQuadBytes = 80;
+constexpr int kTritHeader = 128;                     // the tokens' corrections, 16 ints; bytes in front of a row that idle columns may read
+
+__host__ __device__ constexpr int trit_row_bytes(int steps) { return steps * 4 * kTritQuadBytes + 16; }      // + 16: rows start on other banks
+
+struct TritOps { v4i f[5]; };
+__device__ inline uint32_t high_bytes(uint32_t even, uint32_t odd) { return __builtin_amdgcn_perm(odd, even, 0x07030501u); }
+__device__ inline TritOps trit_quotients(const v4i& w) {
+    TritOps o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const uint32_t b = (uint32_t)w[j], e = b & 0x00FF00FFu, d = __builtin_amdgcn_perm(0u, b, 0x0c030c01u);     // bytes 0, 2 and 1, 3
+        o.f[0][j] = (int)(b ^ 0x80808080u);
+        o.f[1][j] = (int)high_bytes(e * 85u + 0x00530053u, d * 85u + 0x00530053u);
+        o.f[2][j] = (int)(high_bytes(e * 57u, d * 57u) & 0xFEFEFEFEu);
+        o.f[3][j] = (int)(high_bytes(e * 19u, d * 19u) & 0xFEFEFEFEu);
+        o.f[4][j] = (int)(high_bytes(e * 25u + 0x002E002Eu, d * 25u + 0x002E002Eu) & 0xF8F8F8F8u);
+    }
+    return o;
+}
+
+// a row block per wave, kS waves splitting K, kW row slots (kS * kW waves), kD steps of weights in flight, kH groups of eight tokens
+template <int kS, int kW, int kD, int kH>
+__global__ __launch_bounds__(kS * kW * kWave) void linear_quotients_trit5(
+        const int8_t* __restrict__ xq, const uint4* __restrict__ packed, const float* __restrict__ gamma, const float* __restrict__ sx,
+        void* __restrict__ y, int N32, int K32, uint32_t flags /* tokens, output type, wide stores */) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int kThreads = kS * kW * kWave, kRsrc = 0x00020000;
+    extern __shared__ uint4 smem[];
+    char* const lds = reinterpret_cast<char*>(smem);
+    int* const corr = reinterpret_cast<int*>(lds);
+    char* const xl = lds + kTritHeader;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);          // scalar: a wave's steps, row blocks and addresses
+    const int r = lane & 15, g = lane >> 4, ws = wave % kS, ww = wave / kS;
+    const uint32_t K = (uint32_t)K32, N = (uint32_t)N32;
+    const int M = flags_number(flags), steps = (int)((K + kTritStep - 1) / kTritStep), quads = 4 * steps;
+    const uint32_t RB = (N + 15) / 16, rb = blockIdx.x * kW + ww;
+    const OutType yt = flags_out_type(flags);
+    const int rowbytes = trit_row_bytes(steps);
+
+    // x_q, a quad of 80 columns per thread and round; past the row reads as zero (K is a multiple of 16)
+    auto load_quad = [&](int q, v4i (&v)[5]) {
+        const int m = q / quads, c = (q - m * quads) * kTritCols;
+        const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(xq), 0, (int)(M * K), kRsrc);
+#pragma unroll
+        for (int j = 0; j < 5; ++j) {
+            const bool in = q < M * quads && (uint32_t)(c + 16 * j) < K;
+            v[j] = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(xr, in ? (int)(m * K + c + 16 * j) : -16, 0, 0));
+        }
+    };
+    v4i xv[5];
+    load_quad(tid, xv);
+    if (tid < 16) corr[tid] = 0;
+    __syncthreads();                                                    // (all waves' x_q loads go ahead of the weights, too)
+    // the weights: a chunk per descriptor; what is not the wave's own lies past its end
+    const uint64_t step_bytes = (uint64_t)RB * 1024;
+    const char* wbase = reinterpret_cast<const char*>(packed) + step_bytes * (uint32_t)ws + (uint64_t)rb * 1024;
+    int next = ws;
+    auto load = [&](v4i& w) {
+        const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(wbase), 0, next < steps && rb < RB ? 1024 : 0, kRsrc);
+        w = __builtin_bit_cast(v4i, __builtin_amdgcn_raw_buffer_load_b128(wr, lane * 16, 0, 2 /* nt: read once */));
+        wbase += step_bytes * kS;
+        next += kS;
+    };
+    v4i st[kD];
+#pragma unroll
+    for (int d = 0; d < kD; ++d) load(st[d]);
+    // the output scales of the lanes that store (token r, and r + 8)
+    const float gm = gamma[0];
+    float sc[kH];
+#pragma unroll
+    for (int h = 0; h < kH; ++h) sc[h] = yt == OutType::I32 ? 0.0f : sx[min(8 * h + (r & 7), M - 1)];
+    __builtin_amdgcn_sched_barrier(0);
+
+    for (int q = tid;;) {
+        if (q < M * quads) {
+            const int m = q / quads;
+            char* const out = xl + m * rowbytes + (q - m * quads) * kTritQuadBytes;
+            v4i o[4];
+            int all = 0, first = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {                               // bytes [p][d] of 4 x 4 columns -> [d][p]
+                const uint32_t a = (uint32_t)xv[j].x, b = (uint32_t)xv[j].y, c = (uint32_t)xv[j].z, d = (uint32_t)xv[j].w;
+                const uint32_t t0 = __builtin_amdgcn_perm(b, a, 0x05010400u), t1 = __builtin_amdgcn_perm(b, a, 0x07030602u);
+                const uint32_t t2 = __builtin_amdgcn_perm(d, c, 0x05010400u), t3 = __builtin_amdgcn_perm(d, c, 0x07030602u);
+                o[0][j] = (int)__builtin_amdgcn_perm(t2, t0, 0x05040100u);
+                o[1][j] = (int)__builtin_amdgcn_perm(t2, t0, 0x07060302u);
+                o[2][j] = (int)__builtin_amdgcn_perm(t3, t1, 0x05040100u);
+                o[3][j] = (int)__builtin_amdgcn_perm(t3, t1, 0x07060302u);
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                first = __builtin_amdgcn_sdot4(o[0][j], 0x01010101, first, false);
+#pragma unroll
+                for (int d = 1; d < 4; ++d) all = __builtin_amdgcn_sdot4(o[d][j], 0x01010101, all, false);
+                all = __builtin_amdgcn_sdot4(xv[4][j], 0x01010101, all, false);
+            }
+#pragma unroll
+            for (int d = 0; d < 4; ++d) *reinterpret_cast<v4i*>(out + 16 * d) = o[d];
+            *reinterpret_cast<v4i*>(out + 64) = xv[4];
+            int part = 127 * first - all;                               // 128 sum x_0 - sum x
+            part += (int)dpp_u32<0xB1>((uint32_t)part);                 // four lanes have one step of one token
+            part += (int)dpp_u32<0x4E>((uint32_t)part);
+            if ((tid & 3) == 0) atomicAdd(&corr[m], part);
+        }
+        q += kThreads;
+        if (q - tid >= M * quads) break;                                // uniform
+        load_quad(q, xv);
+    }
+    __syncthreads();
+
+    v4i acc[kH][4];                                                     // by quotient: f_0, f_1, f_2 and f_3, f_4
+#pragma unroll
+    for (int h = 0; h < kH; ++h)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) acc[h][k] = (v4i){0, 0, 0, 0};
+    const char* xr[kH];
+#pragma unroll
+    for (int h = 0; h < kH; ++h) xr[h] = xl + min(8 * h + (r & 7), M - 1) * rowbytes + g * kTritQuadBytes - (r & 8 ? 16 : 0);
+    auto mac = [&](const v4i& w, int step) {
+        if (step >= steps) return;                                      // uniform
+        const int off = step * 4 * kTritQuadBytes;
+        const TritOps o = trit_quotients(w);
+#pragma unroll
+        for (int h = 0; h < kH; ++h)
+#pragma unroll
+            for (int d = 0; d < 5; ++d) {
+                const v4i x = *reinterpret_cast<const v4i*>(xr[h] + off + 16 * d);
+                const int k = d < 3 ? d : d - 1;
+                acc[h][k] = __builtin_amdgcn_mfma_i32_16x16x64_i8(o.f[d], x, acc[h][k], 0, 0, 0);
+            }
+    };
+    const int items = ((steps + kS - 1) / kS + kD - 1) / kD * kD;
+    int i = 0;
+    for (; i + kD < items; i += kD) {
+#pragma unroll
+        for (int d = 0; d < kD; ++d) {
+            mac(st[d], ws + (i + d) * kS);
+            __builtin_amdgcn_sched_barrier(0);
+            load(st[d]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+#pragma unroll
+    for (int d = 0; d < kD; ++d) mac(st[d], ws + (i + d) * kS);
+
+    // lanes r < 8 hold their token's first sum, lanes r + 8 the second
+    v4i v[kH];
+#pragma unroll
+    for (int h = 0; h < kH; ++h)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t f = (uint32_t)acc[h][1][e] + (uint32_t)(acc[h][2][e] >> 1) + (uint32_t)(acc[h][3][e] >> 3);
+            v[h][e] = (int)((uint32_t)acc[h][0][e] + f - 3u * dpp_u32<0x128>(f));              // row_ror:8; modulo 2^32, as the result fits
+        }
+    if (kS > 1) {
+        __syncthreads();                                                // every wave is done with x_q
+        v4i* const fold = reinterpret_cast<v4i*>(xl);
+        if (ws > 0) {
+#pragma unroll
+            for (int h = 0; h < kH; ++h) fold[((ww * (kS - 1) + ws - 1) * kH + h) * kWave + lane] = v[h];
+        }
+        __syncthreads();
+        if (ws > 0) return;
+#pragma unroll
+        for (int w = 0; w < kS - 1; ++w)
+#pragma unroll
+            for (int h = 0; h < kH; ++h) v[h] += fold[((ww * (kS - 1) + w) * kH + h) * kWave + lane];
+    }
+    const uint32_t n0 = rb * 16 + 4 * g;
+    if (r >= 8 || n0 >= N) return;
+#pragma unroll
+    for (int h = 0; h < kH; ++h) {
+        const int m = 8 * h + r;
+        if (m >= M) continue;
+        const int c = corr[m], t[4] = {v[h].x + c, v[h].y + c, v[h].z + c, v[h].w + c};
+        const float scale = (gm * sc[h]) / kQb;
+        const int64_t at = (int64_t)m * N + n0;
+        if (flags_vec_store(flags)) {                                   // rows and base allow four outputs in one store
+            if (yt == OutType::BF16)
+                *reinterpret_cast<uint2*>(static_cast<uint16_t*>(y) + at) =
+                    make_uint2(f32_to_bf16((float)t[0] * scale) | (uint32_t)f32_to_bf16((float)t[1] * scale) << 16,
+                               f32_to_bf16((float)t[2] * scale) | (uint32_t)f32_to_bf16((float)t[3] * scale) << 16);
+            else if (yt == OutType::F32)
+                *reinterpret_cast<float4*>(static_cast<float*>(y) + at) = make_float4((float)t[0] * scale, (float)t[1] * scale, (float)t[2] * scale, (float)t[3] * scale);
+            else *reinterpret_cast<int4*>(static_cast<int32_t*>(y) + at) = make_int4(t[0], t[1], t[2], t[3]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (n0 + e >= N) continue;
+                if (yt == OutType::I32) static_cast<int32_t*>(y)[at + e] = t[e];
+                else if (yt == OutType::F32) static_cast<float*>(y)[at + e] = (float)t[e] * scale;
+                else static_cast<uint16_t*>(y)[at + e] = f32_to_bf16((float)t[e] * scale);
+            }
+        }
+    }
+#endif
+}
+
+// ---------------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------------
 hipError_t launch_pack_trit5(const void* W, bool bf16, int64_t N, int64_t K, const float* gamma, void* packed,
@@ -446,10 +662,59 @@ static void launch_trit5(const int8_t* xq, const float* sx, const void* packed, 
                        static_cast<const uint4*>(packed), gamma, sx, y, (int)N, (int)K, product_flags(0, yt) | (uint32_t)M << 4);
 }
 
+// Where the quotients are the faster form, and in which launch shape (128 shapes of 38 ... 1400 row blocks, 3 ... 25 steps, 1 ... 16
+// tokens, and larger ones; us, table / quotients): narrow layers with a long K (600 x 8000, one token 4.65 / 4.40, four on 2048 x
+// 8000 5.02 / 4.90, but 2048 x 2560 3.02 / 3.43: staging x_q costs more than the look-ups), and from 512 row blocks on all but short
+// walks of few tokens (9600 x 2560 4.29 / 4.60, 9600 x 4160 6.10 / 5.56, four on 16384 x 8000 13.1 / 9.6, sixteen 22.1 / 13.2, on
+// 57344 x 8192 47.8 / 34.9).  x_q has to fit the LDS.
+struct QuotientForm { int s, w, d; };                  // kS, kW, kD; none: s = 0
+static QuotientForm pick_quotients(int64_t M, int64_t RB, int64_t steps) {
+    if (RB <= 256) return M <= 8 && steps >= 20 ? QuotientForm{8, 1, 2} : QuotientForm{0, 0, 0};
+    if (RB <= 512) {
+        if (M <= 4) return steps >= 20 ? QuotientForm{8, 1, 2} : QuotientForm{0, 0, 0};
+        return steps >= (M > 8 ? 8 : 10) ? QuotientForm{4, 2, 2} : QuotientForm{0, 0, 0};
+    }
+    if (RB >= (M <= 4 ? 3072 : M <= 8 ? 2048 : 1025)) return {1, 8, 4};
+    if (M > 4 || RB >= 1536 || steps <= 4) return {2, 4, 2};
+    if (steps < 10 && RB <= 1024) return {0, 0, 0};
+    return M == 1 || steps < 20 ? QuotientForm{4, 1, 2} : QuotientForm{4, 2, 2};
+}
+constexpr int64_t kTritMaxLds = 160 * 1024;
+
+template <int kS, int kW, int kD>
+static bool launch_quotients(const int8_t* xq, const float* sx, const void* packed, const float* gamma, int64_t M, int64_t N,
+                             int64_t K, void* y, OutType yt, hipStream_t stream, hipError_t* status) {
+    const int64_t rows = M * trit_row_bytes((int)ceil_div(K, kTritStep)), fold = (int64_t)(kS - 1) * kW * (M <= 8 ? 1 : 2) * 1024;
+    const int64_t lds = kTritHeader + (rows > fold ? rows : fold), wgs = ceil_div(ceil_div(N, kRowsPerBlock), kW);
+    if (lds > kTritMaxLds || wgs * kS * kW * kWave >= kMaxGridThreads) return false;
+    const bool wide = N % 4 == 0 && reinterpret_cast<uintptr_t>(y) % (yt == OutType::BF16 ? 8 : 16) == 0;
+    auto go = [&](auto* kernel, RaisedFlags& raised) -> hipError_t {
+        if (lds > 65536) {
+            const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(kernel), (int)kTritMaxLds, raised);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(kS * kW * kWave), lds, stream, xq, static_cast<const uint4*>(packed), gamma, sx, y,
+                           (int)N, (int)K, product_flags(0, yt, wide) | (uint32_t)M << 4);
+        return hipGetLastError();
+    };
+    static RaisedFlags one = {}, two = {};
+    *status = M <= 8 ? go(linear_quotients_trit5<kS, kW, kD, 1>, one) : go(linear_quotients_trit5<kS, kW, kD, 2>, two);
+    return true;
+}
+
 hipError_t launch_linear_gemv_trit5(const int8_t* xq, const float* sx, const void* packed, const float* gamma,
                                     int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream) {
     const int64_t RB = ceil_div(N, kRowsPerBlock);
     const int64_t steps = ceil_div(K, kTritStep);
+    const QuotientForm f = pick_quotients(M, RB, steps);
+    hipError_t e = hipSuccess;
+#define FORM(S_, W_, D_) if (f.s == S_ && f.w == W_ && f.d == D_ && launch_quotients<S_, W_, D_>(xq, sx, packed, gamma, M, N, K, y, yt, stream, &e)) return e
+    FORM(8, 1, 2);
+    FORM(4, 1, 2);
+    FORM(4, 2, 2);
+    FORM(2, 4, 2);
+    FORM(1, 8, 4);
+#undef FORM
     // the share of a wave's padded K walk (a multiple of the prefetch depth) that is real steps
     auto walk = [&](int ks, int kd) { return (double)steps / (double)(ceil_div(ceil_div(steps, (int64_t)ks), (int64_t)kd) * kd * ks); };
     // Measured on MI355X, M = 1, fifteen forms per shape: 3200 -> 3200 4.0 -> 3.5 us and 3200 -> 17280 8.0 -> 6.6 us with
