@@ -97,11 +97,7 @@ bitnet_status bitnet_quantize_weights(const void* W, bitnet_dtype w_dtype, int64
     bitnet_quantize_weights_workspace(N, K, &need);
     if (workspace_bytes < need) return BITNET_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    if (f == BITNET_PACK_2BIT)
-        return from_hip(bitnet::launch_quantize_weights_2bit(W, w_dtype == BITNET_BF16, N, K, packed, gamma, workspace, s));
-    hipError_t e = bitnet::launch_absmean_gamma(W, w_dtype == BITNET_BF16, N, K, gamma, workspace, s);
-    if (e != hipSuccess) return BITNET_ERR_HIP;
-    return from_hip(bitnet::launch_pack_trit5(W, w_dtype == BITNET_BF16, N, K, gamma, packed, s));
+    return from_hip(bitnet::launch_quantize_weights(W, w_dtype == BITNET_BF16, N, K, f == BITNET_PACK_TRIT5, packed, gamma, workspace, s));
 }
 
 bitnet_status bitnet_abs_sum(const void* W, bitnet_dtype w_dtype, int64_t N, int64_t K, double* sum, void* workspace,
@@ -128,11 +124,7 @@ bitnet_status bitnet_quantize_weights_sharded(const void* W, bitnet_dtype w_dtyp
     if (!aligned(W, dtype_size(w_dtype)) || !aligned(packed, 16) || !aligned(gamma, 4) || !aligned(sums, 8))
         return BITNET_ERR_ALIGN;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    const bool bf16 = w_dtype == BITNET_BF16;
-    if (f == BITNET_PACK_2BIT)
-        return from_hip(bitnet::launch_pack_2bit_with_sums(W, bf16, N, K, sums, nsums, total_rows * K, packed, gamma, s));
-    if (bitnet::launch_gamma_from_sums(sums, nsums, total_rows * K, gamma, s) != hipSuccess) return BITNET_ERR_HIP;
-    return from_hip(bitnet::launch_pack_trit5(W, bf16, N, K, gamma, packed, s));
+    return from_hip(bitnet::launch_pack_with_sums(W, w_dtype == BITNET_BF16, N, K, f == BITNET_PACK_TRIT5, sums, nsums, total_rows * K, packed, gamma, s));
 }
 
 bitnet_status bitnet_quantize_acts(const void* x, bitnet_dtype x_dtype, int64_t M, int64_t K, int8_t* xq,

@@ -13,6 +13,7 @@ constexpr float kQb = 127.0f;          // Q_b for 8-bit symmetric activations (S
 
 constexpr int kRowsPerBlock = 16;      // rows of one packed tile (= MFMA 16x16x64 operand rows)
 constexpr int kColsPerQuad = 64;       // columns held by one 16-byte quad of the 2-bit format
+constexpr int kTritStep = 320;         // columns of one K step of the 5-trit format (4 quads of 80)
 
 __host__ __device__ inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 

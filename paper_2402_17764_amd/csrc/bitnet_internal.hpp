@@ -46,11 +46,9 @@ constexpr int flags_number(uint32_t f) { return (int)(f >> 4); }
 
 // quant_weights.hip
 int quant_weights_num_partials();
-// nout: how many consecutive floats receive gamma (one per 16-row block of a segment; 1 for a whole tensor)
-hipError_t launch_absmean_gamma(const void* W, bool bf16, int64_t N, int64_t K, float* gamma, void* workspace,
-                                hipStream_t stream, int64_t nout = 1);
-hipError_t launch_quantize_weights_2bit(const void* W, bool bf16, int64_t N, int64_t K, void* packed,
-                                        float* gamma, void* workspace, hipStream_t stream);
+// Eq. (1)-(3) + packing of a whole matrix, in either format
+hipError_t launch_quantize_weights(const void* W, bool bf16, int64_t N, int64_t K, bool trit5, void* packed, float* gamma, void* workspace,
+                                   hipStream_t stream);
 // consecutive row segments with a gamma each; gamma_rb: one per 16-row block of the whole matrix
 hipError_t launch_quantize_weights_2bit_segmented(const void* W, bool bf16, int64_t N, int64_t K, const int64_t* seg_rows, int nseg,
                                                   void* packed, float* gamma_rb, void* workspace, hipStream_t stream);
@@ -59,11 +57,9 @@ hipError_t launch_quantize_weights_2bit_segmented(const void* W, bool bf16, int6
 hipError_t launch_abs_sum(const void* W, bool bf16, int64_t N, int64_t K, double* sum, void* workspace, hipStream_t stream);
 // how many (hi, lo) pairs the packing pass can fold (one per thread of a workgroup)
 int quant_weights_max_sums();
-// gamma = fp32((sum of the nsums pairs) / total_count), Eq. (3) over all shards
-hipError_t launch_gamma_from_sums(const double* sums, int nsums, int64_t total_count, float* gamma, hipStream_t stream);
-// Eq. (1)-(2) + packing of these rows with that gamma (written to *gamma as well)
-hipError_t launch_pack_2bit_with_sums(const void* W, bool bf16, int64_t N, int64_t K, const double* sums, int nsums,
-                                      int64_t total_count, void* packed, float* gamma, hipStream_t stream);
+// Eq. (1)-(3) + packing of these rows with gamma = fp32((sum of the nsums pairs) / total_count), written to *gamma as well
+hipError_t launch_pack_with_sums(const void* W, bool bf16, int64_t N, int64_t K, bool trit5, const double* sums, int nsums,
+                                 int64_t total_count, void* packed, float* gamma, hipStream_t stream);
 
 // quant_acts.hip
 hipError_t launch_quantize_acts(const void* x, bool bf16, int64_t M, int64_t K, int8_t* xq, float* sx,
@@ -162,8 +158,6 @@ hipError_t launch_splitk_reduce(const int32_t* part, int splits, const float* sx
                                 int prefill_assoc, int64_t M, int64_t N, void* y, OutType yt, hipStream_t stream);
 
 // trit5.hip
-hipError_t launch_pack_trit5(const void* W, bool bf16, int64_t N, int64_t K, const float* gamma, void* packed,
-                             hipStream_t stream);
 hipError_t launch_unpack_trit5(const void* packed, int64_t N, int64_t K, int8_t* codes, hipStream_t stream);
 hipError_t launch_linear_reference_trit5(const int8_t* xq, const float* sx, const void* packed, const float* gamma,
                                          int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream);

@@ -2,8 +2,7 @@
 //
 //   pass 1  abs_sum_partials : grid-stride |W| sum, double-double per thread, fixed-shape tree
 //                              inside the block, one (hi, lo) pair per block into the workspace
-//   pass 2  finish_gamma     : one block folds the partials in a fixed order, gamma = fp32(S / (N K)); the 2-bit
-//                              packing does this at the top of pass 3 instead (one launch and 4.5 us less)
+//   pass 2                   : gamma = fp32(S / (N K)); done at the top of pass 3 (one launch and 4.5 us less)
 //   pass 3  ternarize_pack   : re-reads W from its end (what pass 1 read last is still in the memory-side
 //                              cache), takes the decision of Eq. (1)-(2) in fp32 and writes the packed
 //                              layout one 1 KiB (row block, K step) chunk per workgroup pass
@@ -184,19 +183,8 @@ __device__ inline dd fold_partials(const double* __restrict__ partials, int npar
     return dd{sh_hi[0], sh_lo[0]};
 }
 
-// gamma[0 .. nout-1] all receive the value (nout > 1: one copy per 16-row block of a segment)
-__global__ __launch_bounds__(kFinishThreads) void finish_gamma(const double* __restrict__ partials, int nparts,
-                                                            int64_t count, float* __restrict__ gamma, int64_t nout) {
-    __shared__ double sh_hi[kFinishThreads];
-    __shared__ double sh_lo[kFinishThreads];
-    const dd t = fold_partials(partials, nparts, sh_hi, sh_lo);
-    const double S = t.hi + t.lo;
-    const float g = (float)(S / (double)count);     // Eq. (3); fp64 IEEE division, one rounding to fp32
-    for (int64_t i = threadIdx.x; i < nout; i += kFinishThreads) gamma[i] = g;
-}
-
 // The sum of pass 1's partials as a normalised double-double pair (hi = fl(hi + lo)): what one shard of a row-sharded
-// matrix contributes to Eq. (3).  Same fixed tree as finish_gamma.
+// matrix contributes to Eq. (3).  A fixed tree.
 __global__ __launch_bounds__(kFinishThreads) void fold_abs_sum(const double* __restrict__ partials, int nparts,
                                                             double* __restrict__ sum) {
     __shared__ double sh_hi[kFinishThreads];
@@ -243,9 +231,8 @@ template <> struct PackVec<uint16_t> {
 // Pass 2 folded into the head of pass 3: while its first rows are on their way every workgroup adds up the partial sums of
 // pass 1 (one per thread; exact sums, so every workgroup gets the same bits) and takes gamma = fp32(S / (N K)), Eq. (3): one
 // fp64 IEEE division, one rounding to fp32.  The segment's first workgroup writes it out, once per 16-row block of it.
-// Returned: the magnitude from which a weight's code is +-1.
-__device__ inline float pack_threshold(const double* __restrict__ partials, const Seg& seg, float* __restrict__ gamma_out,
-                                       double* sh_hi, double* sh_lo) {
+__device__ inline float pack_gamma(const double* __restrict__ partials, const Seg& seg, float* __restrict__ gamma_out,
+                                   double* sh_hi, double* sh_lo) {
     dd part{0.0, 0.0};
     partials += 2 * (int64_t)seg.part0;
     if ((int)threadIdx.x < seg.nparts) part = dd{partials[2 * threadIdx.x], partials[2 * threadIdx.x + 1]};
@@ -253,7 +240,12 @@ __device__ inline float pack_threshold(const double* __restrict__ partials, cons
     const float g = (float)(S / (double)seg.count);
     if ((int)blockIdx.x == seg.pack0)
         for (int64_t o = threadIdx.x; o < seg.nout; o += kPackThreads) gamma_out[seg.g0 + o] = g;
-    const float d = g + kEps;                              // gamma + eps, one fp32 add (Eq. (1))
+    return g;
+}
+// The magnitude from which a weight's code is +-1.
+__device__ inline float pack_threshold(const double* __restrict__ partials, const Seg& seg, float* __restrict__ gamma_out,
+                                       double* sh_hi, double* sh_lo) {
+    const float d = pack_gamma(partials, seg, gamma_out, sh_hi, sh_lo) + kEps;      // gamma + eps, one fp32 add (Eq. (1))
     return ternary_threshold(d);                           // |w| >= thr  <=>  RoundClip(w / d) = +-1
 }
 
@@ -416,6 +408,173 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit_bf16x8(const
 }
 
 // ---------------------------------------------------------------------------------------------------
+// pass 3, 5-trit format
+// ---------------------------------------------------------------------------------------------------
+// A wave takes a 1 KiB chunk of the packed layout: 16 rows x 320 columns, in 16-byte pieces of the rows (ten loads a lane in
+// bf16, twenty in fp32), each piece's successor in the wave's next chunk requested as soon as the piece has been coded.  Chunks
+// are walked from the end of W backwards, like the items of the 2-bit form, neighbouring waves on neighbouring columns.
+//
+// The digit of a weight (its code + 1) is (w > -thr) + (w >= thr): two comparisons, and with a NaN on either side 0, which is what
+// rounding and clipping the quotient make of it.  gamma + eps = infinity has no threshold: there a finite weight's quotient is 0
+// and an infinite one's NaN, which is the digits of w * 0 against any threshold.
+// Four digits, a byte each, become the low four trits of a packed byte in one dot product with (1, 3, 9, 27); the digits of a
+// quad's last 16 columns, times 81, are the other addend of its 16 bytes.  No byte passes 242, so lane 16 g + r adds the two halves
+// of row r, quad g, word by word as they come from the wave's LDS tile, and the wave stores its chunk as one 1 KiB run.
+//
+// kAny: rows that start anywhere or end within a piece; the hardware takes 16-byte loads at element alignment.  A piece may run
+// on into the next row, and one that would run out of W is read from the last 16 bytes of it; chunks that end early move the
+// bytes back and clear what is not theirs.  No load depends on a condition: a wait for one would be a wait for all of them.
+//
+// Both passes, us, before (a wave per chunk from the front, 4-element loads, a division per weight, gamma in a launch of its own)
+// and now: bf16 57344 x 8192 458 / 339 (the bytes of both reads at 5.6 TB/s), 20000 x 5000 113 / 75, 20000 x 5001 149 / 78, 9600 x
+// 3200 43.5 / 28.4, 1024 x 1024 18.8 / 9.9; fp32 57344 x 8192 682 / 656, 20000 x 5001 175 / 143, 9600 x 3200 52.5 / 45.6.
+constexpr int kTritPackWaves = kPackThreads / kWave;
+constexpr int kTritPackBlocks = 768;                       // three per CU: us at one, two, three, four, 20000 x 5001 bf16 108 / 84 / 78 / 78, 9600 x 3200 31.3 / 28.1 / 28.4 / 29.2
+constexpr int kTritTileBytes = 64 * 32;                    // per wave: 64 quads of 16 four-trit bytes and 16 fifth digits
+
+template <typename T, bool kAny>
+__global__ __launch_bounds__(kPackThreads) void ternarize_pack_trit5(const T* __restrict__ W, int64_t K, int64_t RB, SegList<1> list,
+                                                                     const double* __restrict__ partials,
+                                                                     float* __restrict__ gamma_out, uint4* __restrict__ packed) {
+    constexpr int kE = 16 / (int)sizeof(T);                // elements of a piece
+    constexpr int kPieces = kTritStep / kE;                // of a row; five loads a lane cover 320 of them, ...
+    constexpr int kRows5 = 320 / kPieces;                  // ... whole rows,
+    constexpr int kGroups = kRowsPerBlock / kRows5;        // so that lanes meet the same columns again in every group of five
+    constexpr int kRsrc = 0x00020000;                      // raw buffer, 32-bit
+    constexpr int kFifth = 64 / kE;                        // a quad's pieces from here on hold its columns 64 .. 79
+    typedef uint16_t __attribute__((may_alias)) lds_u16;                   // the tile is written and read in different widths
+    typedef uint32_t __attribute__((may_alias)) lds_u32;
+    typedef unsigned lds_u32x4 __attribute__((ext_vector_type(4), may_alias));
+    __shared__ double sh_hi[kTritPackWaves];
+    __shared__ double sh_lo[kTritPackWaves];
+    __shared__ __attribute__((aligned(16))) uint8_t tiles[kTritPackWaves][kTritTileBytes];
+    const Seg& seg = list.s[0];
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int steps = (int)ceil_div(K, kTritStep);
+    const int items = (int)RB * steps;                     // N K < 2^40: below 2^29
+    const int stride = (int)gridDim.x * kTritPackWaves;
+
+    int col[5], at[5], put[5];                             // of the lane's five places: first column, bytes from the chunk's start, LDS
+    bool fifth[5];
+#pragma unroll
+    for (int i = 0; i < 5; ++i) {
+        const int f = i * kWave + lane, row = f / kPieces, c = f - row * kPieces;
+        const int quad = c / (80 / kE), j = c - quad * (80 / kE);
+        col[i] = c * kE;
+        at[i] = (int)((row * K + col[i]) * (int64_t)sizeof(T));           // K <= 2^18
+        fifth[i] = j >= kFifth;
+        put[i] = (quad * kRowsPerBlock + row) * 32 + (fifth[i] ? 16 + (j - kFifth) * kE : j * (kE / 4));
+    }
+
+    struct Chunk { const T* base; int rows, cols, place, lead, bytes; };   // of which rows x cols exist
+    const int64_t total = seg.rows * K;
+    auto chunk = [&](int item) {
+        const int it = items - 1 - item, rb = it / steps, s = it - rb * steps;
+        const int64_t n0 = (int64_t)rb * kRowsPerBlock, left = seg.rows - n0, k0 = (int64_t)s * kTritStep;
+        Chunk c;
+        c.rows = (int)(left < kRowsPerBlock ? left : kRowsPerBlock);
+        c.cols = (int)(K - k0 < kTritStep ? K - k0 : kTritStep);
+        c.place = (int)(s * RB + rb);
+        const int64_t e0 = n0 * K + k0;
+        c.lead = kAny && e0 >= kE ? kE : 0;
+        c.base = W + (e0 - c.lead);
+        const int64_t to_end = (total - (e0 - c.lead)) * (int64_t)sizeof(T);
+        c.bytes = kAny ? (int)(to_end < 1 << 30 ? to_end : 1 << 30) : ((c.rows - 1) * (int)K + c.cols) * (int)sizeof(T);
+        return c;
+    };
+    // piece q of the lane: where it is, in bytes from the chunk's base, and the load
+    auto offset = [&](const Chunk& c, int q) { return c.lead * (int)sizeof(T) + q / 5 * kRows5 * (int)K * (int)sizeof(T) + at[q % 5]; };
+    auto load = [&](const Chunk& c, bool real, int q) {
+        const int bytes = real && (!kAny || c.bytes >= 16) ? c.bytes : 0, from = offset(c, q);
+        const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(c.base), 0, bytes, kRsrc);
+        const int off = kAny ? min(from, bytes - 16) : col[q % 5] < c.cols ? from : 1 << 30;
+        return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rows, off, 0, 2 /* nt: the last use */));
+    };
+    // kAny, a chunk that ends early: what the piece holds of the chunk, moved to its place, and zeros (code 0) behind it
+    auto trimmed = [&](const Chunk& c, int q, uint4 v) {
+        const int i = q % 5, row = q / 5 * kRows5 + (i * kWave + lane) / kPieces, from = offset(c, q), moved = from - min(from, c.bytes - 16);
+        const int have = row < c.rows ? (c.cols - col[i]) * (int)sizeof(T) : 0;                // bytes
+        uint64_t lo = (uint64_t)v.y << 32 | v.x, hi = (uint64_t)v.w << 32 | v.z;
+        if (moved >= 8) { lo = hi; hi = 0; }
+        const int sh = 8 * (moved & 7);
+        lo = lo >> sh | hi << 1 << (63 - sh);
+        hi >>= sh;
+        if (have < 16) hi = have > 8 ? hi & ~(~0ull << (8 * (have - 8))) : 0;
+        if (have < 8) lo = have > 0 ? lo & ~(~0ull << (8 * have)) : 0;
+        return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+    };
+
+    uint4 piece[5 * kGroups];
+    int item = (int)blockIdx.x * kTritPackWaves + wave;
+    Chunk c = chunk(item < items ? item : 0);
+#pragma unroll
+    for (int q = 0; q < 5 * kGroups; ++q) piece[q] = load(c, item < items, q);
+    if (kAny && total < kE) {                              // a matrix of less than one piece: the elements one by one
+#pragma unroll
+        for (int q = 0; q < 5 * kGroups; ++q) {
+            const int i = q % 5, row = q / 5 * kRows5 + (i * kWave + lane) / kPieces;
+            uint32_t u[4] = {0, 0, 0, 0};
+#pragma unroll 1
+            for (int e = 0; e < kE && row < c.rows && col[i] + e < c.cols; ++e) {
+                const T t = W[row * (int)K + col[i] + e];
+                uint32_t bits;
+                if constexpr (sizeof(T) == 2) bits = (uint32_t)t << (16 * (e & 1)); else bits = __float_as_uint(t);
+#pragma unroll
+                for (int h = 0; h < 4; ++h) u[h] |= h == e * (int)sizeof(T) / 4 ? bits : 0u;
+            }
+            piece[q] = make_uint4(u[0], u[1], u[2], u[3]);
+        }
+    }
+
+    const float d = pack_gamma(partials, seg, gamma_out, sh_hi, sh_lo) + kEps;       // Eq. (1): gamma + eps
+    const bool no_threshold = d == __builtin_inff();
+    const float thr = no_threshold ? 1.0f : ternary_threshold(d);
+    const float keep = no_threshold ? 0.0f : 1.0f;
+
+    for (; item < items; item += stride) {                                 // whole waves leave; no workgroup barrier in here
+        const bool more = item + stride < items;
+        const Chunk next = chunk(more ? item + stride : item);
+        const bool early = total >= kE && (c.rows < kRowsPerBlock || c.cols < kTritStep);
+        uint8_t* tile = tiles[wave];
+#pragma unroll
+        for (int q = 0; q < 5 * kGroups; ++q) {
+            uint4 v = piece[q];
+            if (kAny && early) v = trimmed(c, q, v);
+            const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+            uint32_t dg[kE / 4];
+#pragma unroll
+            for (int h = 0; h < kE / 4; ++h) {
+                dg[h] = 0;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const uint32_t x = sizeof(T) == 2 ? u[2 * h + (b >> 1)] : u[b];
+                    const float w = __uint_as_float(sizeof(T) == 4 ? x : (b & 1) ? (x & 0xFFFF0000u) : (x << 16)) * keep;
+                    dg[h] += (w > -thr ? 1u << (8 * b) : 0u) + (w >= thr ? 1u << (8 * b) : 0u);
+                }
+            }
+            piece[q] = load(next, more, q);
+            uint8_t* to = tile + put[q % 5] + q / 5 * kRows5 * 32;
+            if (fifth[q % 5]) {
+#pragma unroll
+                for (int h = 0; h < kE / 4; ++h) reinterpret_cast<lds_u32*>(to)[h] = dg[h] * 81u;
+            } else if (sizeof(T) == 2) {
+                *reinterpret_cast<lds_u16*>(to) = (uint16_t)(__builtin_amdgcn_udot4(dg[0], 0x1B090301u, 0, false) |
+                                                              __builtin_amdgcn_udot4(dg[kE / 4 - 1], 0x1B090301u, 0, false) << 8);
+            } else {
+                *to = (uint8_t)__builtin_amdgcn_udot4(dg[0], 0x1B090301u, 0, false);
+            }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");             // the tile is the wave's own: its LDS accesses complete in order
+        __builtin_amdgcn_wave_barrier();
+        const lds_u32x4 sum = *reinterpret_cast<const lds_u32x4*>(tile + 32 * lane) + *reinterpret_cast<const lds_u32x4*>(tile + 32 * lane + 16);
+        packed[64 * (int64_t)c.place + lane] = make_uint4(sum.x, sum.y, sum.z, sum.w);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        c = next;
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------------------
 int quant_weights_num_partials() { return 2048; }
@@ -468,16 +627,6 @@ static void launch_abs_sum_partials(const void* W, bool bf16, int64_t K, const S
     else      hipLaunchKernelGGL((abs_sum_partials<float, kSegs>), grid, block, 0, stream, static_cast<const float*>(W), K, list, vec_ok, partials);
 }
 
-// Eq. (3) as passes 1 and 2 (the 5-trit packing reads gamma from memory; the 2-bit packing folds pass 2 into pass 3)
-hipError_t launch_absmean_gamma(const void* W, bool bf16, int64_t N, int64_t K, float* gamma, void* workspace,
-                                hipStream_t stream, int64_t nout) {
-    double* partials = static_cast<double*>(workspace);
-    const SegList<1> list = make_segs<1>(&N, 1, 0, K, bf16 ? 2 : 4);
-    launch_abs_sum_partials(W, bf16, K, list, partials, stream);
-    hipLaunchKernelGGL(finish_gamma, dim3(1), dim3(kFinishThreads), 0, stream, partials, list.s[0].nparts, N * K, gamma, nout);
-    return hipGetLastError();
-}
-
 hipError_t launch_abs_sum(const void* W, bool bf16, int64_t N, int64_t K, double* sum, void* workspace, hipStream_t stream) {
     double* partials = static_cast<double*>(workspace);
     const SegList<1> list = make_segs<1>(&N, 1, 0, K, bf16 ? 2 : 4);
@@ -487,11 +636,6 @@ hipError_t launch_abs_sum(const void* W, bool bf16, int64_t N, int64_t K, double
 }
 
 int quant_weights_max_sums() { return kPackThreads; }
-
-hipError_t launch_gamma_from_sums(const double* sums, int nsums, int64_t total_count, float* gamma, hipStream_t stream) {
-    hipLaunchKernelGGL(finish_gamma, dim3(1), dim3(kFinishThreads), 0, stream, sums, nsums, total_count, gamma, (int64_t)1);
-    return hipGetLastError();
-}
 
 // pass 3 over the segments of a packed matrix of RB row blocks
 template <int kSegs>
@@ -512,23 +656,38 @@ static void launch_pack(const void* W, bool bf16, int64_t K, int64_t RB, const S
 #undef PACK
 }
 
-hipError_t launch_pack_2bit_with_sums(const void* W, bool bf16, int64_t N, int64_t K, const double* sums, int nsums,
-                                      int64_t total_count, void* packed, float* gamma, hipStream_t stream) {
-    SegList<1> list = make_segs<1>(&N, 1, 0, K, bf16 ? 2 : 4);
-    list.s[0].nparts = nsums;
-    list.s[0].count = total_count;
-    list.s[0].nout = 1;
-    launch_pack(W, bf16, K, ceil_div(N, kRowsPerBlock), list, sums, packed, gamma, stream);
-    return hipGetLastError();
+static void launch_pack_trit5(const void* W, bool bf16, int64_t K, const SegList<1>& list, const double* partials, void* packed, float* gamma,
+                              hipStream_t stream) {
+    const int64_t RB = ceil_div(list.s[0].rows, kRowsPerBlock), most = ceil_div(RB * ceil_div(K, kTritStep), kTritPackWaves);
+    const bool any = K % (bf16 ? 8 : 4) != 0 || reinterpret_cast<uintptr_t>(W) % 16 != 0;
+    const dim3 grid((unsigned)(most < kTritPackBlocks ? most : kTritPackBlocks)), block(kPackThreads);
+#define PACK(T_, A_) hipLaunchKernelGGL((ternarize_pack_trit5<T_, A_>), grid, block, 0, stream, static_cast<const T_*>(W), K, RB, list, partials, gamma, \
+                                        static_cast<uint4*>(packed))
+    if (bf16) { if (any) PACK(uint16_t, true); else PACK(uint16_t, false); }
+    else { if (any) PACK(float, true); else PACK(float, false); }
+#undef PACK
 }
 
-hipError_t launch_quantize_weights_2bit(const void* W, bool bf16, int64_t N, int64_t K, void* packed,
-                                        float* gamma, void* workspace, hipStream_t stream) {
+// Eq. (1)-(3) + packing of a whole matrix
+hipError_t launch_quantize_weights(const void* W, bool bf16, int64_t N, int64_t K, bool trit5, void* packed, float* gamma, void* workspace,
+                                   hipStream_t stream) {
     double* partials = static_cast<double*>(workspace);
     SegList<1> list = make_segs<1>(&N, 1, 0, K, bf16 ? 2 : 4);
     list.s[0].nout = 1;
     launch_abs_sum_partials(W, bf16, K, list, partials, stream);
-    launch_pack(W, bf16, K, ceil_div(N, kRowsPerBlock), list, partials, packed, gamma, stream);
+    if (trit5) launch_pack_trit5(W, bf16, K, list, partials, packed, gamma, stream);
+    else launch_pack(W, bf16, K, ceil_div(N, kRowsPerBlock), list, partials, packed, gamma, stream);
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_with_sums(const void* W, bool bf16, int64_t N, int64_t K, bool trit5, const double* sums, int nsums,
+                                 int64_t total_count, void* packed, float* gamma, hipStream_t stream) {
+    SegList<1> list = make_segs<1>(&N, 1, 0, K, bf16 ? 2 : 4);
+    list.s[0].nparts = nsums;
+    list.s[0].count = total_count;
+    list.s[0].nout = 1;
+    if (trit5) launch_pack_trit5(W, bf16, K, list, sums, packed, gamma, stream);
+    else launch_pack(W, bf16, K, ceil_div(N, kRowsPerBlock), list, sums, packed, gamma, stream);
     return hipGetLastError();
 }
 
