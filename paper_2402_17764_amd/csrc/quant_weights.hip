@@ -200,33 +200,81 @@ __global__ __launch_bounds__(kFinishThreads) void fold_abs_sum(const double* __r
 // ---------------------------------------------------------------------------------------------------
 // pass 3, 2-bit format
 // ---------------------------------------------------------------------------------------------------
-// One work item is one 1 KiB chunk of the packed layout: a 16-row block x one K step of 256 columns.  A workgroup
-// has four waves; wave w reads rows 4w .. 4w+3 of the item (lane l: columns 4l .. 4l+3 of the step, one 16-byte
-// load per row for fp32, marked streaming: this is the last use of W).  The four codes of a lane land in one word at
-// bits 8 b + 2 i with i = l & 3; OR-ing the four lanes of a quad completes the word, which every lane of the quad
-// then holds.  One ds_bpermute transposes the wave's 4 rows x 16 words so that lane 16 g + 4 t + j holds word j of
-// quad column g for row 4w + t: the wave stores four 64-byte runs, no LDS memory and no barrier.  Items are walked
-// from the end of W backwards, workgroup b taking items b, b + gridDim.x, ...: neighbouring workgroups read
-// neighbouring 1 KiB runs of the same 16 rows, and the next item's rows are requested before this one's are coded.
+// One work item is a 16-row block x one 16-byte piece of a row per lane: one 1 KiB chunk of the packed layout (a K step of 256
+// columns) in fp32, two in bf16.  A workgroup has four waves; wave w reads rows 4w .. 4w+3 of the item, and requests a row of its
+// next item as soon as this one's has been coded.  In fp32 the four codes of a lane land in one word at bits 8 b + 2 i with i = l &
+// 3, and OR-ing the four lanes of a quad completes the word, which every lane of the quad then holds; one ds_bpermute transposes
+// the wave's 4 rows x 16 words so that lane 16 g + 4 t + j holds word j of quad column g for row 4w + t.  In bf16 two lanes
+// complete a word; the pair holds the words of the wave's four rows twice, so the even lane hands out rows 0 and 2, the odd lane
+// rows 1 and 3, and two ds_bpermute per step do the same.  The wave stores four 64-byte runs per step, no LDS memory and no barrier.
+// Items are walked from the end of W backwards, workgroup b taking items b, b + gridDim.x, ...: neighbouring workgroups read
+// neighbouring 1 KiB runs of the same 16 rows.
+// Both passes, us, before (rows that are no whole number of 16-byte loads read element by element, loads under conditions) and now:
+// bf16 28672 x 8191 408 / 182, 20000 x 5001 167 / 79, 20000 x 5004 111 / 80, 9600 x 3200 28.4 / 27.0, 57344 x 8192 342 / 340; fp32
+// 20000 x 5001 167 / 145, 57344 x 8192 651 / 639.  Eight-byte loads in bf16 were slower still (57344 x 8192 496).  Two, three or six
+// workgroups a CU instead of four: within 2 % but for 28672 x 8191, 197 at two and 176 at six.
 constexpr int kPackThreads = 256;
 constexpr int kPackBlocks = 1024;                          // four per CU
 static_assert(kSumBlocks <= kPackThreads, "the packing pass folds one partial sum of pass 1 per thread");
 
-template <typename T> struct PackVec;
-template <> struct PackVec<float> {
-    __device__ static void load(const float* p, float (&f)[4]) {
-        const uint4 q = load_streaming_b128(p);
-        f[0] = __uint_as_float(q.x); f[1] = __uint_as_float(q.y); f[2] = __uint_as_float(q.z); f[3] = __uint_as_float(q.w);
+// A chunk of W of rows x cols elements, read in 16-byte pieces that lie `from` bytes behind its first element.  kAny: rows may
+// start anywhere and end within a piece; the hardware takes 16-byte loads at element alignment.  Such a piece may run on into the
+// next row, and one that would run out of W is read from the last 16 bytes of it: a chunk that ends early moves the bytes back and
+// clears what is not its own (trimmed).  Otherwise the descriptor ends the rows and an offset out of its range the columns.  No load
+// depends on a condition: a wait for one of those is a wait for all that are in flight.
+template <typename T, bool kAny>
+struct Chunk {
+    static constexpr int kE = 16 / (int)sizeof(T);         // elements of a piece
+    const T* base;
+    int rows, cols, lead, bytes;
+
+    __device__ Chunk(const T* W, int64_t N, int64_t K, int64_t n0, int64_t k0, int most_rows, int most_cols) {
+        const int64_t e0 = n0 * K + k0;
+        rows = (int)(N - n0 < most_rows ? N - n0 : most_rows);
+        cols = (int)(K - k0 < most_cols ? K - k0 : most_cols);
+        lead = kAny && e0 >= kE ? 16 : 0;                  // there is always a piece in front of the end of W
+        base = W + e0 - lead / (int)sizeof(T);
+        const int64_t to_end = (N * K - e0) * (int64_t)sizeof(T) + lead;
+        bytes = kAny ? (int)(to_end < 1 << 30 ? to_end : 1 << 30) : ((rows - 1) * (int)K + cols) * (int)sizeof(T);      // K <= 2^18
+    }
+    __device__ uint4 load(bool real, int from, int col) const {
+        const int n = real && (!kAny || bytes >= 16) ? bytes : 0;
+        const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, n, 0x00020000 /* raw, 32-bit */);
+        const int off = kAny ? min(lead + from, n - 16) : col < cols ? from : 1 << 30;
+        return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 2 /* nt: the last use */));
+    }
+    __device__ uint4 trimmed(uint4 v, int from, int row, int col) const {
+        const int moved = lead + from - min(lead + from, bytes - 16), have = row < rows ? (cols - col) * (int)sizeof(T) : 0;
+        uint64_t lo = (uint64_t)v.y << 32 | v.x, hi = (uint64_t)v.w << 32 | v.z;
+        if (moved >= 8) { lo = hi; hi = 0; }
+        const int sh = 8 * (moved & 7);
+        lo = lo >> sh | hi << 1 << (63 - sh);
+        hi >>= sh;
+        if (have < 16) hi = have > 8 ? hi & ~(~0ull << (8 * (have - 8))) : 0;
+        if (have < 8) lo = have > 0 ? lo & ~(~0ull << (8 * have)) : 0;
+        return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+    }
+    // a matrix of less than one piece: its elements one by one
+    __device__ uint4 by_element(const T* W, int K, int row, int col) const {
+        uint32_t u[4] = {0, 0, 0, 0};
+#pragma unroll 1
+        for (int e = 0; e < kE && row < rows && col + e < cols; ++e) {
+            uint32_t bits;
+            if constexpr (sizeof(T) == 2) bits = (uint32_t)W[row * K + col + e] << (16 * (e & 1));
+            else bits = __float_as_uint(W[row * K + col + e]);
+#pragma unroll
+            for (int h = 0; h < 4; ++h) u[h] |= h == e * (int)sizeof(T) / 4 ? bits : 0u;
+        }
+        return make_uint4(u[0], u[1], u[2], u[3]);
     }
 };
-template <> struct PackVec<uint16_t> {
-    __device__ static void load(const uint16_t* p, float (&f)[4]) {
-        typedef unsigned v2u __attribute__((ext_vector_type(2)));
-        const v2u q = __builtin_nontemporal_load(reinterpret_cast<const v2u*>(p));
-        f[0] = __uint_as_float(q.x << 16); f[1] = __uint_as_float(q.x & 0xFFFF0000u);
-        f[2] = __uint_as_float(q.y << 16); f[3] = __uint_as_float(q.y & 0xFFFF0000u);
-    }
-};
+
+// element e of a piece, widened
+template <typename T>
+__device__ inline float piece_elem(const uint32_t (&u)[4], int e) {
+    if (sizeof(T) == 4) return __uint_as_float(u[e & 3]);
+    return __uint_as_float(e & 1 ? u[e >> 1] & 0xFFFF0000u : u[e >> 1] << 16);
+}
 
 // Pass 2 folded into the head of pass 3: while its first rows are on their way every workgroup adds up the partial sums of
 // pass 1 (one per thread; exact sums, so every workgroup gets the same bits) and takes gamma = fp32(S / (N K)), Eq. (3): one
@@ -251,11 +299,12 @@ __device__ inline float pack_threshold(const double* __restrict__ partials, cons
 
 // A segment's rows become row blocks row0 / 16 ... of a packed matrix of RB row blocks in all (segments start on row
 // blocks).
-template <typename T, bool kVec, int kSegs>
+template <typename T, bool kAny, int kSegs>
 __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __restrict__ W_all, int64_t K,
                                                                     int64_t Kq /* quads per row */, int64_t RB,
                                                                     SegList<kSegs> list, const double* __restrict__ partials,
                                                                     float* __restrict__ gamma_out, uint32_t* __restrict__ packed) {
+    constexpr int kE = 16 / (int)sizeof(T), kCols = kWave * kE, kSteps = kCols / 256;      // of an item
     int sg = 0;
     while (sg + 1 < list.n && (int)blockIdx.x >= list.s[sg + 1].pack0) ++sg;
     const Seg& seg = list.s[sg];
@@ -264,146 +313,72 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
     const int stride = seg.npack;
     __shared__ double sh_hi[kPackThreads / kWave];
     __shared__ double sh_lo[kPackThreads / kWave];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int w = threadIdx.x >> 6;
-    const int i = lane & 3;
-    const int steps = (int)ceil_div(Kq, 4);
-    const int items = (int)(ceil_div(N, kRowsPerBlock) * steps);      // N K < 2^40: below 2^29
-    // lane 16 g + 4 t + j takes its word from lane 16 g + 4 j + t (which selected row t's word below)
-    const int src = ((lane & 48) | ((lane & 3) << 2) | ((lane >> 2) & 3)) << 2;
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x >> 6, col = lane * kE;
+    const int per_row = (int)ceil_div(K, kCols);
+    const int items = (int)ceil_div(N, kRowsPerBlock) * per_row;      // N K < 2^40: below 2^29
+    auto chunk = [&](int item) {
+        const int it = items - 1 - item, rb = it / per_row;
+        return Chunk<T, kAny>(W, N, K, (int64_t)rb * kRowsPerBlock, (int64_t)(it - rb * per_row) * kCols, kRowsPerBlock, kCols);
+    };
+    int from[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) from[t] = ((4 * w + t) * (int)K + col) * (int)sizeof(T);
 
-    auto load = [&](int item, float (&f)[4][4]) {
-        item = items - 1 - item;
-        const int rb = item / steps, s = item - rb * steps;
-        const int64_t k = 256 * (int64_t)s + 4 * lane;
+    uint4 piece[4];
+    int item = (int)blockIdx.x - seg.pack0;
+    Chunk<T, kAny> c = chunk(item < items ? item : 0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) piece[t] = c.load(item < items, from[t], col);
+    const bool tiny = kAny && N * K < kE;
+    if (tiny) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) piece[t] = c.by_element(W, (int)K, 4 * w + t, col);
+    }
+
+    const float thr = pack_threshold(partials, seg, gamma_out, sh_hi, sh_lo);
+
+    const int t_out = (lane >> 2) & 3, g = lane >> 4;      // the lane stores word lane & 3 of row 4w + t_out, quad column g
+    for (; item < items; item += stride) {
+        const bool more = item + stride < items;
+        const Chunk<T, kAny> next = chunk(more ? item + stride : item);
+        uint32_t word[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const int64_t n = (int64_t)rb * kRowsPerBlock + 4 * w + t;
+            uint4 v = piece[t];
+            if (kAny && !tiny && (c.rows < kRowsPerBlock || c.cols < kCols)) v = c.trimmed(v, from[t], 4 * w + t, col);
+            const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+            uint32_t code = 0;                             // column 4 h + b of the lane: bits 8 b + 2 h of its part of a word
 #pragma unroll
-            for (int b = 0; b < 4; ++b) f[t][b] = 0.f;     // padding rows / columns quantize to code 0
-            if (n < N) {
-                const T* row = W + n * K;
-                if (kVec) {
-                    if (k < K) PackVec<T>::load(row + k, f[t]);
-                } else {
-#pragma unroll
-                    for (int b = 0; b < 4; ++b)
-                        if (k + b < K) f[t][b] = widen1(row[k + b]);
-                }
+            for (int e = 0; e < kE; ++e) code |= ternary_code2_threshold(piece_elem<T>(u, e), thr) << (8 * (e & 3) + 2 * (e >> 2));
+            piece[t] = next.load(more, from[t], col);
+            __builtin_amdgcn_sched_barrier(0);             // in this place: requested before the next row is waited for
+            if (sizeof(T) == 2) {
+                code <<= 4 * (lane & 1);
+                word[t] = code | dpp_u32<0xB1>(code);      // lane ^ 1
+            } else {
+                word[t] = quad_or(code << (2 * (lane & 3)));
             }
         }
-    };
-
-    float nxt[4][4];
-    int item = (int)blockIdx.x - seg.pack0;
-    if (item < items) load(item, nxt);
-
-    const float thr = pack_threshold(partials, seg, gamma_out, sh_hi, sh_lo);
-
-    for (; item < items; item += stride) {
-        float cur[4][4];
+        const int it = items - 1 - item, rb = it / per_row;
+        const int64_t s0 = (int64_t)(it - rb * per_row) * kSteps;
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int b = 0; b < 4; ++b) cur[t][b] = nxt[t][b];
-        if (item + stride < items) load(item + stride, nxt);
-        uint32_t c[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            uint32_t v = 0;
-#pragma unroll
-            for (int b = 0; b < 4; ++b) v |= ternary_code2_threshold(cur[t][b], thr) << (8 * b + 2 * i);
-            c[t] = quad_or(v);
+        for (int q = 0; q < kSteps; ++q) {
+            uint32_t out;
+            if (sizeof(T) == 2) {
+                const int src = (32 * q + 8 * g + 2 * (lane & 3) + (t_out & 1)) << 2;
+                const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(lane & 1 ? word[1] : word[0]));
+                const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(lane & 1 ? word[3] : word[2]));
+                out = t_out < 2 ? lo : hi;
+            } else {
+                const int i = lane & 3;                    // lane 16 g + 4 t + j takes its word from lane 16 g + 4 j + t
+                const int src = ((lane & 48) | (i << 2) | t_out) << 2;
+                out = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)(i == 0 ? word[0] : i == 1 ? word[1] : i == 2 ? word[2] : word[3]));
+            }
+            const int64_t s = s0 + q, nq = (Kq - 4 * s) < 4 ? (Kq - 4 * s) : 4;      // quads of this step (the last may hold fewer, or none)
+            // word index inside the chunk: ((g * 16 + row) * 4 + j) with row = 4 w + t, and lane & 15 = 4 t + j
+            if (g < nq) packed[quad_index_2bit(4 * s, rb + rb_off, 0, Kq, RB) * 4 + g * 64 + 16 * w + (lane & 15)] = out;
         }
-        const uint32_t sel = i == 0 ? c[0] : i == 1 ? c[1] : i == 2 ? c[2] : c[3];
-        const uint32_t out = (uint32_t)__builtin_amdgcn_ds_bpermute(src, (int)sel);
-        const int it = items - 1 - item;
-        const int rb = it / steps;
-        const int64_t s = it - rb * steps;
-        const int64_t nq = (Kq - 4 * s) < 4 ? (Kq - 4 * s) : 4;     // quads of this step (the last may hold fewer)
-        const int g = lane >> 4;
-        // word index inside the chunk: ((g * 16 + row) * 4 + j) with row = 4 w + t, and lane & 15 = 4 t + j
-        if (g < nq) packed[quad_index_2bit(4 * s, rb + rb_off, 0, Kq, RB) * 4 + g * 64 + 16 * w + (lane & 15)] = out;
-    }
-}
-
-// bf16 rows that start on 16-byte boundaries (K a multiple of 8): items of two K steps, so that a lane's load is 16 bytes
-// (columns 8l .. 8l+7 of the 512) and a row of an item one 1 KiB run, as in the fp32 form; with 8-byte loads the pass moved
-// half the bytes per request and ran at 2.9 TB/s (57344 x 8192, both passes: 496 us, 350 with these; 4096 x 4096 22.7, 19.1; 512 x
-// 512 8.4, 7.5).  Two lanes complete a word; the pair holds the words of the wave's four rows twice, so the even lane hands out
-// rows 0 and 2, the odd lane rows 1 and 3, and two ds_bpermute per step give lane 16 g + 4 t + j word j of quad column g for row
-// 4w + t: four 64-byte runs per step, as above.
-template <int kSegs>
-__global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit_bf16x8(const uint16_t* __restrict__ W_all, int64_t K,
-                                                                           int64_t Kq, int64_t RB, SegList<kSegs> list,
-                                                                           const double* __restrict__ partials,
-                                                                           float* __restrict__ gamma_out, uint32_t* __restrict__ packed) {
-    int sg = 0;
-    while (sg + 1 < list.n && (int)blockIdx.x >= list.s[sg + 1].pack0) ++sg;
-    const Seg& seg = list.s[sg];
-    const uint16_t* W = W_all + seg.row0 * K;
-    const int64_t N = seg.rows, rb_off = seg.row0 / kRowsPerBlock;
-    const int stride = seg.npack;
-    __shared__ double sh_hi[kPackThreads / kWave];
-    __shared__ double sh_lo[kPackThreads / kWave];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int w = threadIdx.x >> 6;
-    const int odd = lane & 1;
-    const int pairs = (int)ceil_div(Kq, 8);                // items per row block
-    const int items = (int)(ceil_div(N, kRowsPerBlock) * pairs);      // N K < 2^40: below 2^29
-    const int t_out = (lane >> 2) & 3;
-    const int src = (8 * (lane >> 4) + 2 * (lane & 3) + (t_out & 1)) << 2;      // of the item's first step; + 32 lanes for the second
-
-    auto load = [&](int item, uint4 (&q)[4]) {
-        item = items - 1 - item;
-        const int rb = item / pairs, sp = item - rb * pairs;
-        const int64_t k = 512 * (int64_t)sp + 8 * lane;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const int64_t n = (int64_t)rb * kRowsPerBlock + 4 * w + t;
-            q[t] = make_uint4(0, 0, 0, 0);                  // padding rows / columns quantize to code 0
-            if (n < N && k < K) q[t] = load_streaming_b128(W + n * K + k);
-        }
-    };
-
-    uint4 nxt[4];
-    int item = (int)blockIdx.x - seg.pack0;
-    if (item < items) load(item, nxt);
-
-    const float thr = pack_threshold(partials, seg, gamma_out, sh_hi, sh_lo);
-
-    for (; item < items; item += stride) {
-        uint4 cur[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) cur[t] = nxt[t];
-        if (item + stride < items) load(item + stride, nxt);
-        uint32_t c[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const uint32_t u[4] = {cur[t].x, cur[t].y, cur[t].z, cur[t].w};
-            uint32_t v = 0;                                 // columns 8 l + 4 h + b: bits 8 b + 2 (2 odd + h) of the word
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const uint32_t x = u[2 * h + (b >> 1)];
-                    v |= ternary_code2_threshold(__uint_as_float((b & 1) ? (x & 0xFFFF0000u) : (x << 16)), thr) << (8 * b + 2 * h);
-                }
-            v <<= 4 * odd;
-            c[t] = v | dpp_u32<0xB1>(v);                    // lane ^ 1
-        }
-        const int even_rows = (int)(odd ? c[1] : c[0]), odd_rows = (int)(odd ? c[3] : c[2]);
-        const int it = items - 1 - item;
-        const int rb = it / pairs, sp = it - rb * pairs;
-        const int g = lane >> 4;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_ds_bpermute(src + 128 * q, even_rows);
-            const uint32_t hi = (uint32_t)__builtin_amdgcn_ds_bpermute(src + 128 * q, odd_rows);
-            const int64_t s = 2 * (int64_t)sp + q;
-            const int64_t nq = (Kq - 4 * s) < 4 ? (Kq - 4 * s) : 4;     // quads of this step (the last may hold fewer, or none)
-            if (g < nq) packed[quad_index_2bit(4 * s, rb + rb_off, 0, Kq, RB) * 4 + g * 64 + 16 * w + (lane & 15)] = t_out < 2 ? lo : hi;
-        }
+        c = next;
     }
 }
 
@@ -421,13 +396,9 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit_bf16x8(const
 // quad's last 16 columns, times 81, are the other addend of its 16 bytes.  No byte passes 242, so lane 16 g + r adds the two halves
 // of row r, quad g, word by word as they come from the wave's LDS tile, and the wave stores its chunk as one 1 KiB run.
 //
-// kAny: rows that start anywhere or end within a piece; the hardware takes 16-byte loads at element alignment.  A piece may run
-// on into the next row, and one that would run out of W is read from the last 16 bytes of it; chunks that end early move the
-// bytes back and clear what is not theirs.  No load depends on a condition: a wait for one would be a wait for all of them.
-//
 // Both passes, us, before (a wave per chunk from the front, 4-element loads, a division per weight, gamma in a launch of its own)
-// and now: bf16 57344 x 8192 458 / 339 (the bytes of both reads at 5.6 TB/s), 20000 x 5000 113 / 75, 20000 x 5001 149 / 78, 9600 x
-// 3200 43.5 / 28.4, 1024 x 1024 18.8 / 9.9; fp32 57344 x 8192 682 / 656, 20000 x 5001 175 / 143, 9600 x 3200 52.5 / 45.6.
+// and now: bf16 57344 x 8192 458 / 340 (the bytes of both reads at 5.5 TB/s), 20000 x 5000 113 / 75, 20000 x 5001 149 / 78, 9600 x
+// 3200 43.5 / 28.4, 1024 x 1024 18.8 / 9.9; fp32 57344 x 8192 682 / 656, 20000 x 5001 175 / 143, 9600 x 3200 52.5 / 44.5.
 constexpr int kTritPackWaves = kPackThreads / kWave;
 constexpr int kTritPackBlocks = 768;                       // three per CU: us at one, two, three, four, 20000 x 5001 bf16 108 / 84 / 78 / 78, 9600 x 3200 31.3 / 28.1 / 28.4 / 29.2
 constexpr int kTritTileBytes = 64 * 32;                    // per wave: 64 quads of 16 four-trit bytes and 16 fifth digits
@@ -440,7 +411,6 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_trit5(const T* __
     constexpr int kPieces = kTritStep / kE;                // of a row; five loads a lane cover 320 of them, ...
     constexpr int kRows5 = 320 / kPieces;                  // ... whole rows,
     constexpr int kGroups = kRowsPerBlock / kRows5;        // so that lanes meet the same columns again in every group of five
-    constexpr int kRsrc = 0x00020000;                      // raw buffer, 32-bit
     constexpr int kFifth = 64 / kE;                        // a quad's pieces from here on hold its columns 64 .. 79
     typedef uint16_t __attribute__((may_alias)) lds_u16;                   // the tile is written and read in different widths
     typedef uint32_t __attribute__((may_alias)) lds_u32;
@@ -466,64 +436,22 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_trit5(const T* __
         put[i] = (quad * kRowsPerBlock + row) * 32 + (fifth[i] ? 16 + (j - kFifth) * kE : j * (kE / 4));
     }
 
-    struct Chunk { const T* base; int rows, cols, place, lead, bytes; };   // of which rows x cols exist
-    const int64_t total = seg.rows * K;
     auto chunk = [&](int item) {
-        const int it = items - 1 - item, rb = it / steps, s = it - rb * steps;
-        const int64_t n0 = (int64_t)rb * kRowsPerBlock, left = seg.rows - n0, k0 = (int64_t)s * kTritStep;
-        Chunk c;
-        c.rows = (int)(left < kRowsPerBlock ? left : kRowsPerBlock);
-        c.cols = (int)(K - k0 < kTritStep ? K - k0 : kTritStep);
-        c.place = (int)(s * RB + rb);
-        const int64_t e0 = n0 * K + k0;
-        c.lead = kAny && e0 >= kE ? kE : 0;
-        c.base = W + (e0 - c.lead);
-        const int64_t to_end = (total - (e0 - c.lead)) * (int64_t)sizeof(T);
-        c.bytes = kAny ? (int)(to_end < 1 << 30 ? to_end : 1 << 30) : ((c.rows - 1) * (int)K + c.cols) * (int)sizeof(T);
-        return c;
+        const int it = items - 1 - item, rb = it / steps;
+        return Chunk<T, kAny>(W, seg.rows, K, (int64_t)rb * kRowsPerBlock, (int64_t)(it - rb * steps) * kTritStep, kRowsPerBlock, kTritStep);
     };
-    // piece q of the lane: where it is, in bytes from the chunk's base, and the load
-    auto offset = [&](const Chunk& c, int q) { return c.lead * (int)sizeof(T) + q / 5 * kRows5 * (int)K * (int)sizeof(T) + at[q % 5]; };
-    auto load = [&](const Chunk& c, bool real, int q) {
-        const int bytes = real && (!kAny || c.bytes >= 16) ? c.bytes : 0, from = offset(c, q);
-        const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(c.base), 0, bytes, kRsrc);
-        const int off = kAny ? min(from, bytes - 16) : col[q % 5] < c.cols ? from : 1 << 30;
-        return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rows, off, 0, 2 /* nt: the last use */));
-    };
-    // kAny, a chunk that ends early: what the piece holds of the chunk, moved to its place, and zeros (code 0) behind it
-    auto trimmed = [&](const Chunk& c, int q, uint4 v) {
-        const int i = q % 5, row = q / 5 * kRows5 + (i * kWave + lane) / kPieces, from = offset(c, q), moved = from - min(from, c.bytes - 16);
-        const int have = row < c.rows ? (c.cols - col[i]) * (int)sizeof(T) : 0;                // bytes
-        uint64_t lo = (uint64_t)v.y << 32 | v.x, hi = (uint64_t)v.w << 32 | v.z;
-        if (moved >= 8) { lo = hi; hi = 0; }
-        const int sh = 8 * (moved & 7);
-        lo = lo >> sh | hi << 1 << (63 - sh);
-        hi >>= sh;
-        if (have < 16) hi = have > 8 ? hi & ~(~0ull << (8 * (have - 8))) : 0;
-        if (have < 8) lo = have > 0 ? lo & ~(~0ull << (8 * have)) : 0;
-        return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
-    };
+    auto from = [&](int q) { return q / 5 * kRows5 * (int)K * (int)sizeof(T) + at[q % 5]; };      // piece q of the lane: bytes, row
+    auto row_of = [&](int q) { return q / 5 * kRows5 + (q % 5 * kWave + lane) / kPieces; };
 
     uint4 piece[5 * kGroups];
     int item = (int)blockIdx.x * kTritPackWaves + wave;
-    Chunk c = chunk(item < items ? item : 0);
+    Chunk<T, kAny> c = chunk(item < items ? item : 0);
 #pragma unroll
-    for (int q = 0; q < 5 * kGroups; ++q) piece[q] = load(c, item < items, q);
-    if (kAny && total < kE) {                              // a matrix of less than one piece: the elements one by one
+    for (int q = 0; q < 5 * kGroups; ++q) piece[q] = c.load(item < items, from(q), col[q % 5]);
+    const bool tiny = kAny && seg.rows * K < kE;
+    if (tiny) {
 #pragma unroll
-        for (int q = 0; q < 5 * kGroups; ++q) {
-            const int i = q % 5, row = q / 5 * kRows5 + (i * kWave + lane) / kPieces;
-            uint32_t u[4] = {0, 0, 0, 0};
-#pragma unroll 1
-            for (int e = 0; e < kE && row < c.rows && col[i] + e < c.cols; ++e) {
-                const T t = W[row * (int)K + col[i] + e];
-                uint32_t bits;
-                if constexpr (sizeof(T) == 2) bits = (uint32_t)t << (16 * (e & 1)); else bits = __float_as_uint(t);
-#pragma unroll
-                for (int h = 0; h < 4; ++h) u[h] |= h == e * (int)sizeof(T) / 4 ? bits : 0u;
-            }
-            piece[q] = make_uint4(u[0], u[1], u[2], u[3]);
-        }
+        for (int q = 0; q < 5 * kGroups; ++q) piece[q] = c.by_element(W, (int)K, row_of(q), col[q % 5]);
     }
 
     const float d = pack_gamma(partials, seg, gamma_out, sh_hi, sh_lo) + kEps;       // Eq. (1): gamma + eps
@@ -533,13 +461,12 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_trit5(const T* __
 
     for (; item < items; item += stride) {                                 // whole waves leave; no workgroup barrier in here
         const bool more = item + stride < items;
-        const Chunk next = chunk(more ? item + stride : item);
-        const bool early = total >= kE && (c.rows < kRowsPerBlock || c.cols < kTritStep);
+        const Chunk<T, kAny> next = chunk(more ? item + stride : item);
         uint8_t* tile = tiles[wave];
 #pragma unroll
         for (int q = 0; q < 5 * kGroups; ++q) {
             uint4 v = piece[q];
-            if (kAny && early) v = trimmed(c, q, v);
+            if (kAny && !tiny && (c.rows < kRowsPerBlock || c.cols < kTritStep)) v = c.trimmed(v, from(q), row_of(q), col[q % 5]);
             const uint32_t u[4] = {v.x, v.y, v.z, v.w};
             uint32_t dg[kE / 4];
 #pragma unroll
@@ -547,12 +474,11 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_trit5(const T* __
                 dg[h] = 0;
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
-                    const uint32_t x = sizeof(T) == 2 ? u[2 * h + (b >> 1)] : u[b];
-                    const float w = __uint_as_float(sizeof(T) == 4 ? x : (b & 1) ? (x & 0xFFFF0000u) : (x << 16)) * keep;
+                    const float w = piece_elem<T>(u, 4 * h + b) * keep;
                     dg[h] += (w > -thr ? 1u << (8 * b) : 0u) + (w >= thr ? 1u << (8 * b) : 0u);
                 }
             }
-            piece[q] = load(next, more, q);
+            piece[q] = next.load(more, from(q), col[q % 5]);
             uint8_t* to = tile + put[q % 5] + q / 5 * kRows5 * 32;
             if (fifth[q % 5]) {
 #pragma unroll
@@ -567,7 +493,8 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_trit5(const T* __
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");             // the tile is the wave's own: its LDS accesses complete in order
         __builtin_amdgcn_wave_barrier();
         const lds_u32x4 sum = *reinterpret_cast<const lds_u32x4*>(tile + 32 * lane) + *reinterpret_cast<const lds_u32x4*>(tile + 32 * lane + 16);
-        packed[64 * (int64_t)c.place + lane] = make_uint4(sum.x, sum.y, sum.z, sum.w);
+        const int it = items - 1 - item, rb = it / steps;
+        packed[64 * ((int64_t)(it - rb * steps) * RB + rb) + lane] = make_uint4(sum.x, sum.y, sum.z, sum.w);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
         c = next;
@@ -641,18 +568,14 @@ int quant_weights_max_sums() { return kPackThreads; }
 template <int kSegs>
 static void launch_pack(const void* W, bool bf16, int64_t K, int64_t RB, const SegList<kSegs>& list, const double* partials, void* packed,
                         float* gamma, hipStream_t stream) {
-    const size_t esz = bf16 ? 2 : 4;
-    const bool vec = (reinterpret_cast<uintptr_t>(W) % (4 * esz)) == 0 && (K % 4 == 0);
-    const bool bf16x8 = bf16 && K % 8 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0;     // 16-byte loads along the rows
+    const bool any = K % (bf16 ? 8 : 4) != 0 || reinterpret_cast<uintptr_t>(W) % 16 != 0;       // a segment starts a multiple of 32 bytes further on
     const int64_t Kq = ceil_div(K, kColsPerQuad);
     const dim3 grid((unsigned)(list.s[list.n - 1].pack0 + list.s[list.n - 1].npack)), block(kPackThreads);
     uint32_t* out = static_cast<uint32_t*>(packed);
-#define PACK(T_, V_) hipLaunchKernelGGL((ternarize_pack_2bit<T_, V_, kSegs>), grid, block, 0, stream, static_cast<const T_*>(W), K, Kq, RB, list, \
+#define PACK(T_, A_) hipLaunchKernelGGL((ternarize_pack_2bit<T_, A_, kSegs>), grid, block, 0, stream, static_cast<const T_*>(W), K, Kq, RB, list, \
                                         partials, gamma, out)
-    if (bf16x8) hipLaunchKernelGGL((ternarize_pack_2bit_bf16x8<kSegs>), grid, block, 0, stream, static_cast<const uint16_t*>(W), K, Kq, RB, list,
-                                   partials, gamma, out);
-    else if (bf16) { if (vec) PACK(uint16_t, true); else PACK(uint16_t, false); }
-    else { if (vec) PACK(float, true); else PACK(float, false); }
+    if (bf16) { if (any) PACK(uint16_t, true); else PACK(uint16_t, false); }
+    else { if (any) PACK(float, true); else PACK(float, false); }
 #undef PACK
 }
 

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import oracle
-from layout_ref import decode_trit5
+from layout_ref import decode_2bit, decode_trit5
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +56,34 @@ def test_five_trit_packing_of_nan_and_infinity(gpu_lib, dtype, K):
     want[3, 7] = want[39, K - 1] = -1
     got, pad_zero = decode_trit5(packed.cpu().numpy(), N, K)
     assert torch.isinf(g).all() and pad_zero and np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("offset", [0, 1, 3, 4])
+@pytest.mark.parametrize("N,K", SHAPES + [(16, 64), (17, 255), (31, 257), (16, 520), (40, 1023), (33, 1032)])
+def test_two_bit_packing_at_the_edges(gpu_lib, N, K, offset, dtype):
+    B = gpu_lib
+    W, Wf = weights(N, K, dtype, offset, 1000 * N + K)
+    codes, gamma = oracle.quantize_weights(Wf)
+    packed, g = B.quantize_weights(W)
+    assert g.cpu().numpy()[0].tobytes() == np.float32(gamma).tobytes()
+    got, pad_zero = decode_2bit(packed.cpu().numpy(), N, K)
+    assert pad_zero and np.array_equal(got, codes)
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("rows,K", [((16, 3), 1), ((32, 16, 5), 3), ((16, 48, 16), 321), ((160, 32, 7), 1001), ((64, 64), 520)])
+def test_segments_end_where_the_next_one_starts(gpu_lib, rows, K, offset, dtype):
+    """Each segment's last rows are read up to their end, whatever follows, and the last one's tail is no whole row block."""
+    B, N = gpu_lib, sum(rows)
+    W, Wf = weights(N, K, dtype, offset, 7 * N + K)
+    packed, g = B.quantize_weights_segmented(W, list(rows))
+    got, pad_zero = decode_2bit(packed.cpu().numpy(), N, K)
+    at, blocks = 0, g.cpu().numpy()
+    for n in rows:
+        codes, gamma = oracle.quantize_weights(Wf[at:at + n])
+        assert np.array_equal(got[at:at + n], codes)
+        assert all(b.tobytes() == np.float32(gamma).tobytes() for b in blocks[at // 16:(at + n + 15) // 16])
+        at += n
+    assert pad_zero
