@@ -245,11 +245,8 @@ struct Chunk {
     }
     __device__ uint4 trimmed(uint4 v, int from, int row, int col) const {
         const int moved = lead + from - min(lead + from, bytes - 16), have = row < rows ? (cols - col) * (int)sizeof(T) : 0;
+        v = shift_down16(v, moved);
         uint64_t lo = (uint64_t)v.y << 32 | v.x, hi = (uint64_t)v.w << 32 | v.z;
-        if (moved >= 8) { lo = hi; hi = 0; }
-        const int sh = 8 * (moved & 7);
-        lo = lo >> sh | hi << 1 << (63 - sh);
-        hi >>= sh;
         if (have < 16) hi = have > 8 ? hi & ~(~0ull << (8 * (have - 8))) : 0;
         if (have < 8) lo = have > 0 ? lo & ~(~0ull << (8 * have)) : 0;
         return make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
