@@ -429,15 +429,18 @@ __global__ __launch_bounds__(kThreads) void swiglu_quantize_kernel(
     }
 }
 
-// The same for bf16 rows of many tokens.  The gate costs ~45 VALU instructions an element (exponential, IEEE division): more
-// time than the bytes.  But silu's argument is a bf16 value, so a workgroup evaluates it once for every value of magnitude
-// 2^-15 ... 2^8 (23 exponents x 128 mantissas x 2 signs, 23 KB of LDS: the very same function, the same bits) and looks it up
-// for all elements of all its tokens.  Zero has an entry too -- a projection's integer sum is 0 for one output in a thousand,
+// The same for bf16 rows.  The gate costs ~45 VALU instructions an element (exponential, IEEE division): more time than the bytes.
+// But silu's argument is a bf16 value, so a workgroup holds it for every value of magnitude 2^-15 ... 2^8 (23 exponents x 128
+// mantissas x 2 signs, 23 KB of LDS: the very same function, the same bits) and looks it up for all elements of all its tokens.
+// kCopy: the table is a constant array, made by the compiler with the steps of silu_one, and comes to LDS beside the first token;
+// evaluating it is 1.8 us in front of that token, which is all a workgroup has where tokens are few (7B stack at 29 tokens 323.8 ->
+// 320.7 us).  Many workgroups evaluate it instead: they would all read the same 23 KB at once.
+// Zero has an entry too -- a projection's integer sum is 0 for one output in a thousand,
 // which is one in half of all wave-wide vectors -- and a wave that holds any other magnitude goes through silu_beyond_table.  A
 // workgroup walks tokens blockIdx.x, + workgroups, ... with the next token's loads in flight under the current one's work.
-// bf16, alone, arithmetic / table: 64 x 11008 8.9 / 5.0 us, 256 x 5120 5.4 / 4.7, 2048 x 13824 38.5 / 25.4, 4096 x 28672 134 / 113
-// (5.2 TB/s, what a device copy reaches).  Gates that are all beyond the table (around 1e4, or 1e-5): 64 x 11008 6.0, 2048 x 13824
-// 31.3, 4096 x 28672 126; only for a few tokens does the table then not pay for itself (1 x 16384 5.7 / 6.6, ordinary gates 4.8).
+// bf16, alone, arithmetic / table: 64 x 11008 4.8 / 4.5 us, 8 x 14336 5.2 / 4.1, 2048 x 13824 38.5 / 25.4, 4096 x 28672 134 / 113
+// (5.2 TB/s, what a device copy reaches).  Gates that are all beyond the table (around 1e4, or 1e-5), table evaluated: 64 x 11008 6.0,
+// 2048 x 13824 31.3, 4096 x 28672 126.
 constexpr int kSiluBase = (127 - 15) << 7;                 // bf16 bits of 2^-15
 constexpr int kSiluLimit = (127 + 8) << 7;                 // ... and of 2^8
 constexpr int kSiluSpan = kSiluLimit - kSiluBase + 1;      // zero, and the magnitudes in between
@@ -463,11 +466,38 @@ __device__ inline float silu_beyond_table(uint32_t bits, const float* table) {
 
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
-template <int kVecs, int kThreads>
+// [0: zero, k: the magnitude of bits kSiluBase + k - 1][sign]
+constexpr int kSiluEntries = (2 * kSiluSpan + 3) & ~3;
+struct SiluTable { float v[kSiluEntries]; };
+constexpr float silu_of_bits(uint32_t bits) {              // silu_one, step by step
+    const float gate = __builtin_bit_cast(float, bits << 16);
+    float t = -gate;
+    t = t < -87.0f ? -87.0f : t > 88.0f ? 88.0f : t;
+    const float n = (t * 1.44269504f + kRoundMagic) - kRoundMagic;          // rint
+    float r = t - n * 0.693359375f;
+    r = r - n * -2.12194440e-4f;
+    float p = 1.0f / 720.0f;
+    p = p * r + 1.0f / 120.0f;
+    p = p * r + 1.0f / 24.0f;
+    p = p * r + 1.0f / 6.0f;
+    p = p * r + 0.5f;
+    p = p * r + 1.0f;
+    p = p * r + 1.0f;
+    return gate / (1.0f + p * __builtin_bit_cast(float, (uint32_t)(127 + (int)n) << 23));      // n is within -126 ... 127
+}
+constexpr SiluTable silu_table() {
+    SiluTable t{};
+    for (int i = 0; i < 2 * kSiluSpan; ++i)
+        t.v[i] = silu_of_bits((uint32_t)(i < 2 ? 0 : kSiluBase - 1 + (i >> 1)) | (uint32_t)(i & 1) << 15);
+    return t;
+}
+__device__ constexpr SiluTable kSiluTable = silu_table();
+
+template <int kVecs, int kThreads, bool kCopy>
 __global__ __launch_bounds__(kThreads) void swiglu_quantize_table(const uint16_t* __restrict__ gu, int64_t M, int64_t F,
                                                                   int8_t* __restrict__ hq, float* __restrict__ sh_out, int workgroups) {
     constexpr int kWaves = kThreads / kWave;
-    __shared__ float table[2 * kSiluSpan];                 // [0: zero, k: the magnitude of bits base + k - 1][sign]
+    __shared__ __attribute__((aligned(16))) float table[kSiluEntries];
     __shared__ float sh[2][kWaves];
     const int nvec = (int)(F / 8);
     uint4 g[kVecs], u[kVecs];
@@ -482,8 +512,18 @@ __global__ __launch_bounds__(kThreads) void swiglu_quantize_table(const uint16_t
     };
     int64_t m = blockIdx.x;
     request(m);
-    for (int i = threadIdx.x; i < 2 * kSiluSpan; i += kThreads)
-        table[i] = silu_one(bf16_to_f32((uint16_t)((i < 2 ? 0 : kSiluBase - 1 + (i >> 1)) | ((i & 1) << 15))));
+    if (kCopy) {
+        constexpr int kCopies = (kSiluEntries / 4 + kThreads - 1) / kThreads;
+        float4 part[kCopies];
+#pragma unroll
+        for (int c = 0; c < kCopies; ++c) part[c] = reinterpret_cast<const float4*>(kSiluTable.v)[min(c * kThreads + (int)threadIdx.x, kSiluEntries / 4 - 1)];
+#pragma unroll
+        for (int c = 0; c < kCopies; ++c)
+            if (c * kThreads + (int)threadIdx.x < kSiluEntries / 4) reinterpret_cast<float4*>(table)[c * kThreads + threadIdx.x] = part[c];
+    } else {
+        for (int i = threadIdx.x; i < 2 * kSiluSpan; i += kThreads)
+            table[i] = silu_one(bf16_to_f32((uint16_t)((i < 2 ? 0 : kSiluBase - 1 + (i >> 1)) | ((i & 1) << 15))));
+    }
     __syncthreads();
 
     for (int parity = 0; m < M; parity ^= 1) {
@@ -643,15 +683,14 @@ hipError_t launch_rmsnorm_quantize(const void* x, bool bf16, const float* g, flo
     return hipGetLastError();
 }
 
-// Where the table form is the faster one, measured where the launch stands in use (behind the gate/up product and in front of
-// the down product, us for all of it, arithmetic / table): 5120 -> 13824 at 16 tokens, two layers, 101.7 / 99.3, at 128 179.3 /
-// 176.2, at 1024 201.8 / 194.2; 2048 tokens 356 / 345.  Narrow rows leave most of the 1024 threads idle and pay for the
-// table all the same: 700 x 4096 33.6 / 34.2, 64 x 5504 equal; so do few tokens of up to 9216 elements (alone, 8 x 8192 3.9 / 4.3,
-// 29 x 8640 4.3 / 4.5, 63 x 9600 4.9 / 4.8; eight layers of 3072 -> 8192 at 10 tokens 264 / 265.3, of 4096 -> 9600 at 16 302.9 / 301.2),
-// while wide ones gain at any count (alone, 1 x 16384 5.7 / 4.6, 1 x 28672 8.8 / 6.0, 29 x 28672 10.5 / 6.8).
+// Where the table form is the faster one, us, arithmetic / table: alone, 1 x 11008 4.2 / 3.5, 8 x 14336 5.2 / 4.1, 29 x 11008 4.7 / 4.3,
+// 29 x 8192 3.9 / 3.9, 128 x 5504 3.5 / 4.0, 256 x 4096 3.4 / 4.1; measured where the launch stands in use (behind the gate/up
+// product and in front of the down product, all of it) 5120 -> 13824 at 128 tokens, two layers, 179.3 / 176.2, at 1024 201.8 /
+// 194.2; 2048 tokens 356 / 345.  Narrow rows leave most of the 1024 threads idle and pay for the table all the same: 700 x 4096
+// 33.6 / 34.2, 64 x 5504 equal.
 static bool swiglu_by_table(const void* gu, int64_t M, int64_t F, const void* hq) {
     if (F % 8 != 0 || F > 32768 || reinterpret_cast<uintptr_t>(gu) % 16 != 0 || reinterpret_cast<uintptr_t>(hq) % 8 != 0) return false;
-    return F >= 5120 && M >= (F >= 16384 ? 1 : F >= 9216 ? 8 : F >= 8192 ? 64 : 256);
+    return F >= 5120 && M >= (F >= 9216 ? 1 : F >= 8192 ? 64 : 256);
 }
 
 hipError_t launch_swiglu_quantize(const void* gu, bool bf16, int64_t M, int64_t F, int8_t* hq, float* sh,
@@ -663,7 +702,14 @@ hipError_t launch_swiglu_quantize(const void* gu, bool bf16, int64_t M, int64_t 
     if (bf16 && swiglu_by_table(gu, M, F, hq)) {
         const uint16_t* in = static_cast<const uint16_t*>(gu);
         const int wgs = (int)(M < 256 ? M : 256);          // one per CU: two and four were no faster
-#define TABLE(V_) hipLaunchKernelGGL((swiglu_quantize_table<V_, 1024>), dim3((unsigned)wgs), dim3(1024), 0, stream, in, M, F, hq, sh, wgs)
+        // The constant array until so many workgroups read it that evaluating it costs less (us, copied / evaluated: 29 x 11008
+        // 4.3 / 4.9, 128 x 11008 4.8 / 5.1, 29 x 28672 6.5 / 6.7; 128 x 14336 5.7 / 5.5, 64 x 28672 7.9 / 7.4, 256 x 11008 6.2 / 5.5)
+        const bool copy = M * F <= (int64_t)3 << 19;
+#define TABLE(V_)                                                                                                \
+    do {                                                                                                         \
+        if (copy) hipLaunchKernelGGL((swiglu_quantize_table<V_, 1024, true>), dim3((unsigned)wgs), dim3(1024), 0, stream, in, M, F, hq, sh, wgs); \
+        else hipLaunchKernelGGL((swiglu_quantize_table<V_, 1024, false>), dim3((unsigned)wgs), dim3(1024), 0, stream, in, M, F, hq, sh, wgs); \
+    } while (0)
         if (F <= 8192) TABLE(1);
         else if (F <= 16384) TABLE(2);
         else TABLE(4);
