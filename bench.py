@@ -127,17 +127,18 @@ def gemv_bytes(M, N, K, out_bytes=2):
 def measured_traffic(N, K, fused=True):
     """HBM bytes per launch of the M = 1 product on an N x K layer, from the committed rocprofv3 --pmc summary
     (profiles/hbm_traffic.json: FETCH_SIZE + WRITE_SIZE, each scaled by what the counter reads for a plain
-    256 MiB copy).  `fused`: the launch that quantizes x itself (fifth template parameter 2 or 3) or the one on int8
-    input (0 or 1).  None if the summary has no entry for this launch shape."""
+    256 MiB copy).  `fused`: the launch that quantizes x itself (linear_decode_2bit without a norm or a gate) or the one on int8
+    input (linear_gemv16_2bit, fifth template parameter 0 or 1).  None if the summary has no entry for this launch shape."""
     path = os.path.join(ROOT, "profiles", "hbm_traffic.json")
     if not os.path.exists(path):
         return None
     with open(path) as f:
         table = json.load(f)
     for key, v in table.get("kernels", {}).items():
-        if key.startswith("linear_gemv16_2bit<") and v.get("N") == N and v.get("K") == K:
-            params = key[key.index("<") + 1:key.index(">")].split(",")
-            if len(params) >= 6 and params[5].strip() == "false" and (int(params[4]) in (2, 3)) == fused:
+        name = "linear_decode_2bit" if fused else "linear_gemv16_2bit"
+        if key.startswith(name + "<") and v.get("N") == N and v.get("K") == K:
+            params = [p.strip() for p in key[key.index("<") + 1:key.index(">")].split(",")]
+            if params[7:9] == ["false", "false"] if fused else len(params) >= 6 and params[5] == "false" and params[4] in ("0", "1"):
                 return int(v["fetch_bytes"] + v["write_bytes"])
     return None
 
@@ -386,7 +387,7 @@ def decode_workload(torch, B, synth, gen, stream, args, workload):
             per_shape[name]["frac_of_plain_read_rate"] = round(floor["us_per_launch"] / per_shape[name]["us_per_launch"], 4)
     progress("%s: per-shape launches and the plain-read floor timed" % workload)
     roofline = {
-        "bound": "hbm", "kernel": "linear_gemv16_2bit", "shape": "%s K=%d N=%d M=%d" % (dname, dK, dN, M),
+        "bound": "hbm", "kernel": "linear_gemv16_2bit" if args.unfused else "linear_decode_2bit", "shape": "%s K=%d N=%d M=%d" % (dname, dK, dN, M),
         "achieved": d["GB/s"], "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": d["frac_hbm_peak"],
         "bytes_per_launch": d["bytes_per_launch"], "us_per_launch": d["us_per_launch"], "traffic": d["traffic"],
         "plain_read_of_the_same_weights": d.get("plain_read"), "frac_of_plain_read_rate": d.get("frac_of_plain_read_rate"),

@@ -1,5 +1,6 @@
 // Weight-streaming BitLinear kernel for decode (M <= 16; the batched-decode kernels for up to 64 tokens are in
-// linear_skinny.hip) on gfx950, with the fused activation quantization and its pre-operations.
+// linear_skinny.hip, the kernel of fused launches of up to four tokens in decode_kernel.hpp) on gfx950, with the fused activation
+// quantization and its pre-operations.
 //
 // They compute acc[m][n] = sum_k x_q[m][k] * Wt[n][k] exactly in int32 and
 // y = acc * gamma * s_x[m] / 127 (Sections 1-2 of arXiv 2402.17764).  At these M the cost is moving
@@ -713,7 +714,9 @@ static hipError_t dispatch16_int8(const void* x, const float* sx, const void* pa
     }
 }
 
-// x is quantized in the kernel (xmode: plain, after RMSNorm, after SwiGLU); sx is unused
+// x is quantized in the kernel (xmode: plain, after RMSNorm, after SwiGLU); sx is unused.  Plain and after RMSNorm, up to four tokens
+// come here only where decode_kernel.hpp does not take them (rows of more vectors than its threads hold, tokens beyond its LDS);
+// the figures of one token below were measured before it was there, and the same forms serve five to seven.
 static hipError_t dispatch16_fused(int xmode, const void* x, const void* packed, const float* gamma, int gstride, int64_t M,
                              int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, const float* gain, float eps,
                              LaunchPlan* plan) {

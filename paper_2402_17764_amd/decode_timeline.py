@@ -1,4 +1,5 @@
-"""Where the time of a decode launch goes: per-workgroup wall-clock stamps inside the M <= 16 decode kernel.
+"""Where the time of a decode launch goes: per-workgroup wall-clock stamps inside the M <= 16 decode kernel of linear_gemv.hip.
+Fused launches of up to four tokens have a kernel of their own (decode_kernel.hpp), so the fused form is stamped at five.
 
     python -m paper_2402_17764_amd.decode_timeline [70b|3b]
 
@@ -48,6 +49,10 @@ def instrumented_source():
     assert src.count(tail) == 1
     src = src.replace(tail, tail[:-1] + "    __builtin_amdgcn_s_waitcnt(0);\n    TS(7);\n}")
     src += '''
+namespace bitnet {      // never the kernel of up to four tokens
+bool launch_decode_fused(bool, bool, bool, const void*, const float*, float, const void*, const float*, int, int64_t, int64_t, int64_t, void*, OutType,
+                         hipStream_t, LaunchPlan*, hipError_t*) { return false; }
+}
 extern "C" int timeline_linear(const void* xq, const float* sx, const void* packed, const float* gamma, long long M, long long N,
                                long long K, void* y, void* stream) {
     return (int)bitnet::launch_linear_gemv16_2bit((const int8_t*)xq, sx, packed, gamma, 0, M, N, K, y, bitnet::OutType::BF16, (hipStream_t)stream, nullptr);
@@ -99,14 +104,17 @@ def run(which="70b"):
             W = torch.randn((N, K), device="cuda", generator=g) * 0.02
             packs.append(B.quantize_weights(W))
             del W
-        x = torch.randn((1, K), device="cuda", generator=g).to(torch.bfloat16)
-        xq, sx = B.quantize_acts(x)
-        y = torch.empty((1, N), dtype=torch.bfloat16, device="cuda")
-        for fused in (True, False):
+        for (M, fused) in ((5, True), (1, False)):
+            if fused and M * (K + 255) // 256 * 256 > 60 * 1024:       # the tokens do not fit the kernel's LDS
+                continue
+            x = torch.randn((M, K), device="cuda", generator=g).to(torch.bfloat16)
+            xq, sx = B.quantize_acts(x)
+            y = torch.empty((M, N), dtype=torch.bfloat16, device="cuda")
+
             def launches(s):
                 for (p, gm) in packs:
-                    rc = (lib.timeline_linear_fused(x.data_ptr(), p.data_ptr(), gm.data_ptr(), 1, N, K, y.data_ptr(), s) if fused
-                          else lib.timeline_linear(xq.data_ptr(), sx.data_ptr(), p.data_ptr(), gm.data_ptr(), 1, N, K, y.data_ptr(), s))
+                    rc = (lib.timeline_linear_fused(x.data_ptr(), p.data_ptr(), gm.data_ptr(), M, N, K, y.data_ptr(), s) if fused
+                          else lib.timeline_linear(xq.data_ptr(), sx.data_ptr(), p.data_ptr(), gm.data_ptr(), M, N, K, y.data_ptr(), s))
                     assert rc == 0, rc
             st = torch.cuda.Stream()
             st.wait_stream(torch.cuda.current_stream())
@@ -134,9 +142,9 @@ def run(which="70b"):
             t = buf.reshape(8192, 8).astype(np.int64)
             t = t[: int((t[:, 0] != 0).sum())]
             r = (t - t[:, 0].min()) * 10.0                              # the wall clock ticks at 100 MHz
-            form = B.entry_describe(B.ENTRY_LINEAR_FUSED if fused else B.ENTRY_LINEAR, 1, N, K)
-            print("%s %d -> %d, M = 1, %s, form %s: %.2f us per launch (instrumented), %d workgroups; ns after the launch's first workgroup started"
-                  % (name, K, N, "bf16 x quantized in the launch" if fused else "int8 x", form["params"], us, len(t)))
+            form = B.entry_describe(B.ENTRY_LINEAR_FUSED if fused else B.ENTRY_LINEAR, M, N, K)
+            print("%s %d -> %d, M = %d, %s, form %s: %.2f us per launch (instrumented), %d workgroups; ns after the launch's first workgroup started"
+                  % (name, K, N, M, "bf16 x quantized in the launch" if fused else "int8 x", form["params"], us, len(t)))
             for k, nm in enumerate(NAMES):
                 if nm and (t[:, k] != 0).all():
                     v = r[:, k]
