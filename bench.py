@@ -391,7 +391,7 @@ def decode_workload(torch, B, synth, gen, stream, args, workload):
         "achieved": d["GB/s"], "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": d["frac_hbm_peak"],
         "bytes_per_launch": d["bytes_per_launch"], "us_per_launch": d["us_per_launch"], "traffic": d["traffic"],
         "plain_read_of_the_same_weights": d.get("plain_read"), "frac_of_plain_read_rate": d.get("frac_of_plain_read_rate"),
-        "traffic_source": "profiles/hbm_traffic.json: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this benchmark, "
+        "traffic_source": "profiles/hbm_traffic.json: rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE runs of this launch, "
                           "committed with the tree (not re-measured in this run)",
     }
     return {
