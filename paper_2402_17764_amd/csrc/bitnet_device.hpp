@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "byte_window.hpp"
+
 namespace bitnet {
 
 constexpr int kWave = 64;              // CDNA wavefront width
@@ -53,24 +55,17 @@ __device__ inline uint4 shift_down16(uint4 v, int n) {
 }
 
 // The same for a row-major matrix of int8 from its byte `first` on (`left` bytes to its end): pieces of 16 bytes at any offset, each
-// one unconditional load -- a load under a condition makes every later wait a wait for all that are in flight.  A piece that would
-// run out of the matrix is read from its last 16 bytes, and placed() moves it to where it belongs; bytes beyond the end are zero
+// one unconditional load -- a load under a condition makes every later wait a wait for all that are in flight.  Where a piece is
+// read from is ByteSpan's rule; placed() moves one that was pulled back to where it belongs, and bytes beyond the end are zero
 // then.  A matrix of less than 16 bytes takes load_any16.
-struct ByteWindow {
+struct ByteWindow : ByteSpan {
     const int8_t* base;
-    int lead, bytes;
-    __device__ ByteWindow(const int8_t* x, int64_t first, int64_t left) {
-        lead = first >= 16 ? 16 : 0;                     // so that 16 bytes precede the end
-        base = x + (first - lead);
-        bytes = (int)(left + lead < 1 << 30 ? left + lead : 1 << 30);
-    }
-    __device__ bool whole() const { return bytes >= 16; }
-    __device__ int at(int off) const { return min(lead + off, bytes - 16); }
+    __device__ ByteWindow(const int8_t* x, int64_t first, int64_t left) : ByteSpan(first, left), base(x + (first - lead)) {}
     __device__ uint4 load(int off) const {
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<int8_t*>(base), 0, bytes, 0x00020000 /* raw, 32-bit */);
         return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, at(off), 0, 0));
     }
-    __device__ uint4 placed(uint4 v, int off) const { return shift_down16(v, lead + off - at(off)); }
+    __device__ uint4 placed(uint4 v, int off) const { return shift_down16(v, moved(off)); }
 };
 
 // bf16 bit pattern -> fp32 (exact).

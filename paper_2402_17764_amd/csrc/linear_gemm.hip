@@ -271,6 +271,7 @@ __device__ __forceinline__ void gemm_tile(
     // (300 x 500 x 1001 10.9 us with loads under a condition, 8.5 with these; 77 x 1003 x 2050 8.0 / 7.1, 200 x 1500 x 3001 15.6 / 14.1)
     uint4 xr[kAny ? kCopies : 1];
     const ByteWindow xw(xq, (int64_t)row0 * K, ((int64_t)M - row0) * K);
+    const bool pulls_back = xw.pulls_back(rows_here, (int)K);
     auto fetch_x = [&](int step) {
         if (xw.whole()) {
 #pragma unroll
@@ -282,7 +283,7 @@ __device__ __forceinline__ void gemm_tile(
         }
     };
     auto put_x = [&](int step, int stage) {
-        if (step == steps - 1 && row0 + kGemmBM >= M && xw.whole()) {             // the end of x_q
+        if (step == steps - 1 && pulls_back && xw.whole()) {                      // pieces at the end of x_q
 #pragma unroll
             for (int t = 0; t < (kAny ? kCopies : 0); ++t) xr[t] = xw.placed(xr[t], (int)xoff[t] + step * 256);
         }
