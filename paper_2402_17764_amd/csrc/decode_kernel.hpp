@@ -379,7 +379,7 @@ hipError_t launch_decode(const DecodeForm& f, const DecodeCall& c) {
         SHAPE(2, 4, 1, 2, 1, 8);
         SHAPE(2, 8, 1, 2, 9, 64);
         SHAPE(2, 4, 2, 2, 5, 64);
-        SHAPE(2, 4, 3, 2, 24, 64);
+        SHAPE(2, 4, 3, 2, 24, 96);                     // twelve waves hold rows of 96 steps
         SHAPE(2, 1, 4, 4, 1, 23);
         SHAPE(2, 1, 4, 5, 5, 23);
         SHAPE(2, 1, 8, 4, 1, 64);

@@ -71,9 +71,20 @@ def test_fused_decode_launches_stay_in_bounds_and_read_the_matrix_once(entry):
         M, bf16 = rng.choice([1, 1, 2, 3, 4]), rng.random() < 0.6
         N = rng.choice([16, 96, 256, 1504, 4096, 4112, 8192, 8208, 9600, 11008, 16384, 16400, 24576, 32768, 32784, 40000, 49152, 49168, 57344])
         N = N if entry.endswith("pair") else N - rng.choice([0, 0, 1, 15])
-        K = 16 * rng.choice([1, 4, 5, 16, 17, 48, 64, 65, 80, 100, 128, 129, 144, 160, 200, 256, 257, 320, 368, 400, 512, 513, 540, 688, 750, 768, 1024, 1025, 1792])
+        K = 16 * rng.choice([1, 4, 5, 16, 17, 48, 64, 65, 80, 100, 128, 129, 144, 160, 200, 256, 257, 320, 368, 400, 512, 513, 540, 688, 750, 768, 1024, 1025, 1153, 1280, 1536, 1792])
         if 512 + M * ceil_div(K, 256) * 256 <= 65536:
             seen.add(check(entry, bf16, M, N, K))
     forms = {f[2:6] for f in seen if f}
     assert len(forms) >= (8 if entry.endswith("pair") else 13), sorted(forms)
     assert {f[6] for f in seen if f} == {1, 2, 3, 4} and {f[7] for f in seen if f} == {1, 2, 4} and None in seen
+
+
+@pytest.mark.parametrize("entry", list(ENTRIES))
+def test_every_size_that_fits_is_served(entry):
+    """what the acceptance rule lets through has a kernel: every K step with its first and last K, in every class of row blocks"""
+    for rb in (1, 256, 257, 400, 512, 513, 640, 641, 1024, 1025, 2048, 2049, 3072, 3073, 4096):
+        for M in (1, 2, 3, 4):
+            for steps in range(1, (65536 - HEADER) // (256 * M) + 1):
+                for K in (256 * steps - 240, 256 * steps):
+                    for dtype in (B.BF16, B.F32):
+                        B.entry_describe(ENTRIES[entry], M, 16 * rb, K, x_dtype=dtype)          # raises for an error status

@@ -3,6 +3,7 @@ steps where the selection changes, remainders of both, the last vectors a thread
 serve more tokens or int8 input, which the oracle pins."""
 import pytest
 
+import oracle
 from paper_2402_17764_amd import binding as B
 
 pytestmark = pytest.mark.gpu
@@ -53,3 +54,16 @@ def test_pairs(gpu_lib, F, K, bf16):
             for M in (1, 2, 3, 4):
                 print("pairs", M, F, K, bf16, norm, h, flush=True)
                 assert torch.equal(B.ffn_gate_up_fused(x[:M].contiguous(), *w, F, norm=norm, g=g, eps=1e-6, gamma_per_block=seg, h_dtype=h), want[:M])
+
+
+@pytest.mark.parametrize("F,K", [(8208, 18448), (11008, 20480), (16384, 24576)])
+def test_pairs_of_rows_beyond_64_steps(gpu_lib, F, K):
+    """the most vectors a thread of twelve waves holds: the gate applied to the outputs of the plain fused launch, bit for bit"""
+    x, w, gain = inputs(2, 2 * F, K, True, False)
+    for M in (1, 2):
+        xm = x[:M].contiguous()
+        for norm in (False, True):
+            print("long pairs", M, F, K, norm, flush=True)
+            y = B.rmsnorm_linear_fused(xm, gain, 1e-6, *w, 2 * F) if norm else B.linear_fused(xm, *w, 2 * F)
+            h = B.ffn_gate_up_fused(xm, *w, F, norm=norm, g=gain if norm else None, eps=1e-6)
+            assert h.cpu().numpy().tobytes() == oracle.swiglu_quantize(y.cpu().numpy())[2].tobytes()
