@@ -49,11 +49,11 @@ def _check_no_scratch(src, stderr):
         raise RuntimeError("%s: kernels that count loads in flight must not spill: %s" % (src, ", ".join(bad)))
 
 
-def skinny_instantiations(source_text):
+def skinny_instantiations(source_text, macro="SKINNY"):
     """The linear_skinny_2bit<kMT, kR, kW, kS, kD, kLx> instantiations that the launcher dispatches: every
-    `SKINNY(a, b, c, d, e, f)` use in the source."""
+    `SKINNY(a, b, c, d, e, f)` use in the source (SKINNY_WS: those of the form with a loader wave)."""
     return sorted({tuple(int(v) for v in m.groups())
-                   for m in re.finditer(r"\bSKINNY\((\d+), (\d+), (\d+), (\d+), (\d+), (\d+)\)", source_text)})
+                   for m in re.finditer(r"\b%s\((\d+), (\d+), (\d+), (\d+), (\d+), (\d+)\)" % macro, source_text)})
 
 
 def check_issue_order(asm_text, expected):
@@ -98,14 +98,72 @@ def check_issue_order(asm_text, expected):
     return checked
 
 
+def lds_reads_at_barriers(asm_text):
+    """For every batched-decode kernel in the assembly the most LDS reads that can be outstanding at one of its barriers, over all
+    paths: {(has a loader wave, parameters): reads}.  A ds_read adds one, s_waitcnt lgkmcnt(n) leaves n at most."""
+    found = {}
+    for m in re.finditer(r"^_ZN6bitnet\d+linear_skinny(_ws)?_2bitI((?:Li\d+E)+)E\S*:[^\n]*\n(.*?)^\.Lfunc_end", asm_text, re.M | re.S):
+        code = []                              # (kind, operand)
+        for line in m.group(3).splitlines():
+            line = line.split(";")[0].strip()
+            label, op = re.match(r"(\.LBB\w+):", line), line.split(" ")[0].split("\t")[0]
+            wait = re.search(r"lgkmcnt\((\d+)\)", line)
+            if label:
+                code.append(("label", label.group(1)))
+            elif op.startswith("ds_read"):
+                code.append(("read", None))
+            elif op == "s_waitcnt" and wait:
+                code.append(("wait", int(wait.group(1))))
+            elif op == "s_barrier":
+                code.append(("barrier", None))
+            elif op in ("s_branch", "s_endpgm") or op.startswith("s_cbranch"):
+                code.append((op[2:], line.split()[-1]))
+        at = {operand: i for i, (kind, operand) in enumerate(code) if kind == "label"}
+        entry, work, most = {0: 0}, [0], 0
+        while work:                            # states grow up to the counter's limit: this ends
+            i = work.pop()
+            n = entry[i]
+            while i < len(code):
+                kind, operand = code[i]
+                n = min(n + 1, 15) if kind == "read" else min(n, operand) if kind == "wait" else n
+                most = max(most, n) if kind == "barrier" else most
+                if "branch" in kind and entry.get(at[operand], -1) < n:
+                    entry[at[operand]] = n
+                    work.append(at[operand])
+                if kind in ("branch", "endpgm"):
+                    break
+                i += 1
+                if i < len(code) and code[i][0] == "label":
+                    if entry.get(i, -1) >= n:
+                        break
+                    entry[i] = n
+        found[(bool(m.group(1)), tuple(int(v) for v in re.findall(r"Li(\d+)E", m.group(2))))] = most
+    return found
+
+
+def check_lds_reads(asm_text, plain, loader):
+    """A barrier of the batched-decode kernels gives the LDS stage that was read in front of it to the next copy: no read of it may
+    be outstanding there, in any dispatched instantiation."""
+    found = lds_reads_at_barriers(asm_text)
+    missing = {(False, p) for p in plain} | {(True, p) for p in loader}
+    if set(found) != missing:
+        raise RuntimeError("batched decode: LDS reads checked for %s, dispatched %s" % (sorted(found), sorted(missing)))
+    bad = sorted(k for k, n in found.items() if n)
+    if bad:
+        raise RuntimeError("batched decode: LDS reads outstanding at a barrier that frees their stage: %s" % bad)
+    return found
+
+
 def _check_issue_order(src):
-    """Runs check_issue_order on the assembly that -save-temps left next to the object: the very text the device
-    code of the shipped object was assembled from."""
-    asm = os.path.join(BUILD, os.path.splitext(src)[0] + "-hip-amdgcn-amd-amdhsa-gfx950.s")
-    expected = skinny_instantiations(open(os.path.join(CSRC, src)).read())
+    """Runs the checks on the assembly that -save-temps left next to the object: the very text the device code of the
+    shipped object was assembled from."""
+    asm = open(os.path.join(BUILD, os.path.splitext(src)[0] + "-hip-amdgcn-amd-amdhsa-gfx950.s")).read()
+    source = open(os.path.join(CSRC, src)).read()
+    expected = skinny_instantiations(source)
     if not expected:
         raise RuntimeError("%s: no SKINNY(...) dispatch found: the issue-order check has nothing to go by" % src)
-    check_issue_order(open(asm).read(), expected)
+    check_issue_order(asm, expected)
+    check_lds_reads(asm, expected, skinny_instantiations(source, "SKINNY_WS"))
 
 
 # Host code with the undefined-behaviour sanitizer compiled in as traps (no runtime library to load): signed overflow,

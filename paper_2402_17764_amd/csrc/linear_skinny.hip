@@ -445,9 +445,13 @@ __global__ __launch_bounds__((kS * kW + 1) * kWave) void linear_skinny_ws_2bit(
         uint4 wst[kD][kR];
 #pragma unroll
         for (int d = 0; d < kD; ++d) load_w(wst[d], d);
-        auto meet = [] {                               // stage i is complete, and this wave's reads of stage i - 1 stay ahead
+        // Stage i is complete, and this wave's reads of stage i - 1 have returned: behind the barrier the loader writes there.  That
+        // they are issued in front of it is not enough -- the MFMAs that consume them, and with those the compiler's own waits,
+        // may move across.  The wait counts LDS operations alone: the weights stay in flight.
+        auto meet = [] {
             asm volatile("" ::: "memory");
             __builtin_amdgcn_sched_barrier(0xF);
+            __builtin_amdgcn_s_waitcnt(0xC07F);        // lgkmcnt(0)
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0xF);
             asm volatile("" ::: "memory");

@@ -1,7 +1,8 @@
 """The build's guard for linear_skinny_2bit (csrc/linear_skinny.hip): that kernel retires its LDS-DMA copies with a
 counted s_waitcnt, which is right only while copies and weight loads are issued in source order.  The guard reads the
 device assembly the shipped object was assembled from; here its parser is run on canned text, good and bad, and on the
-assembly of the current build."""
+assembly of the current build.  So is the one that finds LDS reads outstanding at a barrier: behind it the next copy is
+written to the stage that they read."""
 import os
 
 import pytest
@@ -59,3 +60,35 @@ def test_current_build_passes_the_guard():
     src = open(os.path.join(Bld.CSRC, "linear_skinny.hip")).read()
     checked = Bld.check_issue_order(open(asm).read(), Bld.skinny_instantiations(src))
     assert sorted(checked) == Bld.skinny_instantiations(src)
+    loader = Bld.skinny_instantiations(src, "SKINNY_WS")
+    reads = Bld.check_lds_reads(open(asm).read(), Bld.skinny_instantiations(src), loader)
+    assert len(reads) == len(checked) + len(loader) and not any(reads.values())
+
+
+def _waits(body, name="linear_skinny_ws_2bit", params=(4, 2, 3, 1, 4, 2)):
+    head = "_ZN6bitnet%d%sILi%sEEEvPKa:                  ; @kernel\n; %%bb.0:\n" % (len(name), name, "ELi".join(str(p) for p in params))
+    lines = {"R": "\tds_read_b128 v[0:3], v4 offset:16", "0": "\ts_waitcnt vmcnt(3) lgkmcnt(0)", "1": "\ts_waitcnt lgkmcnt(1)", "v": "\ts_waitcnt vmcnt(0)",
+             "B": "\ts_barrier", "L": ".LBB0_1:                                ; =>This Inner Loop", "J": "\ts_cbranch_scc1 .LBB0_1",
+             "S": "\ts_cbranch_execz .LBB0_2", "T": ".LBB0_2:", "E": "\ts_endpgm"}
+    return head + "\n".join(lines[c] for c in body) + "\n.Lfunc_end0:\n"
+
+
+@pytest.mark.parametrize("body,reads", [
+    ("RR0BE", 0), ("RR1BE", 1), ("RRvBE", 2), ("BRR0E", 0),
+    ("LBRR0JE", 0),                        # a loop that waits before it comes round
+    ("LBRR1JE", 1),                        # ... and one whose barrier meets a read of the round before
+    ("RSR0TBE", 1),                        # a branch past the wait
+    ("RS0TR0BE", 0),
+])
+def test_outstanding_lds_reads_are_found_on_every_path(body, reads):
+    p = (4, 2, 3, 1, 4, 2)
+    assert Bld.lds_reads_at_barriers(_waits(body)) == {(True, p): reads}
+    if reads:
+        with pytest.raises(RuntimeError):
+            Bld.check_lds_reads(_waits(body), [], [p])
+    else:
+        Bld.check_lds_reads(_waits(body), [], [p])
+        with pytest.raises(RuntimeError):                  # an instantiation that the assembly does not hold, one that nobody asked for
+            Bld.check_lds_reads(_waits(body), [p], [p])
+        with pytest.raises(RuntimeError):
+            Bld.check_lds_reads(_waits(body), [], [])
