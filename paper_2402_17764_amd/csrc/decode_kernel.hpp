@@ -379,7 +379,9 @@ hipError_t launch_decode(const DecodeForm& f, const DecodeCall& c) {
         SHAPE(2, 4, 1, 2, 1, 8);
         SHAPE(2, 8, 1, 2, 9, 64);
         SHAPE(2, 4, 2, 2, 5, 64);
-        SHAPE(2, 4, 3, 2, 24, 96);                     // twelve waves hold rows of 96 steps
+        SHAPE(2, 4, 3, 2, 24, 96);                     // twelve waves hold rows of 96 steps, sixteen of 128
+        SHAPE(2, 2, 4, 4, 24, 64);
+        SHAPE(2, 4, 4, 2, 33, 128);
         SHAPE(2, 1, 4, 4, 1, 23);
         SHAPE(2, 1, 4, 5, 5, 23);
         SHAPE(2, 1, 8, 4, 1, 64);
@@ -399,6 +401,9 @@ hipError_t launch_decode(const DecodeForm& f, const DecodeCall& c) {
         SHAPE(1, 2, 4, 4, 5, 64);
         SHAPE(1, 1, 8, 4, 1, 64);
         SHAPE(1, 1, 8, 5, 5, 64);
+        SHAPE(1, 1, 12, 4, 24, 96);
+        SHAPE(2, 1, 8, 2, 1, 3);
+        SHAPE(2, 1, 8, 4, 24, 64);
     }
 #undef SHAPE
     return hipErrorInvalidDeviceFunction;

@@ -10,9 +10,9 @@ pytestmark = pytest.mark.gpu
 
 torch = pytest.importorskip("torch")
 
-# N x K (the pair: F x K): rb 2 ... 3126 row blocks, 1 ... 64 steps
+# N x K (the pair: F x K): 2 ... 3126 row blocks, 1 ... 64 steps
 SHAPES = [(17, 16), (250, 2048), (4096, 2064), (4090, 4096), (100, 4112), (300, 8640), (33, 12304), (4112, 1024), (8192, 1040), (8190, 2048), (5000, 2064),
-          (8192, 5120), (8208, 1024), (9600, 2560), (9600, 3200), (16384, 4112), (16400, 272), (20000, 5120), (32784, 1280), (33000, 6144), (49168, 528), (50001, 2576)]
+          (8192, 5120), (8208, 1024), (9600, 2560), (9600, 3200), (16384, 4112), (16400, 272), (20000, 5120), (32784, 1280), (33000, 6144), (49168, 528), (50001, 2576), (50001, 6160)]
 
 
 def inputs(M, N, K, bf16, seg):
@@ -43,7 +43,7 @@ def test_rows(gpu_lib, N, K, bf16):
 
 
 @pytest.mark.parametrize("bf16", [True, False])
-@pytest.mark.parametrize("F,K", [(N // 16 * 16, K) for (N, K) in SHAPES if N <= 33000 and 5 * K <= 64000] + [(8640, 8208), (1504, 9216), (4096, 6144)])
+@pytest.mark.parametrize("F,K", [(N // 16 * 16, K) for (N, K) in SHAPES if N <= 33000 and 5 * K <= 64000] + [(8640, 8208), (1504, 9216), (4096, 6144), (12320, 6160), (12320, 8208)])
 def test_pairs(gpu_lib, F, K, bf16):
     """five tokens go through the kernel that serves more than four: their first rows"""
     seg = F % 64 == 0
@@ -58,9 +58,12 @@ def test_pairs(gpu_lib, F, K, bf16):
 
 @pytest.mark.parametrize("F,K", [(8208, 18448), (11008, 20480), (16384, 24576)])
 def test_pairs_of_rows_beyond_64_steps(gpu_lib, F, K):
-    """the most vectors a thread of twelve waves holds: the gate applied to the outputs of the plain fused launch, bit for bit"""
-    x, w, gain = inputs(2, 2 * F, K, True, False)
-    for M in (1, 2):
+    """the most vectors a thread of twelve or sixteen waves holds, and three tokens beyond that: the gate applied to the outputs of the
+    plain fused launch, bit for bit"""
+    x, w, gain = inputs(3, 2 * F, K, True, False)
+    for M in (1, 2, 3):
+        if 512 + M * ((K + 255) // 256) * 256 > 65536:
+            continue
         xm = x[:M].contiguous()
         for norm in (False, True):
             print("long pairs", M, F, K, norm, flush=True)
