@@ -570,22 +570,64 @@ static void launch_trit5(const int8_t* xq, const float* sx, const void* packed, 
                        static_cast<const uint4*>(packed), gamma, sx, y, (int)N, (int)K, product_flags(0, yt) | (uint32_t)M << 4);
 }
 
-// Where the quotients are the faster form, and in which launch shape (128 shapes of 38 ... 1400 row blocks, 3 ... 25 steps, 1 ... 16
-// tokens, and larger ones; us, table / quotients): narrow layers with a long K (600 x 8000, one token 4.65 / 4.40, four on 2048 x
-// 8000 5.02 / 4.90, but 2048 x 2560 3.02 / 3.43: staging x_q costs more than the look-ups), and from 512 row blocks on all but short
-// walks of few tokens (9600 x 2560 4.29 / 4.60, 9600 x 4160 6.10 / 5.56, four on 16384 x 8000 13.1 / 9.6, sixteen 22.1 / 13.2, on
-// 57344 x 8192 47.8 / 34.9).  x_q has to fit the LDS.
+// Where the quotients are the faster form, and in which launch shape (six choices over 22 widths of 200 ... 5000 row blocks, 1 ... 30
+// steps, eight token counts; us, table / quotients).  What decides:
+//   * the table's time grows with every token, the quotients' with every group of eight: 8 or 16 tokens go to the quotients earlier
+//     than 5 or 9 do (16480 x 2496, nine tokens 6.2 / 7.6, sixteen 7.5 / 7.7; 40000 x 7616 21.3 / 25.4, 29.0 / 31.0);
+//   * staging x_q and its sums come in front of the first product, so short walks on few row blocks stay with the table (4320 x 2496,
+//     nine tokens 4.0 / 4.7; 8320 x 2496, five 4.3 / 5.1), and long ones leave it (600 x 8000, one token 4.7 / 4.4; 16384 x 8000, four
+//     13.1 / 9.6, sixteen 22.1 / 13.2; 57344 x 8192, sixteen 47.8 / 34.9);
+//   * a launch takes as long as its fullest CU: eight row blocks per workgroup up to 2048, where that is one workgroup each, and from
+//     3072; in between the table's workgroups are dealt out more evenly, and with few tokens in the last group it wins (32960 x 9536,
+//     nine tokens 24.7 / 34.3), else four row blocks with K split in two take half the step from one round to the next;
+//   * the table walks whole rounds of four steps on wide layers: there its best counts are four and eight.
+// The picks are within 5 % of the faster of table and previous picks wherever measured.  x_q has to fit the LDS.
 struct QuotientForm { int s, w, d; };                  // kS, kW, kD; none: s = 0
 static QuotientForm pick_quotients(int64_t M, int64_t RB, int64_t steps) {
-    if (RB <= 256) return M <= 8 && steps >= 20 ? QuotientForm{8, 1, 2} : QuotientForm{0, 0, 0};
+    constexpr QuotientForm table{0, 0, 0}, eight{1, 8, 4}, four{2, 4, 2}, two{4, 2, 2}, one{4, 1, 2}, one_long{8, 1, 2};
+    if (RB <= 256) return M <= 8 && steps >= 20 && (M <= 4 || M > 6 || steps < 28) ? one_long : table;
     if (RB <= 512) {
-        if (M <= 4) return steps >= 20 ? QuotientForm{8, 1, 2} : QuotientForm{0, 0, 0};
-        return steps >= (M > 8 ? 8 : 10) ? QuotientForm{4, 2, 2} : QuotientForm{0, 0, 0};
+        if (M <= 4) return steps >= 20 ? one_long : table;
+        return steps >= (M > 12 || (M > 6 && M <= 8) ? 10 : 14) ? two : table;
     }
-    if (RB >= (M <= 4 ? 3072 : M <= 8 ? 2048 : 1025)) return {1, 8, 4};
-    if (M > 4 || RB >= 1536 || steps <= 4) return {2, 4, 2};
-    if (steps < 10 && RB <= 1024) return {0, 0, 0};
-    return M == 1 || steps < 20 ? QuotientForm{4, 1, 2} : QuotientForm{4, 2, 2};
+    if (RB <= 1024) {
+        const bool narrow = RB <= 768, middle = steps >= 6 && steps <= 8;
+        if (M <= 4) {
+            if (steps <= 4) return narrow ? one : four;
+            if (steps < 10) return table;
+            return M == 1 || steps < 20 ? one : two;
+        }
+        if (M <= 8) {
+            if (narrow && steps <= 5) return one;
+            if (narrow && M <= 6) return steps < 14 ? table : one_long;
+            return middle && (narrow || M <= 6) ? table : four;
+        }
+        if (M <= 10) return (narrow ? steps >= 4 && steps < 14 : middle) ? table : four;
+        return narrow && middle && M <= 12 ? table : four;
+    }
+    if (M <= 4) {
+        if (RB >= 3072) return eight;
+        if (RB > 2048 && steps == 4) return table;
+        if (RB >= 1536) return steps == 8 && RB < 1800 ? one : four;
+        if (steps <= 4) return four;
+        return M == 1 || steps < 20 ? one : two;
+    }
+    if (RB < 1536) {
+        if (M <= 8) return steps <= 3 ? eight : steps <= (M <= 6 ? 12 : 8) ? one : two;
+        if (M <= 10 && steps >= 5 && steps <= (RB <= 1280 ? 14 : 8)) return table;
+        return M <= 12 && steps >= 6 && steps <= 8 ? table : eight;
+    }
+    if (RB > 2048 && RB < 3072) {
+        if (steps <= 2) return eight;
+        if (steps == 4) return table;
+        if (M <= 8) return four;
+        if (M <= 12 && (RB <= 2816 || steps == 3)) return table;
+        if (steps <= 5) return eight;
+        if (M <= 10 && steps == 8) return table;
+        return M > 12 && RB <= 2816 && (steps == 8 || steps >= 16) ? table : four;
+    }
+    if (steps == 8 && (M == 9 || M == 10)) return table;
+    return steps == 4 && RB > 2048 && M > 8 && (M <= 12 || RB < 3600) ? table : eight;
 }
 constexpr int64_t kTritMaxLds = 160 * 1024;
 
@@ -606,7 +648,12 @@ static bool launch_quotients(const int8_t* xq, const float* sx, const void* pack
         return hipGetLastError();
     };
     static RaisedFlags one = {}, two = {};
-    *status = M <= 8 ? go(linear_quotients_trit5<kS, kW, kD, 1>, one) : go(linear_quotients_trit5<kS, kW, kD, 2>, two);
+    if (M <= 8) {
+        *status = go(linear_quotients_trit5<kS, kW, kD, 1>, one);
+    } else {
+        if constexpr (kW == 1) return false;               // not picked for two groups of eight tokens
+        else *status = go(linear_quotients_trit5<kS, kW, kD, 2>, two);
+    }
     return true;
 }
 
