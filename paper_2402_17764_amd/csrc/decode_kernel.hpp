@@ -171,7 +171,8 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_decode_2bit(
             for (int n = 1; n < kWaves; n *= 2)
 #pragma unroll
                 for (int w = 0; w + n < kWaves; w += 2 * n) S[w] += S[w + n];
-            decided = rms_from_rounded_sum(S[0], inv_K, eps, &rms[t]) && decided;
+            const bool here = rms_from_rounded_sum(S[0], inv_K, eps, &rms[t]);
+            decided = (here || t >= M) && decided;                      // the sum 0 of a token that is not there is undecided with eps = 0
         }
         if (__builtin_expect(!decided, 0)) {
             // the exact sums, from memory: nothing of this can be worked out ahead of the branch

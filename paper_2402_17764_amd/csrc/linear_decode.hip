@@ -23,8 +23,8 @@ static double walk(int steps, int kS, int kD) { return (double)steps / (double)(
 //     than 1024 row blocks, where every wave has work of its own anyhow (24576 x 4096 with the norm: 6.55, two K waves 6.92);
 //   * twelve row blocks per workgroup from 24 K steps on where eight would be more than 256 workgroups, as long as twelve are not (2049
 //     ... 3072 row blocks; two row blocks with K split over four waves are up to 1536 workgroups that quantize the tokens each for
-//     itself: 41600 x 6384 with the norm, one token 14.3 -> 13.7 us, four 42.4 -> 18.1; 48960 x 10224, one token 29.1 -> 21.4, four without
-//     the norm 32.3 -> 22.9);
+//     itself: 41600 x 6384 with the norm, one token 15.8 -> 14.6 us, four 42.4 -> 19.1; 48960 x 10224, one token 29.1 -> 21.8, four without
+//     the norm 32.4 -> 23.2);
 //   * two row blocks per wave, and so half as many workgroups that quantize, on more than 3072 row blocks: for three and four tokens
 //     of up to three steps, where quantizing is most of the launch, and from 24 steps on where the workgroups then fit one round (up
 //     to 4096; three and four tokens with the norm beyond that, too) (us, one row block per wave / this: 51200 x 240, four tokens 5.7 /

@@ -35,6 +35,8 @@ def test_rows(gpu_lib, N, K, bf16):
     for M in (1, 2, 3, 4):
         xm = x[4 - M:].contiguous()
         q, qn, qg = B.quantize_acts(xm), B.rmsnorm_quantize(xm, None, 1e-6), B.rmsnorm_quantize(xm, gain, 1e-5)
+        # eps = 0, with three tokens beside a fourth that is not there
+        assert torch.equal(B.rmsnorm_linear_fused(xm, gain, 0.0, *w, N, segmented=seg), lin(*B.rmsnorm_quantize(xm, gain, 0.0), *w, N))
         for y in (B.F32, B.BF16, B.I32):
             print("rows", M, N, K, bf16, y, flush=True)
             assert torch.equal(fused(xm, *w, N, y_dtype=y), lin(*q, *w, N, y_dtype=y))
