@@ -220,8 +220,8 @@ static_assert(kSumBlocks <= kPackThreads, "the packing pass folds one partial su
 // A chunk of W of rows x cols elements, read in 16-byte pieces that lie `from` bytes behind its first element.  kAny: rows may
 // start anywhere and end within a piece; the hardware takes 16-byte loads at element alignment.  Such a piece may run on into the
 // next row, and one that would run out of W is read from the last 16 bytes of it: a chunk that ends early moves the bytes back and
-// clears what is not its own (trimmed).  Otherwise the descriptor ends the rows and an offset out of its range the columns.  No load
-// depends on a condition: a wait for one of those is a wait for all that are in flight.
+// clears what is not its own (trimmed).  Otherwise the descriptor ends the rows.  Columns past the chunk's end are an offset out of its
+// range in both.  No load depends on a condition: a wait for one of those is a wait for all that are in flight.
 template <typename T, bool kAny>
 struct Chunk {
     static constexpr int kE = 16 / (int)sizeof(T);         // elements of a piece
@@ -240,7 +240,7 @@ struct Chunk {
     __device__ uint4 load(bool real, int from, int col) const {
         const int n = real && (!kAny || bytes >= 16) ? bytes : 0;
         const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(base), 0, n, 0x00020000 /* raw, 32-bit */);
-        const int off = kAny ? min(lead + from, n - 16) : col < cols ? from : 1 << 30;
+        const int off = col < cols ? (kAny ? min(lead + from, n - 16) : from) : 1 << 30;
         return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 2 /* nt: the last use */));
     }
     __device__ uint4 trimmed(uint4 v, int from, int row, int col) const {
