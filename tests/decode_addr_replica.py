@@ -27,24 +27,26 @@ class Span:
         return self.lo is None or (self.lo >= 0 and self.hi <= size)
 
 
-def any16_reads(start, avail):
-    """(first byte, bytes) of load_any16 at `start` with `avail` bytes left of x_q: sixteen, or byte by byte what there is"""
-    return start, np.clip(avail, 0, 16)
+def any16_reads(first, left, off):
+    """(first byte, bytes) of the 16-byte piece at `off` from byte `first` of x_q on, `left` bytes to its end: one that would run out
+    is pulled back to the last sixteen; an x_q of less than that is read byte by byte as far as it goes"""
+    lead = 16 if first >= 16 else 0
+    if left + lead < 16:
+        return first + off, np.clip(left - off, 0, 16)
+    return first - lead + np.minimum(lead + off, left + lead - 16), np.full_like(off, 16)
 
 
 def prefill_any_x_span(fm, M, K, bounded=True):
     """x_q bytes that a 32 fm-token tile of the prefill form for any rows reads, first and last tile, every K step (bounded=False:
-    as if each read were of sixteen bytes)."""
+    as if no piece were pulled back)."""
     sp, tokens = Span(), 32 * fm
     row, slot = np.arange(tokens, dtype=np.int64)[:, None], np.arange(16, dtype=np.int64)[None, :]
     last = (ceil_div(M, tokens) - 1) * tokens
     for row0 in {0, last}:
-        m = row0 + np.minimum(row, min(tokens, M - row0) - 1)
+        m = np.minimum(row, min(tokens, M - row0) - 1)
         for step in range(ceil_div(K, 256)):
-            col = step * 256 + ((slot ^ (row & 15)) << 4)
-            first, n = any16_reads(m * K + col, np.where(col < K, M * K - (m * K + col), 0))
-            if not bounded:
-                n = np.where(col < K, 16, 0)
+            off = m * K + step * 256 + ((slot ^ (row & 15)) << 4)
+            first, n = any16_reads(row0 * K, (M - row0) * K, off) if bounded else (row0 * K + off, np.full_like(off, 16))
             for nb in range(1, 17):
                 sp.add(first[n == nb], nb)
     return sp
@@ -106,7 +108,7 @@ def decode_launch_spans(kR, kS, kW, kD, xmode, pair, M, N, K, out_bytes=2, gstri
             rest = M - 16 * tile                                # tokens from the tile's first to the last of all
             v = np.arange(min(rest, 16) * (Kpad >> 4), dtype=np.int64)
             m, kv = v // (Kpad >> 4), v % (Kpad >> 4)
-            first, n = any16_reads(16 * tile * K + m * K + kv * 16, np.where(kv * 16 < K, (rest - m) * K - kv * 16, 0))
+            first, n = any16_reads(16 * tile * K, rest * K, m * K + kv * 16)
             for nb in range(1, 17):
                 sp["x"].add(first[n == nb], nb)
             sp["lds"].add(HEADER + 16 * v, 16)
