@@ -17,8 +17,9 @@
 //   * a wave's sums are one integer per lane (16 rows x up to 4 columns), folded and gated and stored by all lanes at once.
 // A wave issues an instruction every five clocks or so whatever it is, an address path takes a 1 KiB load every 16 to 45, and about
 // 32 KiB are in flight per CU: that is what the order of the prologue and the launch shapes (linear_decode.hip) go by.
-// Measured, HIP graphs over buffers beyond the caches, linear_gemv16_2bit in its best form -> this: 3B QKV with the norm
-// (9600 x 3200) 5.3 -> 3.3 us from its first workgroup's start to its last store, gate/up 7.6 -> 5.2, O 2.5 -> 2.2, down 3.4 -> 3.1;
+// Measured, HIP graphs over buffers beyond the caches: 3B QKV with the norm (9600 x 3200) 3.3 us from its first workgroup's start to
+// the median workgroup's last store, of which weights requested 0.4, sums of squares 0.7, absmax 1.2, x_q staged 1.4, products done
+// 2.6, folded 3.0; gate/up 5.2, O 2.2, down 2.8 (profiles/decode_m1_workgroup_timeline.txt).  linear_gemv16_2bit in its best form -> this,
 // back to back 300 x 512 3.5 -> 2.4 us, 4096 x 4096 3.5 -> 3.0, 9600 x 11008 11.1 -> 7.4, 57344 x 8192 with norm and gate 23.2 ->
 // 21.1 (117 MB: 5.6 TB/s); the 3B stack (104 launches) 593 -> 448 us.
 #pragma once

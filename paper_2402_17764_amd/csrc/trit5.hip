@@ -208,7 +208,9 @@ __global__ __launch_bounds__(kS * kWave, 4) void linear_gemv16_trit5(
 // ---------------------------------------------------------------------------------------------------
 // The kernel above is bound by its table: sixteen look-ups of eight bytes per 80 weights and lane, at random addresses of one 2 KB
 // table, 15 clocks of the CU's LDS each (27648 x 5120 at four tokens: 11.2 us for 28 MB, here 9.9; sixteen 18.4, here
-// 12.7; what bounds it now is the arithmetic, 74 vector instructions a chunk and lane).  Here no digit is ever formed.  With
+// 12.7).  What is left of the 9.9 us: the arithmetic, 74 vector instructions per lane and chunk of 5120 weights, is 4.2 of them (27
+// chunks a SIMD at five clocks an instruction), the bytes 5.5, and 432 workgroups on 256 CUs give 176 of them eight row blocks where
+// the mean is 6.75, each behind a staging of x_q.  Here no digit is ever formed.  With
 // f_d = floor(byte / 3^d) a digit is t_d = f_d - 3 f_(d+1), so
 //     sum_d x_d t_d  =  sum_(d = 0..4) x_d f_d  -  3 sum_(d = 1..4) x_(d-1) f_d,
 // and the quotients are small enough for int8 operands: f_0 is the byte itself (taken as byte - 128), f_1 <= 80, f_2 <= 26, f_3 <= 8,
