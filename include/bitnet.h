@@ -274,7 +274,9 @@ bitnet_status bitnet_linear_variant(const int8_t* xq, const float* sx, const voi
  *   families and their parameters:
  *     decode                 M <= 4: row blocks per wave, K waves, row slots, prefetch depth, x_q source (0 global, 1 LDS)
  *     batched_decode         5 ... 512 tokens: token tiles of 16, row blocks per wave, row slots, K groups, prefetch
- *     batched_decode_loader  depth, LDS lookahead (the second form has a wave that only copies activations)
+ *     batched_decode_loader  depth, LDS lookahead (the second form has a wave that only copies activations; in the first, where a
+ *                            workgroup has up to four row blocks or 32 x 96 outputs, every one of its K groups x row slots waves
+ *                            multiplies all of its row blocks for a share of the K steps)
  *     prefill                tile tokens, tile rows, and 2 as a third parameter for the eight-wave form with two
  *                            K groups (512 tile rows: the eight-wave form with two row groups); grid y = split-K factor
  *     decode_any             K not a multiple of 16: as decode, up to 16 tokens per workgroup (x_q source 8: rows of any

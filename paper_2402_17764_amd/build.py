@@ -15,7 +15,7 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libbitnet_hip.so")
 
-SOURCES = ["api.hip", "quant_weights.hip", "quant_acts.hip", "linear_ref.hip", "linear_gemv.hip", "linear_decode.hip", "linear_skinny.hip", "linear_gemm.hip", "trit5.hip", "static_scratch.hip"]
+SOURCES = ["api.hip", "quant_weights.hip", "quant_acts.hip", "linear_ref.hip", "linear_gemv.hip", "linear_decode.hip", "linear_skinny.hip", "linear_ksplit.hip", "linear_gemm.hip", "trit5.hip", "static_scratch.hip"]
 SOURCES += ["decode%s_%s.hip" % (k, t) for k in ("", "_norm", "_pair", "_norm_pair") for t in ("bf16", "f32")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -33,7 +33,7 @@ FLAGS = [
 
 # Kernels that count the vector-memory loads in flight (explicit s_waitcnt vmcnt(n)): a register spill would
 # add scratch loads to that count, so the build fails if the compiler gives any of them scratch memory.
-NO_SCRATCH = {"linear_skinny.hip": ("linear_skinny_2bit", "linear_skinny_ws_2bit")}
+NO_SCRATCH = {"linear_skinny.hip": ("linear_skinny_2bit", "linear_skinny_ws_2bit"), "linear_ksplit.hip": ("linear_ksplit_2bit",)}
 
 
 def _check_no_scratch(src, stderr):
@@ -154,11 +154,62 @@ def check_lds_reads(asm_text, plain, loader):
     return found
 
 
+def ksplit_instantiations(source_text):
+    """The linear_ksplit_2bit<kMT, kR, kW, kS, kQ> instantiations that the launcher dispatches: KSPLIT(kMT, kR, kW, kS, kLx) uses, kQ
+    slots of 16 tokens a wave."""
+    found = {tuple(int(v) for v in m.groups()) for m in re.finditer(r"\bKSPLIT\((\d+), (\d+), (\d+), (\d+), (\d+)\)", source_text)}
+    return sorted((mt, r, w, s, (lx + 1) * mt // w) for mt, r, w, s, lx in found)
+
+
+def check_ksplit_order(asm_text, expected):
+    """linear_ksplit_2bit waits for a tile's LDS copies with a count of the younger loads, of which there are at least that many only if the
+    loads are issued as in the source: the weights of the first step (W, kR kW of them) and the copies (L, four a tile) of the
+    first kQ tiles; in the loop a step's weights, then for each of its kMT tiles a wait that leaves the copies of kQ - 1 tiles and one step's
+    weights in flight, and the copies that take its slot; behind the loop the steps that the slots still reach, each wait with the copies
+    of the tiles behind it alone.  Raises unless the assembly of every instantiation reads so up to its first barrier."""
+    checked = []
+    for m in re.finditer(r"^_ZN6bitnet\d+linear_ksplit_2bitI((?:Li\d+E)+)E\S*:[^\n]*\n(.*?)^\.Lfunc_end", asm_text, re.M | re.S):
+        p = tuple(int(v) for v in re.findall(r"Li(\d+)E", m.group(1)))
+        kMT, kR, kW, _, kQ = p
+        rows, got, limit = kR * kW, "", None
+        for line in m.group(2).splitlines():
+            line = line.split(";")[0]
+            wait = re.search(r"vmcnt\((\d+)\)", line)
+            if "s_barrier" in line:
+                break
+            if wait:                           # the strictest of the waits in front of a tile's first read
+                limit = int(wait.group(1)) if limit is None else min(limit, int(wait.group(1)))
+            elif "buffer_load_dwordx4" in line:
+                got += "L" if re.search(r"\blds\b", line) else "W"
+                limit = None
+            elif "ds_read_b128" in line and limit is not None:
+                got += "<%d>" % limit
+                limit = None
+            if "v_mfma" in line:
+                limit = None
+        ahead = -(-kQ // kMT)
+        want = "W" * rows + "LLLL" * kQ + "W" * rows + ("<%d>LLLL" % (4 * (kQ - 1) + rows)) * kMT
+        for e in range(ahead - 1, -1, -1):
+            want += "W" * rows if e else ""
+            for t in range(kMT):
+                left = e * kMT + kMT - 1 - t
+                want += "<%d>" % (4 * min(left, kQ - 1)) + ("LLLL" if left >= kQ else "")
+        if got != want:
+            raise RuntimeError("linear_ksplit_2bit<%s>: loads and waits are %s, not %s" % (", ".join(map(str, p)), got, want))
+        checked.append(p)
+    if sorted(checked) != sorted(expected):
+        raise RuntimeError("linear_ksplit_2bit: checked %s, dispatched %s" % (sorted(checked), sorted(expected)))
+    return checked
+
+
 def _check_issue_order(src):
     """Runs the checks on the assembly that -save-temps left next to the object: the very text the device code of the
     shipped object was assembled from."""
     asm = open(os.path.join(BUILD, os.path.splitext(src)[0] + "-hip-amdgcn-amd-amdhsa-gfx950.s")).read()
     source = open(os.path.join(CSRC, src)).read()
+    if src == "linear_ksplit.hip":
+        check_ksplit_order(asm, ksplit_instantiations(source))
+        return
     expected = skinny_instantiations(source)
     if not expected:
         raise RuntimeError("%s: no SKINNY(...) dispatch found: the issue-order check has nothing to go by" % src)

@@ -218,7 +218,7 @@ static bitnet_status linear_any(const int8_t* xq, const float* sx, const void* p
     }
 
     if (which == BITNET_KERNEL_AUTO) {
-        if (bitnet::gemv_supports(M, N, K, xq)) which = BITNET_KERNEL_GEMV;
+        if (bitnet::gemv_chosen(M, N, K, xq)) return from_hip(bitnet::launch_linear_gemv_2bit(xq, sx, packed, gamma, gstride, M, N, K, y, yt, s));
         else if (bitnet::gemm_supports(M, N, K, xq)) which = BITNET_KERNEL_GEMM;
         else switch (any_rows_kernel(M, N, K)) {
             case AnyRows::Decode: return from_hip(bitnet::launch_linear_gemv_any_2bit(xq, sx, packed, gamma, gstride, M, N, K, y, yt, s));
@@ -325,7 +325,7 @@ bitnet_status bitnet_linear_ws(const int8_t* xq, const float* sx, const void* pa
     // kernels from 5 tokens on where they serve it, the prefill kernel otherwise (the M <= 4 decode kernel has no split form)
     const bool skinny_path = f == BITNET_PACK_2BIT && M > 4 && bitnet::gemv_supports(M, N, K, xq) &&
                              (force || (workspace && bitnet::skinny_splitk_splits(M, N, K) > 1));
-    const bool gemm_path = f == BITNET_PACK_2BIT && !skinny_path && (force || !bitnet::gemv_supports(M, N, K, xq)) &&
+    const bool gemm_path = f == BITNET_PACK_2BIT && !skinny_path && (force || !bitnet::gemv_chosen(M, N, K, xq)) &&
                            bitnet::gemm_supports(M, N, K, xq);
     if (!gemm_path && !skinny_path) {
         if (force) return BITNET_ERR_KERNEL;
@@ -376,7 +376,7 @@ bitnet_status bitnet_linear_describe(int64_t M, int64_t N, int64_t K, bitnet_for
     }
     if (f == BITNET_PACK_TRIT5) {
         plan.kernel = bitnet::gemv_trit5_supports(M < 16 ? M : 16, N, K, xq) ? "trit5_decode" : "trit5_reference";
-    } else if (bitnet::gemv_supports(M, N, K, xq)) {
+    } else if (bitnet::gemv_chosen(M, N, K, xq)) {
         const hipError_t e = bitnet::launch_linear_gemv_2bit(xq, fp, vp, fp, 0, M, N, K, vp, OutType::BF16, nullptr, ws, workspace_bytes,
                                                             0, &plan);
         if (e != hipSuccess) return BITNET_ERR_HIP;

@@ -95,6 +95,8 @@ struct LaunchPlan {
 
 // linear_gemv.hip
 bool gemv_supports(int64_t M, int64_t N, int64_t K, const void* xq);
+// where they are taken without being asked for: a few sizes more (beyond 256 tokens on a short K), which have no split-K form
+bool gemv_chosen(int64_t M, int64_t N, int64_t K, const void* xq);
 // workspace (may be null) and force_splits as for launch_linear_gemm_2bit: split-K of the batched-decode kernels
 // (4 < M <= 64); never taken by itself at present (skinny_splitk_splits() is 1 for every shape)
 int skinny_splitk_splits(int64_t M, int64_t N, int64_t K);
@@ -102,6 +104,10 @@ hipError_t launch_linear_gemv_2bit(const int8_t* xq, const float* sx, const void
                                    int gstride, int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream,
                                    void* workspace = nullptr, size_t workspace_bytes = 0, int force_splits = 0,
                                    LaunchPlan* plan = nullptr);
+// linear_ksplit.hip: tiles of 16 kmt tokens and `rows` row blocks per workgroup, K steps dealt out to its waves.  False (and nothing launched)
+// where no such form is built.
+bool launch_linear_ksplit_2bit(int kmt, int rows, const int8_t* xq, const float* sx, const void* packed, const float* gamma, int gstride, int64_t M,
+                               int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan, hipError_t* status);
 // the M <= 16 kernel alone (linear_gemv.hip); launch_linear_gemv_2bit (linear_skinny.hip) routes M <= 4 to it
 hipError_t launch_linear_gemv16_2bit(const int8_t* xq, const float* sx, const void* packed, const float* gamma, int gstride,
                                      int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan = nullptr);

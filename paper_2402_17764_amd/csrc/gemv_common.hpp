@@ -54,4 +54,52 @@ __device__ inline void store_row4(void* y, OutType yt, int64_t base, int64_t n0,
     }
 }
 
+// Waits until at most kN vector-memory loads are in flight: the oldest have arrived.
+template <int kN>
+__device__ inline void wait_loads() {                  // imm: vmcnt[3:0] | expcnt 7 << 4 | lgkmcnt 15 << 8 | vmcnt[5:4] << 14
+    __builtin_amdgcn_s_waitcnt((kN & 15) | 0x0F70 | ((kN >> 4) << 14));
+}
+// The outputs of a wave's kR row blocks and kMT token tiles: four consecutive ones of a token per lane, in one store where rows and
+// base allow it (flags_vec_store; N is then a multiple of four).  As four stores of two bytes, each behind its own choice of the
+// type, they were most of the 1.2 us between a 29-token launch's last product and its end.
+template <int kMT, int kR>
+__device__ inline void store_tiles(void* y, OutType yt, bool wide, int64_t N, int M, int rbw, const v4i (&acc)[kR][kMT], const float (&gm)[kR],
+                                   const float (&sxm)[kMT]) {
+    const int lane = threadIdx.x & (kWave - 1), r = lane & 15, g = lane >> 4;
+    auto each = [&](auto&& put) {
+#pragma unroll
+        for (int t = 0; t < kMT; ++t) {
+            const int m = 16 * t + r;                                  // MFMA output column = token
+            if (m >= M) continue;
+#pragma unroll
+            for (int a = 0; a < kR; ++a) {
+                const int64_t n0 = (int64_t)(rbw + a) * 16 + 4 * g;
+                if (n0 < N) put((int64_t)m * N + n0, n0, acc[a][t], (gm[a] * sxm[t]) / kQb);
+            }
+        }
+    };
+    // (>> 6 drops the decode factor 64, exactly)
+    if (!wide) each([&](int64_t at, int64_t n0, const v4i& v, float scale) { store_row4(y, yt, at, n0, N, v, scale); });
+    else if (yt == OutType::BF16)
+        each([&](int64_t at, int64_t, const v4i& v, float scale) {
+            const uint32_t a = f32_to_bf16((float)(v.x >> 6) * scale), b = f32_to_bf16((float)(v.y >> 6) * scale);
+            const uint32_t c = f32_to_bf16((float)(v.z >> 6) * scale), d = f32_to_bf16((float)(v.w >> 6) * scale);
+            *reinterpret_cast<uint2*>(static_cast<uint16_t*>(y) + at) = make_uint2(a | b << 16, c | d << 16);
+        });
+    else if (yt == OutType::F32)
+        each([&](int64_t at, int64_t, const v4i& v, float scale) {
+            *reinterpret_cast<float4*>(static_cast<float*>(y) + at) =
+                make_float4((float)(v.x >> 6) * scale, (float)(v.y >> 6) * scale, (float)(v.z >> 6) * scale, (float)(v.w >> 6) * scale);
+        });
+    else
+        each([&](int64_t at, int64_t, const v4i& v, float) {
+            *reinterpret_cast<int4*>(static_cast<int32_t*>(y) + at) = make_int4(v.x >> 6, v.y >> 6, v.z >> 6, v.w >> 6);
+        });
+}
+
+// four consecutive outputs from a multiple of four on are one aligned store
+inline bool wide_rows(const void* y, int64_t N, OutType yt) {
+    return N % 4 == 0 && reinterpret_cast<uintptr_t>(y) % (yt == OutType::BF16 ? 8 : 16) == 0;
+}
+
 }  // namespace bitnet

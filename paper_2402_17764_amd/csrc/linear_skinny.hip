@@ -34,54 +34,12 @@ namespace bitnet {
 // The last kD steps stand behind the loop and request nothing that is not there: with the loop's own prefetch a group of two
 // steps asked for four, and the end of the kernel waited for the two that nobody reads (29 tokens, 4096 -> 4096: twice the
 // traffic).  Fewer loads are then in flight behind the copy that a step waits for, last_younger() of them.
-template <int kN>
-__device__ inline void wait_loads() {                  // imm: vmcnt[3:0] | expcnt 7 << 4 | lgkmcnt 15 << 8 | vmcnt[5:4] << 14
-    __builtin_amdgcn_s_waitcnt((kN & 15) | 0x0F70 | ((kN >> 4) << 14));
-}
 // step d of the last kD: what was issued after its copy, in the steps -kLx ... -1 before it -- weights by those of the loop
 // (d < 0), copies by the ones whose target step exists
 constexpr int last_younger(int d, int kR, int kC, int kD, int kLx) {
     int n = 0;
     for (int t = d - kLx; t < d; ++t) n += (t < 0 ? kR : 0) + (t > d - kLx && t < kD - kLx ? kC : 0);
     return n;
-}
-
-// The outputs of a wave's kR row blocks and kMT token tiles: four consecutive ones of a token per lane, in one store where rows and
-// base allow it (flags_vec_store; N is then a multiple of four).  As four stores of two bytes, each behind its own choice of the
-// type, they were most of the 1.2 us between a 29-token launch's last product and its end.
-template <int kMT, int kR>
-__device__ inline void store_tiles(void* y, OutType yt, bool wide, int64_t N, int M, int rbw, const v4i (&acc)[kR][kMT], const float (&gm)[kR],
-                                   const float (&sxm)[kMT]) {
-    const int lane = threadIdx.x & (kWave - 1), r = lane & 15, g = lane >> 4;
-    auto each = [&](auto&& put) {
-#pragma unroll
-        for (int t = 0; t < kMT; ++t) {
-            const int m = 16 * t + r;                                  // MFMA output column = token
-            if (m >= M) continue;
-#pragma unroll
-            for (int a = 0; a < kR; ++a) {
-                const int64_t n0 = (int64_t)(rbw + a) * 16 + 4 * g;
-                if (n0 < N) put((int64_t)m * N + n0, n0, acc[a][t], (gm[a] * sxm[t]) / kQb);
-            }
-        }
-    };
-    // (>> 6 drops the decode factor 64, exactly)
-    if (!wide) each([&](int64_t at, int64_t n0, const v4i& v, float scale) { store_row4(y, yt, at, n0, N, v, scale); });
-    else if (yt == OutType::BF16)
-        each([&](int64_t at, int64_t, const v4i& v, float scale) {
-            const uint32_t a = f32_to_bf16((float)(v.x >> 6) * scale), b = f32_to_bf16((float)(v.y >> 6) * scale);
-            const uint32_t c = f32_to_bf16((float)(v.z >> 6) * scale), d = f32_to_bf16((float)(v.w >> 6) * scale);
-            *reinterpret_cast<uint2*>(static_cast<uint16_t*>(y) + at) = make_uint2(a | b << 16, c | d << 16);
-        });
-    else if (yt == OutType::F32)
-        each([&](int64_t at, int64_t, const v4i& v, float scale) {
-            *reinterpret_cast<float4*>(static_cast<float*>(y) + at) =
-                make_float4((float)(v.x >> 6) * scale, (float)(v.y >> 6) * scale, (float)(v.z >> 6) * scale, (float)(v.w >> 6) * scale);
-        });
-    else
-        each([&](int64_t at, int64_t, const v4i& v, float) {
-            *reinterpret_cast<int4*>(static_cast<int32_t*>(y) + at) = make_int4(v.x >> 6, v.y >> 6, v.z >> 6, v.w >> 6);
-        });
 }
 
 template <int kMT, int kR, int kW, int kS, int kD, int kLx>
@@ -522,8 +480,11 @@ constexpr int64_t kSkinnyMaxTokens = 512;      // beyond 64 tokens only where on
 //     at 256: 22.7 against 28.0 us).  Tiles of 32 tokens while six row blocks per workgroup suffice, else of 64:
 //     the measured best on 30 of 36 cases.  From 257 to 512 tokens the advantage remains only where K is long
 //     (K >= 5120: 7B down at 512 tokens 28.3 against 36.0 us; with K = 3200 the prefill kernel is 1.4x faster there).
+//   * Tiles of 80 tokens on four row blocks (linear_ksplit.hip) where those of 64 would need more than four and five sixths of the
+//     80-token tiles are tokens, no more of them padding than of the 64-token ones: 300 tokens, 11008 -> 4096 17.9 us, 64 x 6 22.4; 200 tokens,
+//     13824 -> 5120 20.8 / 27.3; 160 tokens, 8192 -> 8192 15.3 / 20.8; 300 tokens, 4096 -> 4096 9.6, the prefill kernel 12.5.
 // Returns false where these kernels should not run (above 64 tokens and no such launch); kmt and rpw are valid anyway.
-static bool skinny_shape(int64_t M, int64_t RBc, int* kmt_out, int* rpw_out) {
+static bool skinny_shape(int64_t M, int64_t RBc, int* kmt_out, int* rpw_out, bool tiles_of_80) {
     const int kmt_full = M <= 16 ? 1 : M <= 32 ? 2 : 4;            // the smallest tile that holds all tokens (64 at most)
     int kmt = kmt_full, rpw = 16;
     bool ok = true;
@@ -537,6 +498,10 @@ static bool skinny_shape(int64_t M, int64_t RBc, int* kmt_out, int* rpw_out) {
         if (c2 && c2 <= 6) { kmt = 2; rpw = c2; }
         else if (c4) { kmt = 4; rpw = c4; }
         else ok = false;
+        const int64_t of_80 = ceil_div(M, 80) * 80;
+        if (ok && tiles_of_80 && kmt == 4 && rpw > 4 && 6 * M >= 5 * of_80 && of_80 <= ceil_div(M, 64) * 64 && ceil_div(RBc, 4) * (of_80 / 80) <= 256) {
+            kmt = 5; rpw = 4;
+        }
     } else {
         for (const int c : {8, 6, 4, 2, 1})
             if (ceil_div(RBc, c) <= 256) rpw = c;
@@ -558,19 +523,26 @@ static bool skinny_shape(int64_t M, int64_t RBc, int* kmt_out, int* rpw_out) {
     return ok;
 }
 
-bool gemv_supports(int64_t M, int64_t N, int64_t K, const void* xq) {
-    // x_q offsets are 32-bit; one K step of the packed weights (1 KiB per 16-row block) is addressed as one raw buffer
-    if (!(M >= 1 && M <= kSkinnyMaxTokens && K % 16 == 0 && reinterpret_cast<uintptr_t>(xq) % 16 == 0 &&
-          M * K < ((int64_t)1 << 31) && ceil_div(N, kRowsPerBlock) < ((int64_t)1 << 21)))
-        return false;
-    if (M > 256 && K < 5120) return false;          // a short K: the prefill kernel's few workgroups are done quickly
-    int kmt, rpw;
-    return skinny_shape(M, ceil_div(N, kRowsPerBlock), &kmt, &rpw);
+// x_q offsets are 32-bit; one K step of the packed weights (1 KiB per 16-row block) is addressed as one raw buffer
+static bool skinny_addressable(int64_t M, int64_t N, int64_t K, const void* xq) {
+    return M >= 1 && M <= kSkinnyMaxTokens && K % 16 == 0 && reinterpret_cast<uintptr_t>(xq) % 16 == 0 && M * K < ((int64_t)1 << 31) &&
+           ceil_div(N, kRowsPerBlock) < ((int64_t)1 << 21);
 }
 
-// four consecutive outputs from a multiple of four on are one aligned store
-static bool wide_rows(const void* y, int64_t N, OutType yt) {
-    return N % 4 == 0 && reinterpret_cast<uintptr_t>(y) % (yt == OutType::BF16 ? 8 : 16) == 0;
+bool gemv_supports(int64_t M, int64_t N, int64_t K, const void* xq) {
+    if (!skinny_addressable(M, N, K, xq)) return false;
+    if (M > 256 && K < 5120) return false;          // a short K: the prefill kernel's few workgroups are done quickly
+    int kmt, rpw;
+    return skinny_shape(M, ceil_div(N, kRowsPerBlock), &kmt, &rpw, true);
+}
+
+bool gemv_chosen(int64_t M, int64_t N, int64_t K, const void* xq) {
+    if (M <= 256 || K >= 5120) return gemv_supports(M, N, K, xq);
+    // a short K after all: on small layers (300 tokens, 2048 -> 1024: prefill 7.0 us, here 4.0; 400 tokens, 2048 -> 2048 7.2 / 5.7) and in
+    // tiles of 80 tokens (300 tokens, 4096 -> 4096 12.5 / 9.6)
+    int kmt, rpw;
+    const int64_t RB = ceil_div(N, kRowsPerBlock);
+    return skinny_addressable(M, N, K, xq) && skinny_shape(M, RB, &kmt, &rpw, true) && (kmt == 5 || (RB <= 160 && rpw <= 4));
 }
 
 template <int kMT, int kR, int kW, int kS, int kD, int kLx>
@@ -670,7 +642,11 @@ hipError_t launch_linear_gemv_2bit(const int8_t* xq, const float* sx, const void
     return launch_skinny_ws<__VA_ARGS__>(xq, sx, packed, gamma, gstride, M, N, K, y, yt, stream, splits, workspace, plan)
     // The kernel forms per size come from sweeps over the 3B ... 70B LLaMA family shapes (31 forms, 8 ... 256 tokens).
     int kmt, rpw;
-    skinny_shape(M, RBc, &kmt, &rpw);
+    skinny_shape(M, RBc, &kmt, &rpw, splits == 1);
+    // The smaller workgroup tiles: K steps dealt out to the waves.  With more row blocks the kernels below are the faster ones (16
+    // tokens, 4096 -> 22016: 6.79 us, six row blocks there 6.84; 64 tokens 11.2 / 12.2); they also have the forced split-K.
+    hipError_t status;
+    if (splits == 1 && launch_linear_ksplit_2bit(kmt, rpw, xq, sx, packed, gamma, gstride, M, N, K, y, yt, stream, plan, &status)) return status;
     if (kmt == 1) {
         if (rpw == 16)     SKINNY(1, 4, 4, 2, 2, 2);
         else if (rpw == 8) SKINNY(1, 2, 4, 2, 2, 2);
