@@ -140,7 +140,9 @@ const char* bitnet_status_string(bitnet_status s);
 /* Bytes of the packed buffer for an N x K matrix in format f, written to *bytes (host). */
 bitnet_status bitnet_packed_bytes(int64_t N, int64_t K, bitnet_format f, size_t* bytes);
 
-/* Bytes of scratch bitnet_quantize_weights needs (host out).  Independent of the format. */
+/* Bytes of scratch with which bitnet_quantize_weights runs at its best (host out).  Independent of the format.  32 KiB are enough for any
+ * shape; matrices of 25 million weights and more (up to 2^30) are read once instead of twice if the scratch also holds the notes on which
+ * weights' codes hang on the exact gamma, N K / 16 bytes and no more than 30 MB. */
 bitnet_status bitnet_quantize_weights_workspace(int64_t N, int64_t K, size_t* bytes);
 
 /*
@@ -148,11 +150,12 @@ bitnet_status bitnet_quantize_weights_workspace(int64_t N, int64_t K, size_t* by
  *   W          [N][K], dtype F32 or BF16, 4-byte (F32) / 2-byte (BF16) aligned
  *   packed     out, bitnet_packed_bytes() bytes, 16-byte aligned; padding codes are written as 0
  *   gamma      out, 1 float (device)
- *   workspace  scratch of at least bitnet_quantize_weights_workspace() bytes, 16-byte aligned;
+ *   workspace  scratch of bitnet_quantize_weights_workspace() bytes, or of 32 KiB at least, 16-byte aligned;
  *              contents on entry are ignored, contents on exit are unspecified
- * Two launches on `stream` for the 2-bit format: |W| partial sums (double-double), then the
- * ternarize-and-pack pass, whose workgroups first fold the partial sums to gamma (the 5-trit format keeps
- * that reduction as a launch of its own).  A 16-byte aligned W takes the vector path of the |W| sum.
+ * Two launches on `stream`: |W| partial sums (double-double), then the ternarize-and-pack pass, whose workgroups first
+ * fold the partial sums to gamma.  A 16-byte aligned W takes the vector path of the |W| sum.  Large matrices
+ * in the 2-bit format, 16-byte aligned and with the whole workspace: three launches (a sample, one pass over W, what the
+ * sample left open).  Same bits.
  * One gamma per call: a fused QKV or gate/up matrix passed as one tensor gets one scale.
  */
 bitnet_status bitnet_quantize_weights(const void* W, bitnet_dtype w_dtype, int64_t N, int64_t K,
@@ -167,7 +170,7 @@ bitnet_status bitnet_quantize_weights(const void* W, bitnet_dtype w_dtype, int64
  * results are those of bitnet_quantize_weights, bit for bit.
  *   W, packed, gamma, stream   as for bitnet_quantize_weights
  *   Limit: the partial sums of the shape must fit the static array (BITNET_ERR_WORKSPACE otherwise; true of every
- *   shape the library accepts today, whose need is a fixed 32 KiB).
+ *   shape the library accepts today, whose need is a fixed 32 KiB).  Matrices of any size are read twice.
  * Every call on a GPU uses that GPU's one array: calls that may overlap on one GPU (different streams, no ordering
  * between them) race on it and must use bitnet_quantize_weights with workspaces of their own.  Nothing in the array
  * has to be cleared between calls: the first kernel overwrites every entry the second one reads.

@@ -77,10 +77,13 @@ bitnet_status bitnet_packed_bytes(int64_t N, int64_t K, bitnet_format f, size_t*
     return BITNET_ERR_FORMAT;
 }
 
+// the scratch that no weight-quantizing call can do without
+static size_t partials_bytes() { return (size_t)bitnet::quant_weights_num_partials() * 2 * sizeof(double); }
+
 bitnet_status bitnet_quantize_weights_workspace(int64_t N, int64_t K, size_t* bytes) {
     if (!bytes) return BITNET_ERR_NULL;
     if (!shape_ok(1, N, K)) return BITNET_ERR_SHAPE;
-    *bytes = (size_t)bitnet::quant_weights_num_partials() * 2 * sizeof(double);
+    *bytes = bitnet::quant_weights_workspace_bytes(N, K);
     return BITNET_OK;
 }
 
@@ -93,11 +96,9 @@ bitnet_status bitnet_quantize_weights(const void* W, bitnet_dtype w_dtype, int64
     if (!format_ok(f)) return BITNET_ERR_FORMAT;
     if (!aligned(W, dtype_size(w_dtype)) || !aligned(packed, 16) || !aligned(gamma, 4) || !aligned(workspace, 16))
         return BITNET_ERR_ALIGN;
-    size_t need = 0;
-    bitnet_quantize_weights_workspace(N, K, &need);
-    if (workspace_bytes < need) return BITNET_ERR_WORKSPACE;
+    if (workspace_bytes < partials_bytes()) return BITNET_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    return from_hip(bitnet::launch_quantize_weights(W, w_dtype == BITNET_BF16, N, K, f == BITNET_PACK_TRIT5, packed, gamma, workspace, s));
+    return from_hip(bitnet::launch_quantize_weights(W, w_dtype == BITNET_BF16, N, K, f == BITNET_PACK_TRIT5, packed, gamma, workspace, workspace_bytes, s));
 }
 
 bitnet_status bitnet_abs_sum(const void* W, bitnet_dtype w_dtype, int64_t N, int64_t K, double* sum, void* workspace,
@@ -106,9 +107,7 @@ bitnet_status bitnet_abs_sum(const void* W, bitnet_dtype w_dtype, int64_t N, int
     if (!shape_ok(1, N, K)) return BITNET_ERR_SHAPE;
     if (w_dtype != BITNET_F32 && w_dtype != BITNET_BF16) return BITNET_ERR_DTYPE;
     if (!aligned(W, dtype_size(w_dtype)) || !aligned(sum, 8) || !aligned(workspace, 16)) return BITNET_ERR_ALIGN;
-    size_t need = 0;
-    bitnet_quantize_weights_workspace(N, K, &need);
-    if (workspace_bytes < need) return BITNET_ERR_WORKSPACE;
+    if (workspace_bytes < partials_bytes()) return BITNET_ERR_WORKSPACE;
     return from_hip(bitnet::launch_abs_sum(W, w_dtype == BITNET_BF16, N, K, sum, workspace, static_cast<hipStream_t>(stream)));
 }
 
@@ -455,11 +454,9 @@ bitnet_status bitnet_quantize_weights_segmented(const void* W, bitnet_dtype w_dt
         total += seg_rows[sgm];
     }
     if (total != N) return BITNET_ERR_SHAPE;
-    size_t need = 0;
-    bitnet_quantize_weights_workspace(N, K, &need);
-    if (workspace_bytes < need) return BITNET_ERR_WORKSPACE;
+    if (workspace_bytes < partials_bytes()) return BITNET_ERR_WORKSPACE;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    return from_hip(bitnet::launch_quantize_weights_2bit_segmented(W, w_dtype == BITNET_BF16, N, K, seg_rows, nseg, packed, gamma_rb, workspace, s));
+    return from_hip(bitnet::launch_quantize_weights_2bit_segmented(W, w_dtype == BITNET_BF16, N, K, seg_rows, nseg, packed, gamma_rb, workspace, workspace_bytes, s));
 }
 
 static bitnet_status linear_fused_any(const void* x, bitnet_dtype x_dtype, const void* packed, const float* gamma,

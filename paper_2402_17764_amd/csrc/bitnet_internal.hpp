@@ -46,12 +46,14 @@ constexpr int flags_number(uint32_t f) { return (int)(f >> 4); }
 
 // quant_weights.hip
 int quant_weights_num_partials();
+// what every call needs (the partial sums), or with it room for the notes of large matrices, which are then read once
+size_t quant_weights_workspace_bytes(int64_t N, int64_t K);
 // Eq. (1)-(3) + packing of a whole matrix, in either format
 hipError_t launch_quantize_weights(const void* W, bool bf16, int64_t N, int64_t K, bool trit5, void* packed, float* gamma, void* workspace,
-                                   hipStream_t stream);
+                                   size_t workspace_bytes, hipStream_t stream);
 // consecutive row segments with a gamma each; gamma_rb: one per 16-row block of the whole matrix
 hipError_t launch_quantize_weights_2bit_segmented(const void* W, bool bf16, int64_t N, int64_t K, const int64_t* seg_rows, int nseg,
-                                                  void* packed, float* gamma_rb, void* workspace, hipStream_t stream);
+                                                  void* packed, float* gamma_rb, void* workspace, size_t workspace_bytes, hipStream_t stream);
 
 // one shard's share of Eq. (3): sum[0 .. 1] = the double-double (hi, lo) pair of sum |W| over these rows
 hipError_t launch_abs_sum(const void* W, bool bf16, int64_t N, int64_t K, double* sum, void* workspace, hipStream_t stream);

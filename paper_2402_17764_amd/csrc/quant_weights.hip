@@ -7,7 +7,11 @@
 //                              cache), takes the decision of Eq. (1)-(2) in fp32 and writes the packed
 //                              layout one 1 KiB (row block, K step) chunk per workgroup pass
 //
-// The whole path is HBM-bound at 8.25 B per fp32 weight, 4.25 per bf16 one (two reads of W, one packed write).  Both reading passes
+// From 96 MiB of W on (128 of bf16) (and a workspace with room for it) the two reads become one: a sample of W bounds gamma, and with it
+// the threshold of Eq. (1)-(2), so that one pass adds up |W| and codes every weight but the few between the bounds
+// (guess_pack_2bit below).
+//
+// Otherwise the path is HBM-bound at 8.25 B per fp32 weight, 4.25 per bf16 one (two reads of W, one packed write).  Both reading passes
 // are shaped by what a plain read loop reaches on this chip: 8 waves per CU with four 16-byte loads each in
 // flight read 6.1-6.2 TB/s, 32 waves per CU 5.1-5.3 TB/s.
 #include "bitnet_device.hpp"
@@ -215,7 +219,6 @@ __global__ __launch_bounds__(kFinishThreads) void fold_abs_sum(const double* __r
 // workgroups a CU instead of four: within 2 % but for 28672 x 8191, 197 at two and 176 at six.
 constexpr int kPackThreads = 256;
 constexpr int kPackBlocks = 1024;                          // four per CU
-static_assert(kSumBlocks <= kPackThreads, "the packing pass folds one partial sum of pass 1 per thread");
 
 // A chunk of W of rows x cols elements, read in 16-byte pieces that lie `from` bytes behind its first element.  kAny: rows may
 // start anywhere and end within a piece; the hardware takes 16-byte loads at element alignment.  Such a piece may run on into the
@@ -274,13 +277,13 @@ __device__ inline float piece_elem(const uint32_t (&u)[4], int e) {
 }
 
 // Pass 2 folded into the head of pass 3: while its first rows are on their way every workgroup adds up the partial sums of
-// pass 1 (one per thread; exact sums, so every workgroup gets the same bits) and takes gamma = fp32(S / (N K)), Eq. (3): one
+// pass 1 (exact sums, so every workgroup gets the same bits) and takes gamma = fp32(S / (N K)), Eq. (3): one
 // fp64 IEEE division, one rounding to fp32.  The segment's first workgroup writes it out, once per 16-row block of it.
 __device__ inline float pack_gamma(const double* __restrict__ partials, const Seg& seg, float* __restrict__ gamma_out,
                                    double* sh_hi, double* sh_lo) {
     dd part{0.0, 0.0};
     partials += 2 * (int64_t)seg.part0;
-    if ((int)threadIdx.x < seg.nparts) part = dd{partials[2 * threadIdx.x], partials[2 * threadIdx.x + 1]};
+    for (int i = threadIdx.x; i < seg.nparts; i += kPackThreads) dd_add_dd(part, dd{partials[2 * i], partials[2 * i + 1]});
     const double S = block_sum_dd<kPackThreads / kWave>(part, sh_hi, sh_lo);
     const float g = (float)(S / (double)seg.count);
     if ((int)blockIdx.x == seg.pack0)
@@ -294,22 +297,17 @@ __device__ inline float pack_threshold(const double* __restrict__ partials, cons
     return ternary_threshold(d);                           // |w| >= thr  <=>  RoundClip(w / d) = +-1
 }
 
-// A segment's rows become row blocks row0 / 16 ... of a packed matrix of RB row blocks in all (segments start on row
-// blocks).
-template <typename T, bool kAny, int kSegs>
-__global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __restrict__ W_all, int64_t K,
-                                                                    int64_t Kq /* quads per row */, int64_t RB,
-                                                                    SegList<kSegs> list, const double* __restrict__ partials,
-                                                                    float* __restrict__ gamma_out, uint32_t* __restrict__ packed) {
+// What the walk over the items of a segment does with the weights between two thresholds (guess_pack_2bit).
+struct NoGuess { static constexpr bool kOn = false; };
+
+// The items of one workgroup.  threshold() is called once, with the first rows on their way.  A segment's rows become row blocks row0 / 16
+// ... of a packed matrix of RB row blocks in all (segments start on row blocks).
+template <typename T, bool kAny, typename Threshold, typename Guess>
+__device__ __forceinline__ void pack_items_2bit(const T* __restrict__ W, const Seg& seg, int64_t K, int64_t Kq /* quads per row */, int64_t RB,
+                                       uint32_t* __restrict__ packed, const Threshold& threshold, Guess& guess) {
     constexpr int kE = 16 / (int)sizeof(T), kCols = kWave * kE, kSteps = kCols / 256;      // of an item
-    int sg = 0;
-    while (sg + 1 < list.n && (int)blockIdx.x >= list.s[sg + 1].pack0) ++sg;
-    const Seg& seg = list.s[sg];
-    const T* W = W_all + seg.row0 * K;
     const int64_t N = seg.rows, rb_off = seg.row0 / kRowsPerBlock;
     const int stride = seg.npack;
-    __shared__ double sh_hi[kPackThreads / kWave];
-    __shared__ double sh_lo[kPackThreads / kWave];
     const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x >> 6, col = lane * kE;
     const int per_row = (int)ceil_div(K, kCols);
     const int items = (int)ceil_div(N, kRowsPerBlock) * per_row;      // N K < 2^40: below 2^29
@@ -332,10 +330,10 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
         for (int t = 0; t < 4; ++t) piece[t] = c.by_element(W, (int)K, 4 * w + t, col);
     }
 
-    const float thr = pack_threshold(partials, seg, gamma_out, sh_hi, sh_lo);
+    const float thr = threshold();
 
     const int t_out = (lane >> 2) & 3, g = lane >> 4;      // the lane stores word lane & 3 of row 4w + t_out, quad column g
-    for (; item < items; item += stride) {
+    for (int nth = 0; item < items; item += stride, ++nth) {
         const bool more = item + stride < items;
         const Chunk<T, kAny> next = chunk(more ? item + stride : item);
         uint32_t word[4];
@@ -343,10 +341,15 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
         for (int t = 0; t < 4; ++t) {
             uint4 v = piece[t];
             if (kAny && !tiny && (c.rows < kRowsPerBlock || c.cols < kCols)) v = c.trimmed(v, from[t], 4 * w + t, col);
-            const uint32_t u[4] = {v.x, v.y, v.z, v.w};
-            uint32_t code = 0;                             // column 4 h + b of the lane: bits 8 b + 2 h of its part of a word
+            uint32_t code;                                 // column 4 h + b of the lane: bits 8 b + 2 h of its part of a word
+            if constexpr (Guess::kOn) {
+                code = guess.take(v, (uint32_t)nth << 13 | (uint32_t)(4 * w + t) << 9 | (uint32_t)col);
+            } else {
+                const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+                code = 0;
 #pragma unroll
-            for (int e = 0; e < kE; ++e) code |= ternary_code2_threshold(piece_elem<T>(u, e), thr) << (8 * (e & 3) + 2 * (e >> 2));
+                for (int e = 0; e < kE; ++e) code |= ternary_code2_threshold(piece_elem<T>(u, e), thr) << (8 * (e & 3) + 2 * (e >> 2));
+            }
             piece[t] = next.load(more, from[t], col);
             __builtin_amdgcn_sched_barrier(0);             // in this place: requested before the next row is waited for
             if (sizeof(T) == 2) {
@@ -377,6 +380,369 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
         }
         c = next;
     }
+}
+
+template <int kSegs>
+__device__ inline int pack_segment(const SegList<kSegs>& list) {
+    int sg = 0;
+    while (sg + 1 < list.n && (int)blockIdx.x >= list.s[sg + 1].pack0) ++sg;
+    return sg;
+}
+
+template <typename T, bool kAny, int kSegs>
+__global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __restrict__ W_all, int64_t K, int64_t Kq, int64_t RB,
+                                                                    SegList<kSegs> list, const double* __restrict__ partials,
+                                                                    float* __restrict__ gamma_out, uint32_t* __restrict__ packed) {
+    __shared__ double sh_hi[kPackThreads / kWave];
+    __shared__ double sh_lo[kPackThreads / kWave];
+    const Seg& seg = list.s[pack_segment(list)];
+    NoGuess none;
+    pack_items_2bit<T, kAny>(W_all + seg.row0 * K, seg, K, Kq, RB, packed, [&] { return pack_threshold(partials, seg, gamma_out, sh_hi, sh_lo); }, none);
+}
+
+// ---------------------------------------------------------------------------------------------------
+// 2-bit format, W read once
+// ---------------------------------------------------------------------------------------------------
+// gamma has to be known before the first code, and is only known after the last weight: hence two reads.  But a code asks no more of it
+// than on which side of a threshold T(gamma) a weight lies, and a sample of W says where T is to within a few tenths of a percent:
+//   sample_abs       runs of 1 KiB, evenly spread with a random offset each: the mean of |W| and, from the spread of the runs' own
+//                    sums (which holds whatever goes together within a run or a row), its standard error
+//   guess_pack_2bit  reads W once: adds up |W| exactly as pass 1 does, and codes as pass 3 does with the sample's threshold.  Weights
+//                    between the thresholds of its mean -+ 5 standard errors (a fifth of a percent of normally distributed fp32 ones, of
+//                    bf16 ones those of the one or no value in between) are noted down
+//   settle_2bit      gamma from the exact sum; if it lies between its bounds, all weights but noted ones have their codes, and of those
+//                    the ones between the two thresholds (one in ten) are changed.  If it does not, or a note pad was too small, this
+//                    is pass 3.
+// gamma and codes are those of the two passes bit for bit, whatever the sample says.  What fails is a matrix whose mean hangs on a few
+// weights that the sample missed, or with a value that very many weights share right at the threshold; it then takes up to
+// 1.2 times the two passes (57344 x 8192 bf16 with one weight of 10^8 times the others 357 / 431 us, 22016 x 8192 fp32 293 / 289).
+// us, two passes / this: bf16 57344 x 8192 334 / 207, 28672 x 8192 165 / 107, 20000 x 5001 75.6 / 67, 16384 x 4096 48.3 / 46.1; fp32 57344 x
+// 8192 642 / 388, 22016 x 4096 118 / 81, 9600 x 3200 in three segments 43.6 / 37.9, 7000 x 4096 39.8 / 33.8, 4096 x 4096 24.8 / 26.2.  What bounds it: the
+// pass runs at 0.9 of what pass 3 alone takes in bf16 (187 us for 940 + 117 MB), in fp32 13 instructions a weight and the launches
+// around it (sample 4, settling 4.9 of 36).
+constexpr int64_t kGuessBytesF32 = (int64_t)96 << 20, kGuessBytesBf16 = (int64_t)128 << 20;
+constexpr int64_t kGuessMost = (int64_t)1 << 30;           // weights: a workgroup's notes fit its LDS
+constexpr int kNotes = 3584;                               // of a workgroup: 28 KiB of LDS, four workgroups a CU
+constexpr int kRunVecs = kWave;                            // a run: one 16-byte load per lane
+
+// parts of the workspace: the partial sums from its start, ...
+constexpr int kGuessBlocks = kPackBlocks + kMaxSegs;
+constexpr size_t kSamplesAt = sizeof(double) * 2 * kGuessBlocks;
+constexpr size_t kCountsAt = kSamplesAt + sizeof(double) * 2 * (kSumBlocks + kMaxSegs);
+constexpr size_t kBoundsAt = kCountsAt + sizeof(int) * kGuessBlocks;
+constexpr size_t kNotesAt = 2048 * 2 * sizeof(double);
+static_assert(kBoundsAt % 16 == 0 && kBoundsAt + sizeof(float) * 4 * kMaxSegs <= kNotesAt, "... samples, counts and bounds within the 32 KiB of any call, notes behind them");
+
+template <typename T, int kSegs>
+__global__ __launch_bounds__(kSumThreads) void sample_abs(const T* __restrict__ W_all, int64_t K, SegList<kSegs> list, int batches,
+                                                          double* __restrict__ samples) {
+    constexpr int kWaves = kSumThreads / kWave;
+    int sg = 0;
+    while (sg + 1 < list.n && (int)blockIdx.x >= list.s[sg + 1].part0) ++sg;
+    const Seg& seg = list.s[sg];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const uint4* Wv = reinterpret_cast<const uint4*>(W_all + seg.row0 * K);
+    const int64_t nvec = seg.count * (int64_t)sizeof(T) / 16;          // at least one run: the launcher asks for 2 MiB a segment
+    const int runs = seg.nparts * kWaves * batches * kSumLoads;
+    const int64_t stride = nvec / runs;
+    double sum = 0.0, squares = 0.0;
+    for (int b = 0; b < batches; ++b) {
+        uint4 v[kSumLoads];
+#pragma unroll
+        for (int u = 0; u < kSumLoads; ++u) {
+            const int j = ((b * kSumLoads + u) * seg.nparts + (int)blockIdx.x - seg.part0) * kWaves + wave;
+            uint32_t h = (uint32_t)j * 0x9E3779B1u;                    // the place of run j in its stretch of W: a hash of j
+            h = (h ^ (h >> 15)) * 0x85EBCA77u;
+            h ^= h >> 13;
+            const int64_t at = (int64_t)j * stride + (stride > kRunVecs ? (int64_t)(h % (uint32_t)(stride - kRunVecs + 1)) : 0);
+            v[u] = Wv[(at + kRunVecs <= nvec ? at : nvec - kRunVecs) + lane];
+        }
+#pragma unroll
+        for (int u = 0; u < kSumLoads; ++u) {
+            const uint32_t q[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+            float f = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 16 / (int)sizeof(T); ++e) f += fabsf(piece_elem<T>(q, e));
+            const double run = wave_sum_f64((double)f);
+            sum += run;
+            squares += run * run;
+        }
+    }
+    __shared__ double sh[2][kWaves];
+    if (lane == 0) { sh[0][wave] = sum; sh[1][wave] = squares; }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+        double a = 0.0;
+#pragma unroll
+        for (int q = 0; q < kWaves; ++q) a += sh[threadIdx.x][q];
+        samples[2 * blockIdx.x + threadIdx.x] = a;
+    }
+}
+
+// gamma's bounds from a segment's samples, and the samples' mean; the same bits in every workgroup.  An empty interval (x > y) where they
+// say nothing.
+__device__ inline float3 gamma_bounds(const double* __restrict__ samples, const Seg& seg, int batches, int per_run, double* sh_hi, double* sh_lo) {
+    double s = 0.0, q = 0.0;
+    if ((int)threadIdx.x < seg.nparts) {
+        const double2 v = reinterpret_cast<const double2*>(samples)[seg.part0 + threadIdx.x];
+        s = v.x;
+        q = v.y;
+    }
+    s = wave_sum_f64(s);
+    q = wave_sum_f64(q);
+    if ((threadIdx.x & 63) == 0) { sh_hi[threadIdx.x >> 6] = s; sh_lo[threadIdx.x >> 6] = q; }
+    __syncthreads();
+    s = (sh_hi[0] + sh_hi[1]) + (sh_hi[2] + sh_hi[3]);
+    q = (sh_lo[0] + sh_lo[1]) + (sh_lo[2] + sh_lo[3]);
+    static_assert(kPackThreads == 4 * kWave && kSumBlocks <= kPackThreads, "one sample per thread, four waves");
+    // n runs: (n q - s^2) / n^2 is the variance of one, over n that of their mean; times n it cancels least
+    const double n = (double)(seg.nparts * (kSumThreads / kWave) * batches * kSumLoads);
+    const float inv = 1.0f / ((float)n * (float)per_run), spread = (float)fmax(n * q - s * s, 0.0);
+    const float mean = (float)s * inv, off = 5.0f * inv * sqrtf(spread / (float)n) + 2e-6f * mean;
+    const float lo = fmaxf(mean - off, 0.0f), hi = mean + off;
+    return hi <= 1.02f * lo || hi == 0.0f ? make_float3(lo, hi, mean) : make_float3(1.0f, 0.0f, mean);
+}
+
+// The threshold that weights are coded with before gamma is known.
+__device__ inline float guess_threshold(const float3& b) { return b.x <= b.y ? (b.z + kEps) * 0.5f : 0.5f; }
+
+// What guess_pack_2bit does with a piece of a row.
+//
+// |W| is summed exactly, as pass 1 sums it, but with a conversion and an addition per weight: magnitudes of p significant bits from
+// `least` up are multiples of 2^(1 - p) of it, so that sums of them are exact in fp64 while they stay below 2^(54 - p) of it.  A lane
+// adds those in [least, most) up as they are, most 2^(54 - p) / (values that the lane meets) of least, least far enough below the mean that
+// about one piece in a thousand has a smaller weight that is not zero; pieces with one, or with one of `most` and more, take
+// double-double additions.
+// With pass 1's own additions 9600 x 3200 fp32 took 32.5 us instead of 27.4.  Four workgroups a CU need 128 registers: at 136, bf16 took 213
+// instead of 190; notes whose places went through a counter in LDS cost half a microsecond each (22016 x 4096 bf16 67 / 47).
+template <typename T>
+struct Noting {
+    static constexpr bool kOn = true;
+    static constexpr int kE = 16 / (int)sizeof(T), kBits = sizeof(T) == 2 ? 8 : 24;
+    double sum;
+    dd rest;
+    uint32_t least, most;      // magnitudes of T as integers (bf16: the same one in both halves)
+    uint32_t lo, mid, hi;      // ... from which a weight is noted, from which it is coded +-1, and from which it is no longer noted
+    int room, used;            // of the wave's own pad: no counter in LDS to wait for
+    uint2* pad;
+
+    // per_lane: values that a lane adds up
+    __device__ void set(const float3& b, int per_lane) {
+        const bool known = b.x <= b.y;                     // else nothing is noted: settle_2bit starts anew
+        // T(d) is within a few units in the last place of d / 2
+        const float t[3] = {((known ? b.x : 1.0f) + kEps) * (0.5f - 0x1p-20f), guess_threshold(b), ((known ? b.y : 1.0f) + kEps) * (0.5f + 0x1p-20f)};
+        uint32_t at[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) at[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(sizeof(T) == 2 ? (__float_as_uint(t[i]) + 0xFFFFu) >> 16 : __float_as_uint(t[i])));
+        lo = at[0];
+        mid = at[1];
+        hi = known ? at[2] : lo;
+        const int exponent = b.z > 0.0f && b.z < __builtin_inff() ? max((int)(__float_as_uint(b.z) >> 23), 1) : 127;      // biased, of the mean
+        const int range = 54 - kBits - (32 - __builtin_clz(per_lane)), below = sizeof(T) == 2 ? 22 : range - 8;
+        const int first = exponent - below, from = max(first, 1), to = from + range;
+        uint32_t l = first >= 1 ? (uint32_t)from << 23 : 1u, m = (uint32_t)min(to, 255) << 23;
+        if (sizeof(T) == 2) {
+            l = first >= 1 ? l >> 16 : 1u;
+            l |= l << 16;
+            m = m >> 16 | m;
+        }
+        least = (uint32_t)__builtin_amdgcn_readfirstlane((int)l);
+        most = (uint32_t)__builtin_amdgcn_readfirstlane((int)m);
+    }
+
+    // The lane's elements whose flags are set, one of each lane a round: place and bits.  Flags of bf16 elements 0 ... 3 are bits 0, 8, 16
+    // and 24, of elements 4 ... 7 the bits behind those.  LDS alone: a store in here would make every wait of the loop a wait for all
+    // loads in flight.
+    __device__ __forceinline__ void note(uint32_t flags, uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t place) {
+        asm("" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));      // registers, not an array in scratch memory that is indexed below
+        for (uint64_t who = __ballot(flags != 0); who; who = __ballot(flags != 0)) {
+            if (flags) {
+                const int p = __ffs((int)flags) - 1, e = sizeof(T) == 2 ? (p >> 3) + 4 * (p & 1) : p, h = sizeof(T) == 2 ? e >> 1 : e;
+                const uint32_t w01 = h & 1 ? b : a, w23 = h & 1 ? d : c, w = h & 2 ? w23 : w01;
+                const int at = used + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(who >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)who, 0));
+                if (at < room) pad[at] = make_uint2(place + e, sizeof(T) == 4 ? w : e & 1 ? w & 0xFFFF0000u : w << 16);
+                flags &= flags - 1;
+            }
+            used += __popcll(who);
+        }
+    }
+
+    // a row's piece, its first element at `place`
+    __device__ __forceinline__ uint32_t take(const uint4& v, uint32_t place) {
+        const uint32_t u[4] = {v.x, v.y, v.z, v.w};
+        uint32_t code = 0, flags = 0;
+        bool odd;                                          // a magnitude outside [least, most) that is not zero
+        double s;
+        if constexpr (sizeof(T) == 4) {
+            uint32_t top = 0, d[4], from_mid[4], nearest = 0xFFFFFFFFu;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t m = u[e] & 0x7FFFFFFFu;
+                top = max(top, m - least);                 // smaller ones wrap to the top, zero to the first place there
+                d[e] = m - lo;
+                nearest = min(nearest, d[e]);
+                from_mid[e] = m + (0x80000000u - mid);     // top bit: from mid on
+            }
+            s = ((double)fabsf(__uint_as_float(u[0])) + (double)fabsf(__uint_as_float(u[1]))) +
+                ((double)fabsf(__uint_as_float(u[2])) + (double)fabsf(__uint_as_float(u[3])));
+            odd = top > 0u - least || !(s < (double)__uint_as_float(most));
+            // flags and signs to the tops of four bytes, from there to their bits 0 and 1
+            const uint32_t one = (__builtin_amdgcn_perm(from_mid[1], from_mid[0], 0x0c0c0703u) | __builtin_amdgcn_perm(from_mid[3], from_mid[2], 0x07030c0cu)) & 0x80808080u;
+            const uint32_t sign = __builtin_amdgcn_perm(u[1], u[0], 0x0c0c0703u) | __builtin_amdgcn_perm(u[3], u[2], 0x07030c0cu);
+            code = one >> 7 | (one & sign) >> 6;
+            if (__ballot(nearest < hi - lo)) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) flags |= (d[e] < hi - lo ? 1u : 0u) << e;
+                note(flags, u[0], u[1], u[2], u[3], place);
+            }
+        } else {
+            typedef short s16x2 __attribute__((ext_vector_type(2)));
+            typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+            // two magnitudes of 15 bits to a word: adding 2^15 - m sets a half's top bit from magnitude m on
+            const uint32_t add_lo = 0x80008000u - lo * 0x10001u, add_mid = 0x80008000u - mid * 0x10001u, add_hi = 0x80008000u - hi * 0x10001u;
+            uint32_t from_mid[4];
+            u16x2 top = {0, 0};
+            s16x2 far = {0, 0};
+#pragma unroll
+            for (int h = 0; h < 4; ++h) {
+                const uint32_t m = u[h] & 0x7FFF7FFFu;
+                from_mid[h] = m + add_mid;
+                const u16x2 x = __builtin_bit_cast(u16x2, m) - __builtin_bit_cast(u16x2, least);
+                top = __builtin_elementwise_max(top, x);
+                far = __builtin_elementwise_max(far, __builtin_bit_cast(s16x2, x));
+            }
+            const uint32_t zero = 0x10000u - (least & 0xFFFFu);
+            odd = max((uint32_t)top.x, (uint32_t)top.y) > zero || max((int)far.x, (int)far.y) >= (int)((most & 0xFFFFu) - (least & 0xFFFFu));
+            // flags and signs of elements 4 h .. 4 h + 3 to the tops of four bytes, from there to bits 2 h and 2 h + 1
+            uint32_t two[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t one = __builtin_amdgcn_perm(from_mid[2 * h + 1], from_mid[2 * h], 0x07050301u) & 0x80808080u;
+                two[h] = one >> 1 | (one & __builtin_amdgcn_perm(u[2 * h + 1], u[2 * h], 0x07050301u));
+            }
+            code = two[0] >> 6 | two[1] >> 4;
+            if (lo != hi) {
+                uint32_t b[4];
+#pragma unroll
+                for (int h = 0; h < 4; ++h) b[h] = ((u[h] & 0x7FFF7FFFu) + add_lo) & ~((u[h] & 0x7FFF7FFFu) + add_hi);
+                flags = (__builtin_amdgcn_perm(b[1], b[0], 0x07050301u) >> 7 & 0x01010101u) | (__builtin_amdgcn_perm(b[3], b[2], 0x07050301u) >> 6 & 0x02020202u);
+                note(flags, u[0], u[1], u[2], u[3], place);
+            }
+            double half[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                half[h] = (double)fabsf(__uint_as_float(u[2 * h] << 16)) + (double)fabsf(__uint_as_float(u[2 * h] & 0xFFFF0000u));
+                half[h] += (double)fabsf(__uint_as_float(u[2 * h + 1] << 16)) + (double)fabsf(__uint_as_float(u[2 * h + 1] & 0xFFFF0000u));
+            }
+            s = half[0] + half[1];
+        }
+        sum += odd ? 0.0 : s;
+        if (__ballot(odd) && odd) {
+#pragma unroll
+            for (int e = 0; e < kE; ++e) dd_add_double(rest, (double)fabsf(piece_elem<T>(u, e)));
+        }
+        return code;
+    }
+};
+
+template <typename T, bool kAny, int kSegs>
+__global__ __launch_bounds__(kPackThreads, 4) void guess_pack_2bit(const T* __restrict__ W_all, int64_t K, int64_t Kq, int64_t RB, SegList<kSegs> list,
+                                                                int batches, int cap, char* __restrict__ ws, uint32_t* __restrict__ packed) {
+    __shared__ double sh_hi[kPackThreads / kWave];
+    __shared__ double sh_lo[kPackThreads / kWave];
+    __shared__ uint2 notes[kNotes];
+    __shared__ int used[kPackThreads / kWave];
+    const int sg = pack_segment(list), wave = threadIdx.x >> 6;
+    const Seg& seg = list.s[sg];
+    constexpr int kWaves = kPackThreads / kWave;
+    Noting<T> noting{0.0, {0.0, 0.0}, 0, 0, 0, 0, 0, cap / kWaves, 0, notes + wave * (kNotes / kWaves)};
+    pack_items_2bit<T, kAny>(W_all + seg.row0 * K, seg, K, Kq, RB, packed, [&] {
+        const float3 b = gamma_bounds(reinterpret_cast<const double*>(ws + kSamplesAt), seg, batches, kRunVecs * Noting<T>::kE, sh_hi, sh_lo);
+        if ((int)blockIdx.x == seg.pack0 && threadIdx.x == 0) reinterpret_cast<float4*>(ws + kBoundsAt)[sg] = make_float4(b.x, b.y, guess_threshold(b), 0.0f);
+        const int64_t items = ceil_div(seg.rows, kRowsPerBlock) * ceil_div(K, kWave * Noting<T>::kE);
+        noting.set(b, (int)ceil_div(items, seg.npack) * 4 * Noting<T>::kE);
+        return 0.0f; }, noting);
+
+    __syncthreads();                                       // sh_hi and sh_lo are used again
+    dd acc = noting.rest;
+    dd_add_double(acc, noting.sum);
+    const dd mine = wave_sum_dd(acc);
+    if ((threadIdx.x & 63) == 0) { sh_hi[wave] = mine.hi; sh_lo[wave] = mine.lo; used[wave] = noting.used; }
+    __syncthreads();
+    int n = 0, before = 0;
+    bool over = false;
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) {
+        before += q < wave ? used[q] : 0;
+        n += used[q];
+        over = over || used[q] > cap / kWaves;
+    }
+    uint2* out = reinterpret_cast<uint2*>(ws + kNotesAt) + (int64_t)blockIdx.x * cap + before;
+    for (int i = threadIdx.x & (kWave - 1); i < noting.used && !over; i += kWave) out[i] = noting.pad[i];
+    if (threadIdx.x == 0) {
+        reinterpret_cast<int*>(ws + kCountsAt)[blockIdx.x] = over ? cap + 1 : n;
+        dd t{sh_hi[0], sh_lo[0]};
+#pragma unroll
+        for (int q = 1; q < kWaves; ++q) dd_add_dd(t, dd{sh_hi[q], sh_lo[q]});
+        double* partials = reinterpret_cast<double*>(ws);
+        partials[2 * blockIdx.x] = t.hi;
+        partials[2 * blockIdx.x + 1] = t.lo;
+    }
+}
+
+// A workgroup settles the notes of kPads workgroups of the pass before, as each reads all partial sums and counts of its segment (with one
+// 5.5 us, two 4.9, four 4.5); two workgroups a CU are as fast as four where it comes to packing after all.
+constexpr int kPads = 2;
+template <typename T, bool kAny, int kSegs>
+__global__ __launch_bounds__(kPackThreads) void settle_2bit(const T* __restrict__ W_all, int64_t K, int64_t Kq, int64_t RB, SegList<kSegs> list, int cap,
+                                                            const char* __restrict__ ws, float* __restrict__ gamma_out, uint32_t* __restrict__ packed) {
+    constexpr int kCols = kWave * 16 / (int)sizeof(T);
+    __shared__ double sh_hi[kPackThreads / kWave];
+    __shared__ double sh_lo[kPackThreads / kWave];
+    int sg = 0, block0 = 0;
+    for (; sg + 1 < list.n; ++sg) {
+        const int blocks = (list.s[sg].npack + kPads - 1) / kPads;
+        if ((int)blockIdx.x < block0 + blocks) break;
+        block0 += blocks;
+    }
+    const Seg& was = list.s[sg];
+    Seg seg = was;
+    seg.part0 = was.pack0;                                 // a partial sum per workgroup of the pass before
+    seg.nparts = was.npack;
+    seg.pack0 = block0;
+    seg.npack = (was.npack + kPads - 1) / kPads;
+    const int* counts = reinterpret_cast<const int*>(ws + kCountsAt) + was.pack0;
+    // A pad's words are those of items that no other pad has.  Its first notes are on their way before it is known what for.
+    constexpr int kThreads = kPackThreads / kPads, kAhead = 256 / kThreads;       // cap >= 256
+    const int own = (int)threadIdx.x % kThreads, which = ((int)blockIdx.x - block0) * kPads + (int)threadIdx.x / kThreads;
+    const int pad = min(which, was.npack - 1);
+    const uint2* notes = reinterpret_cast<const uint2*>(ws + kNotesAt) + (int64_t)(was.pack0 + pad) * cap;
+    uint2 first[kAhead];
+#pragma unroll
+    for (int a = 0; a < kAhead; ++a) first[a] = notes[a * kThreads + own];
+    const int n = which < was.npack ? counts[pad] : 0;
+    int most = 0;
+    for (int i = threadIdx.x; i < was.npack; i += kPackThreads) most = max(most, counts[i]);
+    const float4 b = reinterpret_cast<const float4*>(ws + kBoundsAt)[sg];
+    const float gamma = pack_gamma(reinterpret_cast<const double*>(ws), seg, gamma_out, sh_hi, sh_lo), thr = ternary_threshold(gamma + kEps);
+    if (__syncthreads_or(!(gamma >= b.x && gamma <= b.y) || most > cap)) {
+        NoGuess none;
+        pack_items_2bit<T, kAny>(W_all + seg.row0 * K, seg, K, Kq, RB, packed, [&] { return thr; }, none);
+        return;
+    }
+    const int per_row = (int)ceil_div(K, kCols), items = (int)ceil_div(seg.rows, kRowsPerBlock) * per_row;
+    auto settle = [&](const uint2& at) {
+        const float w = __uint_as_float(at.y);
+        if ((fabsf(w) >= thr) == (fabsf(w) >= b.z)) return;
+        const int it = items - 1 - (pad + (int)(at.x >> 13) * was.npack), rb = it / per_row;
+        const int64_t col = (int64_t)(it - rb * per_row) * kCols + (at.x & 511u);
+        const int64_t word = 4 * quad_index_2bit(col >> 6, seg.row0 / kRowsPerBlock + rb, (int)(at.x >> 9 & 15u), Kq, RB) + (col >> 4 & 3);
+        __hip_atomic_fetch_xor(packed + word, (w > 0.0f ? 1u : 3u) << code_shift((int)col & 15), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+#pragma unroll
+    for (int a = 0; a < kAhead; ++a)
+        if (a * kThreads + own < n) settle(first[a]);
+    for (int i = kAhead * kThreads + own; i < n; i += kThreads) settle(notes[i]);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -551,6 +917,27 @@ static void launch_abs_sum_partials(const void* W, bool bf16, int64_t K, const S
     else      hipLaunchKernelGGL((abs_sum_partials<float, kSegs>), grid, block, 0, stream, static_cast<const float*>(W), K, list, vec_ok, partials);
 }
 
+// A workgroup's notes for a matrix of `count` weights: one weight in 128 and some, three times what normally distributed ones need.
+static int guess_cap(int64_t count) {
+    const int64_t want = count / kPackBlocks / 128 + 256;
+    return (int)(want < kNotes ? want : kNotes) / 4 * 4;       // as much for each of its waves
+}
+size_t quant_weights_workspace_bytes(int64_t N, int64_t K) {
+    const int64_t count = N * K;
+    return (count * 4 >= kGuessBytesF32 || count * 2 >= kGuessBytesBf16) && count <= kGuessMost ? kNotesAt + (size_t)kGuessBlocks * guess_cap(count) * sizeof(uint2) : kNotesAt;
+}
+// Whether the segments of a launch are read once.  Each needs a sample: 2 MiB of it at least.
+template <int kSegs>
+static bool guess_applies(const void* W, int64_t N, int64_t K, int64_t esz, const SegList<kSegs>& list, size_t workspace_bytes) {
+    int64_t rows = 0;
+    for (int i = 0; i < list.n; ++i) {
+        rows += list.s[i].rows;
+        if (list.s[i].count * esz < (int64_t)2 << 20) return false;
+    }
+    return rows * K * esz >= (esz == 2 ? kGuessBytesBf16 : kGuessBytesF32) && N * K <= kGuessMost && reinterpret_cast<uintptr_t>(W) % 16 == 0 &&
+           workspace_bytes >= quant_weights_workspace_bytes(N, K);
+}
+
 hipError_t launch_abs_sum(const void* W, bool bf16, int64_t N, int64_t K, double* sum, void* workspace, hipStream_t stream) {
     double* partials = static_cast<double*>(workspace);
     const SegList<1> list = make_segs<1>(&N, 1, 0, K, bf16 ? 2 : 4);
@@ -576,6 +963,31 @@ static void launch_pack(const void* W, bool bf16, int64_t K, int64_t RB, const S
 #undef PACK
 }
 
+// both in one: sample, guess, settle
+template <int kSegs>
+static void launch_guess(const void* W, bool bf16, int64_t N, int64_t K, int64_t RB, const SegList<kSegs>& list, void* packed, float* gamma, void* workspace,
+                         hipStream_t stream) {
+    const int64_t Kq = ceil_div(K, kColsPerQuad), esz = bf16 ? 2 : 4;
+    const bool any = K % (16 / esz) != 0;
+    const Seg& last = list.s[list.n - 1];
+    const dim3 sgrid((unsigned)(last.part0 + last.nparts)), grid((unsigned)(last.pack0 + last.npack));
+    int settling = 0;
+    for (int i = 0; i < list.n; ++i) settling += (list.s[i].npack + kPads - 1) / kPads;
+    // 8 MiB of samples per 128 MiB of W, and never more than 32: 1 in 32 of 940 MB
+    const int64_t want = (last.row0 + last.rows - list.s[0].row0) * K * esz >> 27;
+    const int batches = (int)(want < 1 ? 1 : want > 4 ? 4 : want), cap = guess_cap(N * K);
+    char* ws = static_cast<char*>(workspace);
+    double* samples = reinterpret_cast<double*>(ws + kSamplesAt);
+    uint32_t* out = static_cast<uint32_t*>(packed);
+#define GUESS(T_, A_) \
+    hipLaunchKernelGGL((sample_abs<T_, kSegs>), sgrid, dim3(kSumThreads), 0, stream, static_cast<const T_*>(W), K, list, batches, samples); \
+    hipLaunchKernelGGL((guess_pack_2bit<T_, A_, kSegs>), grid, dim3(kPackThreads), 0, stream, static_cast<const T_*>(W), K, Kq, RB, list, batches, cap, ws, out); \
+    hipLaunchKernelGGL((settle_2bit<T_, A_, kSegs>), dim3((unsigned)settling), dim3(kPackThreads), 0, stream, static_cast<const T_*>(W), K, Kq, RB, list, cap, ws, gamma, out)
+    if (bf16) { if (any) { GUESS(uint16_t, true); } else { GUESS(uint16_t, false); } }
+    else { if (any) { GUESS(float, true); } else { GUESS(float, false); } }
+#undef GUESS
+}
+
 static void launch_pack_trit5(const void* W, bool bf16, int64_t K, const SegList<1>& list, const double* partials, void* packed, float* gamma,
                               hipStream_t stream) {
     const int64_t RB = ceil_div(list.s[0].rows, kRowsPerBlock), most = ceil_div(RB * ceil_div(K, kTritStep), kTritPackWaves);
@@ -590,10 +1002,14 @@ static void launch_pack_trit5(const void* W, bool bf16, int64_t K, const SegList
 
 // Eq. (1)-(3) + packing of a whole matrix
 hipError_t launch_quantize_weights(const void* W, bool bf16, int64_t N, int64_t K, bool trit5, void* packed, float* gamma, void* workspace,
-                                   hipStream_t stream) {
+                                   size_t workspace_bytes, hipStream_t stream) {
     double* partials = static_cast<double*>(workspace);
     SegList<1> list = make_segs<1>(&N, 1, 0, K, bf16 ? 2 : 4);
     list.s[0].nout = 1;
+    if (!trit5 && guess_applies(W, N, K, bf16 ? 2 : 4, list, workspace_bytes)) {
+        launch_guess(W, bf16, N, K, ceil_div(N, kRowsPerBlock), list, packed, gamma, workspace, stream);
+        return hipGetLastError();
+    }
     launch_abs_sum_partials(W, bf16, K, list, partials, stream);
     if (trit5) launch_pack_trit5(W, bf16, K, list, partials, packed, gamma, stream);
     else launch_pack(W, bf16, K, ceil_div(N, kRowsPerBlock), list, partials, packed, gamma, stream);
@@ -612,14 +1028,18 @@ hipError_t launch_pack_with_sums(const void* W, bool bf16, int64_t N, int64_t K,
 }
 
 hipError_t launch_quantize_weights_2bit_segmented(const void* W, bool bf16, int64_t N, int64_t K, const int64_t* seg_rows, int nseg,
-                                                  void* packed, float* gamma_rb, void* workspace, hipStream_t stream) {
+                                                  void* packed, float* gamma_rb, void* workspace, size_t workspace_bytes, hipStream_t stream) {
     double* partials = static_cast<double*>(workspace);
     int64_t row0 = 0;
     for (int first = 0; first < nseg; first += kMaxSegs) {               // groups use the workspace one after the other (stream order)
         const int n = nseg - first < kMaxSegs ? nseg - first : kMaxSegs;
         const SegList<kMaxSegs> list = make_segs<kMaxSegs>(seg_rows + first, n, row0, K, bf16 ? 2 : 4);
-        launch_abs_sum_partials(W, bf16, K, list, partials, stream);
-        launch_pack(W, bf16, K, ceil_div(N, kRowsPerBlock), list, partials, packed, gamma_rb, stream);
+        if (guess_applies(W, N, K, bf16 ? 2 : 4, list, workspace_bytes)) {
+            launch_guess(W, bf16, N, K, ceil_div(N, kRowsPerBlock), list, packed, gamma_rb, workspace, stream);
+        } else {
+            launch_abs_sum_partials(W, bf16, K, list, partials, stream);
+            launch_pack(W, bf16, K, ceil_div(N, kRowsPerBlock), list, partials, packed, gamma_rb, stream);
+        }
         for (int i = 0; i < n; ++i) row0 += seg_rows[first + i];
     }
     return hipGetLastError();

@@ -12,7 +12,7 @@
 
 namespace bitnet {
 
-// 2048 (hi, lo) pairs of doubles: what bitnet_quantize_weights_workspace reports for any shape.  Each GPU the library
+// 2048 (hi, lo) pairs of doubles: what bitnet_quantize_weights needs for any shape (with more, large matrices are read once).  Each GPU the library
 // runs on holds its own copy until the process ends.
 constexpr size_t kStaticScratchBytes = 32768;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
@@ -57,10 +57,6 @@ extern "C" bitnet_status bitnet_quantize_weights_static(const void* W, bitnet_dt
     void* const probe = reinterpret_cast<void*>(uintptr_t{256});
     const bitnet_status pre = bitnet_quantize_weights(W, w_dtype, N, K, f, packed, gamma, probe, 0, stream);
     if (pre != BITNET_ERR_WORKSPACE) return pre == BITNET_OK ? BITNET_ERR_WORKSPACE : pre;
-    size_t need = 0;
-    const bitnet_status q = bitnet_quantize_weights_workspace(N, K, &need);
-    if (q != BITNET_OK) return q;
-    if (need > bitnet::kStaticScratchBytes) return BITNET_ERR_WORKSPACE;   // partial sums beyond the static array
     void* ptr = nullptr;
     size_t have = 0;
     if (bitnet::static_scratch(&ptr, &have) != hipSuccess) return BITNET_ERR_HIP;

@@ -1,0 +1,128 @@
+"""GPU tests of the weight quantizer that reads large matrices once (csrc/quant_weights.hip): codes and gamma are those of the two
+passes bit for bit, whatever the sample says of the matrix.  bitnet_quantize_weights_static has no room for notes and always
+takes the two passes, which the parity tests compare with the oracle."""
+import pytest
+
+from paper_2402_17764_amd import binding as B
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def _normal(N, K, dtype, seed, scale=0.02):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    return torch.empty((N, K), dtype=dtype, device="cuda").normal_(0.0, scale, generator=g)
+
+
+def _two_passes(W):
+    packed = torch.empty(B.packed_bytes(*W.shape), dtype=torch.uint8, device="cuda")
+    return B.quantize_weights_static(W, packed, torch.empty(1, device="cuda"))
+
+
+def _check(W, what):
+    N, K = W.shape
+    assert B.quantize_weights_workspace(N, K) > 32768
+    print("once", what, N, K, W.dtype, flush=True)
+    ref, gamma = _two_passes(W)
+    small = torch.empty(32768, dtype=torch.uint8, device="cuda")
+    for ws in (None, torch.full((B.quantize_weights_workspace(N, K),), 0xFF, dtype=torch.uint8, device="cuda"), small):
+        p, g = B.quantize_weights(W, workspace=ws)
+        assert torch.equal(g.view(torch.int32), gamma.view(torch.int32)) and torch.equal(p, ref)
+
+
+# whole and partial last row blocks and items, rows of any length, one item a row block
+@pytest.mark.parametrize("dtype,N,K", [(torch.float32, 9600, 3200), (torch.float32, 5005, 5124), (torch.float32, 6007, 4301), (torch.float32, 400001, 64),
+                                       (torch.float32, 17, 1 << 18 | 0), (torch.float32, 90, 262143),
+                                       (torch.bfloat16, 16384, 4112), (torch.bfloat16, 15001, 5001), (torch.bfloat16, 1100003, 63), (torch.bfloat16, 300, 262144 - 8)])
+def test_normal_weights(gpu_lib, dtype, N, K):
+    W = _normal(N, K, dtype, N + K)
+    if W.numel() * W.element_size() >= (128 if dtype == torch.bfloat16 else 96) << 20:
+        _check(W, "normal")
+    else:                                                  # below the line: the two passes
+        ref, gamma = _two_passes(W)
+        p, g = B.quantize_weights(W)
+        assert torch.equal(p, ref) and torch.equal(g, gamma)
+
+
+def _cases(W):
+    N, K = W.shape
+    dtype = W.dtype
+    outlier = W.clone()
+    outlier[N // 2 + 1, K // 3] = 2.0e6                    # a weight that no sample sees and that most of the mean hangs on
+    yield "outlier", outlier
+    u = torch.rand((N, K), device="cuda", generator=torch.Generator(device="cuda").manual_seed(7))
+    s = torch.where(W < 0, -1.0, 1.0)
+    yield "at the threshold", (torch.where(u < 0.5, 1.0, 1.0 / 3.0) * s).to(dtype)       # gamma 2/3: half of the weights are noted
+    yield "one magnitude", (0.75 * s).to(dtype)
+    yield "two neighbours", (torch.where(u < 0.5, 1.0, 1.0078125) * s).to(dtype)
+    yield "zeros", torch.zeros_like(W)
+    almost = torch.zeros_like(W)
+    almost[N - 1, K - 1] = -3.0
+    yield "one weight", almost
+    yield "half zeros", torch.where(u < 0.5, torch.zeros_like(W), W)
+    rows = W.clone()
+    rows[: N // 3] *= 1e-3
+    rows[N - 40:] *= 300.0
+    yield "rows of different scales", rows
+    spread = (W.double() * torch.exp2(torch.randint(-40, 40, (1, K), device="cuda", generator=torch.Generator(device="cuda").manual_seed(8)).double())).to(dtype)
+    yield "columns over 80 binades", spread
+    yield "near the smallest floats", (W.double() * 2.0 ** -126).to(dtype)
+    yield "near the largest floats", (W.double() * 2.0 ** 124).to(dtype)
+    yield "ternary already", (torch.where(u < 0.4, 0.0, 0.013) * s).to(dtype)
+
+
+@pytest.mark.parametrize("dtype,N,K", [(torch.float32, 6160, 4100), (torch.float32, 6003, 4301), (torch.bfloat16, 16400, 4104), (torch.bfloat16, 15001, 5001)])
+def test_matrices_that_the_sample_does_not_describe(gpu_lib, dtype, N, K):
+    for what, W in _cases(_normal(N, K, dtype, 5)):
+        _check(W, what)
+
+
+@pytest.mark.parametrize("dtype,rows,K", [(torch.float32, [3200, 3200, 3200], 3200), (torch.float32, [6400, 800, 1013], 4100),
+                                          (torch.bfloat16, [16000, 16, 16384], 2304), (torch.bfloat16, [1024] * 17 + [2048], 4096)])
+def test_segments(gpu_lib, dtype, rows, K):
+    W = _normal(sum(rows), K, dtype, 11)
+    at = 0
+    for i, n in enumerate(rows):
+        W[at:at + n] *= 1.0 + i                            # a gamma of its own for each
+        at += n
+    print("once, segments", rows, K, dtype, flush=True)
+    full, gammas = B.quantize_weights_segmented(W, rows)
+    small = torch.empty(32768, dtype=torch.uint8, device="cuda")
+    p, g = B.quantize_weights_segmented(W, rows, workspace=small)
+    assert torch.equal(p, full) and torch.equal(g.view(torch.int32), gammas.view(torch.int32))
+    at = 0
+    codes = B.unpack_weights(full, sum(rows), K)
+    for n in rows:
+        packed, gamma = _two_passes(W[at:at + n].contiguous())
+        assert (gammas[at // 16:(at + n + 15) // 16] == gamma).all()
+        assert torch.equal(codes[at:at + n], B.unpack_weights(packed, n, K))
+        at += n
+
+
+def test_captured_and_on_two_streams(gpu_lib):
+    """three launches that share nothing but their workspace: replays on changed weights, and two streams at once"""
+    W = [_normal(9600, 3200, torch.float32, s) for s in (1, 2)]
+    V = W[0].clone()
+    n = B.quantize_weights_workspace(9600, 3200)
+    ws = [torch.empty(n, dtype=torch.uint8, device="cuda") for _ in W]
+    out = [(torch.empty(B.packed_bytes(9600, 3200), dtype=torch.uint8, device="cuda"), torch.empty(1, device="cuda")) for _ in W]
+    ref = [_two_passes(w) for w in W]
+    B.quantize_weights(V, packed=out[0][0], gamma=out[0][1], workspace=ws[0])
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        B.quantize_weights(V, packed=out[0][0], gamma=out[0][1], workspace=ws[0])
+    for k in (1, 0, 1):
+        V.copy_(W[k])
+        graph.replay()
+        assert torch.equal(out[0][0], ref[k][0]) and torch.equal(out[0][1], ref[k][1])
+    streams = [torch.cuda.Stream() for _ in W]
+    for s in streams:
+        s.wait_stream(torch.cuda.current_stream())
+    for _ in range(3):
+        for k, s in enumerate(streams):
+            with torch.cuda.stream(s):
+                B.quantize_weights(W[k], packed=out[k][0], gamma=out[k][1], workspace=ws[k])
+    torch.cuda.synchronize()
+    for k in range(2):
+        assert torch.equal(out[k][0], ref[k][0]) and torch.equal(out[k][1], ref[k][1])
