@@ -36,12 +36,11 @@ constexpr int64_t kMaxLoopBlocks = kMaxGridThreads / 256 / 2;      // of 256 thr
 // weights through the caches, either in front of the first address or, where only the epilogue uses it, at the end.
 // (3B decode stack, 104 launches: none preloaded 639 us, the first 12 dwords as the arguments then stood 623, all 608; 7B at
 // 29 tokens, 64 launches: 385 and 369 us without and with.)
-constexpr uint32_t product_flags(int gstride, OutType yt, int vec_store = 0) {
-    return (uint32_t)yt | (uint32_t)(gstride ? 1 : 0) << 2 | (uint32_t)(vec_store ? 1 : 0) << 3;      // the kernel's own number: << 4
+constexpr uint32_t product_flags(int gstride, OutType yt) {
+    return (uint32_t)yt | (uint32_t)(gstride ? 1 : 0) << 2;      // the kernel's own number: << 4
 }
 constexpr OutType flags_out_type(uint32_t f) { return (OutType)(f & 3u); }
 constexpr int flags_gstride(uint32_t f) { return (int)(f >> 2) & 1; }
-constexpr int flags_vec_store(uint32_t f) { return (int)(f >> 3) & 1; }
 constexpr int flags_number(uint32_t f) { return (int)(f >> 4); }
 
 // quant_weights.hip

@@ -48,7 +48,6 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_ksplit_2bit(
     const int Kq = (K32 + kColsPerQuad - 1) / kColsPerQuad;
     const int RB = (int)((N + kRowsPerBlock - 1) / kRowsPerBlock), M_all = flags_number(flags), gstride = flags_gstride(flags);
     const OutType yt = flags_out_type(flags);
-    const bool wide = flags_vec_store(flags);
     const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = lane & 15, g = lane >> 4;
     const int steps = (Kq + 3) >> 2, tail_quads = 16 * (Kq - 4 * (steps - 1));
@@ -210,7 +209,7 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_ksplit_2bit(
 #pragma unroll
         for (int u = 1; u < kTop; ++u) sum[0][0] += fold[(u * kTiles + tile) * kWave + lane];
         void* y = static_cast<char*>(yv) + (int64_t)(m0 + 16 * t) * N * (yt == OutType::BF16 ? 2 : 4);
-        store_tiles<1, 1>(y, yt, wide, N, M - 16 * t, rb0 + a, sum, gm[q], sxm[q]);
+        store_tiles<1, 1>(y, yt, N, M - 16 * t, rb0 + a, sum, gm[q], sxm[q]);
     }
 #endif
 }
@@ -235,7 +234,7 @@ static hipError_t launch(const int8_t* xq, const float* sx, const void* packed, 
         if (e != hipSuccess) return e;
     }
     hipLaunchKernelGGL(kern, grid, dim3(kS * kW * kWave), lds, stream, xq, static_cast<const uint4*>(packed), gamma, sx, y, (int)N, (int)K,
-                       product_flags(gstride, yt, wide_rows(y, N, yt)) | (uint32_t)M << 4);
+                       product_flags(gstride, yt) | (uint32_t)M << 4);
     return hipGetLastError();
 }
 

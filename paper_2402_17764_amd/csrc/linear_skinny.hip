@@ -56,7 +56,6 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_skinny_2bit(
     const int RB = (int)((N + kRowsPerBlock - 1) / kRowsPerBlock), M_all = flags_number(flags), gstride = flags_gstride(flags);
     const int spg = (steps_per_split + kS - 1) / kS;
     const OutType yt = flags_out_type(flags);
-    const bool wide = flags_vec_store(flags);
     constexpr int kRing = kLx + 1;                     // LDS stages per group
     constexpr int kStageBytes = kMT * 16 * 256;        // tokens staged per step x 256 columns
     constexpr int kGroupBytes = kRing * kStageBytes;
@@ -238,7 +237,7 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_skinny_2bit(
                     acc[a][t] += fold[(((q * kW + wv) * kR + a) * kMT + t) * kWave + lane];
     }
 
-    store_tiles<kMT, kR>(y, yt, wide, N, M, rbw, acc, gm, sxm);
+    store_tiles<kMT, kR>(y, yt, N, M, rbw, acc, gm, sxm);
 #endif
 }
 
@@ -268,7 +267,6 @@ __global__ __launch_bounds__((kS * kW + 1) * kWave) void linear_skinny_ws_2bit(
     const int RB = (int)((N + kRowsPerBlock - 1) / kRowsPerBlock), M_all = flags_number(flags), gstride = flags_gstride(flags);
     const int spg = (steps_per_split + kS - 1) / kS;
     const OutType yt = flags_out_type(flags);
-    const bool wide = flags_vec_store(flags);
     constexpr int kRing = kLx + 1;                     // LDS stages per group
     constexpr int kStageBytes = kMT * 16 * 256;        // tokens staged per step x 256 columns
     constexpr int kGroupBytes = kRing * kStageBytes;
@@ -453,7 +451,7 @@ __global__ __launch_bounds__((kS * kW + 1) * kWave) void linear_skinny_ws_2bit(
         if (wave >= kS * kW) return;
     }
 
-    store_tiles<kMT, kR>(y, yt, wide, N, M, rbw, acc, gm, sxm);
+    store_tiles<kMT, kR>(y, yt, N, M, rbw, acc, gm, sxm);
 #endif
 }
 
@@ -570,7 +568,7 @@ static hipError_t launch_skinny(const int8_t* xq, const float* sx, const void* p
         return hipSuccess;
     }
     hipLaunchKernelGGL(kern, grid, dim3(kS * kW * kWave), lds, stream, xq, static_cast<const uint4*>(packed), gamma, sx,
-                       split ? workspace : y, (int)N, (int)K, product_flags(gstride, split ? OutType::I32 : yt, wide_rows(split ? workspace : y, N, split ? OutType::I32 : yt)) | (uint32_t)M << 4, sps);
+                       split ? workspace : y, (int)N, (int)K, product_flags(gstride, split ? OutType::I32 : yt) | (uint32_t)M << 4, sps);
     if (split)
         return launch_splitk_reduce(static_cast<const int32_t*>(workspace), splits, sx, gamma, gstride, 0, M, N, y, yt, stream);
     return hipGetLastError();
@@ -601,7 +599,7 @@ static hipError_t launch_skinny_ws(const int8_t* xq, const float* sx, const void
         return hipSuccess;
     }
     hipLaunchKernelGGL(kern, grid, dim3((kS * kW + 1) * kWave), lds, stream, xq, static_cast<const uint4*>(packed), gamma, sx,
-                       split ? workspace : y, (int)N, (int)K, product_flags(gstride, split ? OutType::I32 : yt, wide_rows(split ? workspace : y, N, split ? OutType::I32 : yt)) | (uint32_t)M << 4, sps);
+                       split ? workspace : y, (int)N, (int)K, product_flags(gstride, split ? OutType::I32 : yt) | (uint32_t)M << 4, sps);
     if (split)
         return launch_splitk_reduce(static_cast<const int32_t*>(workspace), splits, sx, gamma, gstride, 0, M, N, y, yt, stream);
     return hipGetLastError();

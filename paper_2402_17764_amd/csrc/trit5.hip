@@ -9,6 +9,7 @@
 // four registers of a fifth MFMA.  One step = 320 columns = five v_mfma_i32_16x16x64_i8 per row block.
 #include "bitnet_device.hpp"
 #include "bitnet_internal.hpp"
+#include "gemv_common.hpp"
 
 namespace bitnet {
 
@@ -190,15 +191,7 @@ __global__ __launch_bounds__(kS * kWave, 4) void linear_gemv16_trit5(
 #pragma unroll
         for (int a = 0; a < kR; ++a) {
             const int64_t n0 = (int64_t)(rb0 + a) * 16 + 4 * g;
-            const int v[4] = {acc[a].x >> 6, acc[a].y >> 6, acc[a].z >> 6, acc[a].w >> 6};   // drop the factor 64
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (n0 + e >= N) continue;
-                const int64_t idx = (int64_t)r * N + n0 + e;
-                if (yt == OutType::I32) static_cast<int32_t*>(y)[idx] = v[e];
-                else if (yt == OutType::F32) static_cast<float*>(y)[idx] = (float)v[e] * scale;
-                else static_cast<uint16_t*>(y)[idx] = f32_to_bf16((float)v[e] * scale);
-            }
+            if (n0 < N) store_row4(y, yt, (int64_t)r * N + n0, n0, N, acc[a], scale);
         }
     }
 }
@@ -246,7 +239,7 @@ __device__ inline TritOps trit_quotients(const v4i& w) {
 template <int kS, int kW, int kD, int kH>
 __global__ __launch_bounds__(kS * kW * kWave) void linear_quotients_trit5(
         const int8_t* __restrict__ xq, const uint4* __restrict__ packed, const float* __restrict__ gamma, const float* __restrict__ sx,
-        void* __restrict__ y, int N32, int K32, uint32_t flags /* tokens, output type, wide stores */) {
+        void* __restrict__ y, int N32, int K32, uint32_t flags /* tokens, output type */) {
 #if defined(__HIP_DEVICE_COMPILE__)
     constexpr int kThreads = kS * kW * kWave, kRsrc = 0x00020000;
     extern __shared__ uint4 smem[];
@@ -397,26 +390,8 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_quotients_trit5(
     for (int h = 0; h < kH; ++h) {
         const int m = 8 * h + r;
         if (m >= M) continue;
-        const int c = corr[m], t[4] = {v[h].x + c, v[h].y + c, v[h].z + c, v[h].w + c};
-        const float scale = (gm * sc[h]) / kQb;
-        const int64_t at = (int64_t)m * N + n0;
-        if (flags_vec_store(flags)) {                                   // rows and base allow four outputs in one store
-            if (yt == OutType::BF16)
-                *reinterpret_cast<uint2*>(static_cast<uint16_t*>(y) + at) =
-                    make_uint2(f32_to_bf16((float)t[0] * scale) | (uint32_t)f32_to_bf16((float)t[1] * scale) << 16,
-                               f32_to_bf16((float)t[2] * scale) | (uint32_t)f32_to_bf16((float)t[3] * scale) << 16);
-            else if (yt == OutType::F32)
-                *reinterpret_cast<float4*>(static_cast<float*>(y) + at) = make_float4((float)t[0] * scale, (float)t[1] * scale, (float)t[2] * scale, (float)t[3] * scale);
-            else *reinterpret_cast<int4*>(static_cast<int32_t*>(y) + at) = make_int4(t[0], t[1], t[2], t[3]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                if (n0 + e >= N) continue;
-                if (yt == OutType::I32) static_cast<int32_t*>(y)[at + e] = t[e];
-                else if (yt == OutType::F32) static_cast<float*>(y)[at + e] = (float)t[e] * scale;
-                else static_cast<uint16_t*>(y)[at + e] = f32_to_bf16((float)t[e] * scale);
-            }
-        }
+        const int c = corr[m];
+        store_sums4(y, yt, (int64_t)m * N + n0, n0, N, (v4i){v[h].x + c, v[h].y + c, v[h].z + c, v[h].w + c}, (gm * sc[h]) / kQb);
     }
 #endif
 }
@@ -639,14 +614,13 @@ static bool launch_quotients(const int8_t* xq, const float* sx, const void* pack
     const int64_t rows = M * trit_row_bytes((int)ceil_div(K, kTritStep)), fold = (int64_t)(kS - 1) * kW * (M <= 8 ? 1 : 2) * 1024;
     const int64_t lds = kTritHeader + (rows > fold ? rows : fold), wgs = ceil_div(ceil_div(N, kRowsPerBlock), kW);
     if (lds > kTritMaxLds || wgs * kS * kW * kWave >= kMaxGridThreads) return false;
-    const bool wide = N % 4 == 0 && reinterpret_cast<uintptr_t>(y) % (yt == OutType::BF16 ? 8 : 16) == 0;
     auto go = [&](auto* kernel, RaisedFlags& raised) -> hipError_t {
         if (lds > 65536) {
             const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(kernel), (int)kTritMaxLds, raised);
             if (e != hipSuccess) return e;
         }
         hipLaunchKernelGGL(kernel, dim3((unsigned)wgs), dim3(kS * kW * kWave), lds, stream, xq, static_cast<const uint4*>(packed), gamma, sx, y,
-                           (int)N, (int)K, product_flags(0, yt, wide) | (uint32_t)M << 4);
+                           (int)N, (int)K, product_flags(0, yt) | (uint32_t)M << 4);
         return hipGetLastError();
     };
     static RaisedFlags one = {}, two = {};
