@@ -557,11 +557,14 @@ static void launch_trit5(const int8_t* xq, const float* sx, const void* packed, 
 //   * a launch takes as long as its fullest CU: eight row blocks per workgroup up to 2048, where that is one workgroup each, and from
 //     3072; in between the table's workgroups are dealt out more evenly, and with few tokens in the last group it wins (32960 x 9536,
 //     nine tokens 24.7 / 34.3), else four row blocks with K split in two take half the step from one round to the next;
+//     one workgroup on every CU where eight, six or five row blocks are too many or too few for that: five or six with K split in two from
+//     ten steps on (eight tokens: 20480 x 8192 14.9 / 12.0, 17280 x 3200 7.3 / 6.8; sixteen, 22016 x 4096 11.4 / 10.0; with few tokens four
+//     waves a row block hide more), seven and eight without a split for up to four (27648 x 5120 10.2 / 9.7, 32640 x 8320 13.0 / 12.6);
 //   * the table walks whole rounds of four steps on wide layers: there its best counts are four and eight.
 // The picks are within 5 % of the faster of table and previous picks wherever measured.  x_q has to fit the LDS.
 struct QuotientForm { int s, w, d; };                  // kS, kW, kD; none: s = 0
 static QuotientForm pick_quotients(int64_t M, int64_t RB, int64_t steps) {
-    constexpr QuotientForm table{0, 0, 0}, eight{1, 8, 4}, four{2, 4, 2}, two{4, 2, 2}, one{4, 1, 2}, one_long{8, 1, 2};
+    constexpr QuotientForm table{0, 0, 0}, eight{1, 8, 4}, seven{1, 7, 4}, six{2, 6, 2}, five{2, 5, 2}, four{2, 4, 2}, two{4, 2, 2}, one{4, 1, 2}, one_long{8, 1, 2};
     if (RB <= 256) return M <= 8 && steps >= 20 && (M <= 4 || M > 6 || steps < 28) ? one_long : table;
     if (RB <= 512) {
         if (M <= 4) return steps >= 20 ? one_long : table;
@@ -582,16 +585,18 @@ static QuotientForm pick_quotients(int64_t M, int64_t RB, int64_t steps) {
         if (M <= 10) return (narrow ? steps >= 4 && steps < 14 : middle) ? table : four;
         return narrow && middle && M <= 12 ? table : four;
     }
+    if (RB <= 1536 && steps >= 10 && (M > 4 || (M > 2 && RB > 1280))) return RB <= 1280 ? five : six;
+    if (M <= 4 && RB > 1536 && RB <= 2048) return RB <= 1792 ? seven : eight;
     if (M <= 4) {
         if (RB >= 3072) return eight;
         if (RB > 2048 && steps == 4) return table;
-        if (RB >= 1536) return steps == 8 && RB < 1800 ? one : four;
+        if (RB >= 1536) return four;
         if (steps <= 4) return four;
         return M == 1 || steps < 20 ? one : two;
     }
     if (RB < 1536) {
-        if (M <= 8) return steps <= 3 ? eight : steps <= (M <= 6 ? 12 : 8) ? one : two;
-        if (M <= 10 && steps >= 5 && steps <= (RB <= 1280 ? 14 : 8)) return table;
+        if (M <= 8) return steps <= 3 ? eight : M <= 6 || steps <= 8 ? one : two;             // fewer than ten steps
+        if (M <= 10 && steps >= 5 && (RB <= 1280 || steps <= 8)) return table;
         return M <= 12 && steps >= 6 && steps <= 8 ? table : eight;
     }
     if (RB > 2048 && RB < 3072) {
@@ -644,6 +649,9 @@ hipError_t launch_linear_gemv_trit5(const int8_t* xq, const float* sx, const voi
     FORM(4, 1, 2);
     FORM(4, 2, 2);
     FORM(2, 4, 2);
+    FORM(2, 5, 2);
+    FORM(2, 6, 2);
+    FORM(1, 7, 4);
     FORM(1, 8, 4);
 #undef FORM
     // the share of a wave's padded K walk (a multiple of the prefetch depth) that is real steps
