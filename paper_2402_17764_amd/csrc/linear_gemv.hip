@@ -782,9 +782,8 @@ static hipError_t dispatch16_fused(int xmode, const void* x, const void* packed,
 }
 
 // x_q rows of any length and alignment: up to 16 tokens that fit the LDS, and more in tiles of 16 over grid y while the 64 x 128
-// tiles of the GEMM would be few (the weights then come from the L2 for every tile but the first).  Two K-split waves per row
-// block where there are many row blocks, four otherwise (the picks of the aligned kernel for one token on the same layers).
-// Up to two workgroups per CU of that form (quantization included, us, this form / the GEMM's tiles: 77 tokens, 2050 -> 1003, 315
+// tiles of the GEMM would be few (the weights then come from the L2 for every tile but the first).
+// Up to two workgroups per CU of that form (quantization included, us, four K waves on a row block / the GEMM's tiles: 77 tokens, 2050 -> 1003, 315
 // workgroups, 10.6 / 13.6; 150, 2777 -> 500, 320, 11.0 / 18.1; 40, 3900 -> 1900, 357, 11.2 / 19.1; but 200, 3333 -> 1000, 819,
 // 20.6 / 18.0).
 bool gemv_any_supports(int64_t M, int64_t N, int64_t K) {
@@ -796,8 +795,24 @@ hipError_t launch_linear_gemv_any_2bit(const int8_t* x, const float* sx, const v
                                        int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan) {
     const float* gain = nullptr;
     const float eps = 0.0f;
-    if (ceil_div(N, kRowsPerBlock) >= 1024) GEMV16(1, 2, 2, 4, kModesAny, kXLdsAny);
-    GEMV16(1, 4, 1, 4, kModesAny, kXLdsAny);
+    // Eight forms over 160 sizes (us, four K waves on a row block at depth 4 / the pick):
+    //   * one row block per workgroup while that is one round of the CUs, K over eight waves, which also stage x_q in half the time (16
+    //     tokens, 2001 -> 1000 4.8 / 3.8, one on 4097 -> 300 3.8 / 3.2);
+    //   * beyond, two row blocks share a staging of x_q: four K waves for up to four steps, which they request at once (44 tokens, 504
+    //     -> 1588 4.8 / 3.65, 16 on 1001 -> 15000 8.2 / 4.7), else eight (77 tokens, 2050 -> 1003 6.8 / 5.1, 40 on 3900 -> 1900 6.9 / 5.9);
+    //   * from five steps on many row blocks for few tokens hide more with what they had (one token, 2050 -> 9000 4.4, 5.2), more tokens on
+    //     them take two row slots (16 tokens, 4001 -> 9000 13.2 / 7.2, 4 on 4001 -> 15000 7.5 / 6.2).
+    const int64_t RB = ceil_div(N, kRowsPerBlock), steps = ceil_div(K, 256);
+    if (RB * ceil_div(M, 16) <= 256) GEMV16(1, 8, 1, 1, kModesAny, kXLdsAny);
+    if (steps <= 4) GEMV16(2, 4, 1, 1, kModesAny, kXLdsAny);
+    if (M > 16 || (M >= 4 && RB <= 512)) {
+        if (steps <= 8) GEMV16(2, 8, 1, 1, kModesAny, kXLdsAny);
+        GEMV16(2, 8, 1, 2, kModesAny, kXLdsAny);
+    }
+    if (M >= 8 || (M >= 4 && RB > 768)) GEMV16(2, 4, 2, 2, kModesAny, kXLdsAny);
+    if (RB < 1024) GEMV16(1, 4, 1, 4, kModesAny, kXLdsAny);
+    if (steps <= 12) GEMV16(2, 4, 1, 1, kModesAny, kXLdsAny);
+    GEMV16(1, 2, 2, 4, kModesAny, kXLdsAny);
 }
 #undef GEMV16
 
