@@ -78,6 +78,23 @@ def test_matrices_that_the_sample_does_not_describe(gpu_lib, dtype, N, K):
         _check(W, what)
 
 
+@pytest.mark.parametrize("dtype,N,K", [(torch.float32, 6160, 4100), (torch.bfloat16, 15001, 5001)])
+@pytest.mark.parametrize("value", [float("nan"), float("inf"), float("-inf")])
+def test_not_finite(gpu_lib, dtype, N, K, value):
+    """one such weight, which no sample sees, one in every 61 columns, which every sample sees, and nothing else"""
+    for step in (0, 61, 1):
+        W = _normal(N, K, dtype, 6)
+        if step:
+            W[:, ::step] = value
+        else:
+            W[N // 2 + 1, K // 3] = value
+        print("once", value, step, N, K, dtype, flush=True)
+        ref, gamma = _two_passes(W)
+        p, g = B.quantize_weights(W)
+        assert torch.equal(p, ref)
+        assert torch.equal(g, gamma) or (torch.isnan(g).all() and torch.isnan(gamma).all())
+
+
 @pytest.mark.parametrize("dtype,rows,K", [(torch.float32, [3200, 3200, 3200], 3200), (torch.float32, [6400, 800, 1013], 4100),
                                           (torch.bfloat16, [16000, 16, 16384], 2304), (torch.bfloat16, [1024] * 17 + [2048], 4096)])
 def test_segments(gpu_lib, dtype, rows, K):
