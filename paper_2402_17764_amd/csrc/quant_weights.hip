@@ -405,8 +405,11 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
 // ---------------------------------------------------------------------------------------------------
 // gamma has to be known before the first code, and is only known after the last weight: hence two reads.  But a code asks no more of it
 // than on which side of a threshold T(gamma) a weight lies, and a sample of W says where T is to within a few tenths of a percent:
-//   sample_abs       runs of 1 KiB, evenly spread with a random offset each: the mean of |W| and, from the spread of the runs' own
-//                    sums (which holds whatever goes together within a run or a row), its standard error
+//   sample_abs       runs of 128 bytes, one at a random place in each of as many equal stretches of W: the mean of |W| and, from the
+//                    differences of runs side by side, its standard error.  Several runs of a row, and neighbours compared with each
+//                    other alone: rows or heads of different scale do not widen the bounds (with runs of 1 KiB and the spread of all
+//                    of them, a deviation of 10 % between the rows of 3200 x 3200 did, by more than the notes hold; now, us, two passes /
+//                    this, at 50 %: 9600 x 3200 fp32 in three segments 43.7 / 40.5, 8192 x 8192 bf16 47.6 / 44.1, 57344 x 8192 328 / 206)
 //   guess_pack_2bit  reads W once: adds up |W| exactly as pass 1 does, and codes as pass 3 does with the sample's threshold.  Weights
 //                    between the thresholds of its mean -+ 5 standard errors (a fifth of a percent of normally distributed fp32 ones, of
 //                    bf16 ones those of the one or no value in between) are noted down
@@ -423,7 +426,7 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
 constexpr int64_t kGuessBytesF32 = (int64_t)96 << 20, kGuessBytesBf16 = (int64_t)128 << 20;
 constexpr int64_t kGuessMost = (int64_t)1 << 30;           // weights: a workgroup's notes fit its LDS
 constexpr int kNotes = 3584;                               // of a workgroup: 28 KiB of LDS, four workgroups a CU
-constexpr int kRunVecs = kWave;                            // a run: one 16-byte load per lane
+constexpr int kRunVecs = 8;                                // a run: one 16-byte load on each of eight lanes, a line of the caches
 
 // parts of the workspace: the partial sums from its start, ...
 constexpr int kGuessBlocks = kPackBlocks + kMaxSegs;
@@ -436,39 +439,45 @@ static_assert(kBoundsAt % 16 == 0 && kBoundsAt + sizeof(float) * 4 * kMaxSegs <=
 template <typename T, int kSegs>
 __global__ __launch_bounds__(kSumThreads) void sample_abs(const T* __restrict__ W_all, int64_t K, SegList<kSegs> list, int batches,
                                                           double* __restrict__ samples) {
-    constexpr int kWaves = kSumThreads / kWave;
+    constexpr int kWaves = kSumThreads / kWave, kRuns = kWave / kRunVecs;          // runs of one load of a wave
     int sg = 0;
     while (sg + 1 < list.n && (int)blockIdx.x >= list.s[sg + 1].part0) ++sg;
     const Seg& seg = list.s[sg];
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const uint4* Wv = reinterpret_cast<const uint4*>(W_all + seg.row0 * K);
-    const int64_t nvec = seg.count * (int64_t)sizeof(T) / 16;          // at least one run: the launcher asks for 2 MiB a segment
-    const int runs = seg.nparts * kWaves * batches * kSumLoads;
-    const int64_t stride = nvec / runs;
+    const int nvec = (int)(seg.count * (int64_t)sizeof(T) / 16);       // below 2^28; a run at least: the launcher asks for 2 MiB a segment
+    // Every weight is as likely as any other: stretches of a fraction's length leave no end of W out, and a run that starts late runs on into
+    // the next stretch.
+    const double stride = (double)nvec / (double)(seg.nparts * kWaves * batches * kSumLoads * kRuns);
     double sum = 0.0, squares = 0.0;
     for (int b = 0; b < batches; ++b) {
         uint4 v[kSumLoads];
 #pragma unroll
         for (int u = 0; u < kSumLoads; ++u) {
-            const int j = ((b * kSumLoads + u) * seg.nparts + (int)blockIdx.x - seg.part0) * kWaves + wave;
+            const int j = (((b * kSumLoads + u) * seg.nparts + (int)blockIdx.x - seg.part0) * kWaves + wave) * kRuns + lane / kRunVecs;
             uint32_t h = (uint32_t)j * 0x9E3779B1u;                    // the place of run j in its stretch of W: a hash of j
             h = (h ^ (h >> 15)) * 0x85EBCA77u;
             h ^= h >> 13;
-            const int64_t at = (int64_t)j * stride + (stride > kRunVecs ? (int64_t)(h % (uint32_t)(stride - kRunVecs + 1)) : 0);
-            v[u] = Wv[(at + kRunVecs <= nvec ? at : nvec - kRunVecs) + lane];
+            const int at = (int)(j * stride) + (int)__umulhi(h, (uint32_t)stride);
+            v[u] = Wv[min(at, nvec - kRunVecs) + lane % kRunVecs];
         }
 #pragma unroll
         for (int u = 0; u < kSumLoads; ++u) {
             const uint32_t q[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-            float f = 0.0f;
+            float run = 0.0f;
 #pragma unroll
-            for (int e = 0; e < 16 / (int)sizeof(T); ++e) f += fabsf(piece_elem<T>(q, e));
-            const double run = wave_sum_f64((double)f);
-            sum += run;
-            squares += run * run;
+            for (int e = 0; e < 16 / (int)sizeof(T); ++e) run += fabsf(piece_elem<T>(q, e));
+            run += dpp_f32<0xB1>(run);                                 // the eight lanes of the run
+            run += dpp_f32<0x4E>(run);
+            run += dpp_f32<0x141>(run);
+            const double d = (double)run - (double)dpp_f32<0x140>(run);           // against its neighbour
+            sum += (double)run;
+            squares += d * d;
         }
     }
     __shared__ double sh[2][kWaves];
+    sum = wave_sum_f64(sum) * (1.0 / kRunVecs);                        // each run on its eight lanes, each pair on sixteen
+    squares = wave_sum_f64(squares) * (0.5 / kRunVecs);
     if (lane == 0) { sh[0][wave] = sum; sh[1][wave] = squares; }
     __syncthreads();
     if (threadIdx.x < 2) {
@@ -481,7 +490,8 @@ __global__ __launch_bounds__(kSumThreads) void sample_abs(const T* __restrict__ 
 
 // gamma's bounds from a segment's samples, and the samples' mean; the same bits in every workgroup.  An empty interval (x > y) where they
 // say nothing.
-__device__ inline float3 gamma_bounds(const double* __restrict__ samples, const Seg& seg, int batches, int per_run, double* sh_hi, double* sh_lo) {
+template <typename T>
+__device__ inline float3 gamma_bounds(const double* __restrict__ samples, const Seg& seg, int batches, double* sh_hi, double* sh_lo) {
     double s = 0.0, q = 0.0;
     if ((int)threadIdx.x < seg.nparts) {
         const double2 v = reinterpret_cast<const double2*>(samples)[seg.part0 + threadIdx.x];
@@ -495,10 +505,9 @@ __device__ inline float3 gamma_bounds(const double* __restrict__ samples, const 
     s = (sh_hi[0] + sh_hi[1]) + (sh_hi[2] + sh_hi[3]);
     q = (sh_lo[0] + sh_lo[1]) + (sh_lo[2] + sh_lo[3]);
     static_assert(kPackThreads == 4 * kWave && kSumBlocks <= kPackThreads, "one sample per thread, four waves");
-    // n runs: (n q - s^2) / n^2 is the variance of one, over n that of their mean; times n it cancels least
-    const double n = (double)(seg.nparts * (kSumThreads / kWave) * batches * kSumLoads);
-    const float inv = 1.0f / ((float)n * (float)per_run), spread = (float)fmax(n * q - s * s, 0.0);
-    const float mean = (float)s * inv, off = 5.0f * inv * sqrtf(spread / (float)n) + 2e-6f * mean;
+    // the squared difference of two runs side by side is the variance of their sum, so that q is that of s
+    const float sampled = (float)(seg.nparts * (kSumThreads / kWave) * batches * kSumLoads) * (float)(16 * kWave / sizeof(T));
+    const float inv = 1.0f / sampled, mean = (float)s * inv, off = 5.0f * inv * (float)sqrt(q) + 2e-6f * mean;
     const float lo = fmaxf(mean - off, 0.0f), hi = mean + off;
     return hi <= 1.02f * lo || hi == 0.0f ? make_float3(lo, hi, mean) : make_float3(1.0f, 0.0f, mean);
 }
@@ -657,7 +666,7 @@ __global__ __launch_bounds__(kPackThreads, 4) void guess_pack_2bit(const T* __re
     constexpr int kWaves = kPackThreads / kWave;
     Noting<T> noting{0.0, {0.0, 0.0}, 0, 0, 0, 0, 0, cap / kWaves, 0, notes + wave * (kNotes / kWaves)};
     pack_items_2bit<T, kAny>(W_all + seg.row0 * K, seg, K, Kq, RB, packed, [&] {
-        const float3 b = gamma_bounds(reinterpret_cast<const double*>(ws + kSamplesAt), seg, batches, kRunVecs * Noting<T>::kE, sh_hi, sh_lo);
+        const float3 b = gamma_bounds<T>(reinterpret_cast<const double*>(ws + kSamplesAt), seg, batches, sh_hi, sh_lo);
         if ((int)blockIdx.x == seg.pack0 && threadIdx.x == 0) reinterpret_cast<float4*>(ws + kBoundsAt)[sg] = make_float4(b.x, b.y, guess_threshold(b), 0.0f);
         const int64_t items = ceil_div(seg.rows, kRowsPerBlock) * ceil_div(K, kWave * Noting<T>::kE);
         noting.set(b, (int)ceil_div(items, seg.npack) * 4 * Noting<T>::kE);

@@ -143,3 +143,28 @@ def test_captured_and_on_two_streams(gpu_lib):
     torch.cuda.synchronize()
     for k in range(2):
         assert torch.equal(out[k][0], ref[k][0]) and torch.equal(out[k][1], ref[k][1])
+
+
+def _bounds(W, rows):
+    """what the sample said of each segment, out of the scratch (csrc/quant_weights.hip, kBoundsAt): gamma's bounds, empty where it says nothing"""
+    N, K = W.shape
+    ws = torch.zeros(B.quantize_weights_workspace(N, K), dtype=torch.uint8, device="cuda")
+    _, gammas = B.quantize_weights_segmented(W, rows, workspace=ws)
+    at = (1024 + 16) * 16 + (256 + 16) * 16 + (1024 + 16) * 4
+    return ws[at:at + 16 * len(rows)].view(torch.float32).view(-1, 4).cpu(), gammas
+
+
+@pytest.mark.parametrize("dtype,rows,K", [(torch.float32, [3200] * 3, 3200), (torch.bfloat16, [8192], 8192), (torch.float32, [7001], 4099), (torch.bfloat16, [28672], 8192)])
+@pytest.mark.parametrize("deviation,block", [(0.1, 1), (0.3, 1), (0.5, 1), (0.5, 128)])
+def test_rows_of_different_scale_are_read_once(gpu_lib, dtype, rows, K, deviation, block):
+    """rows, or heads of 128 rows, whose scales deviate: the sample bounds gamma all the same"""
+    W = _normal(sum(rows), K, dtype, 21)
+    blocks = -(-W.shape[0] // block)
+    scale = torch.exp(deviation * torch.randn((blocks, 1), device="cuda", generator=torch.Generator(device="cuda").manual_seed(22)))
+    W.mul_(scale.repeat_interleave(block, 0)[: W.shape[0]].to(dtype))
+    print("once, rows of different scale", rows, K, dtype, deviation, block, flush=True)
+    bounds, gammas = _bounds(W, rows)
+    at = 0
+    for n, (lo, hi, _, _) in zip(rows, bounds.tolist()):
+        assert lo <= gammas[at // 16].item() <= hi
+        at += n
