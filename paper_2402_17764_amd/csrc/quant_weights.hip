@@ -85,18 +85,12 @@ struct Seg {
 constexpr int kMaxSegs = 16;     // of one launch; kernels for a whole matrix take a list of one
 template <int kSegs> struct SegList { int n; Seg s[kSegs]; };
 
-template <typename T, int kSegs>
-__global__ __launch_bounds__(kSumThreads) void abs_sum_partials(const T* __restrict__ W_all, int64_t K, SegList<kSegs> list,
-                                                                int vec_ok, double* __restrict__ partials) {
+// The share of thread tid of nthreads of a segment's |W| sum.
+template <typename T>
+__device__ __forceinline__ dd sum_abs(const T* __restrict__ W, const Seg& seg, bool vec_ok, int64_t tid, int64_t nthreads) {
     constexpr int kPer = 16 / (int)sizeof(T);             // elements per 16-byte vector
-    int sg = 0;
-    while (sg + 1 < list.n && (int)blockIdx.x >= list.s[sg + 1].part0) ++sg;
-    const Seg& seg = list.s[sg];
-    const T* W = W_all + seg.row0 * K;
-    const int64_t count = seg.rows * K, stream_vecs = seg.stream_vecs;
+    const int64_t count = seg.count, stream_vecs = seg.stream_vecs;
     dd acc{0.0, 0.0};
-    const int64_t tid = (int64_t)((int)blockIdx.x - seg.part0) * kSumThreads + threadIdx.x;
-    const int64_t nthreads = (int64_t)seg.nparts * kSumThreads;
     int64_t done = 0;
     if (vec_ok) {
         const int64_t nvec = count / kPer;
@@ -136,6 +130,17 @@ __global__ __launch_bounds__(kSumThreads) void abs_sum_partials(const T* __restr
         done = nvec * kPer;
     }
     for (int64_t i = done + tid; i < count; i += nthreads) dd_add_double(acc, (double)fabsf(widen1(W[i])));
+    return acc;
+}
+
+template <typename T, int kSegs>
+__global__ __launch_bounds__(kSumThreads) void abs_sum_partials(const T* __restrict__ W_all, int64_t K, SegList<kSegs> list,
+                                                                int vec_ok, double* __restrict__ partials) {
+    int sg = 0;
+    while (sg + 1 < list.n && (int)blockIdx.x >= list.s[sg + 1].part0) ++sg;
+    const Seg& seg = list.s[sg];
+    const dd acc = sum_abs(W_all + seg.row0 * K, seg, vec_ok, (int64_t)((int)blockIdx.x - seg.part0) * kSumThreads + threadIdx.x,
+                           (int64_t)seg.nparts * kSumThreads);
 
     // fixed-shape tree over the block: the same pairs are always added in the same order
     __shared__ double sh_hi[kSumThreads];
@@ -331,6 +336,9 @@ __device__ __forceinline__ void pack_items_2bit(const T* __restrict__ W, const S
     }
 
     const float thr = threshold();
+    if constexpr (Guess::kOn) {
+        if (!guess.known) return;                          // nothing to code with
+    }
 
     const int t_out = (lane >> 2) & 3, g = lane >> 4;      // the lane stores word lane & 3 of row 4w + t_out, quad column g
     for (int nth = 0; item < items; item += stride, ++nth) {
@@ -413,12 +421,16 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
 //   guess_pack_2bit  reads W once: adds up |W| exactly as pass 1 does, and codes as pass 3 does with the sample's threshold.  Weights
 //                    between the thresholds of its mean -+ 5 standard errors (a fifth of a percent of normally distributed fp32 ones, of
 //                    bf16 ones those of the one or no value in between) are noted down
+//                    Where the bounds are more than 2 % apart it only adds up, as pass 1
 //   settle_2bit      gamma from the exact sum; if it lies between its bounds, all weights but noted ones have their codes, and of those
 //                    the ones between the two thresholds (one in ten) are changed.  If it does not, or a note pad was too small, this
 //                    is pass 3.
-// gamma and codes are those of the two passes bit for bit, whatever the sample says.  What fails is a matrix whose mean hangs on a few
-// weights that the sample missed, or with a value that very many weights share right at the threshold; it then takes up to
-// 1.2 times the two passes (57344 x 8192 bf16 with one weight of 10^8 times the others 357 / 431 us, 22016 x 8192 fp32 293 / 289).
+// gamma and codes are those of the two passes bit for bit, whatever the sample says.  What fails, and what it then costs (us, two passes / this):
+//   * no bounds: rows whose scales spread over decades, small segments of rows that deviate by half.  The sample, and 5 to 12 us: 57344 x
+//     8192 bf16 328 / 357 (coded in vain as well: 403), 8192 x 8192 47.3 / 59.5, 4096 x 8192 fp32 44.5 / 54.6
+//   * a mean that hangs on a few weights that the sample missed, each tens of thousands of times the others; the pass over W is then
+//     in vain: 57344 x 8192 bf16 328 / 410, 8192 x 8192 47.5 / 73.5, 22016 x 8192 fp32 240 / 278, 4096 x 8192 44.5 / 60
+//   * a value right at the threshold that so many weights share that the notes overflow
 // us, two passes / this: bf16 57344 x 8192 334 / 207, 28672 x 8192 165 / 107, 20000 x 5001 75.6 / 67, 16384 x 4096 48.3 / 46.1; fp32 57344 x
 // 8192 642 / 388, 22016 x 4096 118 / 81, 9600 x 3200 in three segments 43.6 / 37.9, 7000 x 4096 39.8 / 33.8, 4096 x 4096 24.8 / 26.2.  What bounds it: the
 // pass runs at 0.9 of what pass 3 alone takes in bf16 (187 us for 940 + 117 MB), in fp32 13 instructions a weight and the launches
@@ -513,7 +525,7 @@ __device__ inline float3 gamma_bounds(const double* __restrict__ samples, const 
 }
 
 // The threshold that weights are coded with before gamma is known.
-__device__ inline float guess_threshold(const float3& b) { return b.x <= b.y ? (b.z + kEps) * 0.5f : 0.5f; }
+__device__ inline float guess_threshold(const float3& b) { return (b.z + kEps) * 0.5f; }
 
 // What guess_pack_2bit does with a piece of a row.
 //
@@ -528,6 +540,7 @@ template <typename T>
 struct Noting {
     static constexpr bool kOn = true;
     static constexpr int kE = 16 / (int)sizeof(T), kBits = sizeof(T) == 2 ? 8 : 24;
+    bool known;                // there are bounds
     double sum;
     dd rest;
     uint32_t least, most;      // magnitudes of T as integers (bf16: the same one in both halves)
@@ -537,15 +550,15 @@ struct Noting {
 
     // per_lane: values that a lane adds up
     __device__ void set(const float3& b, int per_lane) {
-        const bool known = b.x <= b.y;                     // else nothing is noted: settle_2bit starts anew
+        known = b.x <= b.y;
         // T(d) is within a few units in the last place of d / 2
-        const float t[3] = {((known ? b.x : 1.0f) + kEps) * (0.5f - 0x1p-20f), guess_threshold(b), ((known ? b.y : 1.0f) + kEps) * (0.5f + 0x1p-20f)};
+        const float t[3] = {(b.x + kEps) * (0.5f - 0x1p-20f), guess_threshold(b), (b.y + kEps) * (0.5f + 0x1p-20f)};
         uint32_t at[3];
 #pragma unroll
         for (int i = 0; i < 3; ++i) at[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(sizeof(T) == 2 ? (__float_as_uint(t[i]) + 0xFFFFu) >> 16 : __float_as_uint(t[i])));
         lo = at[0];
         mid = at[1];
-        hi = known ? at[2] : lo;
+        hi = at[2];
         const int exponent = b.z > 0.0f && b.z < __builtin_inff() ? max((int)(__float_as_uint(b.z) >> 23), 1) : 127;      // biased, of the mean
         const int range = 54 - kBits - (32 - __builtin_clz(per_lane)), below = sizeof(T) == 2 ? 22 : range - 8;
         const int first = exponent - below, from = max(first, 1), to = from + range;
@@ -664,7 +677,7 @@ __global__ __launch_bounds__(kPackThreads, 4) void guess_pack_2bit(const T* __re
     const int sg = pack_segment(list), wave = threadIdx.x >> 6;
     const Seg& seg = list.s[sg];
     constexpr int kWaves = kPackThreads / kWave;
-    Noting<T> noting{0.0, {0.0, 0.0}, 0, 0, 0, 0, 0, cap / kWaves, 0, notes + wave * (kNotes / kWaves)};
+    Noting<T> noting{false, 0.0, {0.0, 0.0}, 0, 0, 0, 0, 0, cap / kWaves, 0, notes + wave * (kNotes / kWaves)};
     pack_items_2bit<T, kAny>(W_all + seg.row0 * K, seg, K, Kq, RB, packed, [&] {
         const float3 b = gamma_bounds<T>(reinterpret_cast<const double*>(ws + kSamplesAt), seg, batches, sh_hi, sh_lo);
         if ((int)blockIdx.x == seg.pack0 && threadIdx.x == 0) reinterpret_cast<float4*>(ws + kBoundsAt)[sg] = make_float4(b.x, b.y, guess_threshold(b), 0.0f);
@@ -672,9 +685,13 @@ __global__ __launch_bounds__(kPackThreads, 4) void guess_pack_2bit(const T* __re
         noting.set(b, (int)ceil_div(items, seg.npack) * 4 * Noting<T>::kE);
         return 0.0f; }, noting);
 
-    __syncthreads();                                       // sh_hi and sh_lo are used again
     dd acc = noting.rest;
     dd_add_double(acc, noting.sum);
+    // Without bounds the segment is only added up, as by pass 1, and settle_2bit codes it.  By half of the waves, eight a CU: that many read
+    // fastest.
+    if (!noting.known && threadIdx.x < kPackThreads / 2)
+        acc = sum_abs(W_all + seg.row0 * K, seg, true, (int64_t)((int)blockIdx.x - seg.pack0) * (kPackThreads / 2) + threadIdx.x, (int64_t)seg.npack * (kPackThreads / 2));
+    __syncthreads();                                       // sh_hi and sh_lo are used again
     const dd mine = wave_sum_dd(acc);
     if ((threadIdx.x & 63) == 0) { sh_hi[wave] = mine.hi; sh_lo[wave] = mine.lo; used[wave] = noting.used; }
     __syncthreads();

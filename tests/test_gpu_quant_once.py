@@ -168,3 +168,36 @@ def test_rows_of_different_scale_are_read_once(gpu_lib, dtype, rows, K, deviatio
     for n, (lo, hi, _, _) in zip(rows, bounds.tolist()):
         assert lo <= gammas[at // 16].item() <= hi
         at += n
+
+
+def _times(calls, rounds=5):
+    """us of each of the calls, the best of several rounds in turn"""
+    best = [float("inf")] * len(calls)
+    for r in range(rounds + 1):
+        for i, call in enumerate(calls):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(6):
+                call()
+            b.record()
+            torch.cuda.synchronize()
+            if r:                                          # the first round warms up
+                best[i] = min(best[i], a.elapsed_time(b) * 1e3 / 6)
+    return best
+
+
+def _cost_of_failing(W):
+    """the time of quantize_weights over that of the two passes"""
+    N, K = W.shape
+    packed, gamma = torch.empty(B.packed_bytes(N, K), dtype=torch.uint8, device="cuda"), torch.empty(1, device="cuda")
+    ws = torch.empty(B.quantize_weights_workspace(N, K), dtype=torch.uint8, device="cuda")
+    two, once = _times([lambda: B.quantize_weights_static(W, packed, gamma), lambda: B.quantize_weights(W, packed=packed, gamma=gamma, workspace=ws)])
+    print("once, cost of failing: %.1f us, %.1f in two passes" % (once, two), flush=True)
+    return once / two
+
+
+def test_cost_without_bounds(gpu_lib):
+    """rows whose scales spread so far that the sample says nothing: added up, then coded, not coded twice (1.09 of the two passes; coded twice 1.23)"""
+    W = _normal(57344, 8192, torch.bfloat16, 31)
+    W.mul_(torch.exp(2.0 * torch.randn((57344, 1), device="cuda", generator=torch.Generator(device="cuda").manual_seed(32))).to(torch.bfloat16))
+    assert _cost_of_failing(W) < 1.16
