@@ -367,6 +367,9 @@ __device__ __forceinline__ void pack_items_2bit(const T* __restrict__ W, const S
                 word[t] = quad_or(code << (2 * (lane & 3)));
             }
         }
+        if constexpr (Guess::kOn) {
+            if (guess.full()) { c = next; continue; }      // the segment will be coded by settle_2bit
+        }
         const int it = items - 1 - item, rb = it / per_row;
         const int64_t s0 = (int64_t)(it - rb * per_row) * kSteps;
 #pragma unroll
@@ -430,7 +433,9 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
 //     8192 bf16 328 / 357 (coded in vain as well: 403), 8192 x 8192 47.3 / 59.5, 4096 x 8192 fp32 44.5 / 54.6
 //   * a mean that hangs on a few weights that the sample missed, each tens of thousands of times the others; the pass over W is then
 //     in vain: 57344 x 8192 bf16 328 / 410, 8192 x 8192 47.5 / 73.5, 22016 x 8192 fp32 240 / 278, 4096 x 8192 44.5 / 60
-//   * a value right at the threshold that so many weights share that the notes overflow
+//   * a value right at the threshold that very many weights share: from the item on that fills a wave's pad, that wave only adds up.  Two
+//     thirds of the weights there (noted to the end as well: third figure): 57344 x 8192 bf16 325 / 373 (551), 8192 x 8192 46.7 / 63 (92),
+//     22016 x 8192 fp32 240 / 254 (317)
 // us, two passes / this: bf16 57344 x 8192 334 / 207, 28672 x 8192 165 / 107, 20000 x 5001 75.6 / 67, 16384 x 4096 48.3 / 46.1; fp32 57344 x
 // 8192 642 / 388, 22016 x 4096 118 / 81, 9600 x 3200 in three segments 43.6 / 37.9, 7000 x 4096 39.8 / 33.8, 4096 x 4096 24.8 / 26.2.  What bounds it: the
 // pass runs at 0.9 of what pass 3 alone takes in bf16 (187 us for 940 + 117 MB), in fp32 13 instructions a weight and the launches
@@ -587,6 +592,12 @@ struct Noting {
             }
             used += __popcll(who);
         }
+    }
+
+    // Whether the wave's pad is full.  settle_2bit will then code the segment, and nothing is noted any more.
+    __device__ __forceinline__ bool full() {
+        if (used > room) lo = hi;
+        return used > room;
     }
 
     // a row's piece, its first element at `place`

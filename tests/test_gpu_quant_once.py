@@ -54,6 +54,7 @@ def _cases(W):
     u = torch.rand((N, K), device="cuda", generator=torch.Generator(device="cuda").manual_seed(7))
     s = torch.where(W < 0, -1.0, 1.0)
     yield "at the threshold", (torch.where(u < 0.5, 1.0, 1.0 / 3.0) * s).to(dtype)       # gamma 2/3: half of the weights are noted
+    yield "at the threshold in bf16", (torch.where(u < 1.0 / 3.0, 1.0, 0.25) * s).to(dtype)     # gamma 1/2
     yield "one magnitude", (0.75 * s).to(dtype)
     yield "two neighbours", (torch.where(u < 0.5, 1.0, 1.0078125) * s).to(dtype)
     yield "zeros", torch.zeros_like(W)
@@ -201,3 +202,13 @@ def test_cost_without_bounds(gpu_lib):
     W = _normal(57344, 8192, torch.bfloat16, 31)
     W.mul_(torch.exp(2.0 * torch.randn((57344, 1), device="cuda", generator=torch.Generator(device="cuda").manual_seed(32))).to(torch.bfloat16))
     assert _cost_of_failing(W) < 1.16
+
+
+def test_cost_of_full_pads(gpu_lib):
+    """a value of two thirds of the weights right at the threshold: once a pad is full nothing is noted any more (1.15 of the two passes; noted to
+    the end 1.7)"""
+    W = _normal(57344, 8192, torch.bfloat16, 33)
+    for rows in W.split(4096):
+        u = torch.rand(rows.shape, device="cuda", generator=torch.Generator(device="cuda").manual_seed(34))
+        rows.copy_(torch.where(u < 1.0 / 3.0, 1.0, 0.25) * torch.where(rows < 0, -1.0, 1.0))         # gamma 0.5
+    assert _cost_of_failing(W) < 1.4
