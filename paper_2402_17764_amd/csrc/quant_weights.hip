@@ -7,7 +7,7 @@
 //                              cache), takes the decision of Eq. (1)-(2) in fp32 and writes the packed
 //                              layout one 1 KiB (row block, K step) chunk per workgroup pass
 //
-// From 96 MiB of W on (128 of bf16) (and a workspace with room for it) the two reads become one: a sample of W bounds gamma, and with it
+// From 96 MiB of W on (128 of bf16, more for narrow matrices; and a workspace with room for it) the two reads become one: a sample of W bounds gamma, and with it
 // the threshold of Eq. (1)-(2), so that one pass adds up |W| and codes every weight but the few between the bounds
 // (guess_pack_2bit below).
 //
@@ -964,14 +964,22 @@ size_t quant_weights_workspace_bytes(int64_t N, int64_t K) {
     return (count * 4 >= kGuessBytesF32 || count * 2 >= kGuessBytesBf16) && count <= kGuessMost ? kNotesAt + (size_t)kGuessBlocks * guess_cap(count) * sizeof(uint2) : kNotesAt;
 }
 // Whether the segments of a launch are read once.  Each needs a sample: 2 MiB of it at least.
+// The pass that reads once has most to do for each item, and the lanes of an item past the row's end do it in vain: the fewer of them are
+// filled, the larger a matrix has to be (us, two passes / once; share of lanes filled that breaks even at 105 MB of fp32 0.75, at 420 MB
+// 0.35, of bf16 at 136 MB 0.87, at 419 MB 0.42).  fp32, K = 64 (0.25) 54.5 / 71.2 at 105 MB and 196 / 228 at 420, 192 (0.75) 37.3 / 37.3
+// and 140 / 98 (96, 0.38, still loses at 420: 158 / 162); bf16, 256 (0.5) 57.1 / 71.9 at 136 MB and 154 / 142 at 419, 1280 (0.83) 49.5 / 52.2 and 146 / 102, 4100 (0.89)
+// 54.0 / 50.9 and 154 / 110.
 template <int kSegs>
 static bool guess_applies(const void* W, int64_t N, int64_t K, int64_t esz, const SegList<kSegs>& list, size_t workspace_bytes) {
-    int64_t rows = 0;
+    int64_t rows = 0, row_blocks = 0;
     for (int i = 0; i < list.n; ++i) {
         rows += list.s[i].rows;
+        row_blocks += ceil_div(list.s[i].rows, kRowsPerBlock);
         if (list.s[i].count * esz < (int64_t)2 << 20) return false;
     }
-    return rows * K * esz >= (esz == 2 ? kGuessBytesBf16 : kGuessBytesF32) && N * K <= kGuessMost && reinterpret_cast<uintptr_t>(W) % 16 == 0 &&
+    const int64_t bytes = rows * K * esz, least = esz == 2 ? kGuessBytesBf16 : kGuessBytesF32, cols = kWave * 16 / esz;       // of an item
+    const double filled = (double)(rows * K) / (double)(row_blocks * kRowsPerBlock * ceil_div(K, cols) * cols);
+    return bytes >= least && (filled - 0.2) * (double)bytes >= 0.7 * (double)least && N * K <= kGuessMost && reinterpret_cast<uintptr_t>(W) % 16 == 0 &&
            workspace_bytes >= quant_weights_workspace_bytes(N, K);
 }
 

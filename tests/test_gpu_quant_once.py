@@ -34,7 +34,7 @@ def _check(W, what):
 # whole and partial last row blocks and items, rows of any length, one item a row block
 @pytest.mark.parametrize("dtype,N,K", [(torch.float32, 9600, 3200), (torch.float32, 5005, 5124), (torch.float32, 6007, 4301), (torch.float32, 400001, 64),
                                        (torch.float32, 17, 1 << 18 | 0), (torch.float32, 90, 262143),
-                                       (torch.bfloat16, 16384, 4112), (torch.bfloat16, 15001, 5001), (torch.bfloat16, 1100003, 63), (torch.bfloat16, 300, 262144 - 8)])
+                                       (torch.float32, 1100003, 100), (torch.bfloat16, 700001, 250), (torch.bfloat16, 16384, 4112), (torch.bfloat16, 15001, 5001), (torch.bfloat16, 1100003, 63), (torch.bfloat16, 300, 262144 - 8)])
 def test_normal_weights(gpu_lib, dtype, N, K):
     W = _normal(N, K, dtype, N + K)
     if W.numel() * W.element_size() >= (128 if dtype == torch.bfloat16 else 96) << 20:
@@ -212,3 +212,17 @@ def test_cost_of_full_pads(gpu_lib):
         u = torch.rand(rows.shape, device="cuda", generator=torch.Generator(device="cuda").manual_seed(34))
         rows.copy_(torch.where(u < 1.0 / 3.0, 1.0, 0.25) * torch.where(rows < 0, -1.0, 1.0))         # gamma 0.5
     assert _cost_of_failing(W) < 1.4
+
+
+@pytest.mark.parametrize("dtype,N,K,once", [(torch.float32, 400001, 64, False), (torch.float32, 1700000, 64, False), (torch.float32, 1100003, 100, True),
+                                            (torch.float32, 101000, 260, False), (torch.float32, 102400, 256, True), (torch.bfloat16, 530000, 128, False),
+                                            (torch.bfloat16, 266000, 256, False), (torch.bfloat16, 53200, 1280, False), (torch.bfloat16, 820000, 256, True),
+                                            (torch.bfloat16, 16700, 4100, True)])
+def test_narrow_matrices_are_read_twice(gpu_lib, dtype, N, K, once):
+    """where the lanes past a row's end cost more than the second read; the bounds in the scratch are written by the single read alone"""
+    W = _normal(N, K, dtype, 41)
+    ws = torch.full((B.quantize_weights_workspace(N, K),), 0xFF, dtype=torch.uint8, device="cuda")
+    print("once, narrow", N, K, dtype, flush=True)
+    B.quantize_weights(W, workspace=ws)
+    at = (1024 + 16) * 16 + (256 + 16) * 16 + (1024 + 16) * 4
+    assert bool((ws[at:at + 16] == 0xFF).all()) != once
