@@ -4,6 +4,7 @@ device assembly the shipped object was assembled from; here its parser is run on
 assembly of the current build.  So is the one that finds LDS reads outstanding at a barrier: behind it the next copy is
 written to the stage that they read."""
 import os
+import re
 
 import pytest
 
@@ -92,3 +93,24 @@ def test_outstanding_lds_reads_are_found_on_every_path(body, reads):
             Bld.check_lds_reads(_waits(body), [p], [p])
         with pytest.raises(RuntimeError):
             Bld.check_lds_reads(_waits(body), [], [])
+
+
+def _wide_stores_first(asm):
+    """{instantiation: (8-byte stores in front of the first of a single bf16 output, outputs of four that a wave holds)}"""
+    found = {}
+    for m in re.finditer(r"^_ZN6bitnet\d+(linear_skinny(?:_ws)?_2bit)I((?:Li\d+E)+)E\S*:[^\n]*\n(.*?)^\.Lfunc_end", asm, re.M | re.S):
+        p = tuple(int(v) for v in re.findall(r"Li(\d+)E", m.group(2)))
+        head = re.split(r"\bglobal_store_(?:short|byte)", m.group(3), maxsplit=1)[0]
+        found[m.group(1), p] = (len(re.findall(r"\bglobal_store_dwordx2\b", head)), p[0] * p[1])
+    return found
+
+
+def test_stores_by_the_element_stand_apart():
+    """the test for a row's end, and the single stores behind it, in front of every wide store cost short launches 4 %"""
+    asm = os.path.join(Bld.BUILD, "linear_skinny-hip-amdgcn-amd-amdhsa-gfx950.s")
+    if not os.path.exists(asm):
+        pytest.skip("no build directory here (the library was built elsewhere)")
+    found = _wide_stores_first(open(asm).read())
+    assert len(found) >= 10
+    for which, (wide, held) in found.items():
+        assert wide >= held, which
