@@ -480,9 +480,10 @@ constexpr int64_t kSkinnyMaxTokens = 512;      // beyond 64 tokens only where on
 //     (K >= 5120: 7B down at 512 tokens 28.3 against 36.0 us; with K = 3200 the prefill kernel is 1.4x faster there).
 //   * Tiles of 80 tokens on four row blocks (linear_ksplit.hip) where those of 64 would need more than four and five sixths of the
 //     80-token tiles are tokens, no more of them padding than of the 64-token ones: 300 tokens, 11008 -> 4096 17.9 us, 64 x 6 22.4; 200 tokens,
-//     13824 -> 5120 20.8 / 27.3; 160 tokens, 8192 -> 8192 15.3 / 20.8; 300 tokens, 4096 -> 4096 9.6, the prefill kernel 12.5.
+//     13824 -> 5120 20.8 / 27.3; 160 tokens, 8192 -> 8192 15.3 / 20.8; 300 tokens, 4096 -> 4096 9.6, the prefill kernel 12.5.  From seven K
+//     steps on: with fewer most of the eight waves that share them out have none (228 tokens, 560 -> 5120 5.73, 64 x 6 5.41).
 // Returns false where these kernels should not run (above 64 tokens and no such launch); kmt and rpw are valid anyway.
-static bool skinny_shape(int64_t M, int64_t RBc, int* kmt_out, int* rpw_out, bool tiles_of_80) {
+static bool skinny_shape(int64_t M, int64_t RBc, int* kmt_out, int* rpw_out, bool with_80) {
     const int kmt_full = M <= 16 ? 1 : M <= 32 ? 2 : 4;            // the smallest tile that holds all tokens (64 at most)
     int kmt = kmt_full, rpw = 16;
     bool ok = true;
@@ -497,7 +498,7 @@ static bool skinny_shape(int64_t M, int64_t RBc, int* kmt_out, int* rpw_out, boo
         else if (c4) { kmt = 4; rpw = c4; }
         else ok = false;
         const int64_t of_80 = ceil_div(M, 80) * 80;
-        if (ok && tiles_of_80 && kmt == 4 && rpw > 4 && 6 * M >= 5 * of_80 && of_80 <= ceil_div(M, 64) * 64 && ceil_div(RBc, 4) * (of_80 / 80) <= 256) {
+        if (ok && with_80 && kmt == 4 && rpw > 4 && 6 * M >= 5 * of_80 && of_80 <= ceil_div(M, 64) * 64 && ceil_div(RBc, 4) * (of_80 / 80) <= 256) {
             kmt = 5; rpw = 4;
         }
     } else {
@@ -527,20 +528,26 @@ static bool skinny_addressable(int64_t M, int64_t N, int64_t K, const void* xq) 
            ceil_div(N, kRowsPerBlock) < ((int64_t)1 << 21);
 }
 
+static bool tiles_of_80(int64_t K) { return K > 1536; }
+
 bool gemv_supports(int64_t M, int64_t N, int64_t K, const void* xq) {
     if (!skinny_addressable(M, N, K, xq)) return false;
     if (M > 256 && K < 5120) return false;          // a short K: the prefill kernel's few workgroups are done quickly
     int kmt, rpw;
-    return skinny_shape(M, ceil_div(N, kRowsPerBlock), &kmt, &rpw, true);
+    return skinny_shape(M, ceil_div(N, kRowsPerBlock), &kmt, &rpw, tiles_of_80(K));
 }
 
 bool gemv_chosen(int64_t M, int64_t N, int64_t K, const void* xq) {
     if (M <= 256 || K >= 5120) return gemv_supports(M, N, K, xq);
     // a short K after all: on small layers (300 tokens, 2048 -> 1024: prefill 7.0 us, here 4.0; 400 tokens, 2048 -> 2048 7.2 / 5.7) and in
-    // tiles of 80 tokens (300 tokens, 4096 -> 4096 12.5 / 9.6)
+    // tiles of 80 tokens (300 tokens, 4096 -> 4096 12.5 / 9.6).  But not so short that the eight waves have little to share out, the less
+    // the more each has to fold (prefill / here: four row blocks, 467 tokens on 336 -> 1984 4.19 / 4.82, 481 on 1280 -> 2016 5.6 / 5.8, from
+    // six K steps on 0.93; 80 tokens, 476 on 64 -> 2384 3.7 / 5.5, 309 on 1248 -> 3856 5.9 / 6.9, from seven on 0.92; two row blocks lose
+    // 3 % on one step and gain 10 on two).
     int kmt, rpw;
     const int64_t RB = ceil_div(N, kRowsPerBlock);
-    return skinny_addressable(M, N, K, xq) && skinny_shape(M, RB, &kmt, &rpw, true) && (kmt == 5 || (RB <= 160 && rpw <= 4));
+    if (!skinny_addressable(M, N, K, xq) || !skinny_shape(M, RB, &kmt, &rpw, tiles_of_80(K))) return false;
+    return kmt == 5 || (RB <= 160 && rpw <= 4 && (rpw == 1 || K > (rpw == 2 ? 256 : 1280)));
 }
 
 template <int kMT, int kR, int kW, int kS, int kD, int kLx>
@@ -640,7 +647,7 @@ hipError_t launch_linear_gemv_2bit(const int8_t* xq, const float* sx, const void
     return launch_skinny_ws<__VA_ARGS__>(xq, sx, packed, gamma, gstride, M, N, K, y, yt, stream, splits, workspace, plan)
     // The kernel forms per size come from sweeps over the 3B ... 70B LLaMA family shapes (31 forms, 8 ... 256 tokens).
     int kmt, rpw;
-    skinny_shape(M, RBc, &kmt, &rpw, splits == 1);
+    skinny_shape(M, RBc, &kmt, &rpw, splits == 1 && tiles_of_80(K));
     // The smaller workgroup tiles: K steps dealt out to the waves.  With more row blocks the kernels below are the faster ones (16
     // tokens, 4096 -> 22016: 6.79 us, six row blocks there 6.84; 64 tokens 11.2 / 12.2); they also have the forced split-K.
     hipError_t status;

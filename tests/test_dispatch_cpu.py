@@ -395,3 +395,14 @@ def test_no_dispatch_rule_asks_for_an_instantiation_that_is_not_built():
                 assert d["params"][4] in ((2, 4, 6) if dtype == "bf16" else (3, 5, 7)), (entry, M, N, K, d)
                 seen.add((d["kernel"], tuple(d["params"][:4])))
     assert len(seen) >= 15
+
+
+@pytest.mark.parametrize("M,N,K,kernel,tile", [
+    (476, 2384, 64, "prefill", None), (309, 3856, 1248, "prefill", None), (280, 4096, 1536, "prefill", None), (280, 4096, 1552, "batched_decode", 5),
+    (467, 1984, 336, "prefill", None), (481, 2016, 1280, "prefill", None), (481, 2016, 1296, "batched_decode", 4),
+    (300, 800, 256, "prefill", None), (300, 800, 272, "batched_decode", 2), (300, 300, 64, "batched_decode", 2),
+    (228, 5120, 560, "batched_decode_loader", 4), (228, 5120, 1536, "batched_decode_loader", 4), (228, 5120, 1552, "batched_decode", 5)])
+def test_k_dealt_out_to_eight_waves_needs_steps_to_deal(M, N, K, kernel, tile):
+    """few K steps leave most of the eight waves without one: the kernels that share stages, and beyond 256 tokens the prefill kernel, were up to 1.5 times as fast"""
+    d = B.linear_describe(M, N, K)
+    assert d["kernel"] == kernel and (tile is None or d["params"][0] == tile)
