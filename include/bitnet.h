@@ -284,8 +284,10 @@ bitnet_status bitnet_linear_variant(const int8_t* xq, const float* sx, const voi
  *                            K groups (512 tile rows: the eight-wave form with two row groups); grid y = split-K factor
  *     decode_any             K not a multiple of 16: as decode, up to 16 tokens per workgroup (x_q source 8: rows of any
  *     prefill_any            length and alignment, through LDS), and as prefill (no split)
- *     reference              one thread per output; no parameters, like
- *     trit5_decode, trit5_reference
+ *     trit5_decode           5-trit weights, up to 16 tokens (of more: the launch for 16 of them): row blocks per wave, K waves,
+ *                            prefetch depth; or, where the digits are left to the matrix pipe, K waves, row slots, prefetch
+ *                            depth, groups of eight tokens
+ *     reference, trit5_reference   one thread per output; no parameters
  *   5-trit weights, more than 16 tokens and a workspace that holds the 2-bit copy (bitnet_linear_workspace_format):
  *   the plan of the 2-bit launch that follows the repacking pass, with " repack=trit5_to_2bit" appended
  */

@@ -374,7 +374,9 @@ bitnet_status bitnet_linear_describe(int64_t M, int64_t N, int64_t K, bitnet_for
         return (n < 0 || (size_t)n >= text_bytes - at) ? BITNET_ERR_WORKSPACE : BITNET_OK;
     }
     if (f == BITNET_PACK_TRIT5) {
-        plan.kernel = bitnet::gemv_trit5_supports(M < 16 ? M : 16, N, K, xq) ? "trit5_decode" : "trit5_reference";
+        const int64_t m = M < 16 ? M : 16;
+        if (!bitnet::gemv_trit5_supports(m, N, K, xq)) plan.kernel = "trit5_reference";
+        else if (bitnet::launch_linear_gemv_trit5(xq, fp, vp, fp, m, N, K, vp, OutType::BF16, nullptr, &plan) != hipSuccess) return BITNET_ERR_HIP;
     } else if (bitnet::gemv_chosen(M, N, K, xq)) {
         const hipError_t e = bitnet::launch_linear_gemv_2bit(xq, fp, vp, fp, 0, M, N, K, vp, OutType::BF16, nullptr, ws, workspace_bytes,
                                                             0, &plan);

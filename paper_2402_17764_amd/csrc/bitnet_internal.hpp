@@ -172,6 +172,6 @@ hipError_t launch_linear_reference_trit5(const int8_t* xq, const float* sx, cons
 hipError_t launch_repack(const void* in, bool in_trit5, int64_t N, int64_t K, void* out, hipStream_t stream);
 bool gemv_trit5_supports(int64_t M, int64_t N, int64_t K, const void* xq);
 hipError_t launch_linear_gemv_trit5(const int8_t* xq, const float* sx, const void* packed, const float* gamma,
-                                    int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream);
+                                    int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan = nullptr);
 
 }  // namespace bitnet

@@ -541,8 +541,9 @@ bool gemv_trit5_supports(int64_t M, int64_t N, int64_t K, const void* xq) {
 
 template <int kR, int kS, int kD>
 static void launch_trit5(const int8_t* xq, const float* sx, const void* packed, const float* gamma, int64_t M, int64_t N,
-                         int64_t K, void* y, OutType yt, hipStream_t stream) {
+                         int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan) {
     const int RB = (int)ceil_div(N, kRowsPerBlock);
+    if (plan) return plan->set("trit5_decode", {kR, kS, kD}, (unsigned)ceil_div(RB, kR), 1, kS * kWave, 0, 1);
     hipLaunchKernelGGL((linear_gemv16_trit5<kR, kS, kD>), dim3((unsigned)ceil_div(RB, kR)), dim3(kS * kWave), 0, stream, xq,
                        static_cast<const uint4*>(packed), gamma, sx, y, (int)N, (int)K, product_flags(0, yt) | (uint32_t)M << 4);
 }
@@ -615,10 +616,15 @@ constexpr int64_t kTritMaxLds = 160 * 1024;
 
 template <int kS, int kW, int kD>
 static bool launch_quotients(const int8_t* xq, const float* sx, const void* packed, const float* gamma, int64_t M, int64_t N,
-                             int64_t K, void* y, OutType yt, hipStream_t stream, hipError_t* status) {
+                             int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan, hipError_t* status) {
+    if (M > 8 && (kW == 1 || kW == 7)) return false;       // not picked for two groups of eight tokens, and not built
     const int64_t rows = M * trit_row_bytes((int)ceil_div(K, kTritStep)), fold = (int64_t)(kS - 1) * kW * (M <= 8 ? 1 : 2) * 1024;
     const int64_t lds = kTritHeader + (rows > fold ? rows : fold), wgs = ceil_div(ceil_div(N, kRowsPerBlock), kW);
     if (lds > kTritMaxLds || wgs * kS * kW * kWave >= kMaxGridThreads) return false;
+    if (plan) {
+        plan->set("trit5_decode", {kS, kW, kD, M <= 8 ? 1 : 2}, (unsigned)wgs, 1, kS * kW * kWave, (size_t)lds, 1);
+        return true;
+    }
     auto go = [&](auto* kernel, RaisedFlags& raised) -> hipError_t {
         if (lds > 65536) {
             const hipError_t e = raise_dynamic_lds(reinterpret_cast<const void*>(kernel), (int)kTritMaxLds, raised);
@@ -631,20 +637,19 @@ static bool launch_quotients(const int8_t* xq, const float* sx, const void* pack
     static RaisedFlags one = {}, two = {};
     if (M <= 8) {
         *status = go(linear_quotients_trit5<kS, kW, kD, 1>, one);
-    } else {
-        if constexpr (kW == 1) return false;               // not picked for two groups of eight tokens
-        else *status = go(linear_quotients_trit5<kS, kW, kD, 2>, two);
+    } else if constexpr (kW != 1 && kW != 7) {
+        *status = go(linear_quotients_trit5<kS, kW, kD, 2>, two);
     }
     return true;
 }
 
 hipError_t launch_linear_gemv_trit5(const int8_t* xq, const float* sx, const void* packed, const float* gamma,
-                                    int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream) {
+                                    int64_t M, int64_t N, int64_t K, void* y, OutType yt, hipStream_t stream, LaunchPlan* plan) {
     const int64_t RB = ceil_div(N, kRowsPerBlock);
     const int64_t steps = ceil_div(K, kTritStep);
     const QuotientForm f = pick_quotients(M, RB, steps);
     hipError_t e = hipSuccess;
-#define FORM(S_, W_, D_) if (f.s == S_ && f.w == W_ && f.d == D_ && launch_quotients<S_, W_, D_>(xq, sx, packed, gamma, M, N, K, y, yt, stream, &e)) return e
+#define FORM(S_, W_, D_) if (f.s == S_ && f.w == W_ && f.d == D_ && launch_quotients<S_, W_, D_>(xq, sx, packed, gamma, M, N, K, y, yt, stream, plan, &e)) return e
     FORM(8, 1, 2);
     FORM(4, 1, 2);
     FORM(4, 2, 2);
@@ -659,13 +664,13 @@ hipError_t launch_linear_gemv_trit5(const int8_t* xq, const float* sx, const voi
     // Measured on MI355X, M = 1, fifteen forms per shape: 3200 -> 3200 4.0 -> 3.5 us and 3200 -> 17280 8.0 -> 6.6 us with
     // depth 3 (ten steps fill three rounds of four waves exactly; thirteen steps would walk 24), 4096 -> 22016 9.4 -> 8.7 us
     // and 28672 -> 8192 17.9 -> 15.5 us with two row blocks per wave.
-    if (RB >= 2048)                                   launch_trit5<2, 2, 2>(xq, sx, packed, gamma, M, N, K, y, yt, stream);
-    else if (steps >= 64 && RB >= 512)                launch_trit5<2, 8, 2>(xq, sx, packed, gamma, M, N, K, y, yt, stream);
-    else if (steps >= 24)                             launch_trit5<1, 8, 2>(xq, sx, packed, gamma, M, N, K, y, yt, stream);
-    else if (walk(4, 3) > walk(4, 2))                 launch_trit5<1, 4, 3>(xq, sx, packed, gamma, M, N, K, y, yt, stream);
-    else if (RB >= 1024)                              launch_trit5<2, 4, 2>(xq, sx, packed, gamma, M, N, K, y, yt, stream);
-    else                                              launch_trit5<1, 4, 2>(xq, sx, packed, gamma, M, N, K, y, yt, stream);
-    return hipGetLastError();
+    if (RB >= 2048)                                   launch_trit5<2, 2, 2>(xq, sx, packed, gamma, M, N, K, y, yt, stream, plan);
+    else if (steps >= 64 && RB >= 512)                launch_trit5<2, 8, 2>(xq, sx, packed, gamma, M, N, K, y, yt, stream, plan);
+    else if (steps >= 24)                             launch_trit5<1, 8, 2>(xq, sx, packed, gamma, M, N, K, y, yt, stream, plan);
+    else if (walk(4, 3) > walk(4, 2))                 launch_trit5<1, 4, 3>(xq, sx, packed, gamma, M, N, K, y, yt, stream, plan);
+    else if (RB >= 1024)                              launch_trit5<2, 4, 2>(xq, sx, packed, gamma, M, N, K, y, yt, stream, plan);
+    else                                              launch_trit5<1, 4, 2>(xq, sx, packed, gamma, M, N, K, y, yt, stream, plan);
+    return plan ? hipSuccess : hipGetLastError();
 }
 
 }  // namespace bitnet
