@@ -200,10 +200,11 @@ __global__ __launch_bounds__(kS * kWave, 4) void linear_gemv16_trit5(
 // the same product with the digits left to the matrix pipe, M <= 16, x_q in LDS
 // ---------------------------------------------------------------------------------------------------
 // The kernel above is bound by its table: sixteen look-ups of eight bytes per 80 weights and lane, at random addresses of one 2 KB
-// table, 15 clocks of the CU's LDS each (27648 x 5120 at four tokens: 11.2 us for 28 MB, here 9.9; sixteen 18.4, here
-// 12.7).  What is left of the 9.9 us: the arithmetic, 74 vector instructions per lane and chunk of 5120 weights, is 4.2 of them (27
-// chunks a SIMD at five clocks an instruction), the bytes 5.5, and 432 workgroups on 256 CUs give 176 of them eight row blocks where
-// the mean is 6.75, each behind a staging of x_q.  Here no digit is ever formed.  With
+// table, 15 clocks of the CU's LDS each (27648 x 5120 at four tokens: 11.2 us for 28 MB, here 9.4; sixteen 18.4, here
+// 12.7).  What is left of the 9.4 us: the arithmetic, 74 vector instructions per lane and chunk of 5120 weights, is 5.0 of them on the
+// fullest SIMDs (247 workgroups of seven row blocks, a wave each: 32 chunks where the mean is 27, at five clocks an instruction), the
+// bytes 5.5, and in front of both the staging of x_q, with a quarter of a wave's weights (kD of its 16 steps) requested ahead of it.
+//  Here no digit is ever formed.  With
 // f_d = floor(byte / 3^d) a digit is t_d = f_d - 3 f_(d+1), so
 //     sum_d x_d t_d  =  sum_(d = 0..4) x_d f_d  -  3 sum_(d = 1..4) x_(d-1) f_d,
 // and the quotients are small enough for int8 operands: f_0 is the byte itself (taken as byte - 128), f_1 <= 80, f_2 <= 26, f_3 <= 8,
@@ -560,7 +561,7 @@ static void launch_trit5(const int8_t* xq, const float* sx, const void* packed, 
 //     nine tokens 24.7 / 34.3), else four row blocks with K split in two take half the step from one round to the next;
 //     one workgroup on every CU where eight, six or five row blocks are too many or too few for that: five or six with K split in two from
 //     ten steps on (eight tokens: 20480 x 8192 14.9 / 12.0, 17280 x 3200 7.3 / 6.8; sixteen, 22016 x 4096 11.4 / 10.0; with few tokens four
-//     waves a row block hide more), seven and eight without a split for up to four (27648 x 5120 10.2 / 9.7, 32640 x 8320 13.0 / 12.6);
+//     waves a row block hide more: three 21424 x 4608 9.4 / 8.8, 24560 x 3968 8.8 / 8.4, four 20496 x 3520 7.5 / 7.1), seven and eight without a split for up to four (27648 x 5120 10.2 / 9.7, 32640 x 8320 13.0 / 12.6);
 //   * the table walks whole rounds of four steps on wide layers: there its best counts are four and eight.
 // The picks are within 5 % of the faster of table and previous picks wherever measured.  x_q has to fit the LDS.
 struct QuotientForm { int s, w, d; };                  // kS, kW, kD; none: s = 0
@@ -586,7 +587,7 @@ static QuotientForm pick_quotients(int64_t M, int64_t RB, int64_t steps) {
         if (M <= 10) return (narrow ? steps >= 4 && steps < 14 : middle) ? table : four;
         return narrow && middle && M <= 12 ? table : four;
     }
-    if (RB <= 1536 && steps >= 10 && (M > 4 || (M > 2 && RB > 1280))) return RB <= 1280 ? five : six;
+    if (RB <= 1536 && steps >= 10 && (M > 4 || (M == 4 && RB > 1360))) return RB <= 1280 ? five : six;
     if (M <= 4 && RB > 1536 && RB <= 2048) return RB <= 1792 ? seven : eight;
     if (M <= 4) {
         if (RB >= 3072) return eight;
