@@ -797,13 +797,14 @@ hipError_t launch_linear_gemv_any_2bit(const int8_t* x, const float* sx, const v
     const float eps = 0.0f;
     // Eight forms over 160 sizes (us, four K waves on a row block at depth 4 / the pick):
     //   * one row block per workgroup while that is one round of the CUs, K over eight waves, which also stage x_q in half the time (16
-    //     tokens, 2001 -> 1000 4.8 / 3.8, one on 4097 -> 300 3.8 / 3.2);
+    //     tokens, 2001 -> 1000 4.8 / 3.8, one on 4097 -> 300 3.8 / 3.2); but one or two tokens on 9 to 16 steps are staged soon, and four
+    //     waves request four steps each at once, eight of them one of two (one token, 3281 -> 1578 3.2 / 3.9, 3810 -> 750 3.5 / 3.7);
     //   * beyond, two row blocks share a staging of x_q: four K waves for up to four steps, which they request at once (44 tokens, 504
     //     -> 1588 4.8 / 3.65, 16 on 1001 -> 15000 8.2 / 4.7), else eight (77 tokens, 2050 -> 1003 6.8 / 5.1, 40 on 3900 -> 1900 6.9 / 5.9);
     //   * from five steps on many row blocks for few tokens hide more with what they had (one token, 2050 -> 9000 4.4, 5.2), more tokens on
     //     them take two row slots (16 tokens, 4001 -> 9000 13.2 / 7.2, 4 on 4001 -> 15000 7.5 / 6.2).
     const int64_t RB = ceil_div(N, kRowsPerBlock), steps = ceil_div(K, 256);
-    if (RB * ceil_div(M, 16) <= 256) GEMV16(1, 8, 1, 1, kModesAny, kXLdsAny);
+    if (RB * ceil_div(M, 16) <= 256 && (M > 2 || steps <= 8 || steps > 16)) GEMV16(1, 8, 1, 1, kModesAny, kXLdsAny);
     if (steps <= 4) GEMV16(2, 4, 1, 1, kModesAny, kXLdsAny);
     if (M > 16 || (M >= 4 && RB <= 512)) {
         if (steps <= 8) GEMV16(2, 8, 1, 1, kModesAny, kXLdsAny);
