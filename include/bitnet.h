@@ -335,6 +335,7 @@ bitnet_status bitnet_entry_describe(bitnet_entry entry, bitnet_dtype x_dtype, in
  *                    BITNET_KERNEL_GEMM_SPLITK_n to force n splits (BITNET_ERR_WORKSPACE if the buffer is too small
  *                    or K has fewer than n steps of 256 columns); the split then runs on the kernel family the
  *                    automatic choice takes for the shape: batched decode from 5 tokens on where it serves it, else the prefill kernel
+ *                    (which also takes the splits of 257 to 512 tokens on K < 5120)
  *   workspace        device memory, 16-byte aligned, or NULL (then this is bitnet_linear); contents are scratch:
  *                    nothing is expected in it and nothing of value is left; calls that share it must not overlap
  *   workspace_bytes  its size; bitnet_linear_workspace reports the size with which every split the model may want fits

@@ -266,9 +266,9 @@ bitnet_status bitnet_linear_workspace(int64_t M, int64_t N, int64_t K, size_t* b
     // 512 of them); the batched-decode kernels split only when forced
     const int64_t tiles = ((M + 63) / 64) * ((N + 127) / 128);
     const int skinny_splits = bitnet::skinny_splitk_splits(M, N, K);
-    // (the batched-decode kernels serve up to 256 tokens on small layers; x_q is assumed aligned here)
+    // (where the batched-decode kernels are chosen there is nothing to split; x_q is assumed aligned here)
     if (K % 16 != 0) *bytes = 0;                       // the kernel forms for such rows never split K
-    else if (bitnet::gemv_supports(M, N, K, nullptr)) *bytes = skinny_splits > 1 ? bitnet::splitk_workspace_bytes(M, N, skinny_splits) : 0;
+    else if (bitnet::gemv_chosen(M, N, K, nullptr)) *bytes = skinny_splits > 1 ? bitnet::splitk_workspace_bytes(M, N, skinny_splits) : 0;
     else *bytes = tiles < 512 ? bitnet::splitk_workspace_bytes(M, N, 8) : 0;
     return BITNET_OK;
 }

@@ -421,3 +421,14 @@ def test_ragged_rows_of_one_or_two_tokens_request_their_steps_at_once(M, N, K, f
     """nine to sixteen K steps: four each of four waves, not two each, one by one, of eight (up to 1.2 times as fast)"""
     d = B.linear_describe(M, N, K)
     assert d["kernel"] == "decode_any" and d["params"][:4] == form
+
+
+def test_workspace_is_asked_for_where_it_is_used():
+    """a shape that runs on the batched-decode kernels, which never split K by themselves, needs no scratch; 257 to 512 tokens on a short K included"""
+    for M in (5, 48, 130, 256, 257, 300, 400, 480, 512):
+        for N in (256, 1024, 2048, 4096, 8192):
+            for K in (512, 1024, 2048, 4096, 5120, 11008):
+                unsplit = B.linear_describe(M, N, K)["kernel"].startswith(("batched_decode", "decode"))
+                assert (B.linear_workspace(M, N, K) == 0) if unsplit else (B.linear_workspace(M, N, K) in (0, 8 * M * N * 4))
+    assert B.linear_workspace(300, 4096, 4096) == 0 and B.linear_workspace(480, 2048, 2048) == 0
+    assert B.linear_workspace(300, 4096, 2048, B.PACK_TRIT5) == 4096 * 2048 // 4         # the 2-bit copy alone
