@@ -165,37 +165,42 @@ def check_ksplit_order(asm_text, expected):
     """linear_ksplit_2bit waits for a tile's LDS copies with a count of the younger loads, of which there are at least that many only if the
     loads are issued as in the source: the weights of the first step (W, kR kW of them) and the copies (L, four a tile) of the
     first kQ tiles; in the loop a step's weights, then for each of its kMT tiles a wait that leaves the copies of kQ - 1 tiles and one step's
-    weights in flight, and the copies that take its slot; behind the loop the steps that the slots still reach, each wait with the copies
-    of the tiles behind it alone.  Raises unless the assembly of every instantiation reads so up to its first barrier."""
+    weights in flight, the tile's four reads (R), and the copies that take its slot, no read outstanding; behind the loop the steps that the slots
+    still reach, each wait with the copies of the tiles behind it alone.  Raises unless the assembly of every instantiation reads so up to
+    its first barrier, with no read of LDS elsewhere."""
     checked = []
     for m in re.finditer(r"^_ZN6bitnet\d+linear_ksplit_2bitI((?:Li\d+E)+)E\S*:[^\n]*\n(.*?)^\.Lfunc_end", asm_text, re.M | re.S):
         p = tuple(int(v) for v in re.findall(r"Li(\d+)E", m.group(1)))
         kMT, kR, kW, _, kQ = p
-        rows, got, limit = kR * kW, "", None
+        rows, got, limit, reading = kR * kW, "", None, False
         for line in m.group(2).splitlines():
             line = line.split(";")[0]
             wait = re.search(r"vmcnt\((\d+)\)", line)
             if "s_barrier" in line:
                 break
+            if re.search(r"lgkmcnt\(0\)", line):
+                reading = False
             if wait:                           # the strictest of the waits in front of a tile's first read
                 limit = int(wait.group(1)) if limit is None else min(limit, int(wait.group(1)))
             elif "buffer_load_dwordx4" in line:
-                got += "L" if re.search(r"\blds\b", line) else "W"
+                copy = re.search(r"\blds\b", line)
+                got += ("!" if copy and reading else "") + ("L" if copy else "W")
                 limit = None
-            elif "ds_read_b128" in line and limit is not None:
-                got += "<%d>" % limit
-                limit = None
+            elif re.search(r"\bds_read", line):
+                got += ("" if limit is None else "<%d>" % limit) + "R"
+                limit, reading = None, True
             if "v_mfma" in line:
                 limit = None
         ahead = -(-kQ // kMT)
-        want = "W" * rows + "LLLL" * kQ + "W" * rows + ("<%d>LLLL" % (4 * (kQ - 1) + rows)) * kMT
+        want = "W" * rows + "LLLL" * kQ + "W" * rows + ("<%d>RRRRLLLL" % (4 * (kQ - 1) + rows)) * kMT
         for e in range(ahead - 1, -1, -1):
             want += "W" * rows if e else ""
             for t in range(kMT):
                 left = e * kMT + kMT - 1 - t
-                want += "<%d>" % (4 * min(left, kQ - 1)) + ("LLLL" if left >= kQ else "")
+                want += "<%d>RRRR" % (4 * min(left, kQ - 1)) + ("LLLL" if left >= kQ else "")
         if got != want:
-            raise RuntimeError("linear_ksplit_2bit<%s>: loads and waits are %s, not %s" % (", ".join(map(str, p)), got, want))
+            raise RuntimeError("linear_ksplit_2bit<%s>: loads, waits and reads (!: a copy over a slot that is being read) are %s, not %s"
+                               % (", ".join(map(str, p)), got, want))
         checked.append(p)
     if sorted(checked) != sorted(expected):
         raise RuntimeError("linear_ksplit_2bit: checked %s, dispatched %s" % (sorted(checked), sorted(expected)))
