@@ -140,9 +140,11 @@ const char* bitnet_status_string(bitnet_status s);
 /* Bytes of the packed buffer for an N x K matrix in format f, written to *bytes (host). */
 bitnet_status bitnet_packed_bytes(int64_t N, int64_t K, bitnet_format f, size_t* bytes);
 
-/* Bytes of scratch with which bitnet_quantize_weights runs at its best (host out).  Independent of the format.  32 KiB are enough for any
- * shape; matrices of 25 million weights and more (up to 2^30) are read once instead of twice if the scratch also holds the notes on which
- * weights' codes hang on the exact gamma, N K / 16 bytes and no more than 30 MB. */
+/* Bytes of scratch with which bitnet_quantize_weights and bitnet_quantize_weights_segmented run at their best, in any format and type (host
+ * out).  32 KiB are enough for any shape, and more is used by nothing but the 2-bit format's single read of large matrices: up to 2^30
+ * weights, from 96 MiB of F32 (25.2 million weights) and 128 MiB of BF16 (67.1 million) on.  From 25.2 million weights on the query
+ * therefore reports, on top of the 32 KiB, room for notes on the weights whose codes hang on the exact gamma: about N K / 16 bytes and 2.1 MB,
+ * at most 30 MB in all.  With less than it reports, matrices are read twice. */
 bitnet_status bitnet_quantize_weights_workspace(int64_t N, int64_t K, size_t* bytes);
 
 /*
@@ -155,7 +157,7 @@ bitnet_status bitnet_quantize_weights_workspace(int64_t N, int64_t K, size_t* by
  * Two launches on `stream`: |W| partial sums (double-double), then the ternarize-and-pack pass, whose workgroups first
  * fold the partial sums to gamma.  A 16-byte aligned W takes the vector path of the |W| sum.  Large matrices
  * in the 2-bit format, 16-byte aligned and with the whole workspace: three launches (a sample, one pass over W, what the
- * sample left open).  Same bits.
+ * sample left open; narrow ones, of which a workgroup's lanes would be filled in part, only where larger still).  Same bits.
  * One gamma per call: a fused QKV or gate/up matrix passed as one tensor gets one scale.
  */
 bitnet_status bitnet_quantize_weights(const void* W, bitnet_dtype w_dtype, int64_t N, int64_t K,
@@ -166,8 +168,8 @@ bitnet_status bitnet_quantize_weights(const void* W, bitnet_dtype w_dtype, int64
  * bitnet_quantize_weights without a workspace argument and without any allocation, for callers that cannot
  * allocate device memory: code running under HIP-graph capture, tight serving loops, harnesses that forbid
  * hipMalloc.  The block partial sums of the |W| reduction go to a static 32 KiB array in device memory that belongs to
- * the library (one copy per GPU, held until the process ends) instead of a caller's buffer; kernels, launch shapes and
- * results are those of bitnet_quantize_weights, bit for bit.
+ * the library (one copy per GPU, held until the process ends) instead of a caller's buffer; kernels and launch shapes are those of
+ * bitnet_quantize_weights with 32 KiB, results those of bitnet_quantize_weights bit for bit.
  *   W, packed, gamma, stream   as for bitnet_quantize_weights
  *   Limit: the partial sums of the shape must fit the static array (BITNET_ERR_WORKSPACE otherwise; true of every
  *   shape the library accepts today, whose need is a fixed 32 KiB).  Matrices of any size are read twice.
@@ -188,7 +190,7 @@ bitnet_status bitnet_quantize_weights_static(const void* W, bitnet_dtype w_dtype
  * bitnet_abs_sum: sum[0] + sum[1] = sum_ij |W_ij| over these N rows, as a normalised double-double pair.
  *   W          [N][K], F32 or BF16, element-aligned
  *   sum        out, 2 doubles (device), 8-byte aligned
- *   workspace  as for bitnet_quantize_weights (same size query)
+ *   workspace  scratch of 32 KiB at least, 16-byte aligned
  *
  * bitnet_quantize_weights_sharded: Eq. (1)-(2) and the packing of bitnet_quantize_weights for these N rows, with
  * gamma = fp32((sum of the nsums pairs) / (total_rows * K)).

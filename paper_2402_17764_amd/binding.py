@@ -141,6 +141,9 @@ def packed_bytes(N, K, fmt=PACK_2BIT):
     return int(out.value)
 
 
+PARTIALS_BYTES = 32768      # the scratch that every weight-quantizing call needs; more is used by the 2-bit format alone
+
+
 def quantize_weights_workspace(N, K):
     out = ctypes.c_size_t(0)
     _check(load().bitnet_quantize_weights_workspace(N, K, ctypes.byref(out)), "bitnet_quantize_weights_workspace")
@@ -157,7 +160,7 @@ def quantize_weights(W, fmt=PACK_2BIT, packed=None, gamma=None, workspace=None):
     if gamma is None:
         gamma = torch.empty(1, dtype=torch.float32, device=W.device)
     if workspace is None:
-        workspace = torch.empty(quantize_weights_workspace(N, K), dtype=torch.uint8, device=W.device)
+        workspace = torch.empty(quantize_weights_workspace(N, K) if fmt == PACK_2BIT else PARTIALS_BYTES, dtype=torch.uint8, device=W.device)
     _check(lib.bitnet_quantize_weights(wp, _FLOAT[W.dtype], N, K, fmt, _dev(packed, "packed"), _dev(gamma, "gamma"),
                                        _dev(workspace, "workspace"), workspace.numel() * workspace.element_size(),
                                        _stream()), "bitnet_quantize_weights")
@@ -184,7 +187,7 @@ def abs_sum(W, out=None, workspace=None):
     if out is None:
         out = torch.empty(2, dtype=torch.float64, device=W.device)
     if workspace is None:
-        workspace = torch.empty(quantize_weights_workspace(N, K), dtype=torch.uint8, device=W.device)
+        workspace = torch.empty(PARTIALS_BYTES, dtype=torch.uint8, device=W.device)
     _check(lib.bitnet_abs_sum(wp, _FLOAT[W.dtype], N, K, _dev(out, "sum", (torch.float64,)), _dev(workspace, "workspace"),
                               workspace.numel() * workspace.element_size(), _stream()), "bitnet_abs_sum")
     return out

@@ -954,14 +954,16 @@ static void launch_abs_sum_partials(const void* W, bool bf16, int64_t K, const S
     else      hipLaunchKernelGGL((abs_sum_partials<float, kSegs>), grid, block, 0, stream, static_cast<const float*>(W), K, list, vec_ok, partials);
 }
 
-// A workgroup's notes for a matrix of `count` weights: one weight in 128 and some, three times what normally distributed ones need.
+// A workgroup's notes for a matrix of `count` weights: one weight in 128 and some, three times what normally distributed ones need, up to
+// 3584 (one in 293 at 2^30, 1.5 times what one bf16 value next to the threshold takes).
 static int guess_cap(int64_t count) {
     const int64_t want = count / kPackBlocks / 128 + 256;
     return (int)(want < kNotes ? want : kNotes) / 4 * 4;       // as much for each of its waves
 }
+static_assert(kGuessBytesBf16 / 2 >= kGuessBytesF32 / 4, "the query, which is not told the type, answers for fp32");
 size_t quant_weights_workspace_bytes(int64_t N, int64_t K) {
     const int64_t count = N * K;
-    return (count * 4 >= kGuessBytesF32 || count * 2 >= kGuessBytesBf16) && count <= kGuessMost ? kNotesAt + (size_t)kGuessBlocks * guess_cap(count) * sizeof(uint2) : kNotesAt;
+    return count * 4 >= kGuessBytesF32 && count <= kGuessMost ? kNotesAt + (size_t)kGuessBlocks * guess_cap(count) * sizeof(uint2) : kNotesAt;
 }
 // Whether the segments of a launch are read once.  Each needs a sample: 2 MiB of it at least.
 // The pass that reads once has most to do for each item, and the lanes of an item past the row's end do it in vain: the fewer of them are

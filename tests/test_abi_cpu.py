@@ -45,6 +45,10 @@ def test_packed_bytes_follow_the_documented_layouts():
     assert binding.packed_bytes(3200, 3200, binding.PACK_TRIT5) == 3200 * 3200 // 5
     assert binding.packed_bytes(16, 321, binding.PACK_TRIT5) == 16 * 640 // 5
     assert binding.quantize_weights_workspace(57344, 8192) >= 4096
+    # notes: 8 bytes for one weight in 128 and 256 more, for each of 1040 workgroups; up to 3584 of them, and from 96 MiB of fp32 to 2^30 weights
+    assert binding.quantize_weights_workspace(4096, 6143) == 32768 and binding.quantize_weights_workspace(1 << 13, (1 << 17) + 1) == 32768
+    assert binding.quantize_weights_workspace(4096, 6144) == 32768 + 8 * 1040 * (4096 * 6144 // 1024 // 128 + 256) <= 32768 + 4096 * 6144 // 16 + (9 << 18)
+    assert binding.quantize_weights_workspace(1 << 13, 1 << 17) == 32768 + 8 * 1040 * 3584 <= 30e6
     with pytest.raises(binding.BitnetError) as e:
         binding.packed_bytes(0, 5)
     assert e.value.status == 2

@@ -226,3 +226,15 @@ def test_narrow_matrices_are_read_twice(gpu_lib, dtype, N, K, once):
     B.quantize_weights(W, workspace=ws)
     at = (1024 + 16) * 16 + (256 + 16) * 16 + (1024 + 16) * 4
     assert bool((ws[at:at + 16] == 0xFF).all()) != once
+
+
+def test_scratch_is_allocated_where_it_is_used(gpu_lib):
+    """the notes' room belongs to the 2-bit format: 5-trit calls and |W| sums allocate the partial sums alone"""
+    W = _normal(9600, 3200, torch.float32, 51)
+    packed, gamma = torch.empty(B.packed_bytes(9600, 3200, B.PACK_TRIT5), dtype=torch.uint8, device="cuda"), torch.empty(1, device="cuda")
+    out = torch.empty(2, dtype=torch.float64, device="cuda")
+    for call in (lambda: B.quantize_weights(W, B.PACK_TRIT5, packed, gamma), lambda: B.abs_sum(W, out)):
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        call()
+        assert torch.cuda.max_memory_allocated() - before <= 32768
