@@ -174,8 +174,9 @@ __global__ __launch_bounds__(kS * kW * kWave) void linear_ksplit_2bit(
         }
     }
 
-    // Fold: every wave's partial tiles through LDS, where the slots were; a wave adds up and stores the tiles that are its own.  Above 160
-    // KiB of partials the upper half of the waves hands its own to the lower half first.
+    // Fold: every wave's partial tiles through LDS, where the slots were; a wave adds up and stores the tiles that are its own.  Where
+    // the slots do not hold all partials (32 tokens by six row blocks: 96 KiB over 64) the upper half of the waves hands its own to the lower half
+    // first.
     constexpr bool kHalves = kWaves * kTiles * 1024 > kWaves * kQ * kSlot;
     constexpr int kTop = kHalves ? kWaves / 2 : kWaves;
     static_assert(kTop * kTiles * 1024 <= kWaves * kQ * kSlot, "the fold reuses the activation slots");

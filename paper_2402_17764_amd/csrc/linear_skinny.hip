@@ -32,8 +32,8 @@ namespace bitnet {
 // the build checks that every instantiation compiles without scratch memory.
 //
 // The last kD steps stand behind the loop and request nothing that is not there: with the loop's own prefetch a group of two
-// steps asked for four, and the end of the kernel waited for the two that nobody reads (29 tokens, 4096 -> 4096: twice the
-// traffic).  Fewer loads are then in flight behind the copy that a step waits for, last_younger() of them.
+// steps asked for four, and the end of the kernel waited for the two that nobody reads.  Fewer loads are then in flight behind the copy that a
+// step waits for, last_younger() of them.
 // step d of the last kD: what was issued after its copy, in the steps -kLx ... -1 before it -- weights by those of the loop
 // (d < 0), copies by the ones whose target step exists
 constexpr int last_younger(int d, int kR, int kC, int kD, int kLx) {
@@ -626,9 +626,10 @@ hipError_t launch_linear_gemv_2bit(const int8_t* xq, const float* sx, const void
                                    OutType yt, hipStream_t stream, void* workspace, size_t workspace_bytes,
                                    int force_splits, LaunchPlan* plan) {
     const int64_t RB = ceil_div(N, kRowsPerBlock);
-    // Up to four tokens, and up to eight on layers of fewer than 1024 row blocks, the M <= 16 kernel (each wave reads
-    // its own x_q) is the faster one: at eight tokens 3B down 6.1 -> 5.1 us, 7B QKV 6.0 -> 5.5 us, 70B O 6.8 -> 6.1 us;
-    // at sixteen the kernels below win on every layer measured.  A forced split-K stays on the kernels that have one.
+    // Up to four tokens the M <= 16 kernel (each wave reads its own x_q), and up to eight on layers of fewer than 1024 row blocks, where it is
+    // faster than the kernels that share stages: at eight tokens 3B down 6.1 -> 5.1 us, 7B QKV 6.0 -> 5.5 us, 70B O 6.8 -> 6.1 us; at
+    // sixteen the kernels below win on every layer measured.  (linear_ksplit_2bit is 15 to 25 % faster than it at five to eight tokens on
+    // those layers and not routed there yet.)  A forced split-K stays on the kernels that have one.
     if (M <= 4 || (M <= 8 && RB < 1024 && force_splits == 0))
         return launch_linear_gemv16_2bit(xq, sx, packed, gamma, gstride, M, N, K, y, yt, stream, plan);
     // More tokens: the activations of a step outweigh the weights a wave reads with them, so they
@@ -649,7 +650,8 @@ hipError_t launch_linear_gemv_2bit(const int8_t* xq, const float* sx, const void
     int kmt, rpw;
     skinny_shape(M, RBc, &kmt, &rpw, splits == 1 && tiles_of_80(K));
     // The smaller workgroup tiles: K steps dealt out to the waves.  With more row blocks the kernels below are the faster ones (16
-    // tokens, 4096 -> 22016: 6.79 us, six row blocks there 6.84; 64 tokens 11.2 / 12.2); they also have the forced split-K.
+    // tokens, 4096 -> 22016: 6.79 us, six row blocks there 6.84; 64 tokens 11.2 / 12.2).  They also have the forced split-K, which alone
+    // reaches their forms of up to four row blocks (kmt 4: of one and four) and of six with kmt 2.
     hipError_t status;
     if (splits == 1 && launch_linear_ksplit_2bit(kmt, rpw, xq, sx, packed, gamma, gstride, M, N, K, y, yt, stream, plan, &status)) return status;
     if (kmt == 1) {
