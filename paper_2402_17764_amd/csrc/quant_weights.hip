@@ -420,11 +420,11 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
 //                    differences of runs side by side, its standard error.  Several runs of a row, and neighbours compared with each
 //                    other alone: rows or heads of different scale do not widen the bounds (with runs of 1 KiB and the spread of all
 //                    of them, a deviation of 10 % between the rows of 3200 x 3200 did, by more than the notes hold; now, us, two passes /
-//                    this, at 50 %: 9600 x 3200 fp32 in three segments 43.7 / 40.5, 8192 x 8192 bf16 47.6 / 44.1, 57344 x 8192 328 / 206)
+//                    this, at 50 %: 9600 x 3200 fp32 in three segments 43.7 / 40.5, 8192 x 8192 bf16 47.4 / 44.7, 57344 x 8192 328 / 226)
 //   guess_pack_2bit  reads W once: adds up |W| exactly as pass 1 does, and codes as pass 3 does with the sample's threshold.  Weights
 //                    between the thresholds of its mean -+ 5 standard errors (a fifth of a percent of normally distributed fp32 ones, of
-//                    bf16 ones those of the one or no value in between) are noted down
-//                    Where the bounds are more than 2 % apart it only adds up, as pass 1
+//                    bf16 ones those of the one or no value in between) are noted down.  Where the bounds are more than
+//                    2 % apart it only adds up, as pass 1
 //   settle_2bit      gamma from the exact sum; if it lies between its bounds, all weights but noted ones have their codes, and of those
 //                    the ones between the two thresholds (one in ten) are changed.  If it does not, or a note pad was too small, this
 //                    is pass 3.
@@ -436,10 +436,10 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
 //   * a value right at the threshold that very many weights share: from the item on that fills a wave's pad, that wave only adds up.  Two
 //     thirds of the weights there (noted to the end as well: third figure): 57344 x 8192 bf16 325 / 373 (551), 8192 x 8192 46.7 / 63 (92),
 //     22016 x 8192 fp32 240 / 254 (317)
-// us, two passes / this: bf16 57344 x 8192 334 / 207, 28672 x 8192 165 / 107, 20000 x 5001 75.6 / 67, 16384 x 4096 48.3 / 46.1; fp32 57344 x
-// 8192 642 / 388, 22016 x 4096 118 / 81, 9600 x 3200 in three segments 43.6 / 37.9, 7000 x 4096 39.8 / 33.8, 4096 x 4096 24.8 / 26.2.  What bounds it: the
-// pass runs at 0.9 of what pass 3 alone takes in bf16 (187 us for 940 + 117 MB), in fp32 13 instructions a weight and the launches
-// around it (sample 4, settling 4.9 of 36).
+// us, two passes / this: bf16 57344 x 8192 326 / 206, 28672 x 8192 162 / 106, 20000 x 5001 74.7 / 67, 16384 x 4096 48.8 / 47.4; fp32 57344 x
+// 8192 638 / 385, 22016 x 4096 115 / 81, 9600 x 3200 in three segments 43.6 / 38.5, 7000 x 4096 39.8 / 35.0, 4096 x 4096 24.8 / 26.2.  What bounds it: the
+// pass runs at 0.9 of what pass 3 alone takes in bf16 (190 us for 940 + 117 MB), in fp32 13 instructions a weight and the launches
+// around it (sample 5, settling 4.9 of 38).
 constexpr int64_t kGuessBytesF32 = (int64_t)96 << 20, kGuessBytesBf16 = (int64_t)128 << 20;
 constexpr int64_t kGuessMost = (int64_t)1 << 30;           // weights: a workgroup's notes fit its LDS
 constexpr int kNotes = 3584;                               // of a workgroup: 28 KiB of LDS, four workgroups a CU
@@ -1020,9 +1020,10 @@ static void launch_guess(const void* W, bool bf16, int64_t N, int64_t K, int64_t
     const dim3 sgrid((unsigned)(last.part0 + last.nparts)), grid((unsigned)(last.pack0 + last.npack));
     int settling = 0;
     for (int i = 0; i < list.n; ++i) settling += (list.s[i].npack + kPads - 1) / kPads;
-    // 8 MiB of samples per 128 MiB of W, and never more than 32: 1 in 32 of 940 MB
-    const int64_t want = (last.row0 + last.rows - list.s[0].row0) * K * esz >> 27;
-    const int batches = (int)(want < 1 ? 1 : want > 4 ? 4 : want), cap = guess_cap(N * K);
+    // 8 MiB of samples per 256 MiB of W, 8 at least and 24 at most: 1 in 37 of 940 MB.  Eight take 3.3 us of a pass; what closer bounds save is
+    // notes (in fp32 7 % of a pass at eight per 128 MiB; in bf16 10 %, where a value lies between the bounds).
+    const int64_t want = (((last.row0 + last.rows - list.s[0].row0) * K * esz) + ((int64_t)1 << 27)) >> 28;
+    const int batches = (int)(want < 1 ? 1 : want > 3 ? 3 : want), cap = guess_cap(N * K);
     char* ws = static_cast<char*>(workspace);
     double* samples = reinterpret_cast<double*>(ws + kSamplesAt);
     uint32_t* out = static_cast<uint32_t*>(packed);
