@@ -420,11 +420,12 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
 //                    differences of runs side by side, its standard error.  Several runs of a row, and neighbours compared with each
 //                    other alone: rows or heads of different scale do not widen the bounds (with runs of 1 KiB and the spread of all
 //                    of them, a deviation of 10 % between the rows of 3200 x 3200 did, by more than the notes hold; now, us, two passes /
-//                    this, at 50 %: 9600 x 3200 fp32 in three segments 43.7 / 40.5, 8192 x 8192 bf16 47.4 / 44.7, 57344 x 8192 328 / 226)
+//                    this, at 50 %: 9600 x 3200 fp32 in three segments 43.6 / 39.4, 8192 x 8192 bf16 47.4 / 42.4, 57344 x 8192 327 / 227)
 //   guess_pack_2bit  reads W once: adds up |W| exactly as pass 1 does, and codes as pass 3 does with the sample's threshold.  Weights
-//                    between the thresholds of its mean -+ 5 standard errors (a fifth of a percent of normally distributed fp32 ones, of
-//                    bf16 ones those of the one or no value in between) are noted down.  Where the bounds are more than
-//                    2 % apart it only adds up, as pass 1
+//                    between the thresholds of its mean -+ 4 standard errors (0.15 % of normally distributed fp32 ones, of
+//                    bf16 ones those of the one or no value in between; at five, where gamma lies outside once in a million times and
+//                    not once in 16000, 20000 x 5001 bf16 67 / 60) are noted down.  Where the bounds are more than 2 % apart it only
+//                    adds up, as pass 1
 //   settle_2bit      gamma from the exact sum; if it lies between its bounds, all weights but noted ones have their codes, and of those
 //                    the ones between the two thresholds (one in ten) are changed.  If it does not, or a note pad was too small, this
 //                    is pass 3.
@@ -436,8 +437,9 @@ __global__ __launch_bounds__(kPackThreads) void ternarize_pack_2bit(const T* __r
 //   * a value right at the threshold that very many weights share: from the item on that fills a wave's pad, that wave only adds up.  Two
 //     thirds of the weights there (noted to the end as well: third figure): 57344 x 8192 bf16 325 / 373 (551), 8192 x 8192 46.7 / 63 (92),
 //     22016 x 8192 fp32 240 / 254 (317)
-// us, two passes / this: bf16 57344 x 8192 326 / 206, 28672 x 8192 162 / 106, 20000 x 5001 74.7 / 67, 16384 x 4096 48.8 / 47.4; fp32 57344 x
-// 8192 638 / 385, 22016 x 4096 115 / 81, 9600 x 3200 in three segments 43.6 / 38.5, 7000 x 4096 39.8 / 35.0, 4096 x 4096 24.8 / 26.2.  What bounds it: the
+// us, two passes / this: bf16 57344 x 8192 325 / 205, 28672 x 8192 162 / 107, 20000 x 5001 74.3 / 60, 8192 x 8192 47.4 / 40.3 (where the bounds
+// hold a bf16 value these take 10 % more); fp32 57344 x 8192 638 / 385, 22016 x 8192 241 / 151, 9600 x 3200 in three segments 43.6 / 38.1, 7000 x
+// 4096 39.8 / 34.6, 4096 x 4096 24.8 / 26.2.  What bounds it: the
 // pass runs at 0.9 of what pass 3 alone takes in bf16 (190 us for 940 + 117 MB), in fp32 13 instructions a weight and the launches
 // around it (sample 5, settling 4.9 of 38).
 constexpr int64_t kGuessBytesF32 = (int64_t)96 << 20, kGuessBytesBf16 = (int64_t)128 << 20;
@@ -524,7 +526,7 @@ __device__ inline float3 gamma_bounds(const double* __restrict__ samples, const 
     static_assert(kPackThreads == 4 * kWave && kSumBlocks <= kPackThreads, "one sample per thread, four waves");
     // the squared difference of two runs side by side is the variance of their sum, so that q is that of s
     const float sampled = (float)(seg.nparts * (kSumThreads / kWave) * batches * kSumLoads) * (float)(16 * kWave / sizeof(T));
-    const float inv = 1.0f / sampled, mean = (float)s * inv, off = 5.0f * inv * (float)sqrt(q) + 2e-6f * mean;
+    const float inv = 1.0f / sampled, mean = (float)s * inv, off = 4.0f * inv * (float)sqrt(q) + 2e-6f * mean;
     const float lo = fmaxf(mean - off, 0.0f), hi = mean + off;
     return hi <= 1.02f * lo || hi == 0.0f ? make_float3(lo, hi, mean) : make_float3(1.0f, 0.0f, mean);
 }
