@@ -561,7 +561,8 @@ static void launch_trit5(const int8_t* xq, const float* sx, const void* packed, 
 //     nine tokens 24.7 / 34.3), else four row blocks with K split in two take half the step from one round to the next;
 //     one workgroup on every CU where eight, six or five row blocks are too many or too few for that: five or six with K split in two from
 //     ten steps on (eight tokens: 20480 x 8192 14.9 / 12.0, 17280 x 3200 7.3 / 6.8; sixteen, 22016 x 4096 11.4 / 10.0; with few tokens four
-//     waves a row block hide more: three 21424 x 4608 9.4 / 8.8, 24560 x 3968 8.8 / 8.4, four 20496 x 3520 7.5 / 7.1), seven and eight without a split for up to four (27648 x 5120 10.2 / 9.7, 32640 x 8320 13.0 / 12.6);
+//     waves a row block hide more: three 21424 x 4608 9.4 / 8.8, 24560 x 3968 8.8 / 8.4, four 20496 x 3520 7.5 / 7.1;
+//     five on up to 1280 row blocks from thirteen steps on), seven and eight without a split for up to four (27648 x 5120 10.2 / 9.7, 32640 x 8320 13.0 / 12.6);
 //   * the table walks whole rounds of four steps on wide layers: there its best counts are four and eight.
 // The picks are within 5 % of the faster of table and previous picks wherever measured.  x_q has to fit the LDS.
 struct QuotientForm { int s, w, d; };                  // kS, kW, kD; none: s = 0
@@ -587,7 +588,7 @@ static QuotientForm pick_quotients(int64_t M, int64_t RB, int64_t steps) {
         if (M <= 10) return (narrow ? steps >= 4 && steps < 14 : middle) ? table : four;
         return narrow && middle && M <= 12 ? table : four;
     }
-    if (RB <= 1536 && steps >= 10 && (M > 4 || (M == 4 && RB > 1360))) return RB <= 1280 ? five : six;
+    if (RB <= 1536 && steps >= (M == 5 && RB <= 1280 ? 13 : 10) && (M > 4 || (M == 4 && RB > 1360))) return RB <= 1280 ? five : six;
     if (M <= 4 && RB > 1536 && RB <= 2048) return RB <= 1792 ? seven : eight;
     if (M <= 4) {
         if (RB >= 3072) return eight;
@@ -597,7 +598,7 @@ static QuotientForm pick_quotients(int64_t M, int64_t RB, int64_t steps) {
         return M == 1 || steps < 20 ? one : two;
     }
     if (RB < 1536) {
-        if (M <= 8) return steps <= 3 ? eight : M <= 6 || steps <= 8 ? one : two;             // fewer than ten steps
+        if (M <= 8) return steps <= 3 ? eight : M <= 6 || steps <= 8 ? one : two;             // fewer than ten steps, or thirteen
         if (M <= 10 && steps >= 5 && (RB <= 1280 || steps <= 8)) return table;
         return M <= 12 && steps >= 6 && steps <= 8 ? table : eight;
     }

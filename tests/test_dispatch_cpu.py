@@ -409,9 +409,11 @@ def test_k_dealt_out_to_eight_waves_needs_steps_to_deal(M, N, K, kernel, tile):
 
 
 @pytest.mark.parametrize("M,N,K,params", [(3, 21424, 4608, [4, 1, 2, 1]), (3, 24560, 3968, [4, 1, 2, 1]), (3, 21344, 6720, [4, 2, 2, 1]), (4, 20496, 3520, [4, 1, 2, 1]),
-                                          (4, 21760, 4800, [4, 1, 2, 1]), (4, 21776, 4800, [2, 6, 2, 1]), (5, 20496, 3520, [2, 6, 2, 1])])
+                                          (4, 21760, 4800, [4, 1, 2, 1]), (4, 21776, 4800, [2, 6, 2, 1]), (5, 20496, 3520, [2, 6, 2, 1]),
+                                          (5, 20480, 3840, [4, 1, 2, 1]), (5, 20480, 3856, [2, 5, 2, 1]), (6, 20480, 3840, [2, 5, 2, 1])])
 def test_six_row_blocks_of_5_trit_weights_need_four_tokens(M, N, K, params):
-    """1281 to 1536 row blocks: four K waves on a row block hide more of three tokens' work, and of four on up to 1360 (up to 6 % faster)"""
+    """1281 to 1536 row blocks: four K waves on a row block hide more of three tokens' work, and of four on up to 1360 (up to 6 % faster); of five
+    tokens on 1025 to 1280 up to twelve steps (3 %)"""
     assert B.linear_describe(M, N, K, B.PACK_TRIT5)["params"] == params
 
 

@@ -10,7 +10,7 @@ torch = pytest.importorskip("torch")
 
 
 # K waves, row blocks per workgroup, prefetch depth, groups of eight tokens
-FORMS = {(1025, 3200, 5): [2, 5, 2, 1], (1280, 6400, 16): [2, 5, 2, 2], (1281, 4176, 8): [2, 6, 2, 1], (1536, 3200, 9): [2, 6, 2, 2],
+FORMS = {(1025, 3200, 5): [4, 1, 2, 1], (1025, 4176, 5): [2, 5, 2, 1], (1280, 6400, 16): [2, 5, 2, 2], (1281, 4176, 8): [2, 6, 2, 1], (1536, 3200, 9): [2, 6, 2, 2],
          (1537, 320, 1): [1, 7, 4, 1], (1792, 6400, 4): [1, 7, 4, 1], (1793, 2896, 3): [1, 8, 4, 1], (2048, 6400, 4): [1, 8, 4, 1],
          (1537, 6400, 5): [1, 8, 4, 1], (1025, 320, 9): [1, 8, 4, 2], (2048, 6400, 16): [1, 8, 4, 2]}
 
